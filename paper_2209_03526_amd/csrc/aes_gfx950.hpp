@@ -145,12 +145,23 @@ constexpr int kLdsTableWords = 256 * 64;  // 64 KiB
 
 __device__ __forceinline__ uint32_t rotl32(uint32_t x, int k) { return (x << k) | (x >> (32 - k)); }
 
-// Fills the replicated tables; every thread of the workgroup takes part.  The
-// caller synchronises the workgroup before the first lookup.
+// Fills the replicated tables; every wave of the workgroup takes part, all its
+// lanes active (any whole number of waves).  Lane l holds rows 4l .. 4l + 3 of
+// T0 (one 16-byte load per wave); each row is broadcast from its lane and
+// written as 64 words, rotated on lanes 32-63 for T1.  The caller synchronises
+// the workgroup before the first lookup.
 __device__ __forceinline__ void lds_table_fill(uint32_t* tab, const uint32_t* g_t0) {
-    for (int i = threadIdx.x; i < kLdsTableWords; i += blockDim.x) {
-        const uint32_t v = g_t0[i >> 6];
-        tab[i] = (i & 32) ? rotl32(v, 8) : v;     // word i: row i >> 6, table (i >> 5) & 1
+    const uint32_t lane = threadIdx.x & 63u, waves = blockDim.x >> 6;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint4 t = ((const uint4*)g_t0)[lane];
+    const uint32_t sh = lane < 32 ? 0u : 24u;                 // right rotation by 24 = left by 8
+    for (uint32_t q = wave; q < 64; q += waves) {
+        const uint32_t v[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) {
+            const uint32_t r = (uint32_t)__builtin_amdgcn_readlane((int)v[k], (int)q);
+            tab[(4 * q + k) * 64 + lane] = __builtin_amdgcn_alignbit(r, r, sh);
+        }
     }
 }
 

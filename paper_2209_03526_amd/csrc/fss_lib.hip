@@ -9,14 +9,16 @@
 //   k_and_open/close       one party's AND phases (ss_and)             (HBM stream)
 //   k_tail                 a plan's ANDs and hop joins, triples drawn in registers
 //                                                                      (gathers + AES)
-//   k_rss, k_rss_eval, k_eval_points*   the paper's own secEval and RSS arithmetic
+//   k_rss, k_rss_eval, k_eval_points    the paper's own secEval and RSS arithmetic
 // and the host code of the C ABI (validation, launch, match_query plan).
 //
 // Every AES-using kernel runs 1024-thread workgroups that first fill the
-// 64 KiB replicated T-tables in LDS (aes_gfx950.hpp).  One thread owns one
-// table row (one element, one predicate, one party); the 64 lanes of a wave
-// own 64 consecutive rows, so the per-level correction words of a wave are one
-// contiguous 1 KiB read, and the wave's 64 output bits are one ballot.
+// 64 KiB replicated T-tables in LDS (aes_gfx950.hpp); evaluation uses smaller
+// workgroups where a launch has few tiles.  In evaluation one lane owns one
+// tree walk (one element, one predicate, one party), a wave 64 consecutive
+// rows of an equality or 32 of a range, so the per-level correction words of a
+// wave are one contiguous 1 KiB read or two of 512 bytes, and the wave's
+// output bits come from one ballot.
 
 #include <hip/hip_runtime.h>
 #include <stdarg.h>
@@ -73,7 +75,7 @@ namespace {
 constexpr int kBlock = 1024;            // threads per AES workgroup
 constexpr int kEvalInline = 16;         // eval descriptors carried in kernel arguments
 
-__constant__ AesTables g_tables = kTables;
+alignas(16) __constant__ AesTables g_tables = kTables;   // t0 at a multiple of 16 bytes
 
 // ----------------------------------------------------------------- key layout
 
@@ -147,51 +149,69 @@ __device__ __forceinline__ uint32_t block_bit(uint4 g, uint32_t idx) {
 }
 
 // ----------------------------------------------------------------- Eval (DPF, DCF)
+//
+// One lane walks one tree: an equality row is one DPF walk, a range row two DCF
+// walks on two lanes.  A walk is a serial chain of nbits - 6 hashes of ten
+// dependent rounds, each an LDS round trip (2 us a hash on its own), so
+// a launch that does not fill the chip takes one chain's time, however few
+// rows it has; with enough waves the LDS read pipe binds instead.  A lane that
+// walked both trees of a range row held two chains: twice the latency for the
+// same number of table reads.
 
-// A party's DPF output bit at x: nu = nbits - 7 levels, then the 128-bit leaf
-// answers the low 7 bits.  No party index is needed: t is bit 0 of the seed.
-__device__ __forceinline__ uint32_t dpf_eval(const uint8_t* key, uint64_t np, uint64_t row, uint32_t nbits,
-                                             uint32_t x, const uint32_t* tab, LaneOff loff) {
-    const DpfPlanes P{np, nbits - 7};
-    uint4 s = at<uint4>(key, P.root(), row);
-    for (uint32_t i = 0; i < P.nu; i++) {
-        const uint4 cw = at<uint4>(key, P.cw(i), row);
-        const uint32_t xi = (x >> (nbits - 1 - i)) & 1u;
-        uint32_t v;
-        const uint4 h = expand(s, v, tab, loff);
-        s = child(s, h, cw, xi);
+// The 128-bit leaf of a walk over x's high nbits - 7 bits, under its correction
+// word; bit idx of it (idx = the low 7 bits of x) is the DPF's output bit.  A
+// DCF (DCF = true) also accumulates v ^ t * VCW_i of every node it leaves;
+// bit 0 of `v` gets that sum, to be XORed with the leaf's bit.  No party index
+// is needed: t is bit 0 of the seed.  The correction word of the next level is
+// loaded before this level's hash, which covers its latency from HBM.
+template <bool DCF>
+__device__ __forceinline__ uint4 walk_leaf(const uint8_t* tree, uint64_t np, uint64_t row, uint32_t nbits, uint32_t x,
+                                           uint32_t vcw, uint32_t& v, const uint32_t* tab, LaneOff loff) {
+    const uint32_t nu = nbits - 7;              // at least 1
+    const uint64_t plane = 16 * np;
+    const uint8_t* p = tree + 16 * row;         // the row's word of plane 0 (the root), then of each level
+    uint4 s = *(const uint4*)p;
+    p += plane;
+    uint4 cw = *(const uint4*)p;
+    uint32_t hv = 0, tv = 0;                    // value bits (bit 1), t * VCW_i (bit 0)
+    x <<= 32 - nbits;
+    for (uint32_t i = 0; i < nu; i++) {
+        p += plane;
+        if (DCF && i + 1 == nu) p += 4 * np;    // the VCW plane sits before the leaf word's
+        const uint4 next = *(const uint4*)p;
+        uint4 h = tree_hash(s, tab, loff);
+        if (DCF) {
+            hv ^= h.x;
+            tv ^= s.x & vcw;
+            vcw >>= 1;
+        }
+        h.x &= ~2u;
+        s = child(s, h, cw, x >> 31);
+        x <<= 1;
+        cw = next;
     }
-    return block_bit(leaf(s, at<uint4>(key, P.cwleaf(), row), tab, loff), x & 127u);
+    v = (hv >> 1) ^ tv;
+    return leaf(s, cw, tab, loff);
 }
 
-// A party's share of [lo <= x < hi]: DCF_U(x) ^ DCF_L(x) ^ c_b, both walks in
-// step over the nu high bits, each adding v ^ t * VCW_i of the node it leaves;
-// then each DCF's 128-bit leaf answers the low 7 bits.
-__device__ __forceinline__ uint32_t range_eval(const uint8_t* key, uint64_t np, uint64_t row, uint32_t nbits,
-                                               uint32_t x, const uint32_t* tab, LaneOff loff) {
+// A party's DPF output bit at x.
+__device__ __forceinline__ uint32_t dpf_eval(const uint8_t* key, uint64_t np, uint64_t row, uint32_t nbits,
+                                             uint32_t x, const uint32_t* tab, LaneOff loff) {
+    uint32_t v;
+    return block_bit(walk_leaf<false>(key, np, row, nbits, x, 0u, v, tab, loff), x & 127u);
+}
+
+// One tree's half of a party's share of [lo <= x < hi] = DCF_U(x) ^ DCF_L(x) ^
+// c_b: lower = 0 the upper DCF with the wrap share c_b (bit 31 of its VCW
+// word), lower = 1 the lower DCF.  The two halves XOR to the share.
+__device__ __forceinline__ uint32_t range_half(const uint8_t* key, uint64_t np, uint64_t row, uint32_t nbits,
+                                               uint32_t x, uint32_t lower, const uint32_t* tab, LaneOff loff) {
     const DcfPlanes P{np, nbits - 7};
-    const uint8_t* ku = key;
-    const uint8_t* kl = key + P.bytes();
-    uint4 su = at<uint4>(ku, P.root(), row);
-    uint4 sl = at<uint4>(kl, P.root(), row);
-    const uint32_t vcu = at<uint32_t>(ku, P.vcw(), row);
-    const uint32_t vcl = at<uint32_t>(kl, P.vcw(), row);
-    uint32_t v = 0;
-    for (uint32_t i = 0; i < P.nu; i++) {
-        const uint4 cwu = at<uint4>(ku, P.cw(i), row);
-        const uint4 cwl = at<uint4>(kl, P.cw(i), row);
-        const uint32_t xi = (x >> (nbits - 1 - i)) & 1u;
-        uint32_t vu, vl;
-        const uint4 hu = expand(su, vu, tab, loff);
-        const uint4 hl = expand(sl, vl, tab, loff);
-        v ^= vu ^ vl ^ (su.x & (vcu >> i)) ^ (sl.x & (vcl >> i));
-        su = child(su, hu, cwu, xi);
-        sl = child(sl, hl, cwl, xi);
-    }
-    const uint4 gu = leaf(su, at<uint4>(ku, P.cwleaf(), row), tab, loff);
-    const uint4 gl = leaf(sl, at<uint4>(kl, P.cwleaf(), row), tab, loff);
-    const uint32_t idx = x & 127u;
-    return (v ^ block_bit(gu, idx) ^ block_bit(gl, idx) ^ (vcu >> 31)) & 1u;
+    const uint8_t* tree = key + (lower ? P.bytes() : 0);
+    const uint32_t vcw = at<uint32_t>(tree, P.vcw(), row);
+    uint32_t v;
+    const uint4 g = walk_leaf<true>(tree, np, row, nbits, x, vcw, v, tab, loff);
+    return (v ^ block_bit(g, x & 127u) ^ (lower ? 0u : vcw >> 31)) & 1u;
 }
 
 struct EvalDesc {
@@ -202,46 +222,65 @@ struct EvalDesc {
     uint32_t kind;
     uint32_t nbits;
     uint32_t party;
-    uint32_t block_start;   // first workgroup of this descriptor
+    uint32_t tile_start;    // first tile of this descriptor (wave tiles, or the queue's row tiles)
 };
 
-struct EvalBatch {
-    uint32_t count;
-    uint32_t total_blocks;
-    EvalDesc d[kEvalInline];
-};
+// Evaluation works in wave tiles of 64 walks: 64 rows of an equality
+// predicate, 32 rows of a range (the upper tree on lanes 0-31, the lower one
+// on lanes 32-63).
+__host__ __device__ inline uint64_t eval_tiles(uint32_t kind, uint64_t n) {
+    return kind == FSS_EQ ? (n + 63) >> 6 : (n + 31) >> 5;
+}
 
-// One workgroup-sized slice of rows [row0, row0 + kBlock) of descriptor D:
-// every thread evaluates one row, each wave stores its 64 bits as two words.
-__device__ __forceinline__ void eval_rows(const EvalDesc& D, uint64_t row0, const uint32_t* tab, LaneOff loff) {
-    const uint64_t row = row0 + threadIdx.x;
+// Wave tile `tile` of descriptor D (the same on every lane): the wave's
+// ballot gives two packed words of an equality, or a range's one word as the
+// XOR of its halves.
+__device__ __forceinline__ void eval_tile(const EvalDesc& D, uint64_t tile, const uint32_t* tab, LaneOff loff) {
+    const uint32_t lane = threadIdx.x & 63u;
     const uint64_t np = pad_rows(D.n);
     uint32_t bit = 0;
-    if (row < D.n) {
-        const uint32_t x = D.xhat[row];
-        if (D.kind == FSS_EQ)
-            bit = dpf_eval(D.key, np, row, D.nbits, x, tab, loff);
-        else
-            bit = range_eval(D.key, np, row, D.nbits, x, tab, loff);
-    }
-    const uint64_t ballot = __ballot(bit);
-    if ((threadIdx.x & 63u) == 0) {
-        const uint64_t w = row >> 5;          // row is a multiple of 64 here
-        const uint64_t nwords = (D.n + 31) >> 5;
-        if (w < nwords) D.out[w] = (uint32_t)ballot;
-        if (w + 1 < nwords) D.out[w + 1] = (uint32_t)(ballot >> 32);
+    if (D.kind == FSS_EQ) {
+        const uint64_t row = tile * 64 + lane;
+        if (row < D.n) bit = dpf_eval(D.key, np, row, D.nbits, D.xhat[row], tab, loff);
+        const uint64_t ballot = __ballot(bit);
+        if (lane == 0) {
+            const uint64_t w = 2 * tile;
+            D.out[w] = (uint32_t)ballot;
+            if (w + 1 < ((D.n + 31) >> 5)) D.out[w + 1] = (uint32_t)(ballot >> 32);
+        }
+    } else {
+        const uint64_t row = tile * 32 + (lane & 31u);
+        if (row < D.n) bit = range_half(D.key, np, row, D.nbits, D.xhat[row], lane >> 5, tab, loff);
+        const uint64_t ballot = __ballot(bit);
+        if (lane == 0) D.out[tile] = (uint32_t)ballot ^ (uint32_t)(ballot >> 32);
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_eval(EvalBatch batch) {
+struct EvalBatch {
+    uint32_t count;
+    uint32_t total_tiles;
+    uint32_t per;           // tiles per wave
+    EvalDesc d[kEvalInline];
+};
+
+// A workgroup takes `per` consecutive tiles per wave, its waves side by side
+// (their key reads stay together: tiles dealt out wave by wave over the grid
+// cost 11% at 2^23 rows).
+__global__ __launch_bounds__(kBlock, 8) void k_eval(EvalBatch batch) {
     __shared__ uint32_t tab[kLdsTableWords];
     lds_table_fill(tab, g_tables.t0);
     __syncthreads();
-
-    uint32_t di = 0;
-    while (di + 1 < batch.count && blockIdx.x >= batch.d[di + 1].block_start) di++;
-    const EvalDesc& D = batch.d[di];
-    eval_rows(D, (uint64_t)(blockIdx.x - D.block_start) * kBlock, tab, lane_offset());
+    const LaneOff loff = lane_offset();
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t waves = blockDim.x >> 6;
+    for (uint32_t k = 0; k < batch.per; k++) {
+        const uint32_t tile = (blockIdx.x * batch.per + k) * waves + wave;
+        if (tile >= batch.total_tiles) break;
+        uint32_t di = 0;
+        while (di + 1 < batch.count && tile >= batch.d[di + 1].tile_start) di++;
+        const EvalDesc& D = batch.d[di];
+        eval_tile(D, tile - D.tile_start, tab, loff);
+    }
 }
 
 // ----------------------------------------------------------------- dealer (keys, triples)
@@ -421,7 +460,7 @@ struct QKeygen {
 };
 
 struct QEval {
-    EvalDesc d;             // d.block_start = first tile; tiles of kBlock * rows_per_thread rows
+    EvalDesc d;             // d.tile_start = first tile; tiles of kBlock * rows_per_thread rows
 };
 
 __global__ void k_zero_counter(uint32_t* c) {
@@ -488,13 +527,16 @@ __global__ __launch_bounds__(kBlock, 8) void k_eval_queue(const QEval* __restric
     __shared__ uint32_t s_tile;
     lds_table_fill(tab, g_tables.t0);
     const LaneOff loff = lane_offset();
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     for (;;) {
-        const uint32_t tile = next_tile(counter, &s_tile);
+        const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_tile(counter, &s_tile));
         if (tile >= total_tiles) break;
-        const uint32_t di = find_desc(count, tile, [&](uint32_t i) { return q[i].d.block_start; });
+        const uint32_t di = find_desc(count, tile, [&](uint32_t i) { return q[i].d.tile_start; });
         const EvalDesc& D = q[di].d;
-        const uint64_t row0 = (uint64_t)(tile - D.block_start) * kBlock * rows_per_thread;
-        for (uint32_t k = 0; k < rows_per_thread; k++) eval_rows(D, row0 + (uint64_t)k * kBlock, tab, loff);
+        // the wave tiles of the queue tile's rows, one wave after another
+        const uint32_t per = (D.kind == FSS_EQ ? kBlock / 64 : kBlock / 32) * rows_per_thread;
+        const uint64_t first = (uint64_t)(tile - D.tile_start) * per, all = eval_tiles(D.kind, D.n);
+        for (uint32_t k = wave; k < per && first + k < all; k += kBlock / 64) eval_tile(D, first + k, tab, loff);
     }
 }
 
@@ -558,36 +600,15 @@ __global__ __launch_bounds__(kBlock) void k_triples(TripleArgs A) {
 
 // ----------------------------------------------------------------- one-hot RSS secEval (Eq. predEval)
 
-// Full-domain evaluation: key row `row` of a batch (party `party`) at every
-// point x in [0, npoints); each wave packs its 64 bits.
-__global__ __launch_bounds__(kBlock) void k_eval_points(const uint8_t* key, uint64_t n, uint64_t row, uint32_t kind,
-                                                       uint32_t nbits, uint32_t party, uint64_t npoints,
-                                                       uint32_t* out) {
-    __shared__ uint32_t tab[kLdsTableWords];
-    lds_table_fill(tab, g_tables.t0);
-    __syncthreads();
-    const uint64_t x = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    const LaneOff loff = lane_offset();
-    const uint64_t np = pad_rows(n);
-    uint32_t bit = 0;
-    if (x < npoints) {
-        if (kind == FSS_EQ)
-            bit = dpf_eval(key, np, row, nbits, (uint32_t)x, tab, loff);
-        else
-            bit = range_eval(key, np, row, nbits, (uint32_t)x, tab, loff);
-    }
-    const uint64_t ballot = __ballot(bit);
-    if ((threadIdx.x & 63u) == 0) {
-        const uint64_t w = x >> 5, nwords = (npoints + 31) >> 5;
-        if (w < nwords) out[w] = (uint32_t)ballot;
-        if (w + 1 < nwords) out[w + 1] = (uint32_t)(ballot >> 32);
-    }
-}
-
-// Several full-domain evaluations in one launch (blockIdx.y = request): the
-// six keys of one secEval predicate (two per server) are small and
-// latency-bound, so they run side by side instead of one after another.
+// Full-domain evaluation of one key at every point x in [0, npoints).  The
+// 128 points of a leaf share one walk, so a lane walks to its leaf and answers
+// them all: four packed words (a range's two trees on lanes l and l + 32 of a
+// wave).  Up to eight requests run in one launch (blockIdx.y = request): the
+// six keys of one secEval predicate are small and latency-bound.  Six range
+// keys over 2,000 points (192 walks of 5 hashes in all): 11 us, against 33 us
+// with a pair of walks per point.
 constexpr int kEvalAllMax = 8;
+constexpr int kEvalAllBlock = 256;
 
 struct EvalAllReq {
     const uint8_t* key;         // this party's key batch
@@ -597,35 +618,56 @@ struct EvalAllReq {
     uint64_t npoints;
     uint32_t kind;
     uint32_t nbits;
-    uint32_t party;
-    uint32_t pad;
 };
 
 struct EvalAllBatch {
     EvalAllReq r[kEvalAllMax];
 };
 
-__global__ __launch_bounds__(kBlock) void k_eval_points_batch(EvalAllBatch B) {
+__global__ __launch_bounds__(kEvalAllBlock) void k_eval_points(EvalAllBatch B) {
     const EvalAllReq& R = B.r[blockIdx.y];
-    if ((uint64_t)blockIdx.x * kBlock >= R.npoints) return;     // the whole block leaves
+    const uint64_t leaves = (R.npoints + 127) >> 7;
+    const uint32_t per = R.kind == FSS_EQ ? 64 : 32;                       // leaves per wave
+    const uint64_t leaf0 = (uint64_t)blockIdx.x * (kEvalAllBlock / 64) * per;
+    if (leaf0 >= leaves) return;                                           // the whole block leaves
     __shared__ uint32_t tab[kLdsTableWords];
     lds_table_fill(tab, g_tables.t0);
     __syncthreads();
-    const uint64_t x = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
     const LaneOff loff = lane_offset();
     const uint64_t np = pad_rows(R.n);
-    uint32_t bit = 0;
-    if (x < R.npoints) {
-        if (R.kind == FSS_EQ)
-            bit = dpf_eval(R.key, np, R.row, R.nbits, (uint32_t)x, tab, loff);
-        else
-            bit = range_eval(R.key, np, R.row, R.nbits, (uint32_t)x, tab, loff);
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint64_t j = leaf0 + (threadIdx.x >> 6) * per + (lane & (per - 1));   // this lane's leaf
+    uint4 g = make_uint4(0u, 0u, 0u, 0u);
+    if (j < leaves) {
+        const uint32_t x = (uint32_t)j << 7;
+        uint32_t v = 0;
+        if (R.kind == FSS_EQ) {
+            g = walk_leaf<false>(R.key, np, R.row, R.nbits, x, 0u, v, tab, loff);
+        } else {
+            const DcfPlanes P{np, R.nbits - 7};
+            const uint32_t lower = lane >> 5;
+            const uint8_t* tree = R.key + (lower ? P.bytes() : 0);
+            const uint32_t vcw = at<uint32_t>(tree, P.vcw(), R.row);
+            g = walk_leaf<true>(tree, np, R.row, R.nbits, x, vcw, v, tab, loff);
+            const uint32_t flip = 0u - ((v ^ (lower ? 0u : vcw >> 31)) & 1u);
+            g = make_uint4(g.x ^ flip, g.y ^ flip, g.z ^ flip, g.w ^ flip);
+        }
     }
-    const uint64_t ballot = __ballot(bit);
-    if ((threadIdx.x & 63u) == 0) {
-        const uint64_t w = x >> 5, nwords = (R.npoints + 31) >> 5;
-        if (w < nwords) R.out[w] = (uint32_t)ballot;
-        if (w + 1 < nwords) R.out[w + 1] = (uint32_t)(ballot >> 32);
+    if (R.kind != FSS_EQ) {                                                // XOR of the two trees
+        g.x ^= (uint32_t)__shfl_xor((int)g.x, 32);
+        g.y ^= (uint32_t)__shfl_xor((int)g.y, 32);
+        g.z ^= (uint32_t)__shfl_xor((int)g.z, 32);
+        g.w ^= (uint32_t)__shfl_xor((int)g.w, 32);
+        if (lane >= 32) return;
+    }
+    if (j >= leaves) return;
+    const uint32_t w[4] = {g.x, g.y, g.z, g.w};
+#pragma unroll
+    for (uint32_t k = 0; k < 4; k++) {
+        const uint64_t first = 128 * j + 32 * k;                           // first point of the word
+        if (first >= R.npoints) break;
+        const uint64_t left = R.npoints - first;
+        R.out[4 * j + k] = left >= 32 ? w[k] : w[k] & ((1u << (uint32_t)left) - 1u);
     }
 }
 
@@ -1114,23 +1156,44 @@ int check_batch(const fss_keybatch* k, int32_t want_kind, const char* who) {
     return FSS_OK;
 }
 
-// Enqueue one k_eval launch for up to kEvalInline descriptors (heaviest first).
+// Workgroup size and grid of a launch of `tiles` wave tiles of an AES kernel.
+// Up to 16 waves in each of the two workgroups per CU that the LDS tables
+// allow, every wave takes one tile and the workgroups are as small as spreads
+// them over the chip, so that the launch takes one tile's latency (three
+// predicates over 1,024 vertices and 8,192 edges: 52 us, against 148 us with
+// 1024-thread workgroups; four over 10,000: 61 us, against 154).  Beyond that the workgroups are dispatched as others
+// end; a wave of theirs takes up to four tiles, which keeps the table fill
+// under 1%, but no more than leaves four workgroups for every slot.
+struct TileShape {
+    unsigned grid, block, per;
+};
+
+TileShape tile_shape(uint64_t tiles) {
+    const uint64_t wgs = 2ull * (uint64_t)device_cus();
+    const uint64_t waves = std::min<uint64_t>(std::max<uint64_t>((tiles + wgs - 1) / wgs, 1), kBlock / 64);
+    const uint64_t per = std::min<uint64_t>(std::max<uint64_t>(tiles / (4 * wgs * waves), 1), 4);
+    const uint64_t grid = (tiles + waves * per - 1) / (waves * per);
+    return TileShape{(unsigned)std::max<uint64_t>(grid, 1), (unsigned)(64 * waves), (unsigned)per};
+}
+
+// Enqueue one k_eval launch for up to kEvalInline descriptors, ranges first.
 int launch_eval(EvalDesc* descs, uint32_t count, hipStream_t stream) {
-    // range walks cost ~2.5x an equality walk: put them first so the tail is light
     EvalBatch b{};
     uint32_t k = 0;
     for (int pass = 0; pass < 2; pass++)
         for (uint32_t i = 0; i < count; i++)
             if ((pass == 0) == (descs[i].kind == FSS_RANGE) && descs[i].n > 0) b.d[k++] = descs[i];
     b.count = k;
-    uint32_t blocks = 0;
+    uint64_t tiles = 0;
     for (uint32_t i = 0; i < k; i++) {
-        b.d[i].block_start = blocks;
-        blocks += (uint32_t)((b.d[i].n + kBlock - 1) / kBlock);
+        b.d[i].tile_start = (uint32_t)tiles;
+        tiles += eval_tiles(b.d[i].kind, b.d[i].n);
     }
-    b.total_blocks = blocks;
-    if (blocks == 0) return FSS_OK;
-    hipLaunchKernelGGL(k_eval, dim3(blocks), dim3(kBlock), 0, stream, b);
+    if (tiles == 0) return FSS_OK;
+    b.total_tiles = (uint32_t)tiles;     // at most 16 * 2^27
+    const TileShape t = tile_shape(tiles);
+    b.per = t.per;
+    hipLaunchKernelGGL(k_eval, dim3(t.grid), dim3(t.block), 0, stream, b);
     return check_launch("k_eval");
 }
 
@@ -1915,7 +1978,7 @@ int launch_eval_queue(std::vector<EvalDesc>& descs, void* d_ws, uint64_t ws_byte
     const uint64_t tile_rows = (uint64_t)kBlock * g_tuning.rows_per_thread;
     uint64_t tiles = 0;
     for (auto& e : q) {
-        e.d.block_start = (uint32_t)tiles;
+        e.d.tile_start = (uint32_t)tiles;
         tiles += (e.d.n + tile_rows - 1) / tile_rows;
     }
     if (tiles > 0xFFFFFFF0ull) return fail(FSS_EUNSUPPORTED, "batch: too many tiles");
@@ -2117,6 +2180,31 @@ int match_query(const match_plan* P, int32_t party_mask, void* stream) {
 
 uint64_t fss_queue_workspace_bytes(uint64_t count) { return queue_bytes(count); }
 
+static EvalAllReq eval_all_req(const uint8_t* key, uint32_t* out, const fss_keybatch* k, uint64_t row,
+                               uint64_t npoints) {
+    EvalAllReq e{};
+    e.key = key;
+    e.out = out;
+    e.n = k->n;
+    e.row = row;
+    e.npoints = npoints;
+    e.kind = (uint32_t)k->kind;
+    e.nbits = k->nbits;
+    return e;
+}
+
+// The first m requests of B, side by side.
+static int launch_eval_all(const EvalAllBatch& B, uint32_t m, hipStream_t s) {
+    uint64_t blocks = 0;
+    for (uint32_t j = 0; j < m; j++) {
+        const uint64_t per = (kEvalAllBlock / 64) * (B.r[j].kind == FSS_EQ ? 64 : 32);
+        blocks = std::max(blocks, ((B.r[j].npoints + 127) / 128 + per - 1) / per);
+    }
+    if (blocks == 0) return FSS_OK;
+    hipLaunchKernelGGL(k_eval_points, dim3((unsigned)blocks, m), dim3(kEvalAllBlock), 0, s, B);
+    return check_launch("k_eval_points");
+}
+
 int fss_eval_all(int32_t party, const fss_keybatch* k, uint64_t key_row, uint64_t npoints, uint32_t* d_out_bits,
                  void* stream) {
     ogm::last_error().clear();
@@ -2129,10 +2217,9 @@ int fss_eval_all(int32_t party, const fss_keybatch* k, uint64_t key_row, uint64_
     if (npoints > (1ull << k->nbits)) return fail(FSS_EINVAL, "fss_eval_all: more points than the domain");
     if (npoints == 0) return FSS_OK;
     if (!d_out_bits || !k->key[party] || !aligned256(k->key[party])) return fail(FSS_EINVAL, "fss_eval_all: buffers");
-    hipLaunchKernelGGL(k_eval_points, dim3((unsigned)((npoints + kBlock - 1) / kBlock)), dim3(kBlock), 0,
-                       (hipStream_t)stream, (const uint8_t*)k->key[party], k->n, key_row, (uint32_t)k->kind,
-                       k->nbits, (uint32_t)party, npoints, d_out_bits);
-    return check_launch("k_eval_points");
+    EvalAllBatch B{};
+    B.r[0] = eval_all_req((const uint8_t*)k->key[party], d_out_bits, k, key_row, npoints);
+    return launch_eval_all(B, 1, (hipStream_t)stream);
 }
 
 int fss_eval_all_batch(const fss_eval_all_req* reqs, uint32_t count, void* stream) {
@@ -2153,25 +2240,12 @@ int fss_eval_all_batch(const fss_eval_all_req* reqs, uint32_t count, void* strea
     }
     for (uint32_t i0 = 0; i0 < count; i0 += kEvalAllMax) {
         EvalAllBatch B{};
-        uint64_t blocks = 0;
         const uint32_t m = count - i0 < (uint32_t)kEvalAllMax ? count - i0 : (uint32_t)kEvalAllMax;
         for (uint32_t j = 0; j < m; j++) {
             const fss_eval_all_req& r = reqs[i0 + j];
-            EvalAllReq& e = B.r[j];
-            e.key = (const uint8_t*)r.keys->key[r.party];
-            e.out = r.d_out_bits;
-            e.n = r.keys->n;
-            e.row = r.key_row;
-            e.npoints = r.npoints;
-            e.kind = (uint32_t)r.keys->kind;
-            e.nbits = r.keys->nbits;
-            e.party = (uint32_t)r.party;
-            const uint64_t b = (r.npoints + kBlock - 1) / kBlock;
-            blocks = b > blocks ? b : blocks;
+            B.r[j] = eval_all_req((const uint8_t*)r.keys->key[r.party], r.d_out_bits, r.keys, r.key_row, r.npoints);
         }
-        if (blocks == 0) continue;
-        hipLaunchKernelGGL(k_eval_points_batch, dim3((unsigned)blocks, m), dim3(kBlock), 0, (hipStream_t)stream, B);
-        int rc = check_launch("k_eval_points_batch");
+        const int rc = launch_eval_all(B, m, (hipStream_t)stream);
         if (rc) return rc;
     }
     return FSS_OK;
@@ -2428,7 +2502,7 @@ int fss_eval_batch_noalloc(const fss_eval_req* reqs, uint32_t count, void* strea
         for (uint32_t j = 0; j < nq; j++) {
             QEval e{};
             eval_request(reqs[order[first + j]], order[first + j], who, &e.d);   // checked above
-            e.d.block_start = (uint32_t)tile;
+            e.d.tile_start = (uint32_t)tile;
             tile += (e.d.n + tile_rows - 1) / tile_rows;
             memcpy((uint8_t*)c.w + (size_t)j * sizeof(QEval), &e, sizeof(QEval));
         }

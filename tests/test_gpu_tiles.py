@@ -1,0 +1,86 @@
+"""Evaluation at the edges of its wave tiles (64 rows of an equality, 32 rows
+of a range) and of its launch shapes (one wave per workgroup up to 16, then
+several tiles per wave), and full-domain evaluation at the edges of its
+128-point leaves: every sampled share equal to the oracle's, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import DEV, T, U
+from oracle import fss as ofss
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fss():
+    from paper_2209_03526_amd import fss as lib
+    return lib
+
+
+def _rand_u32(seed, n):
+    return np.random.default_rng(seed).integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+
+
+def _check(fss, kind, nbits, n):
+    seed = 1234 + n
+    top = (1 << nbits) - 1
+    r, x = _rand_u32(seed, n), _rand_u32(seed + 1, n) & np.uint32(top)
+    a, hi = (int(x[n // 2]), 0) if kind == 0 else sorted((int(x[0]), int(x[-1]) or 1))
+    xhat = (x.astype(np.uint64) + r).astype(np.uint32)
+    kb = fss.KeyBatch(kind, nbits, n)
+    fss.fss_keygen(seed, 3, 1, a, hi, T(r), kb)
+    rows = np.arange(n) if n <= 20000 else np.unique(np.concatenate(
+        [np.arange(70), np.arange(n - 70, n), np.random.default_rng(n).integers(0, n, 3000)]))
+    if kind == 0:
+        keys = ofss.keygen_eq(nbits, seed, 3, 1, a, r[rows], rows=rows)
+    else:
+        keys = ofss.keygen_range(nbits, seed, 3, 1, a, hi, r[rows], rows=rows)
+    run, ev = (fss.fss_eval_eq, ofss.eval_eq) if kind == 0 else (fss.fss_eval_lt, ofss.eval_range)
+    nw = (n + 31) // 32
+    recon = np.zeros(nw, np.uint32)
+    for b in range(2):
+        out = torch.full((nw + 3,), -1, dtype=torch.int32, device=DEV)
+        run(b, kb, T(xhat), out)
+        got = U(out)
+        assert (got[nw:] == 0xFFFFFFFF).all()                 # nothing past the last word
+        if n % 32:
+            assert got[nw - 1] >> (n % 32) == 0               # pad bits
+        want = ev(nbits, b, keys[b], xhat[rows])
+        np.testing.assert_array_equal(ofss.unpack_bits(got[:nw], n)[rows], want)
+        recon ^= got[:nw]
+    truth = (x == a) if kind == 0 else ((x >= a) & (x < hi))
+    np.testing.assert_array_equal(ofss.unpack_bits(recon, n), truth.astype(np.uint8))
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("nbits,n", [(32, 31), (32, 32), (32, 33), (8, 63), (32, 64), (12, 65), (32, 16383),
+                                     (32, 16385), (32, 32769), (32, 300001)])
+def test_eval_tile_edges(fss, kind, nbits, n):
+    _check(fss, kind, nbits, n)
+
+
+def test_eval_several_tiles_per_wave(fss):
+    """2^21 + 33 range rows: 65,538 wave tiles, more than one per wave."""
+    _check(fss, 1, 32, (1 << 21) + 33)
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("nbits,npoints", [(8, 1), (8, 127), (8, 256), (9, 129), (16, 4097), (16, 33000), (17, 65537)])
+def test_eval_all_leaf_edges(fss, kind, nbits, npoints):
+    """A wave walks 64 leaves of an equality or 32 of a range, a workgroup four waves."""
+    seed, row = 77 + npoints, 1
+    r = np.zeros(3, np.uint32)
+    a, hi = (1 << nbits) // 3, (1 << nbits) - 2
+    kb = fss.KeyBatch(kind, nbits, 3)
+    fss.fss_keygen(seed, 9, 0, a, hi if kind else 0, T(r), kb)
+    keys = (ofss.keygen_range(nbits, seed, 9, 0, a, hi, r) if kind else ofss.keygen_eq(nbits, seed, 9, 0, a, r))
+    ev = ofss.eval_range if kind else ofss.eval_eq
+    xs = np.arange(npoints, dtype=np.uint32)
+    nw = (npoints + 31) // 32
+    for b in range(2):
+        out = torch.full((nw + 3,), -1, dtype=torch.int32, device=DEV)
+        fss.fss_eval_all(b, kb, row, npoints, out)
+        want = ofss.pack_bits(ev(nbits, b, np.repeat(keys[b][row:row + 1], npoints, axis=0), xs))
+        np.testing.assert_array_equal(U(out, nw), want)
+        assert (U(out)[nw:] == 0xFFFFFFFF).all()
