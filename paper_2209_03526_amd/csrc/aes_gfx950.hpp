@@ -252,6 +252,12 @@ __device__ __forceinline__ uint4 and4(uint4 a, uint32_t m) {
     return make_uint4(a.x & m, a.y & m, a.z & m, a.w & m);
 }
 
+// a ^ (b & m), one v_bitop3_b32 a word (truth table 0x78).
+__device__ __forceinline__ uint4 xor_and4(uint4 a, uint4 b, uint32_t m) {
+    return make_uint4(__builtin_amdgcn_bitop3_b32(a.x, b.x, m, 0x78), __builtin_amdgcn_bitop3_b32(a.y, b.y, m, 0x78),
+                      __builtin_amdgcn_bitop3_b32(a.z, b.z, m, 0x78), __builtin_amdgcn_bitop3_b32(a.w, b.w, m, 0x78));
+}
+
 // The linear orthomorphism sigma(a || b) = (a ^ b) || a on the two 64-bit
 // halves of a block (a = bytes 0..7, words x and y).
 __device__ __forceinline__ uint4 sigma(uint4 s) { return make_uint4(s.x ^ s.z, s.y ^ s.w, s.x, s.y); }

@@ -130,8 +130,7 @@ __device__ __forceinline__ uint4 expand(uint4 s, uint32_t& v, const uint32_t* ta
 // The child of s on side xi: h' ^ t(s) * cw ^ xi * s.
 __device__ __forceinline__ uint4 child(uint4 s, uint4 h, uint4 cw, uint32_t xi) {
     const uint32_t tm = 0u - (s.x & 1u), xm = 0u - xi;
-    return make_uint4(xor3(h.x, cw.x & tm, s.x & xm), xor3(h.y, cw.y & tm, s.y & xm),
-                      xor3(h.z, cw.z & tm, s.z & xm), xor3(h.w, cw.w & tm, s.w & xm));
+    return xor_and4(xor_and4(h, cw, tm), s, xm);
 }
 
 // Leaf block of node s under its correction word: H(s ^ 2) ^ t(s) * cwleaf
@@ -139,7 +138,7 @@ __device__ __forceinline__ uint4 child(uint4 s, uint4 h, uint4 cw, uint32_t xi) 
 __device__ __forceinline__ uint4 leaf(uint4 s, uint4 cwleaf, const uint32_t* tab, LaneOff loff) {
     uint4 u = s;
     u.x ^= 2u;
-    return xor4(tree_hash(u, tab, loff), and4(cwleaf, 0u - (s.x & 1u)));
+    return xor_and4(tree_hash(u, tab, loff), cwleaf, 0u - (s.x & 1u));
 }
 
 // Bit idx (0..127) of a 128-bit block.
@@ -404,45 +403,67 @@ __device__ __forceinline__ void tree_roots(const DealerArgs& A, uint32_t j, uint
     s = b ? xor4(s0, delta) : s0;
 }
 
-// Both lanes of row `row`'s pair (b = party of this lane); KIND is the key kind.
+// The dealer works in wave tiles of 32 rows of one tree: lane 2i is party 0,
+// lane 2i + 1 party 1 of the tile's row i.  A range's two trees are two tiles
+// (tile 2k the upper DCF of rows 32k .., tile 2k + 1 the lower one): one after
+// the other on one lane pair they are a chain of 55 blocks (8,192 equality and
+// 1,024 range rows in 1024-thread workgroups: 78 and 148 us; in tiles spread
+// over the chip: 53 and 49 us; 2^20 range rows: 1.3-1.6 ms either way).
+__host__ __device__ inline uint64_t keygen_tiles(uint32_t kind, uint64_t n) {
+    const uint64_t t = (n + 31) >> 5;
+    return kind == FSS_EQ ? t : 2 * t;
+}
+
 template <int KIND>
-__device__ __forceinline__ void keygen_row(const DealerArgs& A, uint64_t row, uint32_t b, const uint32_t* tab,
-                                           LaneOff loff) {
+__device__ __forceinline__ void keygen_tile(const DealerArgs& A, uint64_t tile, const uint32_t* tab, LaneOff loff) {
+    const uint32_t lane = threadIdx.x & 63u, b = lane & 1u;
+    const uint32_t lower = KIND == FSS_EQ ? 0u : (uint32_t)tile & 1u;
+    const uint64_t row = (KIND == FSS_EQ ? tile : tile >> 1) * 32 + (lane >> 1);
+    if (row >= A.n) return;                 // both lanes of a pair leave together
     const uint64_t np = pad_rows(A.n);
     const uint32_t mask = A.nbits >= 32 ? 0xFFFFFFFFu : ((1u << A.nbits) - 1u);
     const uint32_t r = A.r[row];
     const uint32_t e = (uint32_t)row + A.row_offset;
     uint8_t* key = b ? A.key1 : A.key0;
     uint4 s, delta;
-    tree_roots(A, 0, e, b, s, delta, tab, loff);
+    tree_roots(A, lower ? 3u : 0u, e, b, s, delta, tab, loff);
     if (KIND == FSS_EQ) {
         tree_gen<false>(key, np, row, A.nbits, (A.a_or_lo + r) & mask, s, delta, 0u, tab, loff);
     } else {
         const uint32_t U = (A.hi + r) & mask, L = (A.a_or_lo + r) & mask;
-        uint32_t c0 = rng_block(A.rk, 3, 2, A.query, A.pred, e, tab, loff).x & 1u;
-        pin_in_vgprs(c0);
-        const uint32_t cb = c0 ^ (b & (L > U ? 1u : 0u));
-        tree_gen<true>(key, np, row, A.nbits, U, s, delta, cb, tab, loff);
-        tree_roots(A, 3, e, b, s, delta, tab, loff);
-        tree_gen<true>(key + DcfPlanes{np, A.nbits - 7}.bytes(), np, row, A.nbits, L, s, delta, 0u, tab, loff);
+        uint32_t cb = 0;                    // the wrap share goes with the upper tree
+        if (!lower) {
+            uint32_t c0 = rng_block(A.rk, 3, 2, A.query, A.pred, e, tab, loff).x & 1u;
+            pin_in_vgprs(c0);
+            cb = c0 ^ (b & (L > U ? 1u : 0u));
+        }
+        tree_gen<true>(key + (lower ? DcfPlanes{np, A.nbits - 7}.bytes() : 0), np, row, A.nbits, lower ? L : U, s,
+                       delta, cb, tab, loff);
     }
 }
 
-// Two lanes per row (see above); 512 rows per workgroup.  One kernel per key
-// kind, so each is compiled for its own Gen alone.
+// One kernel per key kind, so each is compiled for its own Gen alone.  A
+// workgroup takes `per` consecutive tiles per wave, its waves side by side.
 template <int KIND>
-__device__ __forceinline__ void keygen_grid(const DealerArgs& A) {
+__device__ __forceinline__ void keygen_grid(const DealerArgs& A, uint32_t tiles, uint32_t per) {
     __shared__ uint32_t tab[kLdsTableWords];
     lds_table_fill(tab, g_tables.t0);
     __syncthreads();
-    const uint64_t gid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    const uint64_t row = gid >> 1;
-    if (row >= A.n) return;                 // both lanes of a pair leave together
-    keygen_row<KIND>(A, row, (uint32_t)(gid & 1u), tab, lane_offset());
+    const LaneOff loff = lane_offset();
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t waves = blockDim.x >> 6;
+    for (uint32_t k = 0; k < per; k++) {
+        const uint32_t tile = (blockIdx.x * per + k) * waves + wave;
+        if (tile < tiles) keygen_tile<KIND>(A, tile, tab, loff);
+    }
 }
 
-__global__ __launch_bounds__(kBlock) void k_keygen_eq(DealerArgs A) { keygen_grid<FSS_EQ>(A); }
-__global__ __launch_bounds__(kBlock) void k_keygen_range(DealerArgs A) { keygen_grid<FSS_RANGE>(A); }
+__global__ __launch_bounds__(kBlock, 8) void k_keygen_eq(DealerArgs A, uint32_t tiles, uint32_t per) {
+    keygen_grid<FSS_EQ>(A, tiles, per);
+}
+__global__ __launch_bounds__(kBlock, 8) void k_keygen_range(DealerArgs A, uint32_t tiles, uint32_t per) {
+    keygen_grid<FSS_RANGE>(A, tiles, per);
+}
 
 // ----------------------------------------------------------------- persistent work queue (batches)
 //
@@ -495,16 +516,17 @@ __device__ __forceinline__ void keygen_queue(const QKeygen* __restrict__ q, uint
     __shared__ uint32_t s_tile;
     lds_table_fill(tab, g_tables.t0);
     const LaneOff loff = lane_offset();
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     for (;;) {
-        const uint32_t tile = next_tile(counter, &s_tile);   // also orders the table fill
+        // (also orders the table fill)
+        const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_tile(counter, &s_tile));
         if (tile >= total_tiles) break;
         const uint32_t di = find_desc(count, tile, [&](uint32_t i) { return q[i].tile_start; });
         const DealerArgs& A = q[di].a;
-        const uint64_t row0 = (uint64_t)(tile - q[di].tile_start) * tile_mult * (kBlock / 2) + (threadIdx.x >> 1);
-        for (uint32_t k = 0; k < tile_mult; k++) {
-            const uint64_t row = row0 + (uint64_t)k * (kBlock / 2);
-            if (row < A.n) keygen_row<KIND>(A, row, threadIdx.x & 1u, tab, loff);
-        }
+        const uint32_t per = (uint32_t)keygen_tiles(KIND, kBlock / 2) * tile_mult;
+        const uint64_t first = (uint64_t)(tile - q[di].tile_start) * per, all = keygen_tiles(KIND, A.n);
+        for (uint32_t k = wave; k < per && first + k < all; k += kBlock / 64)
+            keygen_tile<KIND>(A, first + k, tab, loff);
     }
 }
 
@@ -1293,11 +1315,13 @@ int fss_keygen(uint64_t seed, uint32_t query_id, uint32_t pred_id, uint32_t a_or
     A.pred = pred_id;
     A.a_or_lo = a_or_lo;
     A.hi = hi;
-    const dim3 grid((unsigned)((2 * out->n + kBlock - 1) / kBlock));
+    const uint64_t tiles = keygen_tiles(A.kind, A.n);    // at most 2^28
+    const TileShape t = tile_shape(tiles);
     if (out->kind == FSS_EQ)
-        hipLaunchKernelGGL(k_keygen_eq, grid, dim3(kBlock), 0, (hipStream_t)stream, A);
+        hipLaunchKernelGGL(k_keygen_eq, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, (uint32_t)tiles, t.per);
     else
-        hipLaunchKernelGGL(k_keygen_range, grid, dim3(kBlock), 0, (hipStream_t)stream, A);
+        hipLaunchKernelGGL(k_keygen_range, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, (uint32_t)tiles,
+                           t.per);
     return check_launch("k_keygen");
 }
 

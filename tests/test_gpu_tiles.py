@@ -1,12 +1,14 @@
-"""Evaluation at the edges of its wave tiles (64 rows of an equality, 32 rows
-of a range) and of its launch shapes (one wave per workgroup up to 16, then
-several tiles per wave), and full-domain evaluation at the edges of its
-128-point leaves: every sampled share equal to the oracle's, bit for bit."""
+"""Evaluation and the dealer at the edges of their wave tiles (64 rows of an
+equality or 32 of a range; 32 rows of one tree) and of their launch shapes (one
+wave per workgroup up to 16, then several tiles per wave), and full-domain
+evaluation at the edges of its 128-point leaves: every share and key looked at
+equals the oracle's, bit for bit."""
 import numpy as np
 import pytest
 import torch
 
-from gpu_util import DEV, T, U
+from gpu_util import DEV, B, T, U
+from keylayout import from_device
 from oracle import fss as ofss
 
 pytestmark = pytest.mark.gpu
@@ -84,3 +86,19 @@ def test_eval_all_leaf_edges(fss, kind, nbits, npoints):
         want = ofss.pack_bits(ev(nbits, b, np.repeat(keys[b][row:row + 1], npoints, axis=0), xs))
         np.testing.assert_array_equal(U(out, nw), want)
         assert (U(out)[nw:] == 0xFFFFFFFF).all()
+
+
+@pytest.mark.parametrize("kind,nbits,n", [(0, 32, 31), (0, 8, 33), (1, 32, 32), (1, 9, 33), (1, 32, 8193),
+                                          (0, 32, 16417), (1, 32, 40000)])
+def test_keygen_tile_edges(fss, kind, nbits, n):
+    """The dealer's wave tiles: 32 rows of one tree, a range's two trees in two tiles."""
+    seed, r = 4321 + n, _rand_u32(n, n)
+    lo, hi = (1 << nbits) // 5, (1 << nbits) - 3
+    kb = fss.KeyBatch(kind, nbits, n)
+    for t in kb.key:
+        t.fill_(0xA5)
+    fss.fss_keygen(seed, 2, 5, lo, hi if kind else 0, T(r), kb)
+    want = ofss.keygen_range(nbits, seed, 2, 5, lo, hi, r) if kind else ofss.keygen_eq(nbits, seed, 2, 5, lo, r)
+    for b in range(2):
+        got = from_device(kind, nbits, n, B(kb.key[b], kb.bytes_per_party))
+        assert got.tobytes() == want[b].tobytes()
