@@ -151,7 +151,7 @@ __device__ __forceinline__ uint32_t block_bit(uint4 g, uint32_t idx) {
 //
 // One lane walks one tree: an equality row is one DPF walk, a range row two DCF
 // walks on two lanes.  A walk is a serial chain of nbits - 6 hashes of ten
-// dependent rounds, each an LDS round trip (2 us a hash on its own), so
+// dependent rounds, each an LDS round trip (1.6 us a hash on its own), so
 // a launch that does not fill the chip takes one chain's time, however few
 // rows it has; with enough waves the LDS read pipe binds instead.  A lane that
 // walked both trees of a range row held two chains: twice the latency for the
@@ -224,6 +224,13 @@ struct EvalDesc {
     uint32_t tile_start;    // first tile of this descriptor (wave tiles, or the queue's row tiles)
 };
 
+// The wave tile of this wave in a launch shaped by tile_shape: the waves of a
+// workgroup take consecutive tiles (a scalar: the same on every lane).
+__device__ __forceinline__ uint32_t launch_tile() {
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    return blockIdx.x * (blockDim.x >> 6) + wave;
+}
+
 // Evaluation works in wave tiles of 64 walks: 64 rows of an equality
 // predicate, 32 rows of a range (the upper tree on lanes 0-31, the lower one
 // on lanes 32-63).
@@ -255,31 +262,104 @@ __device__ __forceinline__ void eval_tile(const EvalDesc& D, uint64_t tile, cons
     }
 }
 
+// The same in quad tiles, for launches of few walks: a quad of lanes per walk
+// (16 rows of an equality, 8 of a range), so a tile's bits are two bytes or
+// one of a word.  The tiles cover the last word's pad bits.
+__host__ __device__ inline uint64_t eval_quad_tiles(uint32_t kind, uint64_t n) {
+    return ((n + 31) >> 5) * (kind == FSS_EQ ? 2 : 4);
+}
+
+// Bits 0, 4, 8, .. of x side by side.
+__device__ __forceinline__ uint32_t every_fourth(uint64_t x) {
+    x &= 0x1111111111111111ull;
+    x = (x | x >> 3) & 0x0303030303030303ull;
+    x = (x | x >> 6) & 0x000F000F000F000Full;
+    x = (x | x >> 12) & 0x000000FF000000FFull;
+    return (uint32_t)(x | x >> 24) & 0xFFFFu;
+}
+
+__device__ __forceinline__ void eval_quad_tile(const EvalDesc& D, uint64_t tile, const QuadKey& hk, const uint32_t* tab,
+                                               LaneOff loff) {
+    const uint32_t lane = threadIdx.x & 63u, c = lane & 3u;
+    const bool dcf = D.kind != FSS_EQ;
+    const uint32_t lower = dcf ? lane >> 5 : 0u;
+    const uint64_t np = pad_rows(D.n);
+    const uint64_t row = dcf ? tile * 8 + ((lane & 31u) >> 2) : tile * 16 + (lane >> 2);
+    uint32_t bit = 0;
+    if (row < D.n) {                             // whole quads
+        const uint32_t nu = D.nbits - 7, x0 = D.xhat[row];
+        const DcfPlanes P{np, nu};
+        const uint8_t* tree = D.key + (lower ? P.bytes() : 0);
+        const uint64_t plane = 16 * np;
+        const uint8_t* p = tree + 16 * row + 4 * c;
+        uint32_t vcw = dcf ? at<uint32_t>(tree, P.vcw(), row) : 0u;
+        const uint32_t wrap = lower ? 0u : vcw >> 31;
+        uint32_t s = *(const uint32_t*)p;
+        p += plane;
+        uint32_t cw = *(const uint32_t*)p;
+        uint32_t hv = 0, tv = 0, x = x0 << (32 - D.nbits);
+        const uint32_t keep = c ? ~0u : ~2u;     // clears the value bit of the first column
+        for (uint32_t i = 0; i < nu; i++) {
+            p += plane;
+            if (dcf && i + 1 == nu) p += 4 * np;
+            const uint32_t next = *(const uint32_t*)p;
+            const uint32_t h = tree_hash_quad(s, hk, tab, loff);
+            hv ^= h;                             // of these the first column's lane is used
+            tv ^= s & vcw;
+            vcw >>= 1;
+            const uint32_t tm = 0u - (quad_first(s) & 1u), xm = 0u - (x >> 31);
+            s = (h & keep) ^ (cw & tm) ^ (s & xm);
+            x <<= 1;
+            cw = next;
+        }
+        const uint32_t tm = 0u - (quad_first(s) & 1u);
+        const uint32_t g = tree_hash_quad(s ^ (c ? 0u : 2u), hk, tab, loff) ^ (cw & tm);
+        bit = c == ((x0 >> 5) & 3u) ? g >> (x0 & 31u) : 0u;
+        if (dcf && c == 0) bit ^= (hv >> 1) ^ tv ^ wrap;
+        bit &= 1u;
+        bit ^= quad_lane<1>(bit);                // the quad's four bits together
+        bit ^= quad_lane<2>(bit);
+    }
+    const uint64_t ballot = __ballot(bit);
+    if (lane != 0) return;
+    if (dcf)
+        ((uint8_t*)D.out)[tile] = (uint8_t)every_fourth((uint32_t)ballot ^ (uint32_t)(ballot >> 32));
+    else
+        ((uint16_t*)D.out)[tile] = (uint16_t)every_fourth(ballot);
+}
+
 struct EvalBatch {
     uint32_t count;
     uint32_t total_tiles;
-    uint32_t per;           // tiles per wave
     EvalDesc d[kEvalInline];
 };
 
-// A workgroup takes `per` consecutive tiles per wave, its waves side by side
-// (their key reads stay together: tiles dealt out wave by wave over the grid
-// cost 11% at 2^23 rows).
+// A wave takes one tile, the waves of a workgroup consecutive ones (their key
+// reads stay together: tiles dealt out wave by wave over a grid of resident
+// workgroups cost 11% at 2^23 rows; two or four tiles a wave, for fewer table
+// fills, gain nothing there).
 __global__ __launch_bounds__(kBlock, 8) void k_eval(EvalBatch batch) {
     __shared__ uint32_t tab[kLdsTableWords];
     lds_table_fill(tab, g_tables.t0);
     __syncthreads();
-    const LaneOff loff = lane_offset();
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t waves = blockDim.x >> 6;
-    for (uint32_t k = 0; k < batch.per; k++) {
-        const uint32_t tile = (blockIdx.x * batch.per + k) * waves + wave;
-        if (tile >= batch.total_tiles) break;
-        uint32_t di = 0;
-        while (di + 1 < batch.count && tile >= batch.d[di + 1].tile_start) di++;
-        const EvalDesc& D = batch.d[di];
-        eval_tile(D, tile - D.tile_start, tab, loff);
-    }
+    const uint32_t tile = launch_tile();
+    if (tile >= batch.total_tiles) return;
+    uint32_t di = 0;
+    while (di + 1 < batch.count && tile >= batch.d[di + 1].tile_start) di++;
+    const EvalDesc& D = batch.d[di];
+    eval_tile(D, tile - D.tile_start, tab, lane_offset());
+}
+
+__global__ __launch_bounds__(kBlock, 8) void k_eval_quad(EvalBatch batch) {
+    __shared__ uint32_t tab[kLdsTableWords];
+    lds_table_fill(tab, g_tables.t0);
+    __syncthreads();
+    const uint32_t tile = launch_tile();
+    if (tile >= batch.total_tiles) return;
+    uint32_t di = 0;
+    while (di + 1 < batch.count && tile >= batch.d[di + 1].tile_start) di++;
+    const EvalDesc& D = batch.d[di];
+    eval_quad_tile(D, tile - D.tile_start, quad_key(FixedHashKey{}), tab, lane_offset());
 }
 
 // ----------------------------------------------------------------- dealer (keys, triples)
@@ -442,27 +522,121 @@ __device__ __forceinline__ void keygen_tile(const DealerArgs& A, uint64_t tile, 
     }
 }
 
-// One kernel per key kind, so each is compiled for its own Gen alone.  A
-// workgroup takes `per` consecutive tiles per wave, its waves side by side.
+// One kernel per key kind, so each is compiled for its own Gen alone.
 template <int KIND>
-__device__ __forceinline__ void keygen_grid(const DealerArgs& A, uint32_t tiles, uint32_t per) {
+__device__ __forceinline__ void keygen_grid(const DealerArgs& A, uint32_t tiles) {
     __shared__ uint32_t tab[kLdsTableWords];
     lds_table_fill(tab, g_tables.t0);
     __syncthreads();
-    const LaneOff loff = lane_offset();
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t waves = blockDim.x >> 6;
-    for (uint32_t k = 0; k < per; k++) {
-        const uint32_t tile = (blockIdx.x * per + k) * waves + wave;
-        if (tile < tiles) keygen_tile<KIND>(A, tile, tab, loff);
+    const uint32_t tile = launch_tile();
+    if (tile < tiles) keygen_tile<KIND>(A, tile, tab, lane_offset());
+}
+
+__global__ __launch_bounds__(kBlock, 8) void k_keygen_eq(DealerArgs A, uint32_t tiles) {
+    keygen_grid<FSS_EQ>(A, tiles);
+}
+__global__ __launch_bounds__(kBlock, 8) void k_keygen_range(DealerArgs A, uint32_t tiles) {
+    keygen_grid<FSS_RANGE>(A, tiles);
+}
+
+// The dealer's quad tiles, for launches of few rows: 8 rows of one tree, a
+// quad of lanes per row and party, party 0 on lanes 0-31 and party 1 on lanes
+// 32-63, which exchange by swapping halves of the wave.
+__host__ __device__ inline uint64_t keygen_quad_tiles(uint32_t kind, uint64_t n) {
+    const uint64_t t = (n + 7) >> 3;
+    return kind == FSS_EQ ? t : 2 * t;
+}
+
+// Both parties' values: a = party 0's (lanes 0-31), b = party 1's, on both halves.
+__device__ __forceinline__ void both_halves(uint32_t v, uint32_t& a, uint32_t& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+}
+
+// This lane's column of the counter-mode block (domain, j, query, pred, elem).
+__device__ __forceinline__ uint32_t rng_quad(const QuadKey& dk, uint32_t domain, uint32_t j, uint32_t query, uint32_t pred,
+                                             uint32_t elem, const uint32_t* tab, LaneOff loff) {
+    const uint32_t c = threadIdx.x & 3u;
+    const uint32_t lo = c & 1u ? query : domain | (j << 16), hi = c & 1u ? elem : pred;
+    return aes128_quad(c & 2u ? hi : lo, dk, tab, loff);
+}
+
+template <int KIND>
+__device__ __forceinline__ void keygen_quad_tile(const DealerArgs& A, uint64_t tile, const QuadKey& hk,
+                                                 const QuadKey& dk, const uint32_t* tab, LaneOff loff) {
+    constexpr bool DCF = KIND != FSS_EQ;
+    const uint32_t lane = threadIdx.x & 63u, c = lane & 3u, b = lane >> 5;
+    const uint32_t lower = DCF ? (uint32_t)tile & 1u : 0u;
+    const uint64_t row = (DCF ? tile >> 1 : tile) * 8 + ((lane & 31u) >> 2);
+    if (row >= A.n) return;                 // the quads of both parties leave together
+    const uint64_t np = pad_rows(A.n);
+    const uint32_t nu = A.nbits - 7;
+    const DpfPlanes PP{np, nu};
+    const DcfPlanes PC{np, nu};
+    const uint32_t mask = A.nbits >= 32 ? 0xFFFFFFFFu : ((1u << A.nbits) - 1u);
+    const uint32_t r = A.r[row], e = (uint32_t)row + A.row_offset;
+    const uint32_t L = (A.a_or_lo + r) & mask, U = (A.hi + r) & mask;
+    const uint32_t alpha = !DCF || lower ? L : U;
+    uint8_t* k = (b ? A.key1 : A.key0) + (lower ? PC.bytes() : 0);
+    const uint32_t keep = c ? ~0u : ~2u;
+    // the even generator block is s_0, the odd one delta
+    uint32_t s0, delta, p0, p1;
+    both_halves(rng_quad(dk, 3, (lower ? 3u : 0u) + b, A.query, A.pred, e, tab, loff), s0, delta);
+    s0 &= keep;
+    delta = (delta & keep) | (c ? 0u : 1u);
+    uint32_t s = b ? s0 ^ delta : s0;
+    uint32_t wrap = 0;
+    if (DCF && !lower) wrap = (rng_quad(dk, 3, 2, A.query, A.pred, e, tab, loff) & 1u) ^ (b & (L > U ? 1u : 0u));
+    const uint64_t plane = 16 * np;
+    uint8_t* p = k + 16 * row + 4 * c;
+    *(uint32_t*)p = s;
+    uint32_t va = 0, vw = 0;
+    for (uint32_t i = 0; i < nu; i++) {
+        const uint32_t a = (alpha >> (A.nbits - 1 - i)) & 1u;
+        const uint32_t h = tree_hash_quad(s, hk, tab, loff);
+        both_halves(h, p0, p1);
+        const uint32_t d = p0 ^ p1;
+        const uint32_t cw = (d & keep) ^ (delta & (a - 1u));
+        if (DCF) {
+            vw |= (((d >> 1) & 1u) ^ va ^ a) << i;      // of these the first column's lane is used
+            va = a;
+        }
+        const uint32_t tm = 0u - (quad_first(s) & 1u);
+        s = (h & keep) ^ (cw & tm) ^ (s & (0u - a));
+        p += plane;
+        *(uint32_t*)p = cw;
+    }
+    both_halves(tree_hash_quad(s ^ (c ? 0u : 2u), hk, tab, loff), p0, p1);
+    uint32_t cw = p0 ^ p1;
+    const uint32_t low = alpha & 127u, base = 32 * c;
+    if (DCF) {
+        // [j < low] for this column's j, flipped when V_alpha = 1
+        const uint32_t m = low >= base + 32 ? ~0u : low <= base ? 0u : (1u << (low - base)) - 1u;
+        cw ^= m ^ (0u - va);
+        if (c == 0) at_w<uint32_t>(k, PC.vcw(), row) = vw | (wrap << 31);
+        ((uint32_t*)(k + PC.cwleaf() + 16 * row))[c] = cw;
+    } else {
+        cw ^= low >> 5 == c ? 1u << (low & 31u) : 0u;
+        ((uint32_t*)(k + PP.cwleaf() + 16 * row))[c] = cw;
     }
 }
 
-__global__ __launch_bounds__(kBlock, 8) void k_keygen_eq(DealerArgs A, uint32_t tiles, uint32_t per) {
-    keygen_grid<FSS_EQ>(A, tiles, per);
+template <int KIND>
+__device__ __forceinline__ void keygen_quad_grid(const DealerArgs& A, uint32_t tiles) {
+    __shared__ uint32_t tab[kLdsTableWords];
+    lds_table_fill(tab, g_tables.t0);
+    __syncthreads();
+    const uint32_t tile = launch_tile();
+    if (tile < tiles)
+        keygen_quad_tile<KIND>(A, tile, quad_key(FixedHashKey{}), quad_key(ArgKey{A.rk}), tab, lane_offset());
 }
-__global__ __launch_bounds__(kBlock, 8) void k_keygen_range(DealerArgs A, uint32_t tiles, uint32_t per) {
-    keygen_grid<FSS_RANGE>(A, tiles, per);
+
+__global__ __launch_bounds__(kBlock, 8) void k_keygen_quad_eq(DealerArgs A, uint32_t tiles) {
+    keygen_quad_grid<FSS_EQ>(A, tiles);
+}
+__global__ __launch_bounds__(kBlock, 8) void k_keygen_quad_range(DealerArgs A, uint32_t tiles) {
+    keygen_quad_grid<FSS_RANGE>(A, tiles);
 }
 
 // ----------------------------------------------------------------- persistent work queue (batches)
@@ -1178,25 +1352,30 @@ int check_batch(const fss_keybatch* k, int32_t want_kind, const char* who) {
     return FSS_OK;
 }
 
-// Workgroup size and grid of a launch of `tiles` wave tiles of an AES kernel.
-// Up to 16 waves in each of the two workgroups per CU that the LDS tables
-// allow, every wave takes one tile and the workgroups are as small as spreads
-// them over the chip, so that the launch takes one tile's latency (three
-// predicates over 1,024 vertices and 8,192 edges: 52 us, against 148 us with
-// 1024-thread workgroups; four over 10,000: 61 us, against 154).  Beyond that the workgroups are dispatched as others
-// end; a wave of theirs takes up to four tiles, which keeps the table fill
-// under 1%, but no more than leaves four workgroups for every slot.
+// Workgroup size and grid of a launch of `tiles` wave tiles of an AES kernel,
+// one tile per wave.  Up to 16 waves in each of the two workgroups per CU that
+// the LDS tables allow, the workgroups are as small as spreads them over the
+// chip, so that the launch takes one tile's latency (three predicates over
+// 1,024 vertices and 8,192 edges: 52 us, against 148 us with 1024-thread
+// workgroups; four over 10,000: 61 us, against 154).  Beyond that, workgroups
+// of 16 waves are dispatched as others end.
 struct TileShape {
-    unsigned grid, block, per;
+    unsigned grid, block;
 };
 
 TileShape tile_shape(uint64_t tiles) {
     const uint64_t wgs = 2ull * (uint64_t)device_cus();
     const uint64_t waves = std::min<uint64_t>(std::max<uint64_t>((tiles + wgs - 1) / wgs, 1), kBlock / 64);
-    const uint64_t per = std::min<uint64_t>(std::max<uint64_t>(tiles / (4 * wgs * waves), 1), 4);
-    const uint64_t grid = (tiles + waves * per - 1) / (waves * per);
-    return TileShape{(unsigned)std::max<uint64_t>(grid, 1), (unsigned)(64 * waves), (unsigned)per};
+    return TileShape{(unsigned)std::max<uint64_t>((tiles + waves - 1) / waves, 1), (unsigned)(64 * waves)};
 }
+
+// Launches of at most this many wave tiles take quad tiles, four times as
+// many: up to there the latency of a tile's chain counts, beyond it the VALU
+// work.  Measured, wave tiles against quad tiles: evaluation 44 / 20 us at 8
+// tiles, 50 / 28 at 1024, 52 / 50 at 2048, 80 / 90 at 4096; dealer 49 / 22 us
+// at 16, 60 / 36 at 1024, 83 / 76 at 3072, 87 / 98 at 4096.
+constexpr uint64_t kEvalQuadTiles = 2048;
+constexpr uint64_t kKeygenQuadTiles = 3072;
 
 // Enqueue one k_eval launch for up to kEvalInline descriptors, ranges first.
 int launch_eval(EvalDesc* descs, uint32_t count, hipStream_t stream) {
@@ -1207,15 +1386,20 @@ int launch_eval(EvalDesc* descs, uint32_t count, hipStream_t stream) {
             if ((pass == 0) == (descs[i].kind == FSS_RANGE) && descs[i].n > 0) b.d[k++] = descs[i];
     b.count = k;
     uint64_t tiles = 0;
+    for (uint32_t i = 0; i < k; i++) tiles += eval_tiles(b.d[i].kind, b.d[i].n);
+    if (tiles == 0) return FSS_OK;
+    const bool quad = tiles <= kEvalQuadTiles;
+    tiles = 0;
     for (uint32_t i = 0; i < k; i++) {
         b.d[i].tile_start = (uint32_t)tiles;
-        tiles += eval_tiles(b.d[i].kind, b.d[i].n);
+        tiles += quad ? eval_quad_tiles(b.d[i].kind, b.d[i].n) : eval_tiles(b.d[i].kind, b.d[i].n);
     }
-    if (tiles == 0) return FSS_OK;
     b.total_tiles = (uint32_t)tiles;     // at most 16 * 2^27
     const TileShape t = tile_shape(tiles);
-    b.per = t.per;
-    hipLaunchKernelGGL(k_eval, dim3(t.grid), dim3(t.block), 0, stream, b);
+    if (quad)
+        hipLaunchKernelGGL(k_eval_quad, dim3(t.grid), dim3(t.block), 0, stream, b);
+    else
+        hipLaunchKernelGGL(k_eval, dim3(t.grid), dim3(t.block), 0, stream, b);
     return check_launch("k_eval");
 }
 
@@ -1316,12 +1500,20 @@ int fss_keygen(uint64_t seed, uint32_t query_id, uint32_t pred_id, uint32_t a_or
     A.a_or_lo = a_or_lo;
     A.hi = hi;
     const uint64_t tiles = keygen_tiles(A.kind, A.n);    // at most 2^28
+    if (tiles <= kKeygenQuadTiles) {
+        const uint32_t nq = (uint32_t)keygen_quad_tiles(A.kind, A.n);
+        const TileShape t = tile_shape(nq);
+        if (out->kind == FSS_EQ)
+            hipLaunchKernelGGL(k_keygen_quad_eq, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, nq);
+        else
+            hipLaunchKernelGGL(k_keygen_quad_range, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, nq);
+        return check_launch("k_keygen_quad");
+    }
     const TileShape t = tile_shape(tiles);
     if (out->kind == FSS_EQ)
-        hipLaunchKernelGGL(k_keygen_eq, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, (uint32_t)tiles, t.per);
+        hipLaunchKernelGGL(k_keygen_eq, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, (uint32_t)tiles);
     else
-        hipLaunchKernelGGL(k_keygen_range, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, (uint32_t)tiles,
-                           t.per);
+        hipLaunchKernelGGL(k_keygen_range, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, (uint32_t)tiles);
     return check_launch("k_keygen");
 }
 

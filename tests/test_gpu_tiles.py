@@ -1,6 +1,6 @@
 """Evaluation and the dealer at the edges of their wave tiles (64 rows of an
 equality or 32 of a range; 32 rows of one tree) and of their launch shapes (one
-wave per workgroup up to 16, then several tiles per wave), and full-domain
+wave per workgroup up to 16), and full-domain
 evaluation at the edges of its 128-point leaves: every share and key looked at
 equals the oracle's, bit for bit."""
 import numpy as np
@@ -62,8 +62,14 @@ def test_eval_tile_edges(fss, kind, nbits, n):
     _check(fss, kind, nbits, n)
 
 
-def test_eval_several_tiles_per_wave(fss):
-    """2^21 + 33 range rows: 65,538 wave tiles, more than one per wave."""
+@pytest.mark.parametrize("kind,n", [(0, 15), (0, 17), (1, 7), (1, 9), (0, 131072), (0, 131073), (1, 65536), (1, 65537)])
+def test_eval_quad_tile_edges(fss, kind, n):
+    """Quad tiles (16 rows of an equality, 8 of a range; 2,048 wave tiles are the most that take them)."""
+    _check(fss, kind, 32, n)
+
+
+def test_eval_many_workgroups(fss):
+    """2^21 + 33 range rows: 65,538 wave tiles, the last workgroup with two of them."""
     _check(fss, 1, 32, (1 << 21) + 33)
 
 
@@ -89,9 +95,11 @@ def test_eval_all_leaf_edges(fss, kind, nbits, npoints):
 
 
 @pytest.mark.parametrize("kind,nbits,n", [(0, 32, 31), (0, 8, 33), (1, 32, 32), (1, 9, 33), (1, 32, 8193),
-                                          (0, 32, 16417), (1, 32, 40000)])
+                                          (0, 32, 16417), (1, 32, 40000), (0, 32, 7), (1, 32, 9), (0, 32, 98304), (0, 32, 98305),
+                                          (1, 32, 49152), (1, 32, 49153)])
 def test_keygen_tile_edges(fss, kind, nbits, n):
-    """The dealer's wave tiles: 32 rows of one tree, a range's two trees in two tiles."""
+    """The dealer's wave tiles (32 rows of one tree, a range's two trees in two tiles) and, up to 3,072 of
+    them, its quad tiles of 8 rows."""
     seed, r = 4321 + n, _rand_u32(n, n)
     lo, hi = (1 << nbits) // 5, (1 << nbits) - 3
     kb = fss.KeyBatch(kind, nbits, n)
