@@ -221,14 +221,15 @@ struct EvalDesc {
     uint32_t kind;
     uint32_t nbits;
     uint32_t party;
-    uint32_t tile_start;    // first tile of this descriptor (wave tiles, or the queue's row tiles)
+    uint32_t tile_start;    // first wave (or quad) tile of this descriptor
 };
 
-// The wave tile of this wave in a launch shaped by tile_shape: the waves of a
-// workgroup take consecutive tiles (a scalar: the same on every lane).
-__device__ __forceinline__ uint32_t launch_tile() {
+// The wave tile of this wave in a launch shaped by tile_shape, from tile
+// `first` on: the waves of a workgroup take consecutive tiles (a scalar: the
+// same on every lane).
+__device__ __forceinline__ uint32_t launch_tile(uint32_t first) {
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    return blockIdx.x * (blockDim.x >> 6) + wave;
+    return first + blockIdx.x * (blockDim.x >> 6) + wave;
 }
 
 // Evaluation works in wave tiles of 64 walks: 64 rows of an equality
@@ -338,11 +339,11 @@ struct EvalBatch {
 // reads stay together: tiles dealt out wave by wave over a grid of resident
 // workgroups cost 11% at 2^23 rows; two or four tiles a wave, for fewer table
 // fills, gain nothing there).
-__global__ __launch_bounds__(kBlock, 8) void k_eval(EvalBatch batch) {
+__global__ __launch_bounds__(kBlock, 8) void k_eval(EvalBatch batch, uint32_t first) {
     __shared__ uint32_t tab[kLdsTableWords];
     lds_table_fill(tab, g_tables.t0);
     __syncthreads();
-    const uint32_t tile = launch_tile();
+    const uint32_t tile = launch_tile(first);
     if (tile >= batch.total_tiles) return;
     uint32_t di = 0;
     while (di + 1 < batch.count && tile >= batch.d[di + 1].tile_start) di++;
@@ -350,11 +351,11 @@ __global__ __launch_bounds__(kBlock, 8) void k_eval(EvalBatch batch) {
     eval_tile(D, tile - D.tile_start, tab, lane_offset());
 }
 
-__global__ __launch_bounds__(kBlock, 8) void k_eval_quad(EvalBatch batch) {
+__global__ __launch_bounds__(kBlock, 8) void k_eval_quad(EvalBatch batch, uint32_t first) {
     __shared__ uint32_t tab[kLdsTableWords];
     lds_table_fill(tab, g_tables.t0);
     __syncthreads();
-    const uint32_t tile = launch_tile();
+    const uint32_t tile = launch_tile(first);
     if (tile >= batch.total_tiles) return;
     uint32_t di = 0;
     while (di + 1 < batch.count && tile >= batch.d[di + 1].tile_start) di++;
@@ -524,19 +525,19 @@ __device__ __forceinline__ void keygen_tile(const DealerArgs& A, uint64_t tile, 
 
 // One kernel per key kind, so each is compiled for its own Gen alone.
 template <int KIND>
-__device__ __forceinline__ void keygen_grid(const DealerArgs& A, uint32_t tiles) {
+__device__ __forceinline__ void keygen_grid(const DealerArgs& A, uint32_t tiles, uint32_t first) {
     __shared__ uint32_t tab[kLdsTableWords];
     lds_table_fill(tab, g_tables.t0);
     __syncthreads();
-    const uint32_t tile = launch_tile();
+    const uint32_t tile = launch_tile(first);
     if (tile < tiles) keygen_tile<KIND>(A, tile, tab, lane_offset());
 }
 
-__global__ __launch_bounds__(kBlock, 8) void k_keygen_eq(DealerArgs A, uint32_t tiles) {
-    keygen_grid<FSS_EQ>(A, tiles);
+__global__ __launch_bounds__(kBlock, 8) void k_keygen_eq(DealerArgs A, uint32_t tiles, uint32_t first) {
+    keygen_grid<FSS_EQ>(A, tiles, first);
 }
-__global__ __launch_bounds__(kBlock, 8) void k_keygen_range(DealerArgs A, uint32_t tiles) {
-    keygen_grid<FSS_RANGE>(A, tiles);
+__global__ __launch_bounds__(kBlock, 8) void k_keygen_range(DealerArgs A, uint32_t tiles, uint32_t first) {
+    keygen_grid<FSS_RANGE>(A, tiles, first);
 }
 
 // The dealer's quad tiles, for launches of few rows: 8 rows of one tree, a
@@ -623,44 +624,37 @@ __device__ __forceinline__ void keygen_quad_tile(const DealerArgs& A, uint64_t t
 }
 
 template <int KIND>
-__device__ __forceinline__ void keygen_quad_grid(const DealerArgs& A, uint32_t tiles) {
+__device__ __forceinline__ void keygen_quad_grid(const DealerArgs& A, uint32_t tiles, uint32_t first) {
     __shared__ uint32_t tab[kLdsTableWords];
     lds_table_fill(tab, g_tables.t0);
     __syncthreads();
-    const uint32_t tile = launch_tile();
+    const uint32_t tile = launch_tile(first);
     if (tile < tiles)
         keygen_quad_tile<KIND>(A, tile, quad_key(FixedHashKey{}), quad_key(ArgKey{A.rk}), tab, lane_offset());
 }
 
-__global__ __launch_bounds__(kBlock, 8) void k_keygen_quad_eq(DealerArgs A, uint32_t tiles) {
-    keygen_quad_grid<FSS_EQ>(A, tiles);
+__global__ __launch_bounds__(kBlock, 8) void k_keygen_quad_eq(DealerArgs A, uint32_t tiles, uint32_t first) {
+    keygen_quad_grid<FSS_EQ>(A, tiles, first);
 }
-__global__ __launch_bounds__(kBlock, 8) void k_keygen_quad_range(DealerArgs A, uint32_t tiles) {
-    keygen_quad_grid<FSS_RANGE>(A, tiles);
+__global__ __launch_bounds__(kBlock, 8) void k_keygen_quad_range(DealerArgs A, uint32_t tiles, uint32_t first) {
+    keygen_quad_grid<FSS_RANGE>(A, tiles, first);
 }
 
-// ----------------------------------------------------------------- persistent work queue (batches)
+// ----------------------------------------------------------------- batches
 //
-// A batch is a list of descriptors in device memory; descriptor i owns tiles
-// [tile_start_i, tile_start_i + tiles_i) of one global tile range.  A grid of
-// at most two workgroups per CU pulls tile numbers from one atomic counter
-// (zeroed by the launch before) until the range is exhausted, so every
-// workgroup leaves once all tiles are taken.  Each tile is a pure function of
-// its descriptor and rows: results do not depend on which workgroup took it.
+// A batch is a list of descriptors in device memory; descriptor i owns wave
+// tiles [tile_start_i, tile_start_i + tiles_i) of one global tile range, one
+// tile per wave, and the hardware dispatches the workgroups as others end.
+// (Workgroups that stay and pull tiles from an atomic counter meet at a
+// barrier for every tile and keep more scalar registers than there are: 16
+// uneven queries, both steps, DDD us against SSS.)  Each tile is a pure function
+// of its descriptor and rows: results do not depend on where it runs.
 
 struct QKeygen {
     DealerArgs a;
-    uint32_t tile_start;    // tiles of 512 rows
+    uint32_t tile_start;    // first wave (or quad) tile
     uint32_t pad;
 };
-
-struct QEval {
-    EvalDesc d;             // d.tile_start = first tile; tiles of kBlock * rows_per_thread rows
-};
-
-__global__ void k_zero_counter(uint32_t* c) {
-    if (threadIdx.x == 0) *c = 0u;
-}
 
 // Last descriptor whose first tile is <= tile (descriptors in tile order).
 template <class F>
@@ -673,67 +667,54 @@ __device__ __forceinline__ uint32_t find_desc(uint32_t count, uint32_t tile, F s
     return lo;
 }
 
-__device__ __forceinline__ uint32_t next_tile(uint32_t* counter, uint32_t* s_tile) {
-    __syncthreads();                         // everyone is done with the previous tile number
-    if (threadIdx.x == 0) *s_tile = atomicAdd(counter, 1u);
-    __syncthreads();
-    return *s_tile;
+// f(tile) for this wave's tiles of a launch: the next tile of its workgroup,
+// or with MANY `per` of them, the waves of a workgroup side by side.
+template <bool MANY, class F>
+__device__ __forceinline__ void wave_tiles(uint32_t tiles, uint32_t first, uint32_t per, F f) {
+    if constexpr (MANY) {
+        const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        const uint32_t waves = blockDim.x >> 6;
+        for (uint32_t k = 0; k < per; k++) {
+            const uint32_t tile = first + (blockIdx.x * per + k) * waves + wave;
+            if (tile < tiles) f(tile);
+        }
+    } else {
+        const uint32_t tile = launch_tile(first);
+        if (tile < tiles) f(tile);
+    }
 }
 
 // One key kind per launch (the host splits a batch by kind), so each kernel
 // holds one Gen's registers.
-// A tile is tile_mult groups of kBlock / 2 rows (a lane pair per row).
-template <int KIND>
-__device__ __forceinline__ void keygen_queue(const QKeygen* __restrict__ q, uint32_t count, uint32_t total_tiles,
-                                             uint32_t tile_mult, uint32_t* counter) {
+template <int KIND, bool QUAD, bool MANY>
+__global__ __launch_bounds__(kBlock, 8) void k_keygen_list(const QKeygen* __restrict__ q, uint32_t count, uint32_t tiles,
+                                                           uint32_t first, uint32_t per) {
     __shared__ uint32_t tab[kLdsTableWords];
-    __shared__ uint32_t s_tile;
     lds_table_fill(tab, g_tables.t0);
-    const LaneOff loff = lane_offset();
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    for (;;) {
-        // (also orders the table fill)
-        const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_tile(counter, &s_tile));
-        if (tile >= total_tiles) break;
-        const uint32_t di = find_desc(count, tile, [&](uint32_t i) { return q[i].tile_start; });
-        const DealerArgs& A = q[di].a;
-        const uint32_t per = (uint32_t)keygen_tiles(KIND, kBlock / 2) * tile_mult;
-        const uint64_t first = (uint64_t)(tile - q[di].tile_start) * per, all = keygen_tiles(KIND, A.n);
-        for (uint32_t k = wave; k < per && first + k < all; k += kBlock / 64)
-            keygen_tile<KIND>(A, first + k, tab, loff);
-    }
+    __syncthreads();
+    wave_tiles<MANY>(tiles, first, per, [&](uint32_t tile) {
+        const QKeygen& D = q[find_desc(count, tile, [&](uint32_t i) { return q[i].tile_start; })];
+        if constexpr (QUAD)
+            keygen_quad_tile<KIND>(D.a, tile - D.tile_start, quad_key(FixedHashKey{}), quad_key(ArgKey{D.a.rk}), tab,
+                                   lane_offset());
+        else
+            keygen_tile<KIND>(D.a, tile - D.tile_start, tab, lane_offset());
+    });
 }
 
-__global__ __launch_bounds__(kBlock, 8) void k_keygen_queue_eq(const QKeygen* __restrict__ q, uint32_t count,
-                                                           uint32_t total_tiles, uint32_t tile_mult,
-                                                           uint32_t* counter) {
-    keygen_queue<FSS_EQ>(q, count, total_tiles, tile_mult, counter);
-}
-
-__global__ __launch_bounds__(kBlock, 8) void k_keygen_queue_range(const QKeygen* __restrict__ q, uint32_t count,
-                                                              uint32_t total_tiles, uint32_t tile_mult,
-                                                              uint32_t* counter) {
-    keygen_queue<FSS_RANGE>(q, count, total_tiles, tile_mult, counter);
-}
-
-__global__ __launch_bounds__(kBlock, 8) void k_eval_queue(const QEval* __restrict__ q, uint32_t count,
-                                                      uint32_t total_tiles, uint32_t rows_per_thread,
-                                                      uint32_t* counter) {
+template <bool QUAD, bool MANY>
+__global__ __launch_bounds__(kBlock, 8) void k_eval_list(const EvalDesc* __restrict__ q, uint32_t count, uint32_t tiles,
+                                                         uint32_t first, uint32_t per) {
     __shared__ uint32_t tab[kLdsTableWords];
-    __shared__ uint32_t s_tile;
     lds_table_fill(tab, g_tables.t0);
-    const LaneOff loff = lane_offset();
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    for (;;) {
-        const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_tile(counter, &s_tile));
-        if (tile >= total_tiles) break;
-        const uint32_t di = find_desc(count, tile, [&](uint32_t i) { return q[i].d.tile_start; });
-        const EvalDesc& D = q[di].d;
-        // the wave tiles of the queue tile's rows, one wave after another
-        const uint32_t per = (D.kind == FSS_EQ ? kBlock / 64 : kBlock / 32) * rows_per_thread;
-        const uint64_t first = (uint64_t)(tile - D.tile_start) * per, all = eval_tiles(D.kind, D.n);
-        for (uint32_t k = wave; k < per && first + k < all; k += kBlock / 64) eval_tile(D, first + k, tab, loff);
-    }
+    __syncthreads();
+    wave_tiles<MANY>(tiles, first, per, [&](uint32_t tile) {
+        const EvalDesc& D = q[find_desc(count, tile, [&](uint32_t i) { return q[i].tile_start; })];
+        if constexpr (QUAD)
+            eval_quad_tile(D, tile - D.tile_start, quad_key(FixedHashKey{}), tab, lane_offset());
+        else
+            eval_tile(D, tile - D.tile_start, tab, lane_offset());
+    });
 }
 
 struct MaskArgs {
@@ -1369,6 +1350,19 @@ TileShape tile_shape(uint64_t tiles) {
     return TileShape{(unsigned)std::max<uint64_t>((tiles + waves - 1) / waves, 1), (unsigned)(64 * waves)};
 }
 
+// f(first tile, grid) for every launch that `tiles` tiles in this shape take: one,
+// but for the 2^31 threads that a launch is kept to.
+template <class F>
+int launch_tiles(const TileShape& t, uint32_t per, const char* what, F f) {
+    const uint64_t wg_tiles = (uint64_t)(t.block / 64) * per, most = (1ull << 31) / t.block;
+    for (uint64_t first = 0, left = t.grid; left; left -= std::min(left, most), first += most * wg_tiles) {
+        f((uint32_t)first, dim3((unsigned)std::min(left, most)));
+        const int rc = check_launch(what);
+        if (rc) return rc;
+    }
+    return FSS_OK;
+}
+
 // Launches of at most this many wave tiles take quad tiles, four times as
 // many: up to there the latency of a tile's chain counts, beyond it the VALU
 // work.  Measured, wave tiles against quad tiles: evaluation 44 / 20 us at 8
@@ -1396,11 +1390,12 @@ int launch_eval(EvalDesc* descs, uint32_t count, hipStream_t stream) {
     }
     b.total_tiles = (uint32_t)tiles;     // at most 16 * 2^27
     const TileShape t = tile_shape(tiles);
-    if (quad)
-        hipLaunchKernelGGL(k_eval_quad, dim3(t.grid), dim3(t.block), 0, stream, b);
-    else
-        hipLaunchKernelGGL(k_eval, dim3(t.grid), dim3(t.block), 0, stream, b);
-    return check_launch("k_eval");
+    return launch_tiles(t, 1, "k_eval", [&](uint32_t first, dim3 grid) {
+        if (quad)
+            hipLaunchKernelGGL(k_eval_quad, grid, dim3(t.block), 0, stream, b, first);
+        else
+            hipLaunchKernelGGL(k_eval, grid, dim3(t.block), 0, stream, b, first);
+    });
 }
 
 int eval_one(int32_t party, const fss_keybatch* k, int32_t kind, const uint32_t* d_xhat, uint32_t* d_out,
@@ -1500,21 +1495,21 @@ int fss_keygen(uint64_t seed, uint32_t query_id, uint32_t pred_id, uint32_t a_or
     A.a_or_lo = a_or_lo;
     A.hi = hi;
     const uint64_t tiles = keygen_tiles(A.kind, A.n);    // at most 2^28
-    if (tiles <= kKeygenQuadTiles) {
-        const uint32_t nq = (uint32_t)keygen_quad_tiles(A.kind, A.n);
-        const TileShape t = tile_shape(nq);
-        if (out->kind == FSS_EQ)
-            hipLaunchKernelGGL(k_keygen_quad_eq, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, nq);
+    const bool quad = tiles <= kKeygenQuadTiles;
+    const uint32_t nt = (uint32_t)(quad ? keygen_quad_tiles(A.kind, A.n) : tiles);
+    const TileShape t = tile_shape(nt);
+    return launch_tiles(t, 1, "k_keygen", [&](uint32_t first, dim3 grid) {
+        const dim3 block(t.block);
+        const hipStream_t s = (hipStream_t)stream;
+        if (out->kind == FSS_EQ && quad)
+            hipLaunchKernelGGL(k_keygen_quad_eq, grid, block, 0, s, A, nt, first);
+        else if (out->kind == FSS_EQ)
+            hipLaunchKernelGGL(k_keygen_eq, grid, block, 0, s, A, nt, first);
+        else if (quad)
+            hipLaunchKernelGGL(k_keygen_quad_range, grid, block, 0, s, A, nt, first);
         else
-            hipLaunchKernelGGL(k_keygen_quad_range, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, nq);
-        return check_launch("k_keygen_quad");
-    }
-    const TileShape t = tile_shape(tiles);
-    if (out->kind == FSS_EQ)
-        hipLaunchKernelGGL(k_keygen_eq, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, (uint32_t)tiles);
-    else
-        hipLaunchKernelGGL(k_keygen_range, dim3(t.grid), dim3(t.block), 0, (hipStream_t)stream, A, (uint32_t)tiles);
-    return check_launch("k_keygen");
+            hipLaunchKernelGGL(k_keygen_range, grid, block, 0, s, A, nt, first);
+    });
 }
 
 int fss_dealer_masks(uint64_t seed, uint32_t query_id, uint32_t pred_id, uint32_t row_offset, uint64_t n,
@@ -2059,9 +2054,9 @@ int launch_tail_inline(const std::vector<TailOp>& ops, const RoundKeys& rk, hipS
 // ----------------------------------------------------------------- batch queue plumbing
 
 struct Tuning {
-    uint32_t rows_per_thread = 1;   // eval tile = 1024 * rows_per_thread rows
-    uint32_t wg_per_cu = 2;         // persistent grid = wg_per_cu * CUs
-    uint32_t keygen_tile_mult = 1;  // keygen tile = 512 * keygen_tile_mult rows
+    uint32_t rows_per_thread = 1;   // wave tiles a wave takes in a batch evaluation
+    uint32_t wg_per_cu = 2;         // workgroups per CU of the batch launches
+    uint32_t keygen_tile_mult = 1;  // wave tiles a wave takes in a batch keygen
 };
 Tuning g_tuning;
 
@@ -2158,11 +2153,26 @@ int staging_release() {
     return rc;
 }
 
-constexpr uint64_t kQueueHeader = 256;   // the tile counter
+constexpr uint64_t kQueueHeader = 256;   // descriptors start at this offset
 
 uint64_t queue_bytes(uint64_t count) {
-    const uint64_t per = sizeof(QKeygen) > sizeof(QEval) ? sizeof(QKeygen) : sizeof(QEval);
+    const uint64_t per = sizeof(QKeygen) > sizeof(EvalDesc) ? sizeof(QKeygen) : sizeof(EvalDesc);
     return kQueueHeader + ((count * per + 255) & ~255ull);
+}
+
+// Shape of a batch launch of `tiles` wave tiles under the tuning: `per` tiles a
+// wave in workgroups of 16 waves; one workgroup per CU is had by asking for
+// LDS that leaves no room for a second.
+struct BatchShape {
+    TileShape t;
+    uint32_t per;
+    unsigned lds;
+};
+
+BatchShape batch_shape(uint64_t tiles, uint32_t per) {
+    BatchShape b{tile_shape(tiles), per, g_tuning.wg_per_cu == 1 ? 32u * 1024u : 0u};
+    if (per > 1) b.t = TileShape{(unsigned)((tiles + 16ull * per - 1) / (16ull * per)), (unsigned)kBlock};
+    return b;
 }
 
 // Queue order of two requests: ranges before equalities, larger tables first;
@@ -2172,40 +2182,60 @@ bool eval_before(uint32_t kind_a, uint64_t n_a, uint32_t kind_b, uint64_t n_b) {
     return ra != rb ? ra : n_a > n_b;
 }
 
-// The persistent evaluation over a queue already in device memory.
-int launch_eval_kernel(const QEval* dq, uint32_t n, uint64_t tiles, uint32_t* counter, hipStream_t s) {
-    hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(64), 0, s, counter);
-    const uint64_t grid = std::min<uint64_t>(tiles, (uint64_t)g_tuning.wg_per_cu * device_cus());
-    hipLaunchKernelGGL(k_eval_queue, dim3((unsigned)grid), dim3(kBlock), 0, s, dq, n, (uint32_t)tiles,
-                       g_tuning.rows_per_thread, counter);
-    return check_launch("k_eval_queue");
+// Tile numbers of a batch's descriptors: quad tiles when the batch is small
+// (the rule of launch_eval), else wave tiles.
+struct EvalTiles {
+    bool quad;
+    uint64_t total = 0;
+    // first tile of a descriptor of n rows, appended after the ones before it
+    uint32_t add(uint32_t kind, uint64_t n) {
+        const uint64_t first = total;
+        total += quad ? eval_quad_tiles(kind, n) : eval_tiles(kind, n);
+        return (uint32_t)first;
+    }
+};
+
+bool eval_quad(uint64_t wave_tiles) {
+    return wave_tiles <= kEvalQuadTiles && g_tuning.rows_per_thread == 1 && g_tuning.wg_per_cu == 2;
+}
+
+// The evaluation of descriptors already in device memory.
+int launch_eval_list(const EvalDesc* dq, uint32_t n, const EvalTiles& T, hipStream_t s) {
+    const BatchShape b = batch_shape(T.total, g_tuning.rows_per_thread);
+    const dim3 block(b.t.block);
+    const uint32_t nt = (uint32_t)T.total;
+    return launch_tiles(b.t, b.per, "k_eval_list", [&](uint32_t first, dim3 grid) {
+        if (T.quad)
+            hipLaunchKernelGGL((k_eval_list<true, false>), grid, block, b.lds, s, dq, n, nt, first, 1u);
+        else if (b.per == 1)
+            hipLaunchKernelGGL((k_eval_list<false, false>), grid, block, b.lds, s, dq, n, nt, first, 1u);
+        else
+            hipLaunchKernelGGL((k_eval_list<false, true>), grid, block, b.lds, s, dq, n, nt, first, b.per);
+    });
 }
 
 // Heaviest descriptors first, tile offsets, one upload, one launch.
 int launch_eval_queue(std::vector<EvalDesc>& descs, void* d_ws, uint64_t ws_bytes, hipStream_t s) {
-    std::vector<QEval> q;
+    std::vector<EvalDesc> q;
     q.reserve(descs.size());
     for (auto& d : descs)
-        if (d.n > 0) q.push_back(QEval{d});
-    std::stable_sort(q.begin(), q.end(), [](const QEval& a, const QEval& b) {
-        return eval_before(a.d.kind, a.d.n, b.d.kind, b.d.n);
+        if (d.n > 0) q.push_back(d);
+    std::stable_sort(q.begin(), q.end(), [](const EvalDesc& a, const EvalDesc& b) {
+        return eval_before(a.kind, a.n, b.kind, b.n);
     });
     if (q.empty()) return FSS_OK;
-    const uint64_t tile_rows = (uint64_t)kBlock * g_tuning.rows_per_thread;
     uint64_t tiles = 0;
-    for (auto& e : q) {
-        e.d.tile_start = (uint32_t)tiles;
-        tiles += (e.d.n + tile_rows - 1) / tile_rows;
-    }
+    for (auto& e : q) tiles += eval_tiles(e.kind, e.n);
     if (tiles > 0xFFFFFFF0ull) return fail(FSS_EUNSUPPORTED, "batch: too many tiles");
-    const uint64_t need = kQueueHeader + q.size() * sizeof(QEval);
+    EvalTiles T{eval_quad(tiles)};
+    for (auto& e : q) e.tile_start = T.add(e.kind, e.n);
+    const uint64_t need = kQueueHeader + q.size() * sizeof(EvalDesc);
     if (!d_ws || ws_bytes < need)
         return fail(FSS_ENOMEM, "batch: queue workspace needs %llu bytes", (unsigned long long)need);
-    uint32_t* counter = (uint32_t*)d_ws;
-    QEval* dq = (QEval*)((uint8_t*)d_ws + kQueueHeader);
-    const int rc = upload(q.data(), q.size() * sizeof(QEval), dq, s);
+    EvalDesc* dq = (EvalDesc*)((uint8_t*)d_ws + kQueueHeader);
+    const int rc = upload(q.data(), q.size() * sizeof(EvalDesc), dq, s);
     if (rc) return rc;
-    return launch_eval_kernel(dq, (uint32_t)q.size(), tiles, counter, s);
+    return launch_eval_list(dq, (uint32_t)q.size(), T, s);
 }
 
 // Device image of a batch's tail: the plans' key schedules, then the ops of
@@ -2290,11 +2320,11 @@ int eval_requests(const fss_eval_req* reqs, uint32_t count, std::vector<EvalDesc
     return FSS_OK;
 }
 
-// The allocation-free batch evaluation keeps its queue (tile counter and up
-// to FSS_NOALLOC_EVAL_MAX descriptors) in this file-scope device array: one
+// The allocation-free batch evaluation keeps its queue (up to
+// FSS_NOALLOC_EVAL_MAX descriptors) in this file-scope device array: one
 // copy per GPU, alive until the process ends, shared by every call on that GPU.
 constexpr uint64_t kScratchBytes = 64 * 1024;
-static_assert(kQueueHeader + FSS_NOALLOC_EVAL_MAX * sizeof(QEval) <= kScratchBytes, "scratch too small");
+static_assert(kQueueHeader + FSS_NOALLOC_EVAL_MAX * sizeof(EvalDesc) <= kScratchBytes, "scratch too small");
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -2615,41 +2645,51 @@ int fss_keygen_batch(const fss_keygen_req* reqs, uint32_t count, void* d_queue, 
     const size_t n_range = (size_t)(std::find_if(q.begin(), q.end(),
                                                  [](const QKeygen& e) { return e.a.kind != FSS_RANGE; }) -
                                     q.begin());
-    const uint32_t mult = g_tuning.keygen_tile_mult;
-    const uint64_t tile_rows = (uint64_t)mult * (kBlock / 2);
+    const uint32_t per = g_tuning.keygen_tile_mult;
     uint64_t tiles[2] = {0, 0};
-    for (size_t i = 0; i < q.size(); i++) {
-        uint64_t& t = tiles[i < n_range ? 0 : 1];
-        q[i].tile_start = (uint32_t)t;
-        t += (q[i].a.n + tile_rows - 1) / tile_rows;
-    }
+    bool quad[2];
+    for (const QKeygen& e : q) tiles[e.a.kind == FSS_RANGE ? 0 : 1] += keygen_tiles(e.a.kind, e.a.n);
     if (tiles[0] > 0xFFFFFFF0ull || tiles[1] > 0xFFFFFFF0ull)
         return fail(FSS_EUNSUPPORTED, "fss_keygen_batch: too many tiles");
+    for (int k = 0; k < 2; k++) {       // quad tiles when a launch is small (the rule of fss_keygen)
+        quad[k] = tiles[k] <= kKeygenQuadTiles && per == 1 && g_tuning.wg_per_cu == 2;
+        tiles[k] = 0;
+    }
+    for (QKeygen& e : q) {
+        const int k = e.a.kind == FSS_RANGE ? 0 : 1;
+        e.tile_start = (uint32_t)tiles[k];
+        tiles[k] += quad[k] ? keygen_quad_tiles(e.a.kind, e.a.n) : keygen_tiles(e.a.kind, e.a.n);
+    }
     if (!d_queue || queue_bytes_avail < queue_bytes(q.size()))
         return fail(FSS_ENOMEM, "fss_keygen_batch: queue workspace needs %llu bytes",
                     (unsigned long long)queue_bytes(q.size()));
     hipStream_t s = (hipStream_t)stream;
-    uint32_t* counter = (uint32_t*)d_queue;
     QKeygen* dq = (QKeygen*)((uint8_t*)d_queue + kQueueHeader);
     int rc = upload(q.data(), q.size() * sizeof(QKeygen), dq, s);
     if (rc) return rc;
-    const uint64_t slots = (uint64_t)g_tuning.wg_per_cu * device_cus();
-    // the two launches share the counter; stream order puts each zeroing
-    // after the previous launch has drained
-    if (tiles[0]) {
-        hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(64), 0, s, counter);
-        hipLaunchKernelGGL(k_keygen_queue_range, dim3((unsigned)std::min(tiles[0], slots)), dim3(kBlock), 0, s,
-                           dq, (uint32_t)n_range, (uint32_t)tiles[0], mult, counter);
-        rc = check_launch("k_keygen_queue_range");
+    for (int k = 0; k < 2; k++) {
+        if (!tiles[k]) continue;
+        const QKeygen* first = k ? dq + n_range : dq;
+        const uint32_t n = (uint32_t)(k ? q.size() - n_range : n_range), nt = (uint32_t)tiles[k];
+        const BatchShape b = batch_shape(tiles[k], per);
+        const dim3 block(b.t.block);
+        rc = launch_tiles(b.t, b.per, "k_keygen_list", [&](uint32_t t0, dim3 grid) {
+            if (k == 0 && quad[k])
+                hipLaunchKernelGGL((k_keygen_list<FSS_RANGE, true, false>), grid, block, b.lds, s, first, n, nt, t0, 1u);
+            else if (k == 0 && per == 1)
+                hipLaunchKernelGGL((k_keygen_list<FSS_RANGE, false, false>), grid, block, b.lds, s, first, n, nt, t0, 1u);
+            else if (k == 0)
+                hipLaunchKernelGGL((k_keygen_list<FSS_RANGE, false, true>), grid, block, b.lds, s, first, n, nt, t0, per);
+            else if (quad[k])
+                hipLaunchKernelGGL((k_keygen_list<FSS_EQ, true, false>), grid, block, b.lds, s, first, n, nt, t0, 1u);
+            else if (per == 1)
+                hipLaunchKernelGGL((k_keygen_list<FSS_EQ, false, false>), grid, block, b.lds, s, first, n, nt, t0, 1u);
+            else
+                hipLaunchKernelGGL((k_keygen_list<FSS_EQ, false, true>), grid, block, b.lds, s, first, n, nt, t0, per);
+        });
         if (rc) return rc;
     }
-    if (tiles[1]) {
-        hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(64), 0, s, counter);
-        hipLaunchKernelGGL(k_keygen_queue_eq, dim3((unsigned)std::min(tiles[1], slots)), dim3(kBlock), 0, s,
-                           dq + n_range, (uint32_t)(q.size() - n_range), (uint32_t)tiles[1], mult, counter);
-        rc = check_launch("k_keygen_queue_eq");
-    }
-    return rc;
+    return FSS_OK;
 }
 
 int fss_eval_batch(const fss_eval_req* reqs, uint32_t count, void* d_queue, uint64_t queue_bytes_avail,
@@ -2699,35 +2739,32 @@ int fss_eval_batch_noalloc(const fss_eval_req* reqs, uint32_t count, void* strea
         }
     }
     const uint16_t* order = idx[cur];
-    const uint64_t tile_rows = (uint64_t)kBlock * g_tuning.rows_per_thread;
     uint64_t tiles = 0;
-    for (uint32_t j = 0; j < m; j++) tiles += (reqs[order[j]].keys->n + tile_rows - 1) / tile_rows;
+    for (uint32_t j = 0; j < m; j++) tiles += eval_tiles((uint32_t)reqs[order[j]].keys->kind, reqs[order[j]].keys->n);
     if (tiles > 0xFFFFFFF0ull) return fail(FSS_EUNSUPPORTED, "%s: too many tiles", who);
+    EvalTiles T{eval_quad(tiles)};
     void* d_scratch = nullptr;
     int rc = scratch_ptr(&d_scratch, who);
     if (rc) return rc;
-    uint32_t* counter = (uint32_t*)d_scratch;
-    QEval* dq = (QEval*)((uint8_t*)d_scratch + kQueueHeader);
+    EvalDesc* dq = (EvalDesc*)((uint8_t*)d_scratch + kQueueHeader);
     hipStream_t s = (hipStream_t)stream;
-    constexpr uint32_t kPerChunk = kArgChunk / sizeof(QEval);
-    static_assert(sizeof(QEval) % 4 == 0, "descriptors are whole words");
-    uint64_t tile = 0;
+    constexpr uint32_t kPerChunk = kArgChunk / sizeof(EvalDesc);
+    static_assert(sizeof(EvalDesc) % 4 == 0, "descriptors are whole words");
     for (uint32_t first = 0; first < m; first += kPerChunk) {
         const uint32_t nq = std::min(kPerChunk, m - first);
         ArgChunk c{};
         for (uint32_t j = 0; j < nq; j++) {
-            QEval e{};
-            eval_request(reqs[order[first + j]], order[first + j], who, &e.d);   // checked above
-            e.d.tile_start = (uint32_t)tile;
-            tile += (e.d.n + tile_rows - 1) / tile_rows;
-            memcpy((uint8_t*)c.w + (size_t)j * sizeof(QEval), &e, sizeof(QEval));
+            EvalDesc e{};
+            eval_request(reqs[order[first + j]], order[first + j], who, &e);   // checked above
+            e.tile_start = T.add(e.kind, e.n);
+            memcpy((uint8_t*)c.w + (size_t)j * sizeof(EvalDesc), &e, sizeof(EvalDesc));
         }
         hipLaunchKernelGGL(k_put_words, dim3(1), dim3(256), 0, s, (uint32_t*)(dq + first),
-                           (uint32_t)(nq * sizeof(QEval) / 4), c);
+                           (uint32_t)(nq * sizeof(EvalDesc) / 4), c);
         rc = check_launch("k_put_words");
         if (rc) return rc;
     }
-    return launch_eval_kernel(dq, m, tiles, counter, s);
+    return launch_eval_list(dq, m, T, s);
 }
 
 int match_query_batch(const match_plan* plans, uint32_t count, int32_t party_mask, void* d_queue,
