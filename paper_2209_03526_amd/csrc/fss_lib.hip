@@ -647,7 +647,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_keygen_quad_range(DealerArgs A, u
 // tile per wave, and the hardware dispatches the workgroups as others end.
 // (Workgroups that stay and pull tiles from an atomic counter meet at a
 // barrier for every tile and keep more scalar registers than there are: 16
-// uneven queries, both steps, DDD us against SSS.)  Each tile is a pure function
+// uneven queries, keys dealt and evaluated: 11.80 ms against 11.39.)  Each tile is a pure function
 // of its descriptor and rows: results do not depend on where it runs.
 
 struct QKeygen {
