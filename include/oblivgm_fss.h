@@ -258,14 +258,14 @@ int match_rounds(const match_plan* plan, uint32_t* n_rounds, uint64_t* msg_words
 int match_query(const match_plan* plan, int32_t party_mask, void* stream);
 
 /*
- * Batches: many requests in ONE persistent launch each.  The work of all
- * requests is cut into tiles (512 rows for keygen, 1024 x rows_per_thread
- * rows for evaluation); at most wg_per_cu workgroups per CU pull tiles from
- * a device work queue, ranges and larger tables first.  Results are
- * bit-identical to the per-request calls above, whatever the tuning.
+ * Batches: many requests in ONE launch each.  The work of all requests is cut
+ * into tiles of one wave (64 tree walks for evaluation, 32 rows of one tree for
+ * keygen), ranges and larger tables first, and the hardware dispatches
+ * workgroups of them as others end.  Results are bit-identical to the
+ * per-request calls above, whatever the tuning.
  *
  * d_queue: caller-provided device memory of fss_queue_workspace_bytes(count)
- * bytes (256-aligned) holding the queue counter and the descriptors.  The
+ * bytes (256-aligned) holding the descriptors.  The
  * descriptors are staged through the library's ring of pinned host buffers
  * (see the conventions above); on a stream that is being captured into a
  * graph they are written by small store kernels whose arguments carry them
@@ -280,9 +280,9 @@ int match_query(const match_plan* plan, int32_t party_mask, void* stream);
  * fss_eval_batch (DPF / range evaluation for many predicates, parties, queries): each request
  * is one fss_eval_eq / fss_eval_lt call, chosen by keys->kind.
  * match_query_batch (edge matching for many plans): every predicate of every plan (of the
- * parties in party_mask) in one persistent launch; then the plans' ANDs and
- * joins merged into a few launches -- party_mask 3: one per AND level of the
- * deepest fold and one for all hop joins; party_mask 1 / 2: the round
+ * parties in party_mask) in one launch; then the plans' ANDs and joins merged
+ * into a few launches -- party_mask 3: one for all vertex folds and one for all
+ * hop joins with their edge folds; party_mask 1 / 2: the round
  * plans[i].round of every plan (closes, gathers, openings: three launches).
  * Each plan has its own outputs, workspace and messages as in match_query.
  * The tail's descriptors take match_batch_queue_bytes(plans, count) bytes of
@@ -319,7 +319,7 @@ int fss_eval_batch(const fss_eval_req* reqs, uint32_t count, void* d_queue, uint
  * fss_eval_batch for callers that cannot allocate (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the same
  * requests, checks and results, but no d_queue argument and no allocation of
- * any kind -- the queue (tile counter and descriptors) lives in a file-scope
+ * any kind -- the queue of descriptors lives in a file-scope
  * device array of the library, 64 KiB per GPU, held until the process ends,
  * and the descriptors reach it as kernel arguments (no pinned staging).
  * At most FSS_NOALLOC_EVAL_MAX requests per call, else EINVAL.  The array is
@@ -514,10 +514,10 @@ int rss_fetch_many(uint64_t ncand, uint32_t nwords, const uint32_t* const d_tabl
                    uint32_t* const d_out[3], uint32_t* d_rows_out, uint32_t* d_count, void* d_work,
                    uint64_t work_bytes, void* stream);
 
-/* Tile / occupancy shape of the persistent launches (process-wide):
- * rows_per_thread 1..8 (evaluation tile = 1024 * rows_per_thread rows),
- * wg_per_cu 1..2 (both the evaluation and the keygen queue), and the keygen
- * tile, 512 * tile_mult rows (tile_mult 1..8).  Chosen by the package's
+/* Tile / occupancy shape of the batch launches (process-wide):
+ * rows_per_thread 1..8 (wave tiles that a wave of a batch evaluation takes),
+ * wg_per_cu 1..2 (both the evaluation and the keygen batches), and tile_mult
+ * 1..8 (wave tiles that a wave of a batch keygen takes).  Chosen by the package's
  * autotuner; never changes results.  Not for use while another thread
  * enqueues batch calls. */
 int fss_set_tuning(uint32_t rows_per_thread, uint32_t wg_per_cu);

@@ -290,6 +290,13 @@ __device__ __forceinline__ uint32_t quad_first(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x00, 0xF, 0xF, true);
 }
 
+// The four lanes' values on every lane of the quad.
+__device__ __forceinline__ uint4 quad_all(uint32_t v) {
+    return make_uint4(quad_first(v), (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x55, 0xF, 0xF, true),
+                      (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xAA, 0xF, 0xF, true),
+                      (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xFF, 0xF, 0xF, true));
+}
+
 // This lane's column of the eleven round keys (rounds 1..9 rotated, as RoundKeys holds them).
 struct QuadKey {
     uint32_t w[11];

@@ -645,10 +645,10 @@ __global__ __launch_bounds__(kBlock, 8) void k_keygen_quad_range(DealerArgs A, u
 // A batch is a list of descriptors in device memory; descriptor i owns wave
 // tiles [tile_start_i, tile_start_i + tiles_i) of one global tile range, one
 // tile per wave, and the hardware dispatches the workgroups as others end.
-// (Workgroups that stay and pull tiles from an atomic counter meet at a
-// barrier for every tile and keep more scalar registers than there are: 16
-// uneven queries, keys dealt and evaluated: 11.80 ms against 11.39.)  Each tile is a pure function
-// of its descriptor and rows: results do not depend on where it runs.
+// (Workgroups that stay and pull tiles from an atomic counter meet at a barrier
+// for every tile and spill scalar registers in the loop: 16 uneven queries,
+// keys dealt and evaluated, 11.80 ms against 11.39.)  Each tile is a pure
+// function of its descriptor and rows: results do not depend on where it runs.
 
 struct QKeygen {
     DealerArgs a;
@@ -1032,58 +1032,75 @@ __global__ __launch_bounds__(kRssBlock) void k_rss(RssArgs A) {
 // The steps of a plan after its predicate bits exist (the ANDs of each vertex
 // and edge fold, the hop joins) run as tail ops, many ops per launch: op i
 // owns tiles [tile_start_i, tile_start_i + tiles_i) of one global tile range,
-// and each workgroup walks tiles blockIdx.x, blockIdx.x + gridDim.x, ...  A
-// tile is 1024 packed words: one word per thread for the word ops, one wave
-// per 64 words (2048 edges) for the gathering ops.  The Beaver triple words
-// an AND consumes are drawn in registers from the dealer's generator, so no
-// triple buffer exists.
+// one tile per wave.  The Beaver triple words an AND consumes are drawn in
+// registers from the dealer's generator, so no triple buffer exists.  With
+// both parties at hand a fold's ANDs follow one another in the registers of a
+// word's lane, and an edge fold ends inside the hop join that reads it: one
+// launch for the vertex folds, one for the joins.
+//
+// A tile is 64 packed words, a word per lane: the joins gather 2,048 edges in
+// 32 steps, then each lane does its word's ANDs.  Launches of few words take
+// quad tiles instead, 16 words per wave and a quad of lanes per word's AES
+// blocks: eight gathering steps, all in flight, and four times the waves.
+// Two joins over 2^13 edges with their folds 22 us, 2^20 23, 2^23 85 (38, 52
+// and 129 us in 1,024-word tiles that stayed with a workgroup, a launch for
+// every level of the folds); the joins of 2^23 edges are bound by their
+// gathers, L2 requests for 8 bytes each.
 
 enum TailKind : uint32_t {
-    TK_AND = 0,         // both parties: z = x AND y
+    TK_FOLD = 0,        // both parties: z = in_0 AND in_1 AND .. (none: the public 1; flag 1: pairs out)
     TK_AND_OPEN = 1,    // one party: msg = (x_b ^ a_b) || (y_b ^ b_b)
     TK_AND_CLOSE = 2,   // one party: z_b from d = x_b ^ a_b ^ d', e = y_b ^ b_b ^ e' (peer message d' || e')
-    TK_PAIR = 3,        // both parties: pair[w] = (m_0[w], m_1[w])
-    TK_HOP = 4,         // both parties: z = (m_j[src] AND m_j+1[dst]) AND q_j (public operands skipped)
-    TK_GATHER = 5,      // one party: z_b = bits of m_b at the public indices
-    TK_COPY = 6,        // the parties in `party`: z_b = x_b
-    TK_ONE = 7,         // the parties in `party`: their shares of the public constant 1
+    TK_HOP = 3,         // both parties: z = (m_a[src] AND m_b[dst]) AND (in_0 AND ..) (public operands skipped)
+    TK_GATHER = 4,      // one party: z_b = bits of m_b at the public indices
+    TK_COPY = 5,        // the parties in `party`: z_b = x_b
+    TK_ONE = 6,         // the parties in `party`: their shares of the public constant 1
 };
 
-constexpr uint32_t kTailTileWords = 1024;
 constexpr uint32_t kNoAnd = 0xFFFFFFFFu;
 // TK_HOP flags
-constexpr uint32_t kHopSrc = 1, kHopDst = 2, kHopQ = 4;
+constexpr uint32_t kHopSrc = 1, kHopDst = 2;
 
 struct TailOp {
     uint32_t kind;
-    uint32_t party;         // single-party kinds: 0 / 1; COPY / ONE: bit mask of parties; AND: 1 = pairs
+    uint32_t party;         // single-party kinds: 0 / 1; COPY / ONE: bit mask of parties; FOLD: 1 = pairs
                             // out; HOP: flags
     uint32_t query;
-    uint32_t and1;          // AND number of the (first) AND
-    uint32_t and2;          // TK_HOP: number of the AND with q_j
+    uint32_t and1;          // the AND's number; HOP: that of the AND of the endpoints
+    uint32_t and2;          // HOP: number of the AND with the edge fold
+    uint32_t and_in;        // FOLD / HOP: number of the first AND of the inputs' fold
+    uint32_t first_in;      // FOLD / HOP: the op's inputs in the launch's list
+    uint32_t n_in;
     uint32_t rk;            // dealer key schedule (index into the launch's table)
     uint32_t tile_start;
-    uint32_t pad;
     uint64_t nrows;         // rows of the output table
     uint64_t nsrc;          // gathering ops: rows of the vertex table
-    const uint32_t* x[2];   // AND: x; PAIR / COPY / GATHER: the source; HOP: q_j
-    const uint32_t* y[2];   // AND: y; AND_CLOSE: y[1] = the peer message d' || e'
-    uint32_t* z[2];         // outputs (AND_OPEN: z[0] = this party's message; PAIR: z[0] = the pairs)
+    const uint32_t* x[2];   // AND_OPEN / AND_CLOSE: x; COPY / GATHER: the source
+    const uint32_t* y[2];   // AND_OPEN / AND_CLOSE: y; AND_CLOSE: y[1] = the peer message d' || e'
+    uint32_t* z[2];         // outputs (AND_OPEN: z[0] = this party's message; pairs out: z[0] = the pairs)
     const uint32_t* src;    // gathering ops: public indices (HOP: sources)
     const uint32_t* dst;    // HOP: destinations
-    const uint2* gsrc;      // HOP: interleaved shares of m_j
-    const uint2* gdst;      // HOP: interleaved shares of m_j+1
+    const uint2* gsrc;      // HOP: interleaved shares of m_a
+    const uint2* gdst;      // HOP: interleaved shares of m_b
 };
 
-constexpr int kTailInline = 24;
+// One input of a fold: both parties' packed bits.
+struct TailIn {
+    const uint32_t* p[2];
+};
+
+constexpr int kTailInline = 16;
 
 struct TailLaunch {
-    const TailOp* ops;      // device array, or nullptr: the inline ops below
-    const RoundKeys* rks;   // device array, or nullptr: the inline key below
+    const TailOp* ops;      // device arrays (unless INLINE)
+    const TailIn* ins;
+    const RoundKeys* rks;
     uint32_t count;
     uint32_t total_tiles;
+    // INLINE: everything in the kernel's arguments, one key schedule
     RoundKeys rk;
     TailOp op[kTailInline];
+    TailIn in[FSS_MAX_PREDS];
 };
 
 __device__ __forceinline__ uint32_t pick4(uint32_t off, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
@@ -1098,13 +1115,24 @@ struct Triple {
     __device__ uint32_t c1() const { return ((a0 ^ a1) & (b0 ^ b1)) ^ c0; }
 };
 
-__device__ __forceinline__ Triple triple_word(const RoundKeys& rk, uint32_t query, uint32_t and_id, uint64_t w,
-                                              const uint32_t* tab, LaneOff loff) {
+// Drawn by a lane, or (QUAD) by a quad of lanes that all get it, under the
+// quad's key columns dk.
+template <bool QUAD>
+__device__ __forceinline__ Triple triple_word(const RoundKeys& rk, const QuadKey& dk, uint32_t query, uint32_t and_id,
+                                              uint64_t w, const uint32_t* tab, LaneOff loff) {
     const uint64_t k0 = 5 * w;
     const uint32_t blk = (uint32_t)(k0 >> 2), off = (uint32_t)(k0 & 3u);
-    uint4 p = rng_block(rk, 4, 0, query, and_id, blk, tab, loff);
-    pin_in_vgprs(p);
-    const uint4 q = rng_block(rk, 4, 0, query, and_id, blk + 1, tab, loff);
+    uint4 p, q;
+    if constexpr (QUAD) {
+        const uint32_t a = rng_quad(dk, 4, 0, query, and_id, blk, tab, loff);
+        const uint32_t b = rng_quad(dk, 4, 0, query, and_id, blk + 1, tab, loff);
+        p = quad_all(a);
+        q = quad_all(b);
+    } else {
+        p = rng_block(rk, 4, 0, query, and_id, blk, tab, loff);
+        pin_in_vgprs(p);
+        q = rng_block(rk, 4, 0, query, and_id, blk + 1, tab, loff);
+    }
     const uint32_t s0 = p.x, s1 = p.y, s2 = p.z, s3 = p.w, s4 = q.x, s5 = q.y, s6 = q.z, s7 = q.w;
     Triple t;
     t.a0 = pick4(off, s0, s1, s2, s3);
@@ -1124,33 +1152,54 @@ __device__ __forceinline__ void and_both(const Triple& t, uint32_t x0, uint32_t 
     z1 = (t.c1() ^ (d & t.b1) ^ (e & t.a1)) & pm;
 }
 
-// The bits of the 64 rows [row0, row0 + 64) of one wave, gathered at the
-// public indices, become words row0 / 32 and row0 / 32 + 1: lane 2k + h of the
-// wave keeps half h of iteration k's ballot.
+// The bits of 64 rows gathered by one wave at the public indices become two
+// words: words 2 it and 2 it + 1 of the tile go to the lanes that own them.
+template <bool QUAD>
 struct WaveWords {
-    uint32_t lane;
+    uint32_t own;           // this lane's word in the tile
     uint32_t w[2];
     __device__ __forceinline__ void keep(uint32_t it, uint32_t k, uint64_t ballot) {
-        if (lane == 2 * it) w[k] = (uint32_t)ballot;
-        if (lane == 2 * it + 1) w[k] = (uint32_t)(ballot >> 32);
+        if (own == 2 * it) w[k] = (uint32_t)ballot;
+        if (own == 2 * it + 1) w[k] = (uint32_t)(ballot >> 32);
     }
 };
 
-// One tile (1024 words) of op o; `tile` counts from the op's first tile.
-__device__ __forceinline__ void tail_tile(const TailOp& o, const RoundKeys& rk, uint64_t tile, const uint32_t* tab,
-                                          LaneOff loff) {
+// AND of the inputs of op o at word w, one after another (at least one input).
+template <bool QUAD>
+__device__ __forceinline__ void fold_word(const TailOp& o, const TailIn* in, const RoundKeys& rk, const QuadKey& dk,
+                                          uint64_t w, uint32_t pm, const uint32_t* tab, LaneOff loff, uint32_t& r0,
+                                          uint32_t& r1) {
+    r0 = in[o.first_in].p[0][w];
+    r1 = in[o.first_in].p[1][w];
+    for (uint32_t k = 1; k < o.n_in; k++) {
+        const uint32_t y0 = in[o.first_in + k].p[0][w], y1 = in[o.first_in + k].p[1][w];
+        and_both(triple_word<QUAD>(rk, dk, o.query, o.and_in + k - 1, w, tab, loff), r0, r1, y0, y1, pm, r0, r1);
+    }
+}
+
+template <bool QUAD>
+constexpr uint32_t kTailWords = QUAD ? 16 : 64;      // words of a tile
+
+// Tile `tile` of op o (counted from the op's first).  AES = false: the op
+// needs no triple.
+template <bool QUAD, bool AES>
+__device__ __forceinline__ void tail_tile(const TailOp& o, const TailIn* in, const RoundKeys& rk, uint64_t tile,
+                                          const uint32_t* tab) {
     const uint64_t nwords = (o.nrows + 31) >> 5;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t own = QUAD ? lane >> 2 : lane;
+    const bool writes = !QUAD || (lane & 3u) == 0;
+    const uint64_t w0 = tile * kTailWords<QUAD>, w = w0 + own;
+    const LaneOff loff = lane_offset();
+    QuadKey dk{};
+    if constexpr (QUAD && AES) dk = quad_key(ArgKey{rk});
     if (o.kind == TK_HOP || o.kind == TK_GATHER) {
-        // wave v of the workgroup owns words [w0, w0 + 64); lane l ends with word w0 + l
-        const uint32_t lane = threadIdx.x & 63u;
-        const uint64_t w0 = tile * kTailTileWords + (threadIdx.x & ~63u);
-        if (w0 >= nwords) return;                    // whole waves leave
-        WaveWords g{lane, {0u, 0u}}, h{lane, {0u, 0u}};
+        WaveWords<QUAD> g{own, {0u, 0u}}, h{own, {0u, 0u}};
         const bool hop = o.kind == TK_HOP;
         const uint32_t fl = o.party;
         const bool gs = hop ? (fl & kHopSrc) != 0 : true, gd = hop && (fl & kHopDst) != 0;
-#pragma unroll 4
-        for (uint32_t it = 0; it < 32; it++) {
+#pragma unroll kTailWords<QUAD> / (QUAD ? 2 : 16)
+        for (uint32_t it = 0; it < kTailWords<QUAD> / 2; it++) {
             const uint64_t e = (w0 + 2 * it) * 32 + lane;
             uint32_t bs0 = 0, bs1 = 0, bd0 = 0, bd1 = 0;
             if (e < o.nrows) {
@@ -1180,46 +1229,52 @@ __device__ __forceinline__ void tail_tile(const TailOp& o, const RoundKeys& rk, 
             if (gd) h.keep(it, 0, __ballot(bd0));
             if (gd) h.keep(it, 1, __ballot(bd1));
         }
-        const uint64_t w = w0 + lane;
-        if (w >= nwords) return;
-        const uint32_t pm = pad_mask(w, o.nrows);
+        if (w >= nwords) return;                     // a word's lanes leave together
         if (!hop) {
-            o.z[0][w] = g.w[0];
+            if (writes) o.z[0][w] = g.w[0];
             return;
         }
-        // r1 = g AND h (or the one gathered, or public 1); out = r1 AND q (or r1, or q, or public 1)
-        bool r1pub = false;
+        // r = g AND h (or the one gathered, or public 1); out = r AND q (or r, or q, or public 1)
+        const uint32_t pm = pad_mask(w, o.nrows);
         uint32_t r0, r1;
-        if (gs && gd) {
-            and_both(triple_word(rk, o.query, o.and1, w, tab, loff), g.w[0], g.w[1], h.w[0], h.w[1], pm, r0, r1);
-        } else if (gs) {
-            r0 = g.w[0]; r1 = g.w[1];
-        } else if (gd) {
-            r0 = h.w[0]; r1 = h.w[1];
-        } else {
-            r0 = pm; r1 = 0u; r1pub = true;
-        }
-        if (fl & kHopQ) {
-            const uint32_t q0 = o.x[0][w], q1 = o.x[1][w];
-            if (r1pub) {
-                r0 = q0; r1 = q1;
-            } else {
-                and_both(triple_word(rk, o.query, o.and2, w, tab, loff), r0, r1, q0, q1, pm, r0, r1);
+        if constexpr (AES) {
+            if (gs && gd)
+                and_both(triple_word<QUAD>(rk, dk, o.query, o.and1, w, tab, loff), g.w[0], g.w[1], h.w[0], h.w[1], pm, r0, r1);
+            else if (gs || gd)
+                r0 = gs ? g.w[0] : h.w[0], r1 = gs ? g.w[1] : h.w[1];
+            if (o.n_in) {
+                uint32_t q0, q1;
+                fold_word<QUAD>(o, in, rk, dk, w, pm, tab, loff, q0, q1);
+                if (gs || gd)
+                    and_both(triple_word<QUAD>(rk, dk, o.query, o.and2, w, tab, loff), r0, r1, q0, q1, pm, r0, r1);
+                else
+                    r0 = q0, r1 = q1;
+            } else if (!gs && !gd) {
+                r0 = pm, r1 = 0u;
             }
+        } else {
+            r0 = gs ? g.w[0] : gd ? h.w[0] : o.n_in ? in[o.first_in].p[0][w] : pm;
+            r1 = gs ? g.w[1] : gd ? h.w[1] : o.n_in ? in[o.first_in].p[1][w] : 0u;
         }
-        o.z[0][w] = r0;
-        o.z[1][w] = r1;
+        if (writes) {
+            o.z[0][w] = r0;
+            o.z[1][w] = r1;
+        }
         return;
     }
-    const uint64_t w = tile * kTailTileWords + threadIdx.x;
     if (w >= nwords) return;
     const uint32_t pm = pad_mask(w, o.nrows);
     switch (o.kind) {
-    case TK_AND: {
-        uint32_t z0, z1;
-        and_both(triple_word(rk, o.query, o.and1, w, tab, loff), o.x[0][w], o.x[1][w], o.y[0][w], o.y[1][w], pm, z0,
-                 z1);
-        if (o.party & 1u) {                              // the fold's last AND: pairs for the join
+    case TK_FOLD: {
+        uint32_t z0 = pm, z1 = 0u;
+        if constexpr (AES) {
+            if (o.n_in) fold_word<QUAD>(o, in, rk, dk, w, pm, tab, loff, z0, z1);
+        } else if (o.n_in) {
+            z0 = in[o.first_in].p[0][w];
+            z1 = in[o.first_in].p[1][w];
+        }
+        if (!writes) break;
+        if (o.party & 1u) {                              // a query vertex: pairs for the joins
             ((uint2*)o.z[0])[w] = make_uint2(z0, z1);
         } else {
             o.z[0][w] = z0;
@@ -1227,32 +1282,35 @@ __device__ __forceinline__ void tail_tile(const TailOp& o, const RoundKeys& rk, 
         }
         break;
     }
-    case TK_AND_OPEN: {
-        const Triple t = triple_word(rk, o.query, o.and1, w, tab, loff);
-        const uint32_t b = o.party;
-        o.z[0][w] = o.x[0][w] ^ (b ? t.a1 : t.a0);
-        o.z[0][nwords + w] = o.y[0][w] ^ (b ? t.b1 : t.b0);
+    case TK_AND_OPEN:
+        if constexpr (AES) {
+            const Triple t = triple_word<QUAD>(rk, dk, o.query, o.and1, w, tab, loff);
+            const uint32_t b = o.party;
+            if (!writes) break;
+            o.z[0][w] = o.x[0][w] ^ (b ? t.a1 : t.a0);
+            o.z[0][nwords + w] = o.y[0][w] ^ (b ? t.b1 : t.b0);
+        }
         break;
-    }
-    case TK_AND_CLOSE: {
-        const Triple t = triple_word(rk, o.query, o.and1, w, tab, loff);
-        const uint32_t b = o.party;
-        const uint32_t ab = b ? t.a1 : t.a0, bb = b ? t.b1 : t.b0, cb = b ? t.c1() : t.c0;
-        const uint32_t d = o.x[0][w] ^ ab ^ o.y[1][w];
-        const uint32_t e = o.y[0][w] ^ bb ^ o.y[1][nwords + w];
-        uint32_t z = cb ^ (d & bb) ^ (e & ab);
-        if (b == 0) z ^= d & e;
-        o.z[0][w] = z & pm;
-        break;
-    }
-    case TK_PAIR:
-        ((uint2*)o.z[0])[w] = make_uint2(o.x[0][w], o.x[1][w]);
+    case TK_AND_CLOSE:
+        if constexpr (AES) {
+            const Triple t = triple_word<QUAD>(rk, dk, o.query, o.and1, w, tab, loff);
+            const uint32_t b = o.party;
+            const uint32_t ab = b ? t.a1 : t.a0, bb = b ? t.b1 : t.b0, cb = b ? t.c1() : t.c0;
+            if (!writes) break;
+            const uint32_t d = o.x[0][w] ^ ab ^ o.y[1][w];
+            const uint32_t e = o.y[0][w] ^ bb ^ o.y[1][nwords + w];
+            uint32_t z = cb ^ (d & bb) ^ (e & ab);
+            if (b == 0) z ^= d & e;
+            o.z[0][w] = z & pm;
+        }
         break;
     case TK_COPY:
+        if (!writes) break;
         if (o.party & 1u) o.z[0][w] = o.x[0][w];
         if (o.party & 2u) o.z[1][w] = o.x[1][w];
         break;
     case TK_ONE:
+        if (!writes) break;
         if (o.party & 1u) o.z[0][w] = pm;
         if (o.party & 2u) o.z[1][w] = 0u;
         break;
@@ -1261,18 +1319,26 @@ __device__ __forceinline__ void tail_tile(const TailOp& o, const RoundKeys& rk, 
     }
 }
 
-// Ops in tile order; a workgroup fills the AES tables once, then takes every
-// gridDim.x-th tile.
-__global__ __launch_bounds__(kBlock) void k_tail(TailLaunch L) {
-    __shared__ uint32_t tab[kLdsTableWords];
-    lds_table_fill(tab, g_tables.t0);
-    __syncthreads();
-    const LaneOff loff = lane_offset();
-    const TailOp* ops = L.ops ? L.ops : L.op;
-    for (uint32_t tile = blockIdx.x; tile < L.total_tiles; tile += gridDim.x) {
-        const uint32_t di = find_desc(L.count, tile, [&](uint32_t i) { return ops[i].tile_start; });
-        const TailOp& o = ops[di];
-        tail_tile(o, L.rks ? L.rks[o.rk] : L.rk, tile - o.tile_start, tab, loff);
+// Ops in tile order.  A launch without ANDs needs no tables.
+template <bool QUAD, bool AES, bool INLINE>
+__global__ __launch_bounds__(kBlock, QUAD ? 4 : 8) void k_tail(TailLaunch L, uint32_t first) {
+    __shared__ uint32_t tab[AES ? kLdsTableWords : 1];
+    if constexpr (AES) {
+        lds_table_fill(tab, g_tables.t0);
+        __syncthreads();
+    }
+    const uint32_t tile = launch_tile(first);
+    if (tile >= L.total_tiles) return;
+    if constexpr (INLINE) {
+        // L where the launch left it, the kernel's first argument: taken by
+        // name, the compiler copies it to scratch for the indexing
+        const TailLaunch& A = *(const TailLaunch*)__builtin_amdgcn_kernarg_segment_ptr();
+        const uint32_t di = find_desc(A.count, tile, [&](uint32_t i) { return A.op[i].tile_start; });
+        tail_tile<QUAD, AES>(A.op[di], A.in, A.rk, tile - A.op[di].tile_start, tab);
+    } else {
+        const uint32_t di = find_desc(L.count, tile, [&](uint32_t i) { return L.ops[i].tile_start; });
+        const TailOp& o = L.ops[di];
+        tail_tile<QUAD, AES>(o, L.ins, L.rks[o.rk], tile - o.tile_start, tab);
     }
 }
 
@@ -1641,8 +1707,6 @@ struct TailPlan {
         uint32_t id, level;
         uint64_t nrows;
         Shares x, y, z;
-        int32_t vertex;     // fold AND: the query vertex whose fold it ends, else -1
-        bool hop;           // an AND of a hop join
     };
     struct Hop {
         bool g, h, q;               // m_a, m_b, q_j not public
@@ -1660,7 +1724,6 @@ struct TailPlan {
     Shares fold[FSS_MAX_QV + FSS_MAX_QE];
     uint32_t depth[FSS_MAX_QV + FSS_MAX_QE] = {};
     uint32_t npred_of[FSS_MAX_QV + FSS_MAX_QE] = {};
-    uint32_t first_pred[FSS_MAX_QV + FSS_MAX_QE] = {};
     uint2* pair[FSS_MAX_QV] = {};
     std::vector<And> ands;          // in AND-number order
     Hop hop[FSS_MAX_QE];
@@ -1691,7 +1754,6 @@ struct TailPlan {
                 if ((uint32_t)P->preds[k].target != t) continue;
                 if (npred_of[t]++ == 0) {
                     acc = pbits[k];
-                    first_pred[t] = k;
                     continue;
                 }
                 And a{};
@@ -1700,15 +1762,11 @@ struct TailPlan {
                 a.nrows = rows_of(t);
                 a.x = acc;
                 a.y = pbits[k];
-                a.vertex = -1;
-                a.hop = false;
                 if (!ws.take2(words_of(a.nrows), a.z)) return nomem();
                 acc = a.z;
                 ands.push_back(a);
             }
             fold[t] = acc;
-            // the fold's last AND ends query vertex t (pairs for the joins)
-            if (t < n_qv && depth[t] > 0) ands.back().vertex = (int32_t)t;
         }
         if (n_qv == 1) {
             // the output is m_0: its last AND writes it
@@ -1740,8 +1798,6 @@ struct TailPlan {
                 a.nrows = P->n_edges;
                 a.x = H.gs;
                 a.y = H.hs;
-                a.vertex = -1;
-                a.hop = true;
                 if (!ws.take2(we, H.r1)) return nomem();
                 a.z = H.r1;
                 H.a1 = (int32_t)ands.size();
@@ -1758,8 +1814,6 @@ struct TailPlan {
                 a.y = fold[n_qv + j];
                 a.z.p[0] = H.out[0];
                 a.z.p[1] = H.out[1];
-                a.vertex = -1;
-                a.hop = true;
                 H.a2 = (int32_t)ands.size();
                 ands.push_back(a);
             } else if (H.a1 >= 0) {
@@ -1788,79 +1842,71 @@ uint64_t plan_workspace(const match_plan* P) {
     return std::max<uint64_t>(measure.used, 256);
 }
 
-// Number of tail tiles of an op over `nrows` rows.
-uint32_t tail_tiles(uint64_t nrows) { return (uint32_t)((words_of(nrows) + kTailTileWords - 1) / kTailTileWords); }
-
 TailOp tail_op(uint32_t kind, const match_plan* P, uint64_t nrows) {
     TailOp o{};
     o.kind = kind;
     o.query = P->query_id;
-    o.and1 = o.and2 = kNoAnd;
+    o.and1 = o.and2 = o.and_in = kNoAnd;
     o.nrows = nrows;
     return o;
 }
 
-// Both parties at once: per AND level the fold ANDs (a vertex's last AND
-// writes its pairs for the joins), with the pairs of one-predicate vertices
-// and the output of a one-vertex query in the first level, then one level of
-// hop joins.  Level i of the result holds the ops of launch i.
-void fused_levels(const TailPlan& T, uint32_t rk, std::vector<std::vector<TailOp>>& levels) {
+// Whether an op consumes triples.
+bool tail_aes(const TailOp& o) {
+    switch (o.kind) {
+    case TK_FOLD: return o.n_in > 1;
+    case TK_HOP: return o.n_in > 1 || o.and1 != kNoAnd || o.and2 != kNoAnd;
+    default: return o.kind == TK_AND_OPEN || o.kind == TK_AND_CLOSE;
+    }
+}
+
+// Ops of the launches of a plan's tail, launch after launch, and the list of
+// fold inputs that they read.
+struct TailOps {
+    std::vector<std::vector<TailOp>> launch;
+    std::vector<TailIn> in;
+};
+
+// Both parties at once: the vertex folds (pairs for the joins, or the output
+// of a one-vertex query), then the hop joins, each with its edge fold.
+void fused_ops(const TailPlan& T, uint32_t rk, TailOps& ops) {
     const match_plan* P = T.P;
-    uint32_t nlev = 0;
-    for (const auto& a : T.ands) nlev = std::max(nlev, a.level);
-    const uint32_t first = 0, hops = std::max(nlev, 1u);
-    if (levels.size() < hops + 1) levels.resize(hops + 1);
-    auto put = [&](uint32_t lev, TailOp o) { o.rk = rk; levels[lev].push_back(o); };
-    for (const auto& a : T.ands) {
-        if (a.hop) continue;
-        TailOp o = tail_op(TK_AND, P, a.nrows);
-        o.and1 = a.id;
-        o.x[0] = a.x.p[0]; o.x[1] = a.x.p[1];
-        o.y[0] = a.y.p[0]; o.y[1] = a.y.p[1];
-        o.z[0] = a.z.p[0]; o.z[1] = a.z.p[1];
-        if (T.n_qv > 1 && a.vertex >= 0) {
-            o.party = 1;                           // pairs out
-            o.z[0] = (uint32_t*)T.pair[a.vertex];
-            o.z[1] = nullptr;
-        }
-        put(a.level - 1, o);
-    }
-    if (T.n_qv == 1) {
-        if (T.npred_of[0] == 0) {
-            TailOp o = tail_op(TK_ONE, P, P->n_vertices);
-            o.party = 3;
-            o.z[0] = P->d_out[0]; o.z[1] = P->d_out[1];
-            put(first, o);
-        } else if (T.depth[0] == 0) {
-            TailOp o = tail_op(TK_COPY, P, P->n_vertices);
-            o.party = 3;
-            o.x[0] = T.fold[0].p[0]; o.x[1] = T.fold[0].p[1];
-            o.z[0] = P->d_out[0]; o.z[1] = P->d_out[1];
-            put(first, o);
-        }
-        return;
-    }
+    if (ops.launch.size() < 2) ops.launch.resize(2);
+    uint32_t next_and = 0;
+    // the fold of target t into op o (its ANDs are numbered one after another, target by target)
+    auto inputs = [&](uint32_t t, TailOp& o) {
+        o.first_in = (uint32_t)ops.in.size();
+        o.n_in = T.npred_of[t];
+        o.and_in = next_and;
+        next_and += T.depth[t];
+        for (uint32_t k = 0; k < P->n_pred; k++)
+            if ((uint32_t)P->preds[k].target == t) ops.in.push_back(TailIn{{T.pbits[k].p[0], T.pbits[k].p[1]}});
+    };
     for (uint32_t i = 0; i < T.n_qv; i++) {
-        if (T.fold[i].is_public() || T.depth[i] > 0) continue;
-        TailOp o = tail_op(TK_PAIR, P, P->n_vertices);
-        o.x[0] = T.fold[i].p[0]; o.x[1] = T.fold[i].p[1];
-        o.z[0] = (uint32_t*)T.pair[i];
-        put(first, o);
+        if (T.n_qv > 1 && T.fold[i].is_public()) continue;
+        TailOp o = tail_op(TK_FOLD, P, P->n_vertices);
+        o.rk = rk;
+        inputs(i, o);
+        o.party = T.n_qv > 1 ? 1 : 0;
+        o.z[0] = T.n_qv > 1 ? (uint32_t*)T.pair[i] : P->d_out[0];
+        o.z[1] = T.n_qv > 1 ? nullptr : P->d_out[1];
+        ops.launch[0].push_back(o);
     }
     for (uint32_t j = 0; j < T.n_qe; j++) {
         const TailPlan::Hop& H = T.hop[j];
         TailOp o = tail_op(TK_HOP, P, P->n_edges);
-        o.party = (H.g ? kHopSrc : 0) | (H.h ? kHopDst : 0) | (H.q ? kHopQ : 0);
+        o.rk = rk;
+        inputs(T.n_qv + j, o);
+        o.party = (H.g ? kHopSrc : 0) | (H.h ? kHopDst : 0);
         o.nsrc = P->n_vertices;
         o.src = P->d_src;
         o.dst = P->d_dst;
         o.gsrc = T.pair[T.qa[j]];
         o.gdst = T.pair[T.qb[j]];
-        if (H.q) { o.x[0] = T.fold[T.n_qv + j].p[0]; o.x[1] = T.fold[T.n_qv + j].p[1]; }
         if (H.a1 >= 0) o.and1 = T.ands[H.a1].id;
         if (H.a2 >= 0) o.and2 = T.ands[H.a2].id;
         o.z[0] = H.out[0]; o.z[1] = H.out[1];
-        put(hops, o);
+        ops.launch[1].push_back(o);
     }
 }
 
@@ -2021,31 +2067,72 @@ void plan_evals(const TailPlan& T, int32_t mask, std::vector<EvalDesc>& out) {
     }
 }
 
-// Workgroups of a tail launch: two per CU at most (the LDS holds two tables).
-unsigned tail_grid(uint32_t tiles) {
-    const uint32_t cap = 2u * (uint32_t)device_cus();
-    return tiles < 1 ? 1u : (tiles < cap ? tiles : cap);
+// A tail launch of up to so many 64-word tiles takes quad tiles of 16 words.
+// Joins gain from the extra waves' gathers up to larger sizes than folds,
+// where a quad's costlier AES is all there is.  64-word against 16-word tiles:
+// folds and two joins over 2^13 edges 40 / 22 us, 2^21 (2,048 tiles of joins)
+// 43 / 28, 2^22 62 / 52, 2^23 85 / 98; a fold of four over 2^21 rows (1,024
+// tiles) 15 / 11 us, 2^22 14 / 16.
+constexpr uint64_t kHopQuadTiles = 4096, kFoldQuadTiles = 1024;
+
+struct TailShape {
+    bool quad, aes;
+    uint64_t tiles;
+};
+
+// Shape of the launch of ops[0 .. n), whose tile_start it sets.
+TailShape tail_shape(TailOp* ops, size_t n) {
+    uint64_t tiles = 0;
+    TailShape S{false, false, 0};
+    bool hops = false;
+    for (size_t i = 0; i < n; i++) {
+        tiles += (words_of(ops[i].nrows) + kTailWords<false> - 1) / kTailWords<false>;
+        S.aes = S.aes || tail_aes(ops[i]);
+        hops = hops || ops[i].kind == TK_HOP || ops[i].kind == TK_GATHER;
+    }
+    S.quad = tiles <= (hops ? kHopQuadTiles : kFoldQuadTiles);
+    const uint64_t per = S.quad ? kTailWords<true> : kTailWords<false>;
+    for (size_t i = 0; i < n; i++) {
+        ops[i].tile_start = (uint32_t)S.tiles;
+        S.tiles += (words_of(ops[i].nrows) + per - 1) / per;
+    }
+    return S;
+}
+
+template <bool INLINE>
+int launch_tail(const TailLaunch& L, const TailShape& S, hipStream_t s) {
+    const TileShape t = tile_shape(S.tiles);
+    return launch_tiles(t, 1, "k_tail", [&](uint32_t first, dim3 grid) {
+        const dim3 block(t.block);
+        if (S.quad && S.aes)
+            hipLaunchKernelGGL((k_tail<true, true, INLINE>), grid, block, 0, s, L, first);
+        else if (S.quad)
+            hipLaunchKernelGGL((k_tail<true, false, INLINE>), grid, block, 0, s, L, first);
+        else if (S.aes)
+            hipLaunchKernelGGL((k_tail<false, true, INLINE>), grid, block, 0, s, L, first);
+        else
+            hipLaunchKernelGGL((k_tail<false, false, INLINE>), grid, block, 0, s, L, first);
+    });
 }
 
 // One launch per kTailInline ops, all carried in kernel arguments (one plan:
-// its key schedule rides along).
-int launch_tail_inline(const std::vector<TailOp>& ops, const RoundKeys& rk, hipStream_t s) {
+// its key schedule and fold inputs ride along).
+int launch_tail_inline(const std::vector<TailOp>& ops, const std::vector<TailIn>& in, const RoundKeys& rk,
+                       hipStream_t s) {
     for (size_t i0 = 0; i0 < ops.size(); i0 += kTailInline) {
         TailLaunch L{};
         L.rk = rk;
-        uint32_t tiles = 0;
         const size_t n = std::min<size_t>(kTailInline, ops.size() - i0);
         for (size_t i = 0; i < n; i++) {
             L.op[i] = ops[i0 + i];
             L.op[i].rk = 0;
-            L.op[i].tile_start = tiles;
-            tiles += tail_tiles(L.op[i].nrows);
         }
+        for (size_t i = 0; i < in.size(); i++) L.in[i] = in[i];     // at most the plan's predicates
+        const TailShape S = tail_shape(L.op, n);
         L.count = (uint32_t)n;
-        L.total_tiles = tiles;
-        if (tiles == 0) continue;
-        hipLaunchKernelGGL(k_tail, dim3(tail_grid(tiles)), dim3(kBlock), 0, s, L);
-        int rc = check_launch("k_tail");
+        L.total_tiles = (uint32_t)S.tiles;
+        if (S.tiles == 0) continue;
+        const int rc = launch_tail<true>(L, S, s);
         if (rc) return rc;
     }
     return FSS_OK;
@@ -2238,50 +2325,50 @@ int launch_eval_queue(std::vector<EvalDesc>& descs, void* d_ws, uint64_t ws_byte
     return launch_eval_list(dq, (uint32_t)q.size(), T, s);
 }
 
-// Device image of a batch's tail: the plans' key schedules, then the ops of
-// every launch, one upload for all launches.
-uint64_t tail_queue_bytes(uint64_t nplans, uint64_t nops) {
-    return kQueueHeader + ((nplans * sizeof(RoundKeys) + 255) & ~255ull) + nops * sizeof(TailOp);
+// Device image of a batch's tail: the plans' key schedules, the fold inputs,
+// then the ops of every launch, one upload for all launches.
+uint64_t tail_queue_bytes(uint64_t nplans, uint64_t nin, uint64_t nops) {
+    return kQueueHeader + ((nplans * sizeof(RoundKeys) + nin * sizeof(TailIn) + 255) & ~255ull) + nops * sizeof(TailOp);
 }
 
-int launch_tail_queue(const match_plan* plans, uint32_t count, const std::vector<std::vector<TailOp>>& levels,
-                      void* d_ws, uint64_t ws_bytes, hipStream_t s) {
+int launch_tail_queue(const match_plan* plans, uint32_t count, const TailOps& T, void* d_ws, uint64_t ws_bytes,
+                      hipStream_t s) {
     uint64_t nops = 0;
-    for (const auto& l : levels) nops += l.size();
+    for (const auto& l : T.launch) nops += l.size();
     if (nops == 0) return FSS_OK;
-    const uint64_t need = tail_queue_bytes(count, nops);
+    const uint64_t need = tail_queue_bytes(count, T.in.size(), nops);
     if (!d_ws || ws_bytes < need)
         return fail(FSS_ENOMEM, "match_query_batch: queue workspace needs %llu bytes (match_batch_queue_bytes)",
                     (unsigned long long)need);
-    const uint64_t rk_bytes = (count * sizeof(RoundKeys) + 255) & ~255ull;
-    std::vector<uint8_t> img(rk_bytes + nops * sizeof(TailOp));
+    static_assert(sizeof(RoundKeys) % 16 == 0, "the inputs follow the key schedules");
+    const uint64_t in_at = count * sizeof(RoundKeys), ops_at = (in_at + T.in.size() * sizeof(TailIn) + 255) & ~255ull;
+    std::vector<uint8_t> img(ops_at + nops * sizeof(TailOp));
     RoundKeys* rks = (RoundKeys*)img.data();
     for (uint32_t i = 0; i < count; i++) rks[i] = dealer_key(plans[i].seed);
-    TailOp* ops = (TailOp*)(img.data() + rk_bytes);
-    struct Launch { uint64_t first; uint32_t n, tiles; };
+    if (!T.in.empty()) memcpy(img.data() + in_at, T.in.data(), T.in.size() * sizeof(TailIn));
+    TailOp* ops = (TailOp*)(img.data() + ops_at);
+    struct Launch { uint64_t first; uint32_t n; TailShape shape; };
     std::vector<Launch> launches;
     uint64_t k = 0;
-    for (const auto& l : levels) {
-        Launch ln{k, (uint32_t)l.size(), 0};
-        for (const TailOp& o : l) {
-            ops[k] = o;
-            ops[k].tile_start = ln.tiles;
-            ln.tiles += tail_tiles(o.nrows);
-            k++;
-        }
-        if (ln.tiles) launches.push_back(ln);
+    for (const auto& l : T.launch) {
+        if (l.empty()) continue;
+        std::copy(l.begin(), l.end(), ops + k);
+        const TailShape S = tail_shape(ops + k, l.size());
+        if (S.tiles > 0xFFFFFFF0ull) return fail(FSS_EUNSUPPORTED, "match_query_batch: too many tiles");
+        if (S.tiles) launches.push_back(Launch{k, (uint32_t)l.size(), S});
+        k += l.size();
     }
     uint8_t* dbase = (uint8_t*)d_ws + kQueueHeader;
     int rc = upload(img.data(), img.size(), dbase, s);
     if (rc) return rc;
     for (const Launch& ln : launches) {
         TailLaunch L{};
-        L.ops = (const TailOp*)(dbase + rk_bytes) + ln.first;
+        L.ops = (const TailOp*)(dbase + ops_at) + ln.first;
+        L.ins = (const TailIn*)(dbase + in_at);
         L.rks = (const RoundKeys*)dbase;
         L.count = ln.n;
-        L.total_tiles = ln.tiles;
-        hipLaunchKernelGGL(k_tail, dim3(tail_grid(ln.tiles)), dim3(kBlock), 0, s, L);
-        rc = check_launch("k_tail");
+        L.total_tiles = (uint32_t)ln.shape.tiles;
+        rc = launch_tail<false>(L, ln.shape, s);
         if (rc) return rc;
     }
     return FSS_OK;
@@ -2394,10 +2481,10 @@ int match_query(const match_plan* P, int32_t party_mask, void* stream) {
             rc = launch_eval(descs.data() + i, (uint32_t)std::min<size_t>(kEvalInline, descs.size() - i), s);
             if (rc) return rc;
         }
-        std::vector<std::vector<TailOp>> levels;
-        fused_levels(T, 0, levels);
-        for (const auto& ops : levels) {
-            rc = launch_tail_inline(ops, rk, s);
+        TailOps ops;
+        fused_ops(T, 0, ops);
+        for (const auto& l : ops.launch) {
+            rc = launch_tail_inline(l, ops.in, rk, s);
             if (rc) return rc;
         }
         return FSS_OK;
@@ -2418,7 +2505,7 @@ int match_query(const match_plan* P, int32_t party_mask, void* stream) {
     std::vector<TailOp> phase[3];
     party_round(T, b, r, P->d_peer_msg, P->d_msg, 0, phase);
     for (auto& ops : phase) {
-        rc = launch_tail_inline(ops, rk, s);
+        rc = launch_tail_inline(ops, {}, rk, s);
         if (rc) return rc;
     }
     return FSS_OK;
@@ -2798,24 +2885,24 @@ int match_query_batch(const match_plan* plans, uint32_t count, int32_t party_mas
     int rc = launch_eval_queue(descs, d_queue, queue_bytes_avail, s);
     if (rc) return rc;
     // the tail: ops of every plan merged per launch, with one key schedule per plan
-    std::vector<std::vector<TailOp>> levels;
+    TailOps ops;
     for (uint32_t i = 0; i < count; i++) {
         if (party_mask == 3) {
-            fused_levels(tails[i], i, levels);
+            fused_ops(tails[i], i, ops);
         } else {
             std::vector<TailOp> phase[3];
             const match_plan& P = plans[i];
             party_round(tails[i], (uint32_t)party_mask - 1, P.round, P.d_peer_msg, P.d_msg, i, phase);
-            if (levels.size() < 3) levels.resize(3);
-            for (int k = 0; k < 3; k++) levels[k].insert(levels[k].end(), phase[k].begin(), phase[k].end());
+            if (ops.launch.size() < 3) ops.launch.resize(3);
+            for (int k = 0; k < 3; k++) ops.launch[k].insert(ops.launch[k].end(), phase[k].begin(), phase[k].end());
         }
     }
-    return launch_tail_queue(plans, count, levels, d_queue, queue_bytes_avail, s);
+    return launch_tail_queue(plans, count, ops, d_queue, queue_bytes_avail, s);
 }
 
 uint64_t match_batch_queue_bytes(const match_plan* plans, uint32_t count) {
     if (!plans) return 0;
-    uint64_t nevals = 0, nops = 0;
+    uint64_t nevals = 0, nops = 0, nin = 0;
     for (uint32_t i = 0; i < count; i++) {
         if (!match_workspace_bytes(&plans[i])) return 0;
         Arena measure = Arena::measuring();
@@ -2824,11 +2911,12 @@ uint64_t match_batch_queue_bytes(const match_plan* plans, uint32_t count) {
         std::vector<EvalDesc> d;
         plan_evals(T, 3, d);
         nevals += d.size();
-        // every AND, two gathers per hop, one pair op per vertex and one copy per output, at most,
+        nin += plans[i].n_pred;
+        // every AND, two gathers per hop, one fold per vertex and one copy per output, at most,
         // in any launch
         nops += T.ands.size() + 3 * (uint64_t)T.n_qe + T.n_qv + 2;
     }
-    return std::max(queue_bytes(nevals), tail_queue_bytes(count, nops));
+    return std::max(queue_bytes(nevals), tail_queue_bytes(count, nin, nops));
 }
 
 }  // extern "C"

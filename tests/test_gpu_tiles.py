@@ -110,3 +110,46 @@ def test_keygen_tile_edges(fss, kind, nbits, n):
     for b in range(2):
         got = from_device(kind, nbits, n, B(kb.key[b], kb.bytes_per_party))
         assert got.tobytes() == want[b].tobytes()
+
+
+@pytest.mark.parametrize("n_edges", [1, 511, 513, 2049, 70001])
+@pytest.mark.parametrize("npred", [(0, 0, 0), (1, 0, 2), (0, 3, 0), (2, 1, 1), (1, 1, 3), (0, 0, 4)])
+def test_tail_tile_edges(fss, n_edges, npred):
+    """One hop whose vertices and edge carry `npred` predicates, bits given: folds and the join at the edges
+    of 16-word tiles, against the plan rebuilt from the oracle's triples."""
+    seed, qid, nv = 5 + n_edges, 11, 700
+    rng = np.random.default_rng(n_edges + 7 * sum(npred))
+    src, dst = (rng.integers(0, nv, n_edges).astype(np.uint32) for _ in range(2))
+    rows = (nv, nv, n_edges)
+    preds, bits, and_id = [], [], 0
+    for t in range(3):
+        bits.append([])
+        for _ in range(npred[t]):
+            m = ofss.valid_mask(rows[t])
+            b = [_rand_u32(int(rng.integers(1 << 30)), m.size) & m for _ in range(2)]
+            bits[t].append(b)
+            preds.append((t, None, None, (T(b[0]), T(b[1]))))
+    plan = fss.Plan(seed, qid, 2, nv, n_edges, preds, T(src), T(dst)).allocate()
+    fss.match_query(plan)
+
+    def beaver(x, y, n):
+        nonlocal and_id
+        trip = ofss.triples(seed, qid, and_id, (n + 31) // 32)
+        and_id += 1
+        return ofss.beaver_and(x, y, trip, n)
+
+    folds = []
+    for t in range(3):
+        acc = None
+        for b in bits[t]:
+            acc = b if acc is None else beaver(acc, b, rows[t])
+        folds.append(acc)
+    ends = [None if folds[t] is None else [ofss.pack_bits(ofss.unpack_bits(folds[t][b], nv)[ix]) for b in range(2)]
+            for t, ix in ((0, src), (1, dst))]
+    r = ends[0] if ends[1] is None else ends[1] if ends[0] is None else beaver(ends[0], ends[1], n_edges)
+    if folds[2] is not None:
+        r = folds[2] if r is None else beaver(r, folds[2], n_edges)
+    if r is None:
+        r = [ofss.valid_mask(n_edges), np.zeros((n_edges + 31) // 32, np.uint32)]
+    for b in range(2):
+        np.testing.assert_array_equal(U(plan.out[b]), r[b])
