@@ -25,7 +25,6 @@
 
 #include <array>
 #include <atomic>
-#include <initializer_list>
 #include <map>
 #include <mutex>
 
@@ -694,28 +693,49 @@ __global__ __launch_bounds__(1024) void k_bucket_rank(uint64_t n, uint32_t hb, u
 
 // A slice is words [16b, 16b + L) of record r, L = min(16, W - 16b): block
 // (r, b, table, W) of each mask table covers it, and lane c of a quad moves
-// its words 4c .. 4c + 3 (those below L).  VEC: W a multiple of 4 words and
-// every table 16-byte aligned, so a quarter is one 16-byte access.
-template <bool VEC>
+// its words 4c .. 4c + 3 (those below L).  WHOLE: the width is a multiple of
+// four words, so every quarter is whole or absent and moves in one 16-byte
+// access, whatever its alignment (global accesses need only a word's).  Other
+// widths move word by word: 16-byte accesses with a branch for the last words
+// measured 4% slower at 100,003 records of 21 words.
+template <bool WHOLE>
 __device__ __forceinline__ uint4 load_quarter(const uint32_t* __restrict__ t, uint64_t base, uint32_t c, uint32_t len) {
-    if (VEC) return 4 * c < len ? *(const uint4*)(t + base + 4 * c) : make_uint4(0u, 0u, 0u, 0u);
-    uint32_t v[4];
+    const uint32_t* p = t + base + 4 * c;
+    if constexpr (WHOLE) {
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (4 * c < len) __builtin_memcpy(&v, p, 16);
+        return v;
+    } else {
+        uint32_t v[4];
 #pragma unroll
-    for (uint32_t k = 0; k < 4; k++) v[k] = 4 * c + k < len ? t[base + 4 * c + k] : 0u;
-    return make_uint4(v[0], v[1], v[2], v[3]);
+        for (uint32_t k = 0; k < 4; k++) v[k] = 4 * c + k < len ? p[k] : 0u;
+        return make_uint4(v[0], v[1], v[2], v[3]);
+    }
 }
 
-template <bool VEC>
+template <bool WHOLE>
 __device__ __forceinline__ void store_quarter(uint32_t* __restrict__ t, uint64_t base, uint32_t c, uint32_t len,
                                               uint4 v) {
-    if (VEC) {
-        if (4 * c < len) *(uint4*)(t + base + 4 * c) = v;
-        return;
-    }
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    uint32_t* p = t + base + 4 * c;
+    if constexpr (WHOLE) {
+        if (4 * c < len) __builtin_memcpy(p, &v, 16);
+    } else {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-    for (uint32_t k = 0; k < 4; k++)
-        if (4 * c + k < len) t[base + 4 * c + k] = w[k];
+        for (uint32_t k = 0; k < 4; k++)
+            if (4 * c + k < len) p[k] = w[k];
+    }
+}
+
+// Record and slice of quad number sl of a table of nb slices a record.
+__device__ __forceinline__ void slice_of(uint64_t sl, uint32_t nb, uint32_t& i, uint32_t& b) {
+    if (nb == 1) {
+        i = (uint32_t)sl, b = 0;
+    } else if (sl >> 32) {
+        i = (uint32_t)(sl / nb), b = (uint32_t)(sl - (uint64_t)i * nb);
+    } else {                                     // a 32-bit division costs a fifth of a 64-bit one
+        i = (uint32_t)sl / nb, b = (uint32_t)sl - i * nb;
+    }
 }
 
 // An empty asm statement that the words pass through: it keeps the compiler
@@ -728,22 +748,32 @@ __device__ __forceinline__ void pin(uint4& v) {
 // Rounds pi12 and pi31 in one pass, as scatters through both inverse
 // permutations: input row i goes to row j = inv12[i] after pi12 and to row
 // l = inv31[j] after pi31, so
-//   o0[l] = (g0 ^ g1 ^ T12)[i] ^ T31[j]   (CS1's X1)
-//   o1[l] = (g2 ^ T12)[i] ^ T31[j]        (CS3's pi31(Y1 ^ T31), Y1 = CS2's pi12(D3 ^ T12))
+//   x1[l] = (g0 ^ g1 ^ T12)[i] ^ T31[j]   (CS1's X1)
+//   v[l] = (g2 ^ T12)[i] ^ T31[j]         (CS3's pi31(Y1 ^ T31), Y1 = CS2's pi12(D3 ^ T12))
 //   r12[i] = R2, r31[i] = R1.
 // The masks are indexed by the row they are XORed at: T12 before pi12, T31
-// before pi31.  A quad of lanes takes one slice.
-template <bool VEC>
+// before pi31.  A quad of lanes takes one slice.  The two tables x1 and v that
+// the final round gathers lie in xv: interleaved slice by slice for widths of
+// whole quarters, so that a gathered 16-word slice is one whole 128-byte line
+// instead of the halves of two (2^22 records of 64 bytes: final round 285-340
+// -> 240-290 us); one after the other for ragged widths, whose slices straddle
+// lines either way (100,003 records of 21 words: 23.4 us, interleaved 25.8).
+template <bool WHOLE>
+struct XvAt {
+    uint64_t x1, v;      // word offsets of slice b of row l
+    __device__ __forceinline__ XvAt(uint64_t l, uint32_t b, uint32_t len, uint64_t nrows, uint32_t nwords)
+        : x1(WHOLE ? 2 * l * nwords + 32 * b : l * nwords + 16 * b), v(WHOLE ? x1 + len : x1 + nrows * nwords) {}
+};
+
+template <bool WHOLE>
 __device__ __forceinline__ void first_slice(uint64_t t, uint64_t nrows, uint32_t nwords, ChachaKey k12, ChachaKey k31,
                                             const uint32_t* __restrict__ inv12, const uint32_t* __restrict__ inv31,
                                             const uint32_t* __restrict__ g0, const uint32_t* __restrict__ g1,
-                                            const uint32_t* __restrict__ g2, uint32_t* __restrict__ o0,
-                                            uint32_t* __restrict__ o1, uint32_t* __restrict__ r12,
-                                            uint32_t* __restrict__ r31) {
-    const uint32_t nb = (nwords + 15) >> 4;
+                                            const uint32_t* __restrict__ g2, uint32_t* __restrict__ xv,
+                                            uint32_t* __restrict__ r12, uint32_t* __restrict__ r31) {
     const uint32_t c = threadIdx.x & 3u;
-    const uint64_t sl = t >> 2;
-    const uint32_t i = (uint32_t)(sl / nb), b = (uint32_t)(sl - (uint64_t)i * nb);
+    uint32_t i, b;
+    slice_of(t >> 2, (nwords + 15) >> 4, i, b);
     const uint32_t len = nwords - 16 * b < 16 ? nwords - 16 * b : 16;
     // The blocks that do not need the load in flight are drawn while it is:
     // T12 while inv12[i] is, R2 and R1 while inv31[j] is.  A quad shares its
@@ -752,58 +782,55 @@ __device__ __forceinline__ void first_slice(uint64_t t, uint64_t nrows, uint32_t
     // row unwritten.
     const uint64_t src = (uint64_t)i * nwords + 16 * b;
     const uint32_t j = inv12[i];
-    const uint4 x = load_quarter<VEC>(g0, src, c, len), y = load_quarter<VEC>(g1, src, c, len);
-    const uint4 z = load_quarter<VEC>(g2, src, c, len);
+    const uint4 x = load_quarter<WHOLE>(g0, src, c, len), y = load_quarter<WHOLE>(g1, src, c, len);
+    const uint4 z = load_quarter<WHOLE>(g2, src, c, len);
     const uint4 t12 = chacha_quad(k12, i, b, kT12, nwords);
     if (j >= nrows) return;
     const uint32_t l = inv31[j];
     const uint4 r2 = chacha_quad(k12, i, b, kR2, nwords), r1 = chacha_quad(k31, i, b, kR1, nwords);
     const uint4 m = xor4(t12, chacha_quad(k31, j, b, kT31, nwords));
     if (l >= nrows) return;
-    const uint64_t dst = (uint64_t)l * nwords + 16 * b;
-    store_quarter<VEC>(r12, src, c, len, r2);
-    store_quarter<VEC>(r31, src, c, len, r1);
-    store_quarter<VEC>(o0, dst, c, len, xor4(xor4(x, y), m));
-    store_quarter<VEC>(o1, dst, c, len, xor4(z, m));
+    const XvAt<WHOLE> dst(l, b, len, nrows, nwords);
+    store_quarter<WHOLE>(r12, src, c, len, r2);
+    store_quarter<WHOLE>(r31, src, c, len, r1);
+    store_quarter<WHOLE>(xv, dst.x1, c, len, xor4(xor4(x, y), m));
+    store_quarter<WHOLE>(xv, dst.v, c, len, xor4(z, m));
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(kBlock) void k_shuffle_first(uint64_t nrows, uint32_t nwords, ChachaKey k12, ChachaKey k31,
+template <bool WHOLE>
+__global__ __launch_bounds__(kBlock, WHOLE ? 8 : 1) void k_shuffle_first(uint64_t nrows, uint32_t nwords, ChachaKey k12, ChachaKey k31,
                                                         const uint32_t* __restrict__ inv12,
                                                         const uint32_t* __restrict__ inv31,
                                                         const uint32_t* __restrict__ g0,
                                                         const uint32_t* __restrict__ g1,
-                                                        const uint32_t* __restrict__ g2, uint32_t* __restrict__ o0,
-                                                        uint32_t* __restrict__ o1, uint32_t* __restrict__ r12,
-                                                        uint32_t* __restrict__ r31) {
+                                                        const uint32_t* __restrict__ g2, uint32_t* __restrict__ xv,
+                                                        uint32_t* __restrict__ r12, uint32_t* __restrict__ r31) {
     const uint64_t total = nrows * ((nwords + 15) >> 4) * 4;
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
     for (uint64_t t = (uint64_t)blockIdx.x * kBlock + threadIdx.x; t < total; t += stride)
-        first_slice<VEC>(t, nrows, nwords, k12, k31, inv12, inv31, g0, g1, g2, o0, o1, r12, r31);
+        first_slice<WHOLE>(t, nrows, nwords, k12, k31, inv12, inv31, g0, g1, g2, xv, r12, r31);
 }
 
 // Round pi23 as a gather (its outputs are the result shares, written in
 // order): with p = perm[i],
-//   out[i] = C1 ^ C2, C1 = (g0 ^ T23)[p] ^ R2[i], C2 = (g1 ^ T23)[p] ^ R1[i]
+//   out[i] = C1 ^ C2, C1 = (x1 ^ T23)[p] ^ R2[i], C2 = (v ^ T23)[p] ^ R1[i]
 // (CS2's C1 = pi23(X1 ^ T23) ^ R2, CS3's C2 = pi23(pi31(Y1 ^ T31) ^ T23) ^ R1
 // and CS2's R3 = C1 ^ C2; with the servers simulated together C1 and C2 are
 // not stored).  R1 and R2 are made again from their pairs' keys rather than
 // read back.
 // open: 0 none; 1 secFetch's flag of each record (bit 0 of word 0); 2 the
 // secAccess filter's flag (parity of all bits) of records of at most 16
-// words (one slice).  The opened record is R1 ^ R2 ^ R3 = x ^ y, which the
+// words (one slice).  The opened record is R1 ^ R2 ^ R3 = x1 ^ v, which the
 // three servers' exchange reconstructs; the flag of output row i goes to
 // flags[i].
-template <bool VEC>
+template <bool WHOLE>
 __device__ __forceinline__ void final_slice(uint64_t t, uint64_t nrows, uint32_t nwords, ChachaKey k12, ChachaKey k23,
                                             ChachaKey k31, const uint32_t* __restrict__ perm,
-                                            const uint32_t* __restrict__ g0, const uint32_t* __restrict__ g1,
-                                            uint32_t* __restrict__ out, uint32_t open = 0,
-                                            uint32_t* __restrict__ flags = nullptr) {
-    const uint32_t nb = (nwords + 15) >> 4;
+                                            const uint32_t* __restrict__ xv, uint32_t* __restrict__ out,
+                                            uint32_t open = 0, uint32_t* __restrict__ flags = nullptr) {
     const uint32_t c = threadIdx.x & 3u;
-    const uint64_t sl = t >> 2;
-    const uint32_t i = (uint32_t)(sl / nb), b = (uint32_t)(sl - (uint64_t)i * nb);
+    uint32_t i, b;
+    slice_of(t >> 2, (nwords + 15) >> 4, i, b);
     const uint32_t len = nwords - 16 * b < 16 ? nwords - 16 * b : 16;
     const uint32_t p = perm[i];
     // R2 and R1 (indexed by the output row) while the load of p is in flight
@@ -812,14 +839,15 @@ __device__ __forceinline__ void final_slice(uint64_t t, uint64_t nrows, uint32_t
         if (open && b == 0 && c == 0) flags[i] = 0u;
         return;
     }
-    const uint64_t src = (uint64_t)p * nwords + 16 * b, dst = (uint64_t)i * nwords + 16 * b;
-    const uint4 x = load_quarter<VEC>(g0, src, c, len), y = load_quarter<VEC>(g1, src, c, len);
+    const XvAt<WHOLE> src(p, b, len, nrows, nwords);
+    const uint64_t dst = (uint64_t)i * nwords + 16 * b;
+    const uint4 x = load_quarter<WHOLE>(xv, src.x1, c, len), y = load_quarter<WHOLE>(xv, src.v, c, len);
     const uint4 m = chacha_quad(k23, p, b, kT23, nwords);
     uint4 c1 = xor4(x, m);
     pin(c1);
     c1 = xor4(c1, r2);
     const uint4 c2 = xor4(xor4(y, m), r1);
-    store_quarter<VEC>(out, dst, c, len, xor4(c1, c2));
+    store_quarter<WHOLE>(out, dst, c, len, xor4(c1, c2));
     if (open == 1) {
         if (b == 0 && c == 0) flags[i] = (x.x ^ y.x) & 1u;
     } else if (open == 2) {
@@ -830,16 +858,15 @@ __device__ __forceinline__ void final_slice(uint64_t t, uint64_t nrows, uint32_t
     }
 }
 
-template <bool VEC>
+template <bool WHOLE>
 __global__ __launch_bounds__(kBlock) void k_shuffle_final(uint64_t nrows, uint32_t nwords, ChachaKey k12, ChachaKey k23,
                                                         ChachaKey k31, const uint32_t* __restrict__ perm,
-                                                        const uint32_t* __restrict__ g0,
-                                                        const uint32_t* __restrict__ g1, uint32_t* __restrict__ out,
+                                                        const uint32_t* __restrict__ xv, uint32_t* __restrict__ out,
                                                         uint32_t open, uint32_t* __restrict__ flags) {
     const uint64_t total = nrows * ((nwords + 15) >> 4) * 4;
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
     for (uint64_t t = (uint64_t)blockIdx.x * kBlock + threadIdx.x; t < total; t += stride)
-        final_slice<VEC>(t, nrows, nwords, k12, k23, k31, perm, g0, g1, out, open, flags);
+        final_slice<WHOLE>(t, nrows, nwords, k12, k23, k31, perm, xv, out, open, flags);
 }
 
 // Case I: XOR over candidates of (r_i & m_i) ^ (r_j & m_i) ^ (r_i & m_j), the
@@ -1046,14 +1073,13 @@ __global__ __launch_bounds__(1024) void k_open_compact_small(uint32_t n, uint32_
 // with compact = 1 (secFetch: bit 0 of word 0) or 2 (secAccess filter: parity
 // of all bits), the open and compaction of the shuffled table.  The same
 // per-slice code as the multi-workgroup launches, so the same shares; the
-// rounds meet through global memory (x1, v, out) behind workgroup barriers.
+// rounds meet through global memory (xv, out) behind workgroup barriers.
 constexpr uint32_t kFusedSlices = 1024;
 
 struct SmallShuffle {
     ChachaKey k12, k23, k31;
     const uint32_t* g[3];
-    uint32_t* x1;
-    uint32_t* v;
+    uint32_t* xv;
     uint32_t* out[3];              // R1, R2, R3
     uint32_t compact;
     uint32_t* kept[3];
@@ -1061,7 +1087,7 @@ struct SmallShuffle {
     uint32_t* count;
 };
 
-template <bool VEC>
+template <bool WHOLE>
 __global__ __launch_bounds__(1024) void k_shuffle_small(uint32_t n, uint32_t nwords, SmallShuffle A) {
     __shared__ uint64_t key[kSmallPerm];
     __shared__ uint32_t perm[3][kSmallPerm];     // inverse of pi12, inverse of pi31, pi23
@@ -1072,11 +1098,10 @@ __global__ __launch_bounds__(1024) void k_shuffle_small(uint32_t n, uint32_t nwo
     small_perm(A.k23, kP23, 0u, n, key, perm[2]);
     const uint64_t total = (uint64_t)n * ((nwords + 15) >> 4) * 4;
     for (uint64_t t = threadIdx.x; t < total; t += blockDim.x)
-        first_slice<VEC>(t, n, nwords, A.k12, A.k31, perm[0], perm[1], A.g[0], A.g[1], A.g[2], A.x1, A.v, A.out[1],
-                         A.out[0]);
+        first_slice<WHOLE>(t, n, nwords, A.k12, A.k31, perm[0], perm[1], A.g[0], A.g[1], A.g[2], A.xv, A.out[1], A.out[0]);
     __syncthreads();
     for (uint64_t t = threadIdx.x; t < total; t += blockDim.x)
-        final_slice<VEC>(t, n, nwords, A.k12, A.k23, A.k31, perm[2], A.x1, A.v, A.out[2]);
+        final_slice<WHOLE>(t, n, nwords, A.k12, A.k23, A.k31, perm[2], A.xv, A.out[2]);
     if (!A.compact) return;
     __syncthreads();
     open_compact_block(n, nwords, A.compact == 2, A.out[0], A.out[1], A.out[2], A.kept[0], A.kept[1], A.kept[2],
@@ -1257,38 +1282,22 @@ int perm_step(int step, uint64_t nrows, const PermJob& j, uint32_t method) {
     }
 }
 
-// The 16-byte path needs the width a multiple of 4 words and every table
-// 16-byte aligned.
-bool vec_quarters(uint32_t nwords, std::initializer_list<const void*> tables) {
-    if (nwords & 3u) return false;
-    for (const void* t : tables)
-        if (!aligned16(t)) return false;
-    return true;
-}
-
 int shuffle_first(uint64_t nrows, uint32_t nwords, ChachaKey k12, ChachaKey k31, const uint32_t* inv12,
-                  const uint32_t* inv31, const uint32_t* g0, const uint32_t* g1, const uint32_t* g2, uint32_t* o0,
-                  uint32_t* o1, uint32_t* r12, uint32_t* r31, hipStream_t s) {
+                  const uint32_t* inv31, const uint32_t* g0, const uint32_t* g1, const uint32_t* g2, uint32_t* xv,
+                  uint32_t* r12, uint32_t* r31, hipStream_t s) {
     const unsigned grid = slice_grid(nrows * ((nwords + 15) / 16) * 4);
-    if (vec_quarters(nwords, {g0, g1, g2, o0, o1, r12, r31}))
-        hipLaunchKernelGGL(k_shuffle_first<true>, dim3(grid), dim3(kBlock), 0, s, nrows, nwords, k12, k31, inv12,
-                           inv31, g0, g1, g2, o0, o1, r12, r31);
-    else
-        hipLaunchKernelGGL(k_shuffle_first<false>, dim3(grid), dim3(kBlock), 0, s, nrows, nwords, k12, k31, inv12,
-                           inv31, g0, g1, g2, o0, o1, r12, r31);
+    auto k = nwords & 3u ? k_shuffle_first<false> : k_shuffle_first<true>;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(kBlock), 0, s, nrows, nwords, k12, k31, inv12, inv31, g0, g1, g2, xv, r12,
+                       r31);
     return check_launch("k_shuffle_first");
 }
 
 int shuffle_final(uint64_t nrows, uint32_t nwords, ChachaKey k12, ChachaKey k23, ChachaKey k31, const uint32_t* perm,
-                  const uint32_t* g0, const uint32_t* g1, uint32_t* out, uint32_t open, uint32_t* flags,
-                  hipStream_t s) {
+                  const uint32_t* xv, uint32_t* out, uint32_t open, uint32_t* flags, hipStream_t s) {
     const unsigned grid = slice_grid(nrows * ((nwords + 15) / 16) * 4);
-    if (vec_quarters(nwords, {g0, g1, out}))
-        hipLaunchKernelGGL(k_shuffle_final<true>, dim3(grid), dim3(kBlock), 0, s, nrows, nwords, k12, k23, k31, perm,
-                           g0, g1, out, open, flags);
-    else
-        hipLaunchKernelGGL(k_shuffle_final<false>, dim3(grid), dim3(kBlock), 0, s, nrows, nwords, k12, k23, k31, perm,
-                           g0, g1, out, open, flags);
+    auto k = nwords & 3u ? k_shuffle_final<false> : k_shuffle_final<true>;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(kBlock), 0, s, nrows, nwords, k12, k23, k31, perm, xv, out,
+                       open, flags);
     return check_launch("k_shuffle_final");
 }
 
@@ -1416,24 +1425,24 @@ struct PermSet {
 };
 
 // The data-dependent part of Alg. 5 (all three servers simulated), given the
-// permutations: out[0..2] = R1, R2, R3.  x1 and v are workspace tables.
+// permutations: out[0..2] = R1, R2, R3.  xv is a workspace table of two widths.
 // open / flags: the final round's optional open (final_slice).
 int shuffle_rounds(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], const uint64_t seeds[3],
-                   const uint32_t* inv12, const uint32_t* inv31, const uint32_t* p23, uint32_t* x1, uint32_t* v,
+                   const uint32_t* inv12, const uint32_t* inv31, const uint32_t* p23, uint32_t* xv,
                    uint32_t* const out[3], hipStream_t s, PermSet* pending, uint32_t open = 0,
                    uint32_t* flags = nullptr) {
     const ChachaKey k12 = pair_key(seeds[0]), k23 = pair_key(seeds[1]), k31 = pair_key(seeds[2]);
     // pi12 then pi31: CS1's X1, CS3's pi31(Y1 ^ T31); R2 and R1 drawn
     if (pending) pending->join(0);
     int rc = pending ? pending->rc : 0;
-    if (!rc) rc = shuffle_first(nrows, nwords, k12, k31, inv12, inv31, d[0], d[1], d[2], x1, v, out[1], out[0], s);
+    if (!rc) rc = shuffle_first(nrows, nwords, k12, k31, inv12, inv31, d[0], d[1], d[2], xv, out[1], out[0], s);
     // pi23: CS2's C1 = pi23(X1 ^ T23) ^ R2, CS3's C2 = pi23(pi31(Y1 ^ T31) ^ T23) ^ R1,
     // R3 = C1 ^ C2
     if (pending) {
         pending->join(1);
         if (!rc) rc = pending->rc;
     }
-    if (!rc) rc = shuffle_final(nrows, nwords, k12, k23, k31, p23, x1, v, out[2], open, flags, s);
+    if (!rc) rc = shuffle_final(nrows, nwords, k12, k23, k31, p23, xv, out[2], open, flags, s);
     return rc;
 }
 
@@ -1447,7 +1456,7 @@ bool fused_shuffle(uint64_t nrows, uint32_t nwords) {
 // The one-workgroup shuffle; compact: 0 none, 1 secFetch's open, 2 the
 // secAccess filter's (then kept / rows_out / count receive the compaction).
 int launch_fused(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], const uint64_t seeds[3],
-                 uint32_t* const out[3], uint32_t* x1, uint32_t* v, uint32_t compact, uint32_t* const kept[3],
+                 uint32_t* const out[3], uint32_t* xv, uint32_t compact, uint32_t* const kept[3],
                  uint32_t* rows_out, uint32_t* count, hipStream_t s) {
     SmallShuffle A{};
     A.k12 = pair_key(seeds[0]), A.k23 = pair_key(seeds[1]), A.k31 = pair_key(seeds[2]);
@@ -1456,27 +1465,24 @@ int launch_fused(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], co
         A.out[i] = out[i];
         A.kept[i] = kept ? kept[i] : nullptr;
     }
-    A.x1 = x1, A.v = v, A.compact = compact, A.rows_out = rows_out, A.count = count;
-    if (vec_quarters(nwords, {d[0], d[1], d[2], x1, v, out[0], out[1], out[2]}))
-        hipLaunchKernelGGL(k_shuffle_small<true>, dim3(1), dim3(1024), 0, s, (uint32_t)nrows, nwords, A);
-    else
-        hipLaunchKernelGGL(k_shuffle_small<false>, dim3(1), dim3(1024), 0, s, (uint32_t)nrows, nwords, A);
+    A.xv = xv, A.compact = compact, A.rows_out = rows_out, A.count = count;
+    auto k = nwords & 3u ? k_shuffle_small<false> : k_shuffle_small<true>;
+    hipLaunchKernelGGL(k, dim3(1), dim3(1024), 0, s, (uint32_t)nrows, nwords, A);
     return check_launch("k_shuffle_small");
 }
 
 int run_shuffle(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], const uint64_t seeds[3],
                 uint32_t* const out[3], Carve& ws, hipStream_t s, uint32_t open = 0, uint32_t* flags = nullptr) {
     const uint64_t tw = nrows * nwords;
-    uint32_t* x1 = ws.take<uint32_t>(tw);      // CS1 -> CS2: X1
-    uint32_t* v = ws.take<uint32_t>(tw);       // CS3: pi31(Y1 ^ T31)
+    uint32_t* xv = ws.take<uint32_t>(2 * tw);  // CS1 -> CS2: X1; CS3: pi31(Y1 ^ T31)
     uint32_t* inv12 = ws.take<uint32_t>(nrows);
     uint32_t* inv31 = ws.take<uint32_t>(nrows);
     uint32_t* p23 = ws.take<uint32_t>(nrows);
     if (!ws.ok) return fail(FSS_ENOMEM, "rss_shuffle: workspace too small");
-    if (fused_shuffle(nrows, nwords)) return launch_fused(nrows, nwords, d, seeds, out, x1, v, 0, nullptr, nullptr, nullptr, s);
+    if (fused_shuffle(nrows, nwords)) return launch_fused(nrows, nwords, d, seeds, out, xv, 0, nullptr, nullptr, nullptr, s);
     PermSet ps{s};
     ps.begin(nrows, seeds, inv12, inv31, p23, ws);
-    const int rc = shuffle_rounds(nrows, nwords, d, seeds, inv12, inv31, p23, x1, v, out, s, &ps, open, flags);
+    const int rc = shuffle_rounds(nrows, nwords, d, seeds, inv12, inv31, p23, xv, out, s, &ps, open, flags);
     ps.finish();
     return rc;
 }
@@ -1599,10 +1605,9 @@ int rss_shuffle_prepared(uint64_t nrows, uint32_t nwords, const uint32_t* const 
                     (unsigned long long)rss_shuffle_prepared_workspace_bytes(nrows, nwords));
     Carve ws{(uint8_t*)d_work, work_bytes};
     const uint64_t tw = nrows * nwords;
-    uint32_t* x1 = ws.take<uint32_t>(tw);
-    uint32_t* v = ws.take<uint32_t>(tw);
+    uint32_t* xv = ws.take<uint32_t>(2 * tw);
     if (!ws.ok) return fail(FSS_ENOMEM, "rss_shuffle_prepared: workspace too small");
-    return shuffle_rounds(nrows, nwords, d_in, seeds, d_perms, d_perms + nrows, d_perms + 2 * nrows, x1, v, d_out,
+    return shuffle_rounds(nrows, nwords, d_in, seeds, d_perms, d_perms + nrows, d_perms + 2 * nrows, xv, d_out,
                           (hipStream_t)stream, nullptr);
 }
 
@@ -1693,10 +1698,9 @@ static int shuffle_open_compact(uint64_t ncand, uint32_t nwords, const uint32_t*
     if (fused_shuffle(ncand, nwords)) {
         // the shuffle, the open and the compaction in one workgroup
         const uint64_t tw = ncand * nwords;
-        uint32_t* x1 = ws.take<uint32_t>(tw);
-        uint32_t* v = ws.take<uint32_t>(tw);
+        uint32_t* xv = ws.take<uint32_t>(2 * tw);
         if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
-        return launch_fused(ncand, nwords, d_table, seeds, sh, x1, v, parity ? 2u : 1u, d_out, d_rows_out, d_count, s);
+        return launch_fused(ncand, nwords, d_table, seeds, sh, xv, parity ? 2u : 1u, d_out, d_rows_out, d_count, s);
     }
     const bool small = ncand <= kSmallPerm;
     // the final round opens secFetch's bit, and the secAccess filter's parity
