@@ -5,7 +5,8 @@
 //   k_place_ids,
 //   k_split_records        one-hot posting records in CSR order, split into
 //                          binary RSS with the ChaCha12 PRF     (HBM stream)
-//   k_csr_select           P_m[l] = XOR_c id_m[c] AND id_{c,l}  (HBM stream, 16-byte loads, XOR atomics)
+//   k_csr_select           P_m[l] = XOR_c id_m[c] AND id_{c,l}, for up to eight
+//                          matched vertices m at once           (HBM stream, XOR atomics)
 //   k_attr_select          d = XOR_x id[x] AND d_x per kept ID  (HBM stream, XOR atomics)
 // rss_sec_access chains the selection, the RSS re-share, the shuffle with the
 // parity open and compaction (shuffle.hip) and the attribute selection.
@@ -132,155 +133,174 @@ struct Out3 {
     uint32_t* p[3];
 };
 
-// Zeroes n words of each of three buffers (one launch for the three shares).
-__global__ void k_zero3(uint64_t n, Out3 o) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) {
-        o.p[0][k] = 0u;
-        o.p[1][k] = 0u;
-        o.p[2][k] = 0u;
+// Slot l = blockIdx.y of the fetched lists of M calls (call0 = blockIdx.z * M):
+// XOR over this block's candidates c with l < len_c of id_m[c] AND record
+// (off_c + l), into out[.][call * lmax * wx + l * wx + w].  First the block
+// lists in LDS the candidates whose (public, padded) list reaches slot l, with
+// the three mask bits of each call; then its threads stream those records, V
+// words per load and two records per step, and add each to the sums of all M
+// calls: with the calls one by one the posting lists, the bulk of the bytes,
+// were read once per call (8 calls over 30,011 candidates and 1,000-byte
+// records: 8 x 52 us, now 105 us).  With t_i = r_i ^ r_j, j = i + 1, a product
+// x_i r_i ^ x_i r_j ^ x_j r_i is (t_i & x_i) ^ (r_i & x_j): two three-input
+// operations a word.  The threads' sums meet in LDS by XOR atomics, then go to
+// the zeroed output by 8-byte XOR atomics, 3 M wx / 2 a block.  Those bound a
+// grid of many blocks (86, 171 and 341 blocks a slot, 4-byte atomics: 109, 182
+// and 323 us), so the
+// sparse slots take fewer: N posting records in all leave at most N / (l + 1)
+// lists that reach slot l, and slot l gets 1 / (l + 1) of slot 0's blocks.
+constexpr int kSelThreads = 512;
+constexpr uint32_t kSelCand = 1024;       // candidates listed at a time
+constexpr uint32_t kSelTile = 256;        // record words per pass
+
+// Blocks of slot l, of which slot 0 has `most`; a block takes at most 2 kSelCand candidates.
+__host__ __device__ inline uint64_t sel_chunks(uint64_t ncand, uint64_t most, uint32_t l) {
+    const uint64_t least = (ncand + 2 * kSelCand - 1) / (2 * kSelCand), c = (most + l) / (l + 1);
+    return c > least ? c : least;
+}
+
+struct IdmSet {
+    const uint32_t* p[kSideCalls][3];
+};
+
+template <int V>
+__device__ __forceinline__ void load_words(uint32_t (&r)[V], const uint32_t* __restrict__ p, uint32_t left) {
+    if (left >= V) {
+        __builtin_memcpy(r, p, 4 * V);
+    } else {
+#pragma unroll
+        for (uint32_t q = 0; q < V; q++) r[q] = q < left ? p[q] : 0u;
     }
 }
 
-// Slot l = blockIdx.y of the fetched list: XOR over this block's candidates c
-// with l < len_c of id_m[c] AND record (off_c + l), into out[.][l * wx + w].
-// First the block lists in LDS the candidates whose (public, padded) list
-// reaches slot l, with their three mask bits; then its threads stream those
-// records, V words (16 bytes for V = 4) per load and two records per step, so
-// that each lane keeps six loads in flight.  At most kSelCand candidates per
-// block (the host sizes the grid for it).
-constexpr uint32_t kSelCand = 512;
-
-template <int V>
-struct SelVec;
-template <>
-struct SelVec<1> {
-    using T = uint32_t;
-    static __device__ __forceinline__ T zero() { return 0u; }
-    static __device__ __forceinline__ void prod(const uint32_t m[3], const T r[3], T acc[3]) { rss_product(m, r, acc); }
-    static __device__ __forceinline__ uint32_t word(const T& v, int) { return v; }
-};
-template <>
-struct SelVec<4> {
-    using T = uint4;
-    static __device__ __forceinline__ T zero() { return make_uint4(0u, 0u, 0u, 0u); }
-    static __device__ __forceinline__ void prod(const uint32_t m[3], const T r[3], T acc[3]) {
+template <int M, int V>
+__device__ __forceinline__ void sel_add(uint32_t (&acc)[M][3][V], const uint32_t (&r)[3][V], uint32_t bits) {
+    uint32_t t[3][V];
 #pragma unroll
-        for (int i = 0; i < 3; i++) {
-            const int j = (i + 1) % 3;
-            acc[i].x ^= (r[i].x & m[i]) ^ (r[j].x & m[i]) ^ (r[i].x & m[j]);
-            acc[i].y ^= (r[i].y & m[i]) ^ (r[j].y & m[i]) ^ (r[i].y & m[j]);
-            acc[i].z ^= (r[i].z & m[i]) ^ (r[j].z & m[i]) ^ (r[i].z & m[j]);
-            acc[i].w ^= (r[i].w & m[i]) ^ (r[j].w & m[i]) ^ (r[i].w & m[j]);
-        }
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int q = 0; q < V; q++) t[i][q] = r[i][q] ^ r[(i + 1) % 3][q];
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+        uint32_t x[3];
+#pragma unroll
+        for (int i = 0; i < 3; i++) x[i] = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 3 * m + i, 1);
+#pragma unroll
+        for (int i = 0; i < 3; i++)
+#pragma unroll
+            for (int q = 0; q < V; q++) {
+                const uint32_t a = __builtin_amdgcn_bitop3_b32(acc[m][i][q], t[i][q], x[i], 0x78);   // a ^ (b & c)
+                acc[m][i][q] = __builtin_amdgcn_bitop3_b32(a, r[i][q], x[(i + 1) % 3], 0x78);
+            }
     }
-    static __device__ __forceinline__ uint32_t word(const T& v, int q) {
-        return q == 0 ? v.x : q == 1 ? v.y : q == 2 ? v.z : v.w;
-    }
-};
+}
 
-template <int V>
-__global__ __launch_bounds__(kSelBlock) void k_csr_select(uint64_t ncand, uint32_t wx, Shares3 idm,
-                                                          const uint32_t* __restrict__ off, Shares3 post, Out3 out) {
-    using S = SelVec<V>;
-    using T = typename S::T;
+template <int M, int V>
+__global__ __launch_bounds__(kSelThreads) void k_csr_select(uint64_t ncand, uint32_t wx, uint32_t ncalls, uint64_t tw,
+                                                            IdmSet idm, const uint32_t* __restrict__ off, Shares3 post,
+                                                            Out3 out) {
     __shared__ uint32_t rec[kSelCand];
     __shared__ uint32_t msk[kSelCand];
     __shared__ uint32_t nsel;
-    __shared__ T part[3][kSelBlock];
-    const uint32_t l = blockIdx.y;
-    const uint64_t per = (ncand + gridDim.x - 1) / gridDim.x;
-    const uint64_t c0 = (uint64_t)blockIdx.x * per;
-    const uint64_t c1 = c0 + per < ncand ? c0 + per : ncand;
+    __shared__ uint32_t sum[M * 3][kSelTile];
+    const uint32_t l = blockIdx.y, call0 = blockIdx.z * M;
+    const uint32_t nm = min(ncalls - call0, (uint32_t)M);
+    const uint64_t chunks = sel_chunks(ncand, gridDim.x, l);
+    if (blockIdx.x >= chunks) return;
+    const uint64_t per = (ncand + chunks - 1) / chunks;
+    const uint64_t c1 = min((blockIdx.x + 1) * per, ncand);
     const uint32_t t = threadIdx.x;
-    if (t == 0) nsel = 0;
-    __syncthreads();
-    for (uint64_t c = c0 + t; c < c1; c += kSelBlock) {
-        const uint32_t o = off[c];
-        if (l >= off[c + 1] - o) continue;              // the list ends before slot l
-        uint32_t m = 0;
+    for (uint64_t c0 = blockIdx.x * per; c0 < c1; c0 += kSelCand) {
+        if (t == 0) nsel = 0;
+        __syncthreads();
+        const uint64_t ce = min(c0 + kSelCand, c1);
+        for (uint64_t c = c0 + t; c < ce; c += kSelThreads) {
+            const uint32_t o = off[c];
+            if (l >= off[c + 1] - o) continue;              // the list ends before slot l
+            uint32_t bits = 0;
 #pragma unroll
-        for (int i = 0; i < 3; i++) m |= ((idm.p[i][c >> 5] >> (c & 31)) & 1u) << i;
-        const uint32_t k = atomicAdd(&nsel, 1u);         // order-free: the products are XORed
-        if (k < kSelCand) {
+            for (int m = 0; m < M; m++)
+                if ((uint32_t)m < nm)
+#pragma unroll
+                    for (int i = 0; i < 3; i++)
+                        bits |= ((idm.p[call0 + m][i][c >> 5] >> (c & 31)) & 1u) << (3 * m + i);
+            const uint32_t k = atomicAdd(&nsel, 1u);         // order-free: the products are XORed
             rec[k] = o + l;
-            msk[k] = m;
+            msk[k] = bits;
         }
-    }
-    __syncthreads();
-    const uint32_t n = nsel < kSelCand ? nsel : kSelCand;
-    const uint32_t nv = wx / V;                          // loads per record
-    const T* src[3] = {(const T*)post.p[0], (const T*)post.p[1], (const T*)post.p[2]};
-    for (uint32_t v0 = 0; v0 < nv; v0 += kSelBlock) {
-        const uint32_t tw = nv - v0 < kSelBlock ? nv - v0 : kSelBlock;
-        const uint32_t lanes = kSelBlock / tw;
-        const uint32_t w = t % tw, g = t / tw;
-        T acc[3] = {S::zero(), S::zero(), S::zero()};
-        if (g < lanes) {
-            uint32_t k = g;
-            for (; k + lanes < n; k += 2 * lanes) {
-                const uint64_t a = (uint64_t)rec[k] * nv + v0 + w, b = (uint64_t)rec[k + lanes] * nv + v0 + w;
-                T ra[3], rb[3];
-#pragma unroll
-                for (int i = 0; i < 3; i++) {
-                    ra[i] = src[i][a];
-                    rb[i] = src[i][b];
-                }
-                uint32_t ma[3], mb[3];
-#pragma unroll
-                for (int i = 0; i < 3; i++) {
-                    ma[i] = 0u - ((msk[k] >> i) & 1u);
-                    mb[i] = 0u - ((msk[k + lanes] >> i) & 1u);
-                }
-                S::prod(ma, ra, acc);
-                S::prod(mb, rb, acc);
-            }
-            if (k < n) {
-                const uint64_t a = (uint64_t)rec[k] * nv + v0 + w;
-                T ra[3];
-                uint32_t ma[3];
-#pragma unroll
-                for (int i = 0; i < 3; i++) {
-                    ra[i] = src[i][a];
-                    ma[i] = 0u - ((msk[k] >> i) & 1u);
-                }
-                S::prod(ma, ra, acc);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 3; i++) part[i][t] = acc[i];
         __syncthreads();
-        if (t < tw) {
+        const uint32_t n = nsel;
+        for (uint32_t w0 = 0; n && w0 < wx; w0 += kSelTile) {
+            const uint32_t words = min(wx - w0, kSelTile);
+            const uint32_t nv = (words + V - 1) / V;         // loads per record
+            const uint32_t lanes = kSelThreads / nv;
+            const uint32_t v = t % nv, g = t / nv;
+            const uint32_t left = words - v * V;
+            for (uint32_t k = t; k < M * 3 * kSelTile; k += kSelThreads) (&sum[0][0])[k] = 0u;
+            __syncthreads();
+            if (g < lanes) {
+                uint32_t acc[M][3][V] = {};
+                const uint32_t* src[3];
 #pragma unroll
-            for (int i = 0; i < 3; i++) {
-                T v = S::zero();
-                for (uint32_t k = 0; k < lanes; k++) {
-                    const T p = part[i][k * tw + t];
-                    if constexpr (V == 4) {
-                        v.x ^= p.x; v.y ^= p.y; v.z ^= p.z; v.w ^= p.w;
-                    } else {
-                        v ^= p;
+                for (int i = 0; i < 3; i++) src[i] = post.p[i] + w0 + v * V;
+                uint32_t k = g;
+                for (; k + lanes < n; k += 2 * lanes) {
+                    const uint64_t a = (uint64_t)rec[k] * wx, b = (uint64_t)rec[k + lanes] * wx;
+                    uint32_t ra[3][V], rb[3][V];
+#pragma unroll
+                    for (int i = 0; i < 3; i++) {
+                        load_words<V>(ra[i], src[i] + a, left);
+                        load_words<V>(rb[i], src[i] + b, left);
                     }
+                    sel_add<M, V>(acc, ra, msk[k]);
+                    sel_add<M, V>(acc, rb, msk[k + lanes]);
+                }
+                if (k < n) {
+                    uint32_t ra[3][V];
+#pragma unroll
+                    for (int i = 0; i < 3; i++) load_words<V>(ra[i], src[i] + (uint64_t)rec[k] * wx, left);
+                    sel_add<M, V>(acc, ra, msk[k]);
                 }
 #pragma unroll
-                for (int q = 0; q < V; q++) {
-                    const uint32_t x = S::word(v, q);
-                    if (x) atomicXor(&out.p[i][(uint64_t)l * wx + (uint64_t)(v0 + t) * V + q], x);
-                }
+                for (int m = 0; m < M; m++)
+#pragma unroll
+                    for (int i = 0; i < 3; i++)
+#pragma unroll
+                        for (int q = 0; q < V; q++)
+                            if (v * V + q < words) atomicXor(&sum[3 * m + i][v * V + q], acc[m][i][q]);
             }
+            __syncthreads();
+            // pairs of words at multiples of 8 bytes, with the odd word at either end on its own
+            const uint32_t items = words / 2 + 1;
+            for (uint32_t k = t; k < 3 * nm * items; k += kSelThreads) {
+                const uint32_t mi = k / items, m = mi / 3;
+                uint32_t* to = out.p[mi - 3 * m] + (call0 + m) * tw + (uint64_t)l * wx + w0;
+                const uint32_t odd = ((uintptr_t)to >> 2) & 1u;
+                const int w = 2 * (int)(k - mi * items) - (int)odd;     // -1: word 0 alone
+                const uint32_t lo = w >= 0 && w < (int)words ? sum[mi][w] : 0u;
+                const uint32_t hi = w + 1 < (int)words ? sum[mi][w + 1] : 0u;
+                if (w >= 0 && w + 1 < (int)words)
+                    atomicXor((unsigned long long*)(to + w), (unsigned long long)lo | ((unsigned long long)hi << 32));
+                else if (w >= 0 && w < (int)words)
+                    atomicXor(to + w, lo);
+                else if (w + 1 < (int)words)
+                    atomicXor(to + w + 1, hi);
+            }
+            __syncthreads();
         }
-        __syncthreads();
+        __syncthreads();                                     // the list is free again
     }
 }
 
-// Kept ID k = blockIdx.y (exits when k >= *count): XOR over this block's
-// attribute rows x < x_bits of bit x of the kept record AND row x.
+// Kept ID k = blockIdx.y of call blockIdx.z (exits when k >= its count): XOR
+// over this block's attribute rows x < x_bits of bit x of the kept record AND
+// row x.
 __global__ __launch_bounds__(kSelBlock) void k_attr_select(uint32_t x_bits, uint32_t wx, uint32_t wd,
                                                            const uint32_t* __restrict__ count, Shares3 ids,
                                                            Shares3 attr, Out3 out) {
     __shared__ uint32_t part[3][kSelBlock];
-    const uint32_t k = blockIdx.y;
-    if (k >= *count) return;                                      // uniform over the block
+    if (blockIdx.y >= count[blockIdx.z]) return;                  // uniform over the block
+    const uint64_t k = (uint64_t)blockIdx.z * gridDim.y + blockIdx.y;
     const uint64_t per = ((uint64_t)x_bits + gridDim.x - 1) / gridDim.x;
     const uint64_t x0 = (uint64_t)blockIdx.x * per;
     const uint64_t x1 = x0 + per < x_bits ? x0 + per : x_bits;
@@ -295,13 +315,13 @@ __global__ __launch_bounds__(kSelBlock) void k_attr_select(uint32_t x_bits, uint
                 uint32_t m[3], r[3];
 #pragma unroll
                 for (int i = 0; i < 3; i++) {
-                    m[i] = 0u - ((ids.p[i][(uint64_t)k * wx + (x >> 5)] >> (x & 31)) & 1u);
+                    m[i] = 0u - ((ids.p[i][k * wx + (x >> 5)] >> (x & 31)) & 1u);
                     r[i] = attr.p[i][x * wd + w0 + w];
                 }
                 rss_product(m, r, acc);
             }
         }
-        reduce_out(part, acc, tw, lanes, out.p, (uint64_t)k * wd + w0);
+        reduce_out(part, acc, tw, lanes, out.p, k * wd + w0);
     }
 }
 
@@ -407,6 +427,98 @@ uint64_t rss_sec_access_workspace_bytes(uint32_t lmax, uint32_t x_bits, uint32_t
     return 6 * rnd(l * wx) + 3 * rnd(l * attr_words) + rss_fetch_many_workspace_bytes(l, (uint32_t)wx) + 256;
 }
 
+// The calls of a secAccess batch, as many side by side as the workspace holds
+// single calls (each step one launch for all of them), the rest after them.
+static int sec_access_calls(uint32_t count, uint64_t ncand, uint32_t x_bits, const uint32_t* const* d_idm,
+                            const uint32_t* d_off, uint32_t lmax, const uint32_t* const* d_post, uint32_t attr_words,
+                            const uint32_t* const* d_attr, const uint64_t* prf_keys, const uint32_t* counters,
+                            const uint64_t* seeds, uint32_t* const* d_ids, uint32_t* const* d_attrs,
+                            uint32_t* d_rows_out, uint32_t* d_count, void* d_work, uint64_t work_bytes, void* stream,
+                            const char* who) {
+    if (x_bits == 0 || attr_words == 0) return fail(FSS_EINVAL, "%s: empty IDs or attribute records", who);
+    if (lmax == 0 || lmax > 65535) return fail(FSS_EINVAL, "%s: lmax %u outside 1..65535", who, lmax);
+    if (!d_off || !d_post || !d_attr || !prf_keys) return fail(FSS_EINVAL, "%s: NULL argument", who);
+    for (int i = 0; i < 3; i++)
+        if (!d_post[i] || !d_attr[i]) return fail(FSS_EINVAL, "%s: NULL share %d", who, i);
+    if (ncand > 0xFFFFFFFFull) return fail(FSS_EUNSUPPORTED, "%s: more than 2^32 candidates", who);
+    const uint32_t wx = (x_bits + 31) / 32, wd = attr_words;
+    const uint64_t single = rss_sec_access_workspace_bytes(lmax, x_bits, wd);
+    if (!d_work || work_bytes < single)
+        return fail(FSS_ENOMEM, "%s: workspace needs %llu bytes", who, (unsigned long long)single);
+    hipStream_t s = (hipStream_t)stream;
+    const uint64_t tw = (uint64_t)lmax * wx, ta = (uint64_t)lmax * wd;
+    // side by side: tables that one workgroup shuffles
+    const bool small = small_shuffle_fits(lmax, wx);
+    const uint32_t most = small ? (uint32_t)std::min<uint64_t>(std::min<uint64_t>(count, kSideCalls), work_bytes / single)
+                                : 1u;
+    std::vector<uint32_t> row0(most + 1);
+    for (uint32_t c = 0; c <= most; c++) row0[c] = c * lmax;
+    for (uint32_t c0 = 0; c0 < count; c0 += most) {
+        const uint32_t n = std::min(count - c0, most);
+        Carve ws{(uint8_t*)d_work, work_bytes};
+        uint32_t* zeroed = ws.take(3 * n * (tw + ta));
+        uint32_t* add[3] = {zeroed, zeroed + n * tw, zeroed + 2 * n * tw};
+        uint32_t* att[3];
+        for (int i = 0; i < 3; i++) att[i] = zeroed + 3 * n * tw + i * n * ta;
+        uint32_t* rss[3] = {ws.take(n * tw), ws.take(n * tw), ws.take(n * tw)};
+        if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
+        uint32_t *ids[3], *attrs[3];
+        for (int i = 0; i < 3; i++) {
+            ids[i] = d_ids[i] + c0 * tw;
+            attrs[i] = d_attrs[i] + c0 * ta;
+        }
+        // 1. P_m[l] = XOR_c id_m[c] AND id_{c,l}: additive shares
+        hipLaunchKernelGGL(k_fill, dim3(blocks_for(3 * n * (tw + ta), 256, 4096)), dim3(256), 0, s, 3 * n * (tw + ta), 0u,
+                           zeroed);
+        if (ncand) {
+            IdmSet idm{};
+            for (uint32_t c = 0; c < n; c++)
+                for (int i = 0; i < 3; i++) idm.p[c][i] = d_idm[3 * (uint64_t)(c0 + c) + i];
+            // blocks of slot 0, the most of any slot: enough to fill the chip over lmax slots
+            const uint64_t chunks = sel_chunks(ncand, std::min<uint64_t>((ncand + 63) / 64, 4096 / lmax + 1), 0);
+            const uint32_t m = n > 4 ? 8 : n > 1 ? 4 : 1;      // calls per pass over the lists
+            const dim3 grid((unsigned)chunks, lmax, (n + m - 1) / m);
+            const Shares3 post{{d_post[0], d_post[1], d_post[2]}};
+            const Out3 o{{add[0], add[1], add[2]}};
+            auto k = m == 8 ? k_csr_select<8, 2> : m == 4 ? k_csr_select<4, 4> : k_csr_select<1, 4>;
+            hipLaunchKernelGGL(k, grid, dim3(kSelThreads), 0, s, ncand, wx, n, tw, idm, d_off, post, o);
+        }
+        int rc = check_launch("k_csr_select");
+        if (rc) return rc;
+        // ... re-shared into RSS
+        const uint32_t* a3[3] = {add[0], add[1], add[2]};
+        rc = reshare_calls(n, tw, a3, prf_keys, counters + c0, 0, rss, stream);
+        if (rc) return rc;
+        // 2. shuffle, open the parity of each record, keep the valid IDs
+        const uint32_t* r3[3] = {rss[0], rss[1], rss[2]};
+        if (small) {
+            uint32_t* sh[3] = {ws.take(n * tw), ws.take(n * tw), ws.take(n * tw)};
+            uint32_t* xv = ws.take(2 * n * tw);
+            if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
+            rc = small_shuffles(n, row0.data(), wx, r3, seeds + 3 * (uint64_t)c0, xv, sh, 2u, ids,
+                                d_rows_out + (uint64_t)c0 * lmax, d_count + c0, stream);
+        } else {
+            const uint64_t cws = rss_fetch_many_workspace_bytes(lmax, wx);
+            uint32_t* cwork = ws.take((cws + 3) / 4);
+            if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
+            rc = rss_compact_valid(lmax, wx, r3, seeds + 3 * (uint64_t)c0, ids, d_rows_out + (uint64_t)c0 * lmax,
+                                   d_count + c0, cwork, cws, stream);
+        }
+        if (rc) return rc;
+        // 3. the attribute record of every kept ID, then one re-share of them all
+        const uint64_t xchunks = std::max<uint64_t>(1, std::min<uint64_t>((x_bits + 255) / 256, 2048 / lmax + 1));
+        hipLaunchKernelGGL(k_attr_select, dim3((unsigned)xchunks, lmax, n), dim3(kSelBlock), 0, s, x_bits, wx, wd,
+                           d_count + c0, Shares3{{ids[0], ids[1], ids[2]}}, Shares3{{d_attr[0], d_attr[1], d_attr[2]}},
+                           Out3{{att[0], att[1], att[2]}});
+        rc = check_launch("k_attr_select");
+        if (rc) return rc;
+        const uint32_t* t3[3] = {att[0], att[1], att[2]};
+        rc = reshare_calls(n, ta, t3, prf_keys, counters + c0, 1, attrs, stream);
+        if (rc) return rc;
+    }
+    return FSS_OK;
+}
+
 int rss_sec_access(uint64_t ncand, uint32_t x_bits, const uint32_t* const d_idm[3], const uint32_t* d_off,
                    uint32_t lmax, const uint32_t* const d_post[3], uint32_t attr_words,
                    const uint32_t* const d_attr[3], const uint64_t prf_keys[3], uint32_t counter,
@@ -414,64 +526,12 @@ int rss_sec_access(uint64_t ncand, uint32_t x_bits, const uint32_t* const d_idm[
                    uint32_t* d_rows_out, uint32_t* d_count, void* d_work, uint64_t work_bytes, void* stream) {
     last_error().clear();
     const char* who = "rss_sec_access";
-    if (x_bits == 0 || attr_words == 0) return fail(FSS_EINVAL, "%s: empty IDs or attribute records", who);
-    if (lmax == 0 || lmax > 65535) return fail(FSS_EINVAL, "%s: lmax %u outside 1..65535", who, lmax);
-    if (!d_idm || !d_off || !d_post || !d_attr || !prf_keys || !seeds || !d_ids || !d_attrs || !d_rows_out || !d_count)
+    if (!d_idm || !seeds || !d_ids || !d_attrs || !d_rows_out || !d_count)
         return fail(FSS_EINVAL, "%s: NULL argument", who);
     for (int i = 0; i < 3; i++)
-        if (!d_idm[i] || !d_post[i] || !d_attr[i] || !d_ids[i] || !d_attrs[i])
-            return fail(FSS_EINVAL, "%s: NULL share %d", who, i);
-    if (ncand > 0xFFFFFFFFull) return fail(FSS_EUNSUPPORTED, "%s: more than 2^32 candidates", who);
-    const uint32_t wx = (x_bits + 31) / 32, wd = attr_words;
-    if (!d_work || work_bytes < rss_sec_access_workspace_bytes(lmax, x_bits, wd))
-        return fail(FSS_ENOMEM, "%s: workspace needs %llu bytes", who,
-                    (unsigned long long)rss_sec_access_workspace_bytes(lmax, x_bits, wd));
-    hipStream_t s = (hipStream_t)stream;
-    Carve ws{(uint8_t*)d_work, work_bytes};
-    const uint64_t tw = (uint64_t)lmax * wx, ta = (uint64_t)lmax * wd;
-    uint32_t* add[3] = {ws.take(tw), ws.take(tw), ws.take(tw)};
-    uint32_t* rss[3] = {ws.take(tw), ws.take(tw), ws.take(tw)};
-    uint32_t* att[3] = {ws.take(ta), ws.take(ta), ws.take(ta)};
-    const uint64_t cws = rss_fetch_many_workspace_bytes(lmax, wx);
-    uint8_t* cwork = (uint8_t*)ws.take((cws + 3) / 4);
-    if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
-    // 1. P_m[l] = XOR_c id_m[c] AND id_{c,l}: additive shares
-    hipLaunchKernelGGL(k_zero3, dim3(blocks_for(tw, 256, 4096)), dim3(256), 0, s, tw, Out3{{add[0], add[1], add[2]}});
-    if (ncand) {
-        // enough chunks to fill the chip over lmax slots, and at most kSelCand candidates per chunk
-        const uint64_t chunks = std::max<uint64_t>((ncand + kSelCand - 1) / kSelCand,
-                                                   std::min<uint64_t>((ncand + 63) / 64, 4096 / lmax + 1));
-        const Shares3 idm{{d_idm[0], d_idm[1], d_idm[2]}}, post{{d_post[0], d_post[1], d_post[2]}};
-        const Out3 o{{add[0], add[1], add[2]}};
-        bool vec = wx % 4 == 0;
-        for (int i = 0; i < 3; i++) vec = vec && ((uintptr_t)d_post[i] & 15) == 0;
-        if (vec)
-            hipLaunchKernelGGL(k_csr_select<4>, dim3((unsigned)chunks, lmax), dim3(kSelBlock), 0, s, ncand, wx, idm,
-                               d_off, post, o);
-        else
-            hipLaunchKernelGGL(k_csr_select<1>, dim3((unsigned)chunks, lmax), dim3(kSelBlock), 0, s, ncand, wx, idm,
-                               d_off, post, o);
-    }
-    int rc = check_launch("k_csr_select");
-    if (rc) return rc;
-    // ... re-shared into RSS
-    const uint32_t* a3[3] = {add[0], add[1], add[2]};
-    rc = rss_reshare(32 * tw, a3, prf_keys, counter, rss, stream);
-    if (rc) return rc;
-    // 2. shuffle, open the parity of each record, keep the valid IDs
-    const uint32_t* r3[3] = {rss[0], rss[1], rss[2]};
-    rc = rss_compact_valid(lmax, wx, r3, seeds, d_ids, d_rows_out, d_count, cwork, cws, stream);
-    if (rc) return rc;
-    // 3. the attribute record of every kept ID, then one re-share of them all
-    hipLaunchKernelGGL(k_zero3, dim3(blocks_for(ta, 256, 4096)), dim3(256), 0, s, ta, Out3{{att[0], att[1], att[2]}});
-    const uint64_t xchunks = std::max<uint64_t>(1, std::min<uint64_t>((x_bits + 255) / 256, 2048 / lmax + 1));
-    hipLaunchKernelGGL(k_attr_select, dim3((unsigned)xchunks, lmax), dim3(kSelBlock), 0, s, x_bits, wx, wd, d_count,
-                       Shares3{{d_ids[0], d_ids[1], d_ids[2]}}, Shares3{{d_attr[0], d_attr[1], d_attr[2]}},
-                       Out3{{att[0], att[1], att[2]}});
-    rc = check_launch("k_attr_select");
-    if (rc) return rc;
-    const uint32_t* t3[3] = {att[0], att[1], att[2]};
-    return rss_reshare(32 * ta, t3, prf_keys, counter + 1, d_attrs, stream);
+        if (!d_idm[i] || !d_ids[i] || !d_attrs[i]) return fail(FSS_EINVAL, "%s: NULL share %d", who, i);
+    return sec_access_calls(1, ncand, x_bits, d_idm, d_off, lmax, d_post, attr_words, d_attr, prf_keys, &counter, seeds,
+                            d_ids, d_attrs, d_rows_out, d_count, d_work, work_bytes, stream, who);
 }
 
 int rss_sec_access_batch(uint32_t count, uint64_t ncand, uint32_t x_bits, const uint32_t* const* d_idm,
@@ -488,22 +548,8 @@ int rss_sec_access_batch(uint32_t count, uint64_t ncand, uint32_t x_bits, const 
         if (!d_idm[k]) return fail(FSS_EINVAL, "%s: NULL matched-ID share %llu", who, (unsigned long long)k);
     for (int i = 0; i < 3; i++)
         if (!d_ids[i] || !d_attrs[i]) return fail(FSS_EINVAL, "%s: NULL output share %d", who, i);
-    const uint64_t wx = (x_bits + 31) / 32;
-    for (uint32_t c = 0; c < count; c++) {
-        uint32_t* ids[3];
-        uint32_t* attrs[3];
-        for (int i = 0; i < 3; i++) {
-            ids[i] = d_ids[i] + (uint64_t)c * lmax * wx;
-            attrs[i] = d_attrs[i] + (uint64_t)c * lmax * attr_words;
-        }
-        // the shared arguments are checked by the first call; the rest differ
-        // only in pointers checked above
-        const int rc = rss_sec_access(ncand, x_bits, d_idm + 3ull * c, d_off, lmax, d_post, attr_words, d_attr,
-                                      prf_keys, counters[c], seeds + 3ull * c, ids, attrs,
-                                      d_rows_out + (uint64_t)c * lmax, d_count + c, d_work, work_bytes, stream);
-        if (rc) return rc;
-    }
-    return FSS_OK;
+    return sec_access_calls(count, ncand, x_bits, d_idm, d_off, lmax, d_post, attr_words, d_attr, prf_keys, counters,
+                            seeds, d_ids, d_attrs, d_rows_out, d_count, d_work, work_bytes, stream, who);
 }
 
 }  // extern "C"

@@ -1027,6 +1027,44 @@ __global__ __launch_bounds__(kRssBlock) void k_rss(RssArgs A) {
     }
 }
 
+// The re-share alone, for several tables of nwords whole words each: call c =
+// blockIdx.y at word c * nwords, under its own counter.
+struct ReshareCalls {
+    ChachaKey prf[3];
+    const uint32_t* x[3];
+    uint32_t* z[3];
+    uint64_t nwords;
+    uint32_t counter[kSideCalls];
+};
+
+__global__ __launch_bounds__(kRssBlock) void k_reshare_calls(ReshareCalls A) {
+    const uint64_t m = (uint64_t)blockIdx.x * kRssBlock + threadIdx.x;
+    const uint64_t base = blockIdx.y * A.nwords + 4 * m;
+    const uint32_t left = 4 * m < A.nwords ? (uint32_t)min(A.nwords - 4 * m, (uint64_t)4) : 0u;   // words of this thread
+    uint32_t v[3][4] = {};
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        if (left == 4)
+            __builtin_memcpy(v[i], A.x[i] + base, 16);
+        else
+            for (uint32_t k = 0; k < left; k++) v[i][k] = A.x[i][base + k];
+    }
+    uint4 f[3];
+#pragma unroll
+    for (int i = 0; i < 3; i++) f[i] = chacha_quad(A.prf[i], (uint32_t)(m >> 2), A.counter[blockIdx.y], 0u, 0u);
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        const uint4 a = xor4(f[i], f[(i + 2) % 3]);
+        const uint32_t z[4] = {v[i][0] ^ a.x, v[i][1] ^ a.y, v[i][2] ^ a.z, v[i][3] ^ a.w};
+        if (left == 4)
+            __builtin_memcpy(A.z[i] + base, z, 16);
+        else
+#pragma unroll
+            for (uint32_t k = 0; k < 4; k++)
+                if (k < left) A.z[i][base + k] = z[k];
+    }
+}
+
 // ----------------------------------------------------------------- plan tail: ANDs and hop joins
 //
 // The steps of a plan after its predicate bits exist (the ANDs of each vertex
@@ -1498,6 +1536,30 @@ int launch_triples(uint64_t seed, uint32_t query_id, uint32_t and_id, uint64_t n
 }
 
 }  // namespace
+
+namespace ogm {
+
+int reshare_calls(uint32_t calls, uint64_t nwords, const uint32_t* const x[3], const uint64_t prf_keys[3],
+                  const uint32_t* counters, uint32_t add, uint32_t* const z[3], void* stream) {
+    const uint64_t groups = (nwords + 3) / 4;
+    for (uint32_t c0 = 0; c0 < calls && nwords; c0 += kSideCalls) {
+        const uint32_t n = calls - c0 < kSideCalls ? calls - c0 : kSideCalls;
+        ReshareCalls A{};
+        for (int i = 0; i < 3; i++) {
+            A.prf[i] = chacha_key(prf_keys[i], 5);
+            A.x[i] = x[i] + c0 * nwords;
+            A.z[i] = z[i] + c0 * nwords;
+        }
+        A.nwords = nwords;
+        for (uint32_t c = 0; c < n; c++) A.counter[c] = counters[c0 + c] + add;
+        hipLaunchKernelGGL(k_reshare_calls, dim3((unsigned)((groups + kRssBlock - 1) / kRssBlock), n), dim3(kRssBlock), 0,
+                           (hipStream_t)stream, A);
+        if (const int rc = check_launch("k_reshare_calls")) return rc;
+    }
+    return FSS_OK;
+}
+
+}  // namespace ogm
 
 // ================================================================= C ABI
 

@@ -1067,45 +1067,64 @@ __global__ __launch_bounds__(1024) void k_open_compact_small(uint32_t n, uint32_
     open_compact_block(n, nwords, parity, a, b, c, o0, o1, o2, rows_out, count, flag, incl);
 }
 
-// A whole shuffle of a small table (at most kSmallPerm records and
-// kFusedSlices 16-word slices) in one workgroup: the three permutations into
-// LDS, the first round (first_slice), the final round (final_slice), and,
-// with compact = 1 (secFetch: bit 0 of word 0) or 2 (secAccess filter: parity
-// of all bits), the open and compaction of the shuffled table.  The same
-// per-slice code as the multi-workgroup launches, so the same shares; the
-// rounds meet through global memory (xv, out) behind workgroup barriers.
+// Whole shuffles of small tables (at most kSmallPerm records and kFusedSlices
+// 16-word slices), a workgroup each: the three permutations into LDS, the
+// first round (first_slice), the final round (final_slice), and, with compact
+// = 1 (secFetch: bit 0 of word 0) or 2 (secAccess filter: parity of all bits),
+// the open and compaction of the shuffled table.  The same per-slice code as
+// the multi-workgroup launches, so the same shares; the rounds meet through
+// global memory (xv, out) behind workgroup barriers.  One shuffle takes 10 to 27
+// us, a chain of barriers and ChaCha blocks on one CU, so the shuffles of a
+// batch run side by side (blockIdx.x = call).
 constexpr uint32_t kFusedSlices = 1024;
 
 struct SmallShuffle {
-    ChachaKey k12, k23, k31;
     const uint32_t* g[3];
     uint32_t* xv;
     uint32_t* out[3];              // R1, R2, R3
     uint32_t compact;
+    uint32_t nwords;
     uint32_t* kept[3];
     uint32_t* rows_out;
     uint32_t* count;
+    uint32_t row0[kSideCalls + 1]; // call c: rows row0[c] .. row0[c + 1]
+    uint64_t seeds[kSideCalls][3]; // s12, s23, s31
 };
 
+__device__ __forceinline__ ChachaKey pair_key_of(uint64_t seed) {
+    return ChachaKey{(uint32_t)seed, (uint32_t)(seed >> 32), kShuffleDomain};
+}
+
 template <bool WHOLE>
-__global__ __launch_bounds__(1024) void k_shuffle_small(uint32_t n, uint32_t nwords, SmallShuffle A) {
+__global__ __launch_bounds__(1024) void k_shuffle_small(SmallShuffle A) {
     __shared__ uint64_t key[kSmallPerm];
     __shared__ uint32_t perm[3][kSmallPerm];     // inverse of pi12, inverse of pi31, pi23
     __shared__ uint32_t flag[kSmallPerm];
     __shared__ uint32_t incl[kSmallPerm];
-    small_perm(A.k12, kP12, 1u, n, key, perm[0]);
-    small_perm(A.k31, kP31, 1u, n, key, perm[1]);
-    small_perm(A.k23, kP23, 0u, n, key, perm[2]);
+    const uint32_t call = blockIdx.x, nwords = A.nwords;
+    const uint32_t r0 = A.row0[call], n = A.row0[call + 1] - r0;
+    if (n == 0) {
+        if (A.compact && threadIdx.x == 0) A.count[call] = 0u;
+        return;
+    }
+    const ChachaKey k12 = pair_key_of(A.seeds[call][0]), k23 = pair_key_of(A.seeds[call][1]),
+                    k31 = pair_key_of(A.seeds[call][2]);
+    const uint64_t at = (uint64_t)r0 * nwords;
+    uint32_t *xv = A.xv + 2 * at, *s0 = A.out[0] + at, *s1 = A.out[1] + at, *s2 = A.out[2] + at;
+    small_perm(k12, kP12, 1u, n, key, perm[0]);
+    small_perm(k31, kP31, 1u, n, key, perm[1]);
+    small_perm(k23, kP23, 0u, n, key, perm[2]);
     const uint64_t total = (uint64_t)n * ((nwords + 15) >> 4) * 4;
     for (uint64_t t = threadIdx.x; t < total; t += blockDim.x)
-        first_slice<WHOLE>(t, n, nwords, A.k12, A.k31, perm[0], perm[1], A.g[0], A.g[1], A.g[2], A.xv, A.out[1], A.out[0]);
+        first_slice<WHOLE>(t, n, nwords, k12, k31, perm[0], perm[1], A.g[0] + at, A.g[1] + at, A.g[2] + at, xv, s1, s0);
     __syncthreads();
     for (uint64_t t = threadIdx.x; t < total; t += blockDim.x)
-        final_slice<WHOLE>(t, n, nwords, A.k12, A.k23, A.k31, perm[2], A.xv, A.out[2]);
+        final_slice<WHOLE>(t, n, nwords, k12, k23, k31, perm[2], xv, s2);
     if (!A.compact) return;
     __syncthreads();
-    open_compact_block(n, nwords, A.compact == 2, A.out[0], A.out[1], A.out[2], A.kept[0], A.kept[1], A.kept[2],
-                       A.rows_out, A.count, flag, incl);
+    const uint64_t kat = (uint64_t)r0 * (A.compact == 2 ? nwords : nwords - 1);
+    open_compact_block(n, nwords, A.compact == 2, s0, s1, s2, A.kept[0] + kat, A.kept[1] + kat, A.kept[2] + kat,
+                       A.rows_out + r0, A.count + call, flag, incl);
 }
 
 // count of kept records = last exclusive prefix + last flag
@@ -1447,30 +1466,8 @@ int shuffle_rounds(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], 
 }
 
 // Alg. 5 with all three servers simulated; out[0..2] = R1, R2, R3.  The
-// permutation pi23 is still being made while the first launch runs.
-// Whether a shuffle runs in one workgroup (k_shuffle_small).
-bool fused_shuffle(uint64_t nrows, uint32_t nwords) {
-    return nrows <= kSmallPerm && nrows * ((nwords + 15) / 16) <= kFusedSlices;
-}
-
-// The one-workgroup shuffle; compact: 0 none, 1 secFetch's open, 2 the
-// secAccess filter's (then kept / rows_out / count receive the compaction).
-int launch_fused(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], const uint64_t seeds[3],
-                 uint32_t* const out[3], uint32_t* xv, uint32_t compact, uint32_t* const kept[3],
-                 uint32_t* rows_out, uint32_t* count, hipStream_t s) {
-    SmallShuffle A{};
-    A.k12 = pair_key(seeds[0]), A.k23 = pair_key(seeds[1]), A.k31 = pair_key(seeds[2]);
-    for (int i = 0; i < 3; i++) {
-        A.g[i] = d[i];
-        A.out[i] = out[i];
-        A.kept[i] = kept ? kept[i] : nullptr;
-    }
-    A.xv = xv, A.compact = compact, A.rows_out = rows_out, A.count = count;
-    auto k = nwords & 3u ? k_shuffle_small<false> : k_shuffle_small<true>;
-    hipLaunchKernelGGL(k, dim3(1), dim3(1024), 0, s, (uint32_t)nrows, nwords, A);
-    return check_launch("k_shuffle_small");
-}
-
+// permutation pi23 is still being made while the first launch runs.  A table
+// that one workgroup shuffles takes no permutation buffers.
 int run_shuffle(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], const uint64_t seeds[3],
                 uint32_t* const out[3], Carve& ws, hipStream_t s, uint32_t open = 0, uint32_t* flags = nullptr) {
     const uint64_t tw = nrows * nwords;
@@ -1479,7 +1476,10 @@ int run_shuffle(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], con
     uint32_t* inv31 = ws.take<uint32_t>(nrows);
     uint32_t* p23 = ws.take<uint32_t>(nrows);
     if (!ws.ok) return fail(FSS_ENOMEM, "rss_shuffle: workspace too small");
-    if (fused_shuffle(nrows, nwords)) return launch_fused(nrows, nwords, d, seeds, out, xv, 0, nullptr, nullptr, nullptr, s);
+    if (small_shuffle_fits(nrows, nwords)) {
+        const uint32_t row0[2] = {0u, (uint32_t)nrows};
+        return small_shuffles(1, row0, nwords, d, seeds, xv, out, 0, nullptr, nullptr, nullptr, s);
+    }
     PermSet ps{s};
     ps.begin(nrows, seeds, inv12, inv31, p23, ws);
     const int rc = shuffle_rounds(nrows, nwords, d, seeds, inv12, inv31, p23, xv, out, s, &ps, open, flags);
@@ -1490,6 +1490,32 @@ int run_shuffle(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], con
 }  // namespace
 
 namespace ogm {
+
+bool small_shuffle_fits(uint64_t nrows, uint32_t nwords) {
+    return nrows <= kSmallPerm && nrows * ((nwords + 15) / 16) <= kFusedSlices;
+}
+
+int small_shuffles(uint32_t calls, const uint32_t* row0, uint32_t nwords, const uint32_t* const g[3],
+                   const uint64_t* seeds, uint32_t* xv, uint32_t* const out[3], uint32_t compact,
+                   uint32_t* const kept[3], uint32_t* rows_out, uint32_t* count, void* stream) {
+    for (uint32_t c0 = 0; c0 < calls; c0 += kSideCalls) {
+        const uint32_t n = calls - c0 < kSideCalls ? calls - c0 : kSideCalls;
+        SmallShuffle A{};
+        for (int i = 0; i < 3; i++) {
+            A.g[i] = g[i];
+            A.out[i] = out[i];
+            A.kept[i] = kept ? kept[i] : nullptr;
+        }
+        A.xv = xv, A.compact = compact, A.nwords = nwords, A.rows_out = rows_out, A.count = count ? count + c0 : nullptr;
+        for (uint32_t c = 0; c <= n; c++) A.row0[c] = row0[c0 + c];
+        for (uint32_t c = 0; c < n; c++)
+            for (int k = 0; k < 3; k++) A.seeds[c][k] = seeds[3 * (uint64_t)(c0 + c) + k];
+        auto k = nwords & 3u ? k_shuffle_small<false> : k_shuffle_small<true>;
+        hipLaunchKernelGGL(k, dim3(n), dim3(1024), 0, (hipStream_t)stream, A);
+        if (const int rc = check_launch("k_shuffle_small")) return rc;
+    }
+    return FSS_OK;
+}
 
 // The shuffle's own streams, for fss_shutdown: each is drained, then
 // destroyed; the next shuffle creates them again.
@@ -1695,12 +1721,12 @@ static int shuffle_open_compact(uint64_t ncand, uint32_t nwords, const uint32_t*
     (void)hipcub::DeviceScan::ExclusiveSum(nullptr, scan, (const uint32_t*)nullptr, (uint32_t*)nullptr, (int)ncand);
     void* scan_tmp = ws.take<uint8_t>(scan);
     if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
-    if (fused_shuffle(ncand, nwords)) {
+    if (small_shuffle_fits(ncand, nwords)) {
         // the shuffle, the open and the compaction in one workgroup
-        const uint64_t tw = ncand * nwords;
         uint32_t* xv = ws.take<uint32_t>(2 * tw);
         if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
-        return launch_fused(ncand, nwords, d_table, seeds, sh, xv, parity ? 2u : 1u, d_out, d_rows_out, d_count, s);
+        const uint32_t row0[2] = {0u, (uint32_t)ncand};
+        return small_shuffles(1, row0, nwords, d_table, seeds, xv, sh, parity ? 2u : 1u, d_out, d_rows_out, d_count, s);
     }
     const bool small = ncand <= kSmallPerm;
     // the final round opens secFetch's bit, and the secAccess filter's parity

@@ -578,9 +578,11 @@ def rss_sec_access_batch(ncand: int, x_bits: int, idm_ptrs, off, lmax: int, post
                          prf_keys, counters, seeds, ids3, attrs3, rows_out, count, stream=None):
     """len(counters) secAccess calls in one library call: idm_ptrs holds the
     3 device addresses of each call's matched-ID shares, seeds 3 values per
-    call; call c's outputs sit at offset c times one call's capacity."""
+    call; call c's outputs sit at offset c times one call's capacity.  The
+    workspace holds up to 64 calls (within 256 MiB), which then run side by side."""
     n = len(counters)
-    nbytes = int(LIB.rss_sec_access_workspace_bytes(lmax, x_bits, attr_words))
+    single = int(LIB.rss_sec_access_workspace_bytes(lmax, x_bits, attr_words))
+    nbytes = single * max(1, min(n, 64, (256 << 20) // max(single, 1)))
     work = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=ids3[0].device)
     _check(LIB.rss_sec_access_batch(n, ncand, x_bits, (ctypes.c_void_p * (3 * n))(*idm_ptrs), _ptr(off), lmax,
                                     _ptr3(post3), attr_words, _ptr3(attr3), (ctypes.c_uint64 * 3)(*prf_keys),

@@ -147,6 +147,44 @@ def test_sec_access_batch_equals_oracle_per_call(fss, enc):
             np.testing.assert_array_equal(ga, want_attrs[i], err_msg=f"call {c} attribute share {i + 1}")
 
 
+@pytest.mark.parametrize("count,side", [(2, 2), (5, 5), (8, 3), (9, 9), (66, 64)])
+def test_sec_access_batch_equals_single_calls(fss, enc, count, side):
+    """Batches of one, several and partly filled passes over the lists (eight calls a pass, 64 a launch), with
+    a workspace for `side` calls side by side, equal the single calls; matched-ID shares of random bits."""
+    X, WX = enc["X"], enc["WX"]
+    rng = np.random.default_rng(count)
+    lmax, keys = int(enc["padded"].max()), [51, 52, 53]
+    idm = [[T(rng.integers(0, 2**32, (NC + 31) // 32, dtype=np.uint64).astype(np.uint32)) for _ in range(3)]
+           for _ in range(count)]
+    attr = [T(rng.integers(0, 2**32, X * 3, dtype=np.uint64).astype(np.uint32)) for _ in range(3)]
+    counters = [7 + 2 * c for c in range(count)]
+    seeds = [int(v) for v in rng.integers(0, 2**62, 3 * count)]
+
+    def buffers(n):
+        return ([torch.full((n * lmax * WX,), -1, dtype=torch.int32, device=DEV) for _ in range(3)],
+                [torch.full((n * lmax * 3,), -1, dtype=torch.int32, device=DEV) for _ in range(3)],
+                torch.full((n * lmax,), -1, dtype=torch.int32, device=DEV),
+                torch.full((n,), -1, dtype=torch.int32, device=DEV))
+
+    ids, attrs, rows, cnt = buffers(count)
+    work = torch.empty(side * int(fss.LIB.rss_sec_access_workspace_bytes(lmax, X, 3)), dtype=torch.uint8, device=DEV)
+    P, u32, u64 = fss.ctypes.c_void_p, fss.ctypes.c_uint32, fss.ctypes.c_uint64
+    assert fss.LIB.rss_sec_access_batch(count, NC, X, (P * (3 * count))(*[t.data_ptr() for c in idm for t in c]),
+                                        enc["d_off"].data_ptr(), lmax, fss._ptr3(enc["out"]), 3, fss._ptr3(attr),
+                                        (u64 * 3)(*keys), (u32 * count)(*counters), (u64 * (3 * count))(*seeds),
+                                        fss._ptr3(ids), fss._ptr3(attrs), rows.data_ptr(), cnt.data_ptr(),
+                                        work.data_ptr(), work.numel(), fss._stream(None)) == fss.OK
+    for c in range(0, count, max(1, count // 7)):
+        i1, a1, r1, c1 = buffers(1)
+        fss.rss_sec_access(NC, X, idm[c], enc["d_off"], lmax, list(enc["out"]), 3, attr, keys, counters[c],
+                           seeds[3 * c:3 * c + 3], i1, a1, r1, c1)
+        assert U(cnt)[c] == U(c1)[0]
+        np.testing.assert_array_equal(U(rows)[c * lmax:(c + 1) * lmax], U(r1))
+        for i in range(3):
+            np.testing.assert_array_equal(U(ids[i]).reshape(count, -1)[c], U(i1[i]))
+            np.testing.assert_array_equal(U(attrs[i]).reshape(count, -1)[c], U(a1[i]))
+
+
 def test_sec_access_measured_size(fss):
     """secAccess at the measured size (65,536 candidates, 16,384 neighbour IDs:
     2 KB one-hot records, lists of 0..24 IDs, k = 4): for the vertex with the
