@@ -619,6 +619,24 @@ int rss_sec_access_batch(uint32_t count, uint64_t ncand, uint32_t x_bits, const 
                          const uint64_t* seeds, uint32_t* const d_ids[3], uint32_t* const d_attrs[3],
                          uint32_t* d_rows_out, uint32_t* d_count, void* d_work, uint64_t work_bytes, void* stream);
 
+/* rss_sec_fetch_groups: secEval, the re-share and secFetch Case II of one
+ * target's groups of candidates (Alg. 2 fetches once per group), together.
+ * Group c (host arrays src, n) is rows src[c] .. src[c] + n[c] - 1 of the
+ * one-hot records d_vals (ceil(npos/32) words) and d_ids (id_words words; NULL
+ * for 0).  Its result is that of rss_sec_eval_records with (d_eval[2i],
+ * d_eval[2i+1]) on shares i and i + 1 for each server i, rss_reshare under
+ * counter + c, rss_fetch_table and rss_fetch_many with seeds[3c .. 3c+2]: the
+ * kept records {id || value} from row n[0] + .. + n[c-1] of d_out[i] on, their
+ * shuffled positions from that entry of d_rows_out on, their number d_count[c].
+ * An empty group has count 0.  Outputs must overlap neither the inputs nor the
+ * workspace.  Errors as those calls'. */
+uint64_t rss_sec_fetch_groups_workspace_bytes(uint32_t ngroups, const uint32_t* n, uint32_t npos, uint32_t id_words);
+int rss_sec_fetch_groups(uint32_t ngroups, const uint32_t* src, const uint32_t* n, uint32_t npos,
+                         const uint32_t* const d_eval[6], uint32_t id_words, const uint32_t* const d_ids[3],
+                         const uint32_t* const d_vals[3], const uint64_t prf_keys[3], uint32_t counter,
+                         const uint64_t* seeds, uint32_t* const d_out[3], uint32_t* d_rows_out, uint32_t* d_count,
+                         void* d_work, uint64_t work_bytes, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

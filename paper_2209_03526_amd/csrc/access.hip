@@ -325,6 +325,71 @@ __global__ __launch_bounds__(kSelBlock) void k_attr_select(uint32_t x_bits, uint
     }
 }
 
+// secEval, the re-share and secFetch's table {x || id || d} of several groups of
+// candidates in one launch (blockIdx.x = group, blockIdx.y = a block of its
+// rows): a wave takes a row, its lanes the record's words.  Group c's rows are
+// rows src[c] .. of the one-hot records and rows row0[c] .. row0[c + 1] of the
+// table.  Server s's share of a row's bit is the parity of (ea_s & d_s) ^
+// (eb_s & d_{s+1}); the row's bit of the group's zero sharing (bit r % 32 of
+// word r / 32 of F(k_i, counter) ^ F(k_{i-1}, counter)) makes it RSS.  Small
+// groups are launch-bound: five launches each for 196 groups of 1 to 40 rows.
+constexpr uint32_t kGroupRows = 16;       // rows per block of four waves
+constexpr uint32_t kGroupMost = 1024;     // rows of a group, at most (32 words of bits)
+
+struct GroupTable {
+    ChachaKey prf[3];
+    const uint32_t* eval[6];        // ea_1, eb_1, ea_2, eb_2, ea_3, eb_3
+    const uint32_t* ids[3];
+    const uint32_t* vals[3];
+    uint32_t* out[3];
+    uint32_t wi, wv;
+    uint32_t src[kSideCalls];
+    uint32_t row0[kSideCalls + 1];
+    uint32_t counter[kSideCalls];
+};
+
+__global__ __launch_bounds__(256) void k_group_table(GroupTable A) {
+    __shared__ uint32_t f[3][32];
+    const uint32_t call = blockIdx.x, t = threadIdx.x, lane = t & 63u;
+    const uint32_t row0 = A.row0[call], n = A.row0[call + 1] - row0;
+    if (blockIdx.y * kGroupRows >= n) return;            // the whole block leaves
+    if (t < 64) {                                        // six PRF blocks: two of each key
+        const uint32_t q = t >> 2, k = q % 3, blk = q / 3;
+        const uint4 o = chacha_quad(A.prf[k], blk, A.counter[call], 0u, 0u);
+        if (q < 6) {
+            uint32_t* to = &f[k][16 * blk + 4 * (t & 3u)];
+            to[0] = o.x, to[1] = o.y, to[2] = o.z, to[3] = o.w;
+        }
+    }
+    __syncthreads();
+    const uint32_t W = 1 + A.wi + A.wv;
+    for (uint32_t j = t >> 6; j < kGroupRows; j += 4) {
+        const uint32_t r = blockIdx.y * kGroupRows + j;
+        if (r >= n) break;                               // whole waves
+        const uint64_t from = (uint64_t)A.src[call] + r, to = (uint64_t)(row0 + r) * W;
+        uint32_t acc[3] = {0u, 0u, 0u};
+        for (uint32_t w = lane; w < A.wv; w += 64) {
+            uint32_t d[3];
+#pragma unroll
+            for (int i = 0; i < 3; i++) {
+                d[i] = A.vals[i][from * A.wv + w];
+                A.out[i][to + 1 + A.wi + w] = d[i];
+            }
+#pragma unroll
+            for (int i = 0; i < 3; i++) acc[i] ^= (A.eval[2 * i][w] & d[i]) ^ (A.eval[2 * i + 1][w] & d[(i + 1) % 3]);
+        }
+        for (uint32_t w = lane; w < A.wi; w += 64)
+#pragma unroll
+            for (int i = 0; i < 3; i++) A.out[i][to + 1 + w] = A.ids[i][from * A.wi + w];
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            const uint64_t odd = __ballot(__builtin_popcount(acc[i]) & 1);
+            const uint32_t z = (f[i][r >> 5] ^ f[(i + 2) % 3][r >> 5]) >> (r & 31u);
+            if (lane == 0) A.out[i][to] = ((uint32_t)__builtin_popcountll(odd) ^ z) & 1u;
+        }
+    }
+}
+
 struct Carve {
     uint8_t* base;
     uint64_t size, used = 0;
@@ -425,6 +490,125 @@ int rss_enc_posting_lists(uint64_t n, uint32_t x_bits, const uint32_t* d_adj_off
 uint64_t rss_sec_access_workspace_bytes(uint32_t lmax, uint32_t x_bits, uint32_t attr_words) {
     const uint64_t wx = (x_bits + 31) / 32, l = lmax ? lmax : 1;
     return 6 * rnd(l * wx) + 3 * rnd(l * attr_words) + rss_fetch_many_workspace_bytes(l, (uint32_t)wx) + 256;
+}
+
+// Whether one workgroup shuffles a group of n rows of W words.
+static bool group_fits(uint32_t n, uint32_t W) { return n <= kGroupMost && small_shuffle_fits(n, W); }
+
+uint64_t rss_sec_fetch_groups_workspace_bytes(uint32_t ngroups, const uint32_t* n, uint32_t npos, uint32_t id_words) {
+    const uint32_t W = 1 + id_words + (npos + 31) / 32;
+    uint64_t most = 0;
+    for (uint32_t c = 0; n && c < ngroups;) {
+        if (!group_fits(n[c], W)) {
+            most = std::max(most, 6 * rnd((n[c] + 31) / 32) + 3 * rnd((uint64_t)n[c] * W) +
+                                      rss_fetch_many_workspace_bytes(n[c], W));
+            c++;
+            continue;
+        }
+        uint64_t rows = 0;
+        for (uint32_t m = 0; m < kSideCalls && c < ngroups && group_fits(n[c], W); m++) rows += n[c++];
+        most = std::max(most, 8 * rnd(rows * W));       // the tables, their shuffle's two and three
+    }
+    return most + 256;
+}
+
+int rss_sec_fetch_groups(uint32_t ngroups, const uint32_t* src, const uint32_t* n, uint32_t npos,
+                         const uint32_t* const d_eval[6], uint32_t id_words, const uint32_t* const d_ids[3],
+                         const uint32_t* const d_vals[3], const uint64_t prf_keys[3], uint32_t counter,
+                         const uint64_t* seeds, uint32_t* const d_out[3], uint32_t* d_rows_out, uint32_t* d_count,
+                         void* d_work, uint64_t work_bytes, void* stream) {
+    last_error().clear();
+    const char* who = "rss_sec_fetch_groups";
+    if (ngroups == 0) return FSS_OK;
+    if (npos == 0) return fail(FSS_EINVAL, "%s: no positions", who);
+    if (!src || !n || !d_eval || !d_vals || (id_words && !d_ids) || !prf_keys || !seeds || !d_out || !d_rows_out ||
+        !d_count)
+        return fail(FSS_EINVAL, "%s: NULL argument", who);
+    const uint32_t wv = (npos + 31) / 32;
+    for (int i = 0; i < 6; i++)
+        if (!d_eval[i]) return fail(FSS_EINVAL, "%s: NULL evaluation %d", who, i);
+    for (int i = 0; i < 3; i++)
+        if (!d_vals[i] || (id_words && !d_ids[i]) || !d_out[i]) return fail(FSS_EINVAL, "%s: NULL share %d", who, i);
+    if ((uint64_t)id_words + wv + 1 > 65535)
+        return fail(FSS_EUNSUPPORTED, "%s: more than 65535 words per record", who);
+    const uint32_t W = 1 + id_words + wv;
+    uint64_t all = 0;
+    for (uint32_t c = 0; c < ngroups; c++) all += n[c];
+    if (all > 0x7FFFFFFFull) return fail(FSS_EUNSUPPORTED, "%s: more than 2^31 rows", who);
+    if (!d_work || work_bytes < rss_sec_fetch_groups_workspace_bytes(ngroups, n, npos, id_words))
+        return fail(FSS_ENOMEM, "%s: workspace needs %llu bytes", who,
+                    (unsigned long long)rss_sec_fetch_groups_workspace_bytes(ngroups, n, npos, id_words));
+    hipStream_t s = (hipStream_t)stream;
+    // runs of consecutive groups that one workgroup each can shuffle go together
+    uint64_t row = 0;
+    for (uint32_t c0 = 0; c0 < ngroups;) {
+        Carve ws{(uint8_t*)d_work, work_bytes};
+        uint32_t* out[3] = {d_out[0] + row * (W - 1), d_out[1] + row * (W - 1), d_out[2] + row * (W - 1)};
+        if (group_fits(n[c0], W)) {
+            GroupTable A{};
+            uint32_t m = 0, most = 0;
+            for (; m < kSideCalls && c0 + m < ngroups && group_fits(n[c0 + m], W); m++) {
+                A.src[m] = src[c0 + m];
+                A.row0[m + 1] = A.row0[m] + n[c0 + m];
+                A.counter[m] = counter + c0 + m;
+                most = std::max(most, n[c0 + m]);
+            }
+            const uint64_t tw = (uint64_t)A.row0[m] * W;
+            uint32_t* table[3] = {ws.take(tw), ws.take(tw), ws.take(tw)};
+            uint32_t* xv = ws.take(2 * tw);
+            uint32_t* sh[3] = {ws.take(tw), ws.take(tw), ws.take(tw)};
+            if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
+            for (int i = 0; i < 3; i++) {
+                A.prf[i] = chacha_key(prf_keys[i], 5);
+                A.ids[i] = id_words ? d_ids[i] : nullptr;
+                A.vals[i] = d_vals[i];
+                A.out[i] = table[i];
+            }
+            for (int i = 0; i < 6; i++) A.eval[i] = d_eval[i];
+            A.wi = id_words, A.wv = wv;
+            if (most) {
+                hipLaunchKernelGGL(k_group_table, dim3(m, (most + kGroupRows - 1) / kGroupRows), dim3(256), 0, s, A);
+                if (const int rc = check_launch("k_group_table")) return rc;
+            }
+            const uint32_t* g[3] = {table[0], table[1], table[2]};
+            const int rc = small_shuffles(m, A.row0, W, g, seeds + 3 * (uint64_t)c0, xv, sh, 1u, out, d_rows_out + row,
+                                          d_count + c0, stream);
+            if (rc) return rc;
+            row += A.row0[m];
+            c0 += m;
+            continue;
+        }
+        // a larger group, step by step
+        const uint64_t rows = n[c0], bw = (rows + 31) / 32;
+        uint32_t* x3[3] = {ws.take(bw), ws.take(bw), ws.take(bw)};
+        uint32_t* z3[3] = {ws.take(bw), ws.take(bw), ws.take(bw)};
+        uint32_t* table[3] = {ws.take(rows * W), ws.take(rows * W), ws.take(rows * W)};
+        const uint64_t fws = rss_fetch_many_workspace_bytes(rows, W);
+        uint32_t* fwork = ws.take((fws + 3) / 4);
+        if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
+        const uint32_t *ids[3], *vals[3];
+        for (int i = 0; i < 3; i++) {
+            ids[i] = id_words ? d_ids[i] + (uint64_t)src[c0] * id_words : nullptr;
+            vals[i] = d_vals[i] + (uint64_t)src[c0] * wv;
+        }
+        for (int i = 0; i < 3; i++) {
+            const int rc = rss_sec_eval_records(rows, npos, d_eval[2 * i], d_eval[2 * i + 1], vals[i], vals[(i + 1) % 3],
+                                                x3[i], stream);
+            if (rc) return rc;
+        }
+        const uint32_t* xc[3] = {x3[0], x3[1], x3[2]};
+        int rc = rss_reshare(rows, xc, prf_keys, counter + c0, z3, stream);
+        const uint32_t* zc[3] = {z3[0], z3[1], z3[2]};
+        if (!rc) rc = rss_fetch_table(rows, zc, id_words, ids, wv, vals, table, stream);
+        const uint32_t* tc[3] = {table[0], table[1], table[2]};
+        if (!rc)
+            rc = rss_fetch_many(rows, W, tc, seeds + 3 * (uint64_t)c0, out, d_rows_out + row, d_count + c0, fwork, fws,
+                                stream);
+        if (rc) return rc;
+        row += rows;
+        c0++;
+    }
+    return FSS_OK;
 }
 
 // The calls of a secAccess batch, as many side by side as the workspace holds

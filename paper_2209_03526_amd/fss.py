@@ -124,6 +124,8 @@ def _load():
         "rss_sec_access": ([u64, u32, P, P, u32, P, u32, P, P, u32, P, P, P, P, P, P, u64, P], ctypes.c_int),
         "rss_sec_access_batch": ([u32, u64, u32, P, P, u32, P, u32, P, P, P, P, P, P, P, P, P, u64, P],
                                  ctypes.c_int),
+        "rss_sec_fetch_groups_workspace_bytes": ([u32, P, u32, u32], u64),
+        "rss_sec_fetch_groups": ([u32, P, P, u32, P, u32, P, P, P, u32, P, P, P, P, P, u64, P], ctypes.c_int),
     }
     for name, (args, res) in sigs.items():
         f = getattr(lib, name)
@@ -142,7 +144,8 @@ EXPORTS = ("fss_key_bytes", "fss_keybatch_bytes", "fss_last_error", "fss_version
            "rss_shuffle_prepared_workspace_bytes", "rss_shuffle_prepared", "rss_fetch_unique",
            "rss_fetch_many_workspace_bytes",
            "rss_fetch_many", "rss_compact_valid", "rss_sec_eval_records", "rss_fetch_table", "rss_group_k", "rss_group_k_lists", "rss_enc_posting_lists",
-           "rss_sec_access_workspace_bytes", "rss_sec_access", "rss_sec_access_batch")
+           "rss_sec_access_workspace_bytes", "rss_sec_access", "rss_sec_access_batch",
+           "rss_sec_fetch_groups_workspace_bytes", "rss_sec_fetch_groups")
 
 
 def _check(rc: int):
@@ -599,4 +602,19 @@ def rss_sec_access(ncand: int, x_bits: int, idm3, off, lmax: int, post3, attr_wo
     _check(LIB.rss_sec_access(ncand, x_bits, _ptr3(idm3), _ptr(off), lmax, _ptr3(post3), attr_words, _ptr3(attr3),
                               (ctypes.c_uint64 * 3)(*prf_keys), counter, (ctypes.c_uint64 * 3)(*seeds), _ptr3(ids3),
                               _ptr3(attrs3), _ptr(rows_out), _ptr(count), _ptr(work), work.numel(), _stream(stream)))
+    return work
+
+
+def rss_sec_fetch_groups(src, n, npos: int, evals6, id_words: int, ids3, vals3, prf_keys, counter: int, seeds, out3,
+                         rows_out, count, stream=None):
+    """src, n: numpy uint32 arrays (a group's first record row and its rows); evals6: each server's two
+    full-domain evaluations in turn; seeds: 3 values per group."""
+    g = len(n)
+    nbytes = int(LIB.rss_sec_fetch_groups_workspace_bytes(g, n.ctypes.data, npos, id_words))
+    work = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=out3[0].device)
+    _check(LIB.rss_sec_fetch_groups(g, src.ctypes.data, n.ctypes.data, npos,
+                                    (ctypes.c_void_p * 6)(*[_ptr(t) for t in evals6]), id_words, _ptr3(ids3),
+                                    _ptr3(vals3), (ctypes.c_uint64 * 3)(*prf_keys), counter,
+                                    (ctypes.c_uint64 * (3 * g))(*seeds), _ptr3(out3), _ptr(rows_out), _ptr(count),
+                                    _ptr(work), work.numel(), _stream(stream)))
     return work

@@ -4,11 +4,12 @@ encoding, on the GPU: for a tree query over a typed graph (a path V_1 -> V_2
 target by target
 
   secEval (Alg. 3: full-domain evaluations of the replicated token,
-           `fss_eval_all`; each server's two terms, `rss_sec_eval_records`),
-  the re-share of its three-out-of-three bits into RSS (`rss_reshare`),
-  secFetch Case II (Alg. 4: the table {x || id || d}, `rss_fetch_table`;
-           shuffle, open, keep, `rss_fetch_many`),
-  secAccess (Alg. 6, `rss_sec_access`) of every kept vertex's neighbours of
+           `fss_eval_all_batch`; each server's two terms),
+  the re-share of its three-out-of-three bits into RSS,
+  secFetch Case II (Alg. 4: the table {x || id || d}; shuffle, open, keep),
+           these three for all groups of the target at once
+           (`rss_sec_fetch_groups`),
+  secAccess (Alg. 6, `rss_sec_access_batch`) of every kept vertex's neighbours of
            the next target's type, over the k-grouped posting lists of Alg. 1
            (`rss_enc_posting_lists`).
 
@@ -130,13 +131,20 @@ def encode_graph(n: dict, domains: dict, shares: dict, adj: dict, slots: dict, k
 
 
 @dataclass
-class _Group:
-    parent: object        # (hop, group, kept row) of the parent; None at hop 0
-    n: int                # candidates
-    ids: list             # three device tensors, n one-hot ID records
-    vals: list            # three device tensors, n one-hot attribute records
-    kept: list = None     # three device tensors of kept {id || d} records
-    nkept: int = 0
+class _Target:
+    """One target's groups of candidates: group g is rows base[g] .. of the
+    one-hot records ids / vals (three device tensors each), n[g] of them, the
+    neighbours of the kept vertex parent[g] = (group, kept row) of the parent
+    target (None at target 0).  After secFetch: nkept[g] kept {id || d}
+    records from row row0[g] of kept."""
+    ids: list
+    vals: list
+    base: np.ndarray
+    n: np.ndarray
+    parent: list
+    kept: list = None
+    row0: np.ndarray = None
+    nkept: np.ndarray = None
 
 
 def sec_match(eg: EncodedGraph, query, tok_seed: int, prf_keys, counter0: int, seed0: int, device=None):
@@ -150,122 +158,107 @@ def sec_match(eg: EncodedGraph, query, tok_seed: int, prf_keys, counter0: int, s
     q = len(query.targets)
     children = [[c for c in range(1, q) if query.parent(c) == i] for i in range(q)]
     t0 = query.targets[0]
-    groups = [[] for _ in range(q)]
-    groups[0].append(_Group(None, eg.n[t0.vtype], eg.shares[("id", t0.vtype)], eg.shares[("attr", t0.vtype, t0.attr)]))
+    one = lambda v: np.array([v], np.uint32)  # noqa: E731
+    targets = [None] * q
+    targets[0] = _Target(eg.shares[("id", t0.vtype)], eg.shares[("attr", t0.vtype, t0.attr)], one(0),
+                         one(eg.n[t0.vtype]), [None])
     zero3 = torch.zeros(3, dtype=torch.int32, device=dev)
+
+    def empty(k):
+        return torch.empty(max(1, k), dtype=torch.int32, device=dev)
+
     for i, tgt in enumerate(query.targets):
+        st = targets[i]
         npos = eg.domains[(tgt.vtype, tgt.attr)]
-        nb = domain_bits(npos)
-        kind = fss.EQ if tgt.kind == "eq" else fss.RANGE
-        kb = fss.KeyBatch(kind, nb, 3, dev)
+        kb = fss.KeyBatch(fss.EQ if tgt.kind == "eq" else fss.RANGE, domain_bits(npos), 3, dev)
         fss.fss_keygen(tok_seed, query.query_id, i, tgt.a if tgt.kind == "eq" else tgt.lo, tgt.hi, zero3, kb)
-        ev = {}
-        for party in (0, 1):
-            for rep in range(3):
-                ev[(party, rep)] = torch.empty(words(npos), dtype=torch.int32, device=dev)
-                fss.fss_eval_all(party, kb, rep, npos, ev[(party, rep)])
+        ev = {(party, rep): empty(words(npos)) for party in (0, 1) for rep in range(3)}
+        fss.fss_eval_all_batch([(party, kb, rep, npos, t) for (party, rep), t in ev.items()])
         wi, wv = words(eg.n[tgt.vtype]), words(npos)
-        rec = 1 + wi + wv
-        live = [gi for gi, g in enumerate(groups[i]) if g.n > 0]
-        # every group's secEval, re-share and secFetch, enqueued without waiting
-        # (the temporaries are shared by the groups: one stream orders their uses)
-        fetched = torch.zeros(max(len(live), 1), dtype=torch.int32, device=dev)
-        nmax = max([groups[i][gi].n for gi in live], default=1)
-        x3 = [torch.empty(words(nmax), dtype=torch.int32, device=dev) for _ in range(3)]
-        z3 = [torch.empty(words(nmax), dtype=torch.int32, device=dev) for _ in range(3)]
-        table = [torch.empty(nmax * rec, dtype=torch.int32, device=dev) for _ in range(3)]
-        for k, gi in enumerate(live):
-            g = groups[i][gi]
-            # secEval, then the re-share into RSS
-            for s, ((pa, ra, ja), (pb, rb, jb)) in enumerate(SERVER_TERMS):
-                fss.rss_sec_eval_records(g.n, npos, ev[(pa, ra)], ev[(pb, rb)], g.vals[ja], g.vals[jb], x3[s])
-            fss.rss_reshare(g.n, x3, prf_keys, counter, z3)
-            counter += 1
-            # secFetch Case II on {x || id || d}
-            fss.rss_fetch_table(g.n, z3, wi, g.ids, wv, g.vals, table)
-            g.kept = [torch.empty(g.n * (rec - 1), dtype=torch.int32, device=dev) for _ in range(3)]
-            pos = torch.empty(g.n, dtype=torch.int32, device=dev)
-            work = fss.rss_fetch_many(g.n, rec, table, (seed0 + 3 * step, seed0 + 3 * step + 1, seed0 + 3 * step + 2),
-                                      g.kept, pos, fetched[k:k + 1])
-            step += 1
-            del work, pos                        # stream-ordered: reused only after these calls' kernels
-        del x3, z3, table
-        # the opens reveal how many candidates of each group match
-        for k, m in enumerate(fetched.cpu().tolist()[:len(live)]):
-            groups[i][live[k]].nkept = m
+        rec = wi + wv
+        # every group's secEval, re-share and secFetch, one library call (an
+        # empty group takes no randomness)
+        live = np.flatnonzero(st.n)
+        n_live = np.ascontiguousarray(st.n[live])
+        total = int(n_live.sum())
+        st.row0 = np.zeros(st.n.size, np.int64)
+        st.row0[live] = np.cumsum(n_live, dtype=np.int64) - n_live
+        st.nkept = np.zeros(st.n.size, np.int64)
+        st.kept = [empty(total * rec) for _ in range(3)]
+        if live.size:
+            fetched = empty(live.size)
+            evals = [ev[(p, r)] for terms in SERVER_TERMS for p, r, _ in terms]
+            seeds = range(seed0 + 3 * step, seed0 + 3 * (step + live.size))
+            work = fss.rss_sec_fetch_groups(np.ascontiguousarray(st.base[live]), n_live, npos, evals, wi, st.ids,
+                                            st.vals, prf_keys, counter, seeds, st.kept, empty(total), fetched)
+            del work                             # stream-ordered: reused only after the call's kernels
+            counter += live.size
+            step += live.size
+            # the opens reveal how many candidates of each group match
+            st.nkept[live] = fetched.cpu().numpy()
         # secAccess of every kept vertex of every group, for each child target:
-        # call k (in this order) takes counter + 2k and shuffle step + k; the
-        # calls of one child target go to the library as one batch, and the
-        # validity opens' counts are read together
-        calls = [(gi, c, r) for gi in live for c in children[i] for r in range(groups[i][gi].nkept)]
-        made, batches = [None] * len(calls), []
-        for c in children[i]:
-            ks = [k for k, call in enumerate(calls) if call[1] == c]
-            if not ks:
-                continue
+        # call k (group by group, child by child) takes counter + 2k and
+        # shuffle step + k; the calls of one child target go to the library as
+        # one batch, and the validity opens' counts are read together
+        nk = st.nkept
+        first = len(children[i]) * (np.cumsum(nk) - nk)      # first call of each group
+        base = [t.data_ptr() for t in st.kept]
+        opened = []
+        for ci, c in enumerate(children[i]):
             nt = query.targets[c]
             pair = (tgt.vtype, nt.vtype)
             wx2, wv2 = words(eg.n[nt.vtype]), words(eg.domains[(nt.vtype, nt.attr)])
-            lmax = eg.lmax[pair]
-            nc = len(ks)
-            idm, counters, seeds = [], [], []
-            for k in ks:
-                gi, _, r = calls[k]
-                idm += [groups[i][gi].kept[j].data_ptr() + 4 * r * (rec - 1) for j in range(3)]
-                counters.append(counter + 2 * k)
-                seeds += [seed0 + 3 * (step + k) + j for j in range(3)]
-            ids3 = [torch.empty(nc * lmax * wx2, dtype=torch.int32, device=dev) for _ in range(3)]
-            vals3 = [torch.empty(nc * lmax * wv2, dtype=torch.int32, device=dev) for _ in range(3)]
-            rows = torch.empty(nc * lmax, dtype=torch.int32, device=dev)
-            cnt = torch.empty(nc, dtype=torch.int32, device=dev)
-            work = fss.rss_sec_access_batch(eg.n[tgt.vtype], eg.n[nt.vtype], idm, eg.off[pair], lmax, eg.post[pair],
-                                            wv2, eg.shares[("attr", nt.vtype, nt.attr)], prf_keys, counters, seeds,
-                                            ids3, vals3, rows, cnt)
-            batches.append((ks, cnt))
-            del work, rows
-            for q_, k in enumerate(ks):
-                made[k] = ([t[q_ * lmax * wx2:(q_ + 1) * lmax * wx2] for t in ids3],
-                           [t[q_ * lmax * wv2:(q_ + 1) * lmax * wv2] for t in vals3])
-        counter += 2 * len(calls)
-        step += len(calls)
-        opened = [0] * len(calls)
-        for ks, cnt in batches:              # the first read waits for all of them
-            for k, m in zip(ks, cnt.cpu().tolist()):
-                opened[k] = m
-        for k, (gi, c, r) in enumerate(calls):
-            groups[c].append(_Group((i, gi, r), opened[k], *made[k]))
-    return _results(groups, query, eg)
+            lmax, nc = eg.lmax[pair], int(nk.sum())
+            group = np.repeat(np.arange(nk.size), nk)
+            r = np.arange(nc) - np.repeat(np.cumsum(nk) - nk, nk)
+            k = first[group] + ci * nk[group] + r
+            at = 4 * rec * (st.row0[group] + r)
+            ids3, vals3 = [empty(nc * lmax * wx2) for _ in range(3)], [empty(nc * lmax * wv2) for _ in range(3)]
+            cnt = empty(nc)
+            if nc:
+                idm = (np.array(base, np.int64)[None, :] + at[:, None]).ravel()
+                seeds = (seed0 + 3 * (step + k)[:, None] + np.arange(3)[None, :]).ravel()
+                work = fss.rss_sec_access_batch(eg.n[tgt.vtype], eg.n[nt.vtype], idm.tolist(), eg.off[pair], lmax,
+                                                eg.post[pair], wv2, eg.shares[("attr", nt.vtype, nt.attr)], prf_keys,
+                                                (counter + 2 * k).tolist(), seeds.tolist(), ids3, vals3,
+                                                empty(nc * lmax), cnt)
+                del work
+            targets[c] = _Target(ids3, vals3, (np.arange(nc) * lmax).astype(np.uint32), None,
+                                 list(zip(group.tolist(), r.tolist())))
+            opened.append((c, nc, cnt))
+        calls = len(children[i]) * int(nk.sum())
+        counter += 2 * calls
+        step += calls
+        for c, nc, cnt in opened:            # the first read waits for all of them
+            targets[c].n = cnt.cpu().numpy()[:nc].astype(np.uint32)
+    return _results(targets, query, eg)
 
 
-def _results(groups, query, eg):
+def _results(targets, query, eg):
     """Every assignment of one kept vertex per target, each in the group its
     parent's vertex made (targets in index order), as host share records."""
     q = len(query.targets)
     out = []
-    host = {}
-
-    def kept_ids(i, gi):
-        if (i, gi) not in host:
-            g = groups[i][gi]
-            t = query.targets[i]
-            wi, wv = words(eg.n[t.vtype]), words(eg.domains[(t.vtype, t.attr)])
-            host[(i, gi)] = [g.kept[j][:g.nkept * (wi + wv)].cpu().numpy().view(np.uint32).reshape(
-                g.nkept, wi + wv)[:, :wi] for j in range(3)]
-        return host[(i, gi)]
+    if not all(t.nkept.any() for t in targets):
+        return out                           # some target keeps no vertex: no result, and nothing to copy
+    ids = []                                 # per target, the kept one-hot IDs of the three shares
+    for t, st in zip(query.targets, targets):
+        wi, wv = words(eg.n[t.vtype]), words(eg.domains[(t.vtype, t.attr)])
+        ids.append([k.cpu().numpy().view(np.uint32).reshape(-1, wi + wv)[:, :wi] for k in st.kept])
+    groups_of = []                           # per target, the groups that a parent's kept vertex made
+    for st in targets:
+        of = {}
+        for gi, p in enumerate(st.parent):
+            of.setdefault(p, []).append(gi)
+        groups_of.append(of)
 
     def walk(i, chosen):
         if i == q:
-            out.append([[kept_ids(t, gi)[j][r] for j in range(3)] for t, (gi, r) in enumerate(chosen)])
+            out.append([[ids[t][j][targets[t].row0[gi] + r] for j in range(3)] for t, (gi, r) in enumerate(chosen)])
             return
-        if i == 0:
-            cands = [0]
-        else:
-            p = query.parent(i)
-            cands = [gi for gi, g in enumerate(groups[i]) if g.parent == (p,) + chosen[p]]
-        for gi in cands:
-            for r in range(groups[i][gi].nkept):
+        for gi in groups_of[i].get(None if i == 0 else chosen[query.parent(i)], []):
+            for r in range(int(targets[i].nkept[gi])):
                 walk(i + 1, chosen + [(gi, r)])
 
-    if groups[0]:
-        walk(0, [])
+    walk(0, [])
     return out
