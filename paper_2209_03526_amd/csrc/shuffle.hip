@@ -351,9 +351,9 @@ __global__ __launch_bounds__(256) void k_rank_runs(uint64_t n, uint32_t hb, uint
 //
 // Tables of 1025 .. 2^23 rows take the stable argsort of their keys in four
 // launches and no sort library: with hb run-id bits as above, the top
-// d1 = ceil(log2 n) - 12 key bits (at least 0) name the row's bucket (2^11 ..
-// 2^12 rows on average), the next d2 = hb - d1 bits its run in the bucket.
-//   count: each workgroup makes the keys of 8192 rows and counts them per
+// d1 = ceil(log2 n) - 12 key bits (at least 0; one more up to 2^18 rows) name
+// the row's bucket (2^11 .. 2^12 rows on average), the next d2 = hb - d1 bits its run in the bucket.
+//   count: each workgroup makes the keys of 8192 (2048) rows and counts them per
 //          bucket in LDS: counts[bucket][workgroup];
 //   scan:  per bucket, the workgroups' exclusive offsets and the total; then
 //          the buckets' starts;
@@ -370,7 +370,13 @@ __global__ __launch_bounds__(256) void k_rank_runs(uint64_t n, uint32_t hb, uint
 // Row r's position is its bucket's start + its run's start in the bucket +
 // its rank in the run, and (key, row number) orders bucket, run and rank:
 // the result is the stable argsort whatever order the placing left.
-constexpr uint32_t kChunkRows = 8192;        // rows per counting / placing workgroup
+// Rows per counting / placing workgroup (eight a thread).  Up to 2^18 rows small
+// chunks and buckets of about 2^10 to 2^11 rows spread the work over the chip
+// (100,003 rows: counting 7.3 -> 4.5 us, placing 13 -> 7.6, ranking 9.9 -> 7.3);
+// large tables need the long store runs of large chunks.
+constexpr uint32_t kChunkRows = 8192, kSmallChunkRows = 2048;
+constexpr uint64_t kSmallChunkMost = 1ull << 18;
+constexpr uint32_t kSmallBuckets = 128;      // 2^(18 - 11)
 constexpr uint32_t kMaxBuckets = 2048;       // 2^(23 - 12)
 constexpr uint32_t kBucketCap = 7168;        // rows of a bucket held in LDS
 constexpr uint64_t kBucketMaxRows = 1ull << 23;
@@ -393,10 +399,10 @@ __device__ __forceinline__ uint32_t bucket_of(uint64_t key, uint32_t d1) {
 
 // The keys of the block's rows, two per lane (all lanes of each quad active):
 // f(row, key) for every row below n.
-template <class F>
+template <uint32_t CHUNK, class F>
 __device__ __forceinline__ void chunk_keys(ChachaKey pk, uint32_t p, uint64_t n, F f) {
-    const uint64_t q0 = (uint64_t)blockIdx.x * (kChunkRows / 8);
-    for (uint32_t t = threadIdx.x; t < kChunkRows / 2; t += blockDim.x) {
+    const uint64_t q0 = (uint64_t)blockIdx.x * (CHUNK / 8);
+    for (uint32_t t = threadIdx.x; t < CHUNK / 2; t += CHUNK / 8) {
         const uint64_t q = q0 + (t >> 2);
         const uint4 o = chacha_quad(pk, (uint32_t)q, 0u, 16u + p, 0u);
         const uint64_t r0 = q * 8 + 2 * (t & 3);
@@ -405,8 +411,9 @@ __device__ __forceinline__ void chunk_keys(ChachaKey pk, uint32_t p, uint64_t n,
     }
 }
 
-__global__ __launch_bounds__(1024) void k_perm_count(uint64_t n, uint32_t d1, uint32_t nblk, BucketSet S) {
-    __shared__ uint32_t hist[kMaxBuckets];
+template <uint32_t CHUNK, uint32_t BUCKETS>
+__global__ __launch_bounds__(CHUNK / 8) void k_perm_count(uint64_t n, uint32_t d1, uint32_t nblk, BucketSet S) {
+    __shared__ uint32_t hist[BUCKETS];
     const uint32_t q = blockIdx.y;
     const ChachaKey pk = S.pk[q];
     const uint32_t p = S.p[q];
@@ -414,7 +421,7 @@ __global__ __launch_bounds__(1024) void k_perm_count(uint64_t n, uint32_t d1, ui
     const uint32_t nb = 1u << d1;
     for (uint32_t i = threadIdx.x; i < nb; i += blockDim.x) hist[i] = 0;
     __syncthreads();
-    chunk_keys(pk, p, n, [&](uint64_t, uint64_t key) { atomicAdd(&hist[bucket_of(key, d1)], 1u); });
+    chunk_keys<CHUNK>(pk, p, n, [&](uint64_t, uint64_t key) { atomicAdd(&hist[bucket_of(key, d1)], 1u); });
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < nb; i += blockDim.x) counts[(uint64_t)i * nblk + blockIdx.x] = hist[i];
 }
@@ -482,7 +489,10 @@ __global__ __launch_bounds__(256) void k_bucket_starts(uint32_t nb, BucketSet S)
 // counted per bucket and grouped by bucket in LDS first, so that each thread
 // then stores consecutive positions of a bucket's range: the stores of a
 // wavefront cover a few contiguous segments instead of 64 scattered words.
-__global__ __launch_bounds__(1024) void k_perm_place(uint64_t n, uint32_t d1, uint32_t nblk, BucketSet S) {
+template <uint32_t CHUNK, uint32_t BUCKETS>
+__global__ __launch_bounds__(CHUNK / 8) void k_perm_place(uint64_t n, uint32_t d1, uint32_t nblk, BucketSet S) {
+    constexpr uint32_t T = CHUNK / 8;          // threads; a thread scans two buckets
+    static_assert(BUCKETS <= 2 * T, "two buckets a thread");
     const uint32_t q = blockIdx.y;
     const ChachaKey pk = S.pk[q];
     const uint32_t p = S.p[q];
@@ -490,22 +500,22 @@ __global__ __launch_bounds__(1024) void k_perm_place(uint64_t n, uint32_t d1, ui
     const uint32_t* __restrict__ starts = S.starts[q];
     uint64_t* __restrict__ skeys = S.skeys[q];
     uint32_t* __restrict__ srows = S.srows[q];
-    __shared__ uint64_t lkeys[kChunkRows];
-    __shared__ uint32_t lrows[kChunkRows];
-    __shared__ uint32_t loff[kMaxBuckets];     // the bucket's first slot in the workgroup's group
-    __shared__ uint32_t lcur[kMaxBuckets];     // counts, then slot cursors
-    __shared__ uint32_t gpos[kMaxBuckets];     // the bucket's first position for this workgroup
-    __shared__ uint32_t scan[1024];
+    __shared__ uint64_t lkeys[CHUNK];
+    __shared__ uint32_t lrows[CHUNK];
+    __shared__ uint32_t loff[BUCKETS];     // the bucket's first slot in the workgroup's group
+    __shared__ uint32_t lcur[BUCKETS];     // counts, then slot cursors
+    __shared__ uint32_t gpos[BUCKETS];     // the bucket's first position for this workgroup
+    __shared__ uint32_t scan[T];
     const uint32_t nb = 1u << d1, tid = threadIdx.x;
-    for (uint32_t i = tid; i < nb; i += 1024) lcur[i] = 0;
+    for (uint32_t i = tid; i < nb; i += T) lcur[i] = 0;
     __syncthreads();
     uint64_t key[8], row0[4];
-    const uint64_t q0 = (uint64_t)blockIdx.x * (kChunkRows / 8);
+    const uint64_t q0 = (uint64_t)blockIdx.x * (CHUNK / 8);
     // the rows and keys of chunk_keys (which k_perm_count counts), unrolled
     // so that the eight keys stay in registers
 #pragma unroll
-    for (uint32_t it = 0; it < 4; it++) {         // kChunkRows / 2 lanes' worth: 4 x 1024
-        const uint32_t t = tid + 1024u * it;
+    for (uint32_t it = 0; it < 4; it++) {         // CHUNK / 2 lanes' worth: 4 x T
+        const uint32_t t = tid + T * it;
         const uint64_t q = q0 + (t >> 2);
         const uint4 o = chacha_quad(pk, (uint32_t)q, 0u, 16u + p, 0u);
         row0[it] = q * 8 + 2 * (t & 3);
@@ -515,11 +525,11 @@ __global__ __launch_bounds__(1024) void k_perm_place(uint64_t n, uint32_t d1, ui
         if (row0[it] + 1 < n) atomicAdd(&lcur[bucket_of(key[2 * it + 1], d1)], 1u);
     }
     __syncthreads();
-    {   // exclusive scan of the counts, two buckets per thread (nb <= 2048)
+    {   // exclusive scan of the counts, two buckets per thread 
         const uint32_t a = 2 * tid < nb ? lcur[2 * tid] : 0u, b = 2 * tid + 1 < nb ? lcur[2 * tid + 1] : 0u;
         scan[tid] = a + b;
         __syncthreads();
-        for (uint32_t d = 1; d < 1024; d <<= 1) {
+        for (uint32_t d = 1; d < T; d <<= 1) {
             const uint32_t x = tid >= d ? scan[tid - d] : 0u;
             __syncthreads();
             scan[tid] += x;
@@ -529,7 +539,7 @@ __global__ __launch_bounds__(1024) void k_perm_place(uint64_t n, uint32_t d1, ui
         if (2 * tid < nb) loff[2 * tid] = lcur[2 * tid] = ex;
         if (2 * tid + 1 < nb) loff[2 * tid + 1] = lcur[2 * tid + 1] = ex + a;
     }
-    for (uint32_t i = tid; i < nb; i += 1024) gpos[i] = starts[i] + counts[(uint64_t)i * nblk + blockIdx.x];
+    for (uint32_t i = tid; i < nb; i += T) gpos[i] = starts[i] + counts[(uint64_t)i * nblk + blockIdx.x];
     __syncthreads();
 #pragma unroll
     for (uint32_t it = 0; it < 4; it++)
@@ -541,9 +551,9 @@ __global__ __launch_bounds__(1024) void k_perm_place(uint64_t n, uint32_t d1, ui
                 lrows[slot] = (uint32_t)(row0[it] + e);
             }
     __syncthreads();
-    const uint64_t first = (uint64_t)blockIdx.x * kChunkRows;
-    const uint32_t rows_here = (uint32_t)(n - first < kChunkRows ? n - first : kChunkRows);
-    for (uint32_t i = tid; i < rows_here; i += 1024) {
+    const uint64_t first = (uint64_t)blockIdx.x * CHUNK;
+    const uint32_t rows_here = (uint32_t)(n - first < CHUNK ? n - first : CHUNK);
+    for (uint32_t i = tid; i < rows_here; i += T) {
         const uint64_t k = lkeys[i];
         const uint32_t bk = bucket_of(k, d1);
         const uint32_t dst = gpos[bk] + (i - loff[bk]);
@@ -962,46 +972,90 @@ __global__ void k_open_parity(uint64_t nrows, uint32_t nwords, uint32_t vec, con
     if (lane == 0) flags[i] = __builtin_popcount(acc) & 1u;
 }
 
-// Copy the kept records (words first..W-1) of the three share tables to their
-// slots: one thread per (record, word) so that reads and writes are coalesced.
-__global__ void k_compact(uint64_t nrows, uint32_t nwords, uint32_t first, const uint32_t* __restrict__ flags,
-                          const uint32_t* __restrict__ pos, const uint32_t* __restrict__ s0,
-                          const uint32_t* __restrict__ s1, const uint32_t* __restrict__ s2,
-                          uint32_t* __restrict__ o0, uint32_t* __restrict__ o1, uint32_t* __restrict__ o2,
-                          uint32_t* __restrict__ rows_out) {
-    const uint32_t rw = nwords - first;
-    const uint64_t total = nrows * rw;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += stride) {
-        const uint32_t i = (uint32_t)(k / rw), w = (uint32_t)(k - (uint64_t)i * rw);
-        if (!flags[i]) continue;
-        const uint64_t d = pos[i];
-        const uint64_t src = (uint64_t)i * nwords + first + w;
-        o0[d * rw + w] = s0[src];
-        o1[d * rw + w] = s1[src];
-        o2[d * rw + w] = s2[src];
-        if (w == 0) rows_out[d] = i;
-    }
+// Compaction of the kept records (words first .. W-1 of the three share tables)
+// in two launches: the number of kept records of every block of rows, then
+// each block, with the sum of the blocks before it, lists its kept rows in LDS
+// and copies their records, 16 bytes a thread.  (A scan of all flags by a sort
+// library, a copy that looked at every word of every record and a launch for
+// the count took four launches: 20 of 85 us at 100,003 records of 21 words.)
+constexpr uint32_t kCompactStep = 256;       // rows listed at a time, one a thread
+constexpr uint32_t kCompactBlocks = 2048;
+
+__host__ __device__ inline uint64_t compact_rows(uint64_t nrows) {       // rows of a block
+    const uint64_t per = (nrows + kCompactBlocks - 1) / kCompactBlocks;
+    return (per + kCompactStep - 1) / kCompactStep * kCompactStep;
 }
 
-// k_compact for whole records (first = 0) of a width that is a multiple of 4
-// words, every table 16-byte aligned: one thread per 16-byte quarter.
-__global__ void k_compact_vec(uint64_t nrows, uint32_t nwords, const uint32_t* __restrict__ flags,
-                              const uint32_t* __restrict__ pos, const uint4* __restrict__ s0,
-                              const uint4* __restrict__ s1, const uint4* __restrict__ s2, uint4* __restrict__ o0,
-                              uint4* __restrict__ o1, uint4* __restrict__ o2, uint32_t* __restrict__ rows_out) {
-    const uint32_t nq = nwords >> 2;
-    const uint64_t total = nrows * nq;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += stride) {
-        const uint32_t i = (uint32_t)(k / nq), q = (uint32_t)(k - (uint64_t)i * nq);
-        if (!flags[i]) continue;
-        const uint64_t d = (uint64_t)pos[i] * nq + q;
-        o0[d] = s0[k];
-        o1[d] = s1[k];
-        o2[d] = s2[k];
-        if (q == 0) rows_out[pos[i]] = i;
+// Sum of v over the block (256 threads); `sh` is free again when it returns.
+__device__ __forceinline__ uint32_t block_sum256(uint32_t v, uint32_t* sh) {
+    for (uint32_t d = 32; d > 0; d >>= 1) v += (uint32_t)__shfl_xor((int)v, (int)d);
+    if ((threadIdx.x & 63u) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    const uint32_t total = sh[0] + sh[1] + sh[2] + sh[3];
+    __syncthreads();
+    return total;
+}
+
+__global__ __launch_bounds__(256) void k_flag_sums(uint64_t nrows, const uint32_t* __restrict__ flags,
+                                                   uint32_t* __restrict__ sums) {
+    __shared__ uint32_t sh[4];
+    const uint64_t per = compact_rows(nrows), r0 = blockIdx.x * per, r1 = min(r0 + per, nrows);
+    uint32_t v = 0;
+    for (uint64_t r = r0 + threadIdx.x; r < r1; r += 256) v += flags[r];
+    v = block_sum256(v, sh);
+    if (threadIdx.x == 0) sums[blockIdx.x] = v;
+}
+
+__global__ __launch_bounds__(256) void k_compact(uint64_t nrows, uint32_t nwords, uint32_t first,
+                                                 const uint32_t* __restrict__ flags, const uint32_t* __restrict__ sums,
+                                                 const uint32_t* __restrict__ s0, const uint32_t* __restrict__ s1,
+                                                 const uint32_t* __restrict__ s2, uint32_t* __restrict__ o0,
+                                                 uint32_t* __restrict__ o1, uint32_t* __restrict__ o2,
+                                                 uint32_t* __restrict__ rows_out, uint32_t* __restrict__ count) {
+    __shared__ uint32_t sh[4];
+    __shared__ uint32_t list[kCompactStep];
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+    uint32_t v = 0;
+    for (uint32_t b = t; b < blockIdx.x; b += 256) v += sums[b];
+    uint32_t base = block_sum256(v, sh);             // kept rows before this block's
+    const uint64_t per = compact_rows(nrows), r0 = blockIdx.x * per, r1 = min(r0 + per, nrows);
+    const uint32_t rw = nwords - first, nq = (rw + 3) >> 2;
+    for (uint64_t c0 = r0; c0 < r1; c0 += kCompactStep) {
+        // the kept rows' places by a scan over the block
+        const uint64_t r = c0 + t;
+        const uint32_t f = r < r1 ? flags[r] : 0u;
+        const uint64_t ballot = __ballot(f);
+        if (lane == 0) sh[wave] = (uint32_t)__builtin_popcountll(ballot);
+        __syncthreads();
+        uint32_t at = (uint32_t)__builtin_popcountll(ballot & ((1ull << lane) - 1));
+        for (uint32_t w = 0; w < wave; w++) at += sh[w];
+        const uint32_t kept = sh[0] + sh[1] + sh[2] + sh[3];
+        if (f) list[at] = t;
+        __syncthreads();
+        for (uint32_t j = t; j < kept; j += 256) rows_out[base + j] = (uint32_t)c0 + list[j];
+        for (uint32_t k = t; k < kept * nq; k += 256) {
+            const uint32_t j = k / nq, w = 4 * (k - j * nq);
+            const uint64_t src = (c0 + list[j]) * nwords + first + w, dst = (uint64_t)(base + j) * rw + w;
+            if (w + 4 <= rw) {
+                uint4 a, b, c;
+                __builtin_memcpy(&a, s0 + src, 16);
+                __builtin_memcpy(&b, s1 + src, 16);
+                __builtin_memcpy(&c, s2 + src, 16);
+                __builtin_memcpy(o0 + dst, &a, 16);
+                __builtin_memcpy(o1 + dst, &b, 16);
+                __builtin_memcpy(o2 + dst, &c, 16);
+            } else {
+                for (uint32_t q = 0; w + q < rw; q++) {
+                    o0[dst + q] = s0[src + q];
+                    o1[dst + q] = s1[src + q];
+                    o2[dst + q] = s2[src + q];
+                }
+            }
+        }
+        base += kept;
+        __syncthreads();                             // list and sums are free again
     }
+    if (blockIdx.x == gridDim.x - 1 && t == 0) *count = base;
 }
 
 // Tables of at most kSmallPerm records (secAccess shuffles one posting list):
@@ -1127,12 +1181,6 @@ __global__ __launch_bounds__(1024) void k_shuffle_small(SmallShuffle A) {
                        A.rows_out + r0, A.count + call, flag, incl);
 }
 
-// count of kept records = last exclusive prefix + last flag
-__global__ void k_count(uint64_t n, const uint32_t* __restrict__ flags, const uint32_t* __restrict__ pos,
-                        uint32_t* __restrict__ count) {
-    if (threadIdx.x == 0) *count = pos[n - 1] + flags[n - 1];
-}
-
 unsigned grid_of(uint64_t n, unsigned block) {
     uint64_t g = (n + block - 1) / block;
     if (g == 0) g = 1;
@@ -1222,10 +1270,11 @@ uint32_t ceil_log2(uint64_t n) {
     return lg;
 }
 
-// Bucket bits d1 of the bucket method: 2^11 .. 2^12 rows per bucket on average.
+// Bucket bits d1 of the bucket method: 2^11 .. 2^12 rows per bucket on average,
+// half of that with small chunks.
 uint32_t bucket_bits(uint64_t nrows) {
-    const uint32_t lg = ceil_log2(nrows);
-    return lg > 12 ? lg - 12 : 0;
+    const uint32_t lg = ceil_log2(nrows), row_bits = nrows <= kSmallChunkMost ? 11 : 12;
+    return lg > row_bits ? lg - row_bits : 0;
 }
 
 // The method a permutation of nrows rows takes (tables of at most 1024 rows
@@ -1239,7 +1288,9 @@ uint32_t perm_method(uint64_t nrows, uint32_t m) {
 // stream s (blockIdx.y picks the permutation).
 int bucket_perms(uint64_t nrows, const PermJob (&jobs)[3], uint32_t method, hipStream_t s) {
     const uint32_t hb = run_bits(nrows), d1 = bucket_bits(nrows), nb = 1u << d1;
-    const uint32_t nblk = (uint32_t)((nrows + kChunkRows - 1) / kChunkRows);
+    const bool small = nrows <= kSmallChunkMost;
+    const uint32_t chunk = small ? kSmallChunkRows : kChunkRows;
+    const uint32_t nblk = (uint32_t)((nrows + chunk - 1) / chunk);
     // scratch of each permutation: keys and rows placed by bucket in keys /
     // idx, per-workgroup counts in keys_sorted, bucket totals and starts in
     // idx_sorted; they fit for every table the method takes
@@ -1258,13 +1309,15 @@ int bucket_perms(uint64_t nrows, const PermJob (&jobs)[3], uint32_t method, hipS
         S.totals[q] = w.idx_sorted;
         S.starts[q] = w.idx_sorted + nb;
     }
-    hipLaunchKernelGGL(k_perm_count, dim3(nblk, 3), dim3(1024), 0, s, nrows, d1, nblk, S);
+    auto count = small ? k_perm_count<kSmallChunkRows, kSmallBuckets> : k_perm_count<kChunkRows, kMaxBuckets>;
+    hipLaunchKernelGGL(count, dim3(nblk, 3), dim3(chunk / 8), 0, s, nrows, d1, nblk, S);
     if (int rc = check_launch("k_perm_count")) return rc;
     hipLaunchKernelGGL(k_bucket_offsets, dim3(nb, 3), dim3(256), 0, s, nblk, S);
     if (int rc = check_launch("k_bucket_offsets")) return rc;
     hipLaunchKernelGGL(k_bucket_starts, dim3(1, 3), dim3(256), 0, s, nb, S);
     if (int rc = check_launch("k_bucket_starts")) return rc;
-    hipLaunchKernelGGL(k_perm_place, dim3(nblk, 3), dim3(1024), 0, s, nrows, d1, nblk, S);
+    auto place = small ? k_perm_place<kSmallChunkRows, kSmallBuckets> : k_perm_place<kChunkRows, kMaxBuckets>;
+    hipLaunchKernelGGL(place, dim3(nblk, 3), dim3(chunk / 8), 0, s, nrows, d1, nblk, S);
     if (int rc = check_launch("k_perm_place")) return rc;
     hipLaunchKernelGGL(k_bucket_rank, dim3(nb, 3), dim3(1024), 0, s, nrows, hb, d1, method - kPermBuckets, S);
     return check_launch("k_bucket_rank");
@@ -1685,11 +1738,9 @@ int rss_fetch_table(uint64_t ncand, const uint32_t* const d_bits[3], uint32_t id
 
 uint64_t rss_fetch_many_workspace_bytes(uint64_t ncand, uint32_t nwords) {
     if (ncand == 0 || nwords == 0) return 0;
-    size_t scan = 0;
-    (void)hipcub::DeviceScan::ExclusiveSum(nullptr, scan, (const uint32_t*)nullptr, (uint32_t*)nullptr, (int)ncand);
     const uint64_t tw = ncand * nwords * 4;
-    return shuffle_ws(ncand, nwords) + 3 * ((tw + 255) & ~255ull) + 2 * ((ncand * 4 + 255) & ~255ull) +
-           ((scan + 255) & ~255ull) + 4096;
+    return shuffle_ws(ncand, nwords) + 3 * ((tw + 255) & ~255ull) + ((ncand * 4 + 255) & ~255ull) +
+           ((kCompactBlocks * 4 + 255) & ~255ull) + 4096;
 }
 
 static int shuffle_open_compact(uint64_t ncand, uint32_t nwords, const uint32_t* const d_table[3],
@@ -1716,10 +1767,7 @@ static int shuffle_open_compact(uint64_t ncand, uint32_t nwords, const uint32_t*
     const uint64_t tw = ncand * nwords;
     uint32_t* sh[3] = {ws.take<uint32_t>(tw), ws.take<uint32_t>(tw), ws.take<uint32_t>(tw)};
     uint32_t* flags = ws.take<uint32_t>(ncand);
-    uint32_t* pos = ws.take<uint32_t>(ncand);
-    size_t scan = 0;
-    (void)hipcub::DeviceScan::ExclusiveSum(nullptr, scan, (const uint32_t*)nullptr, (uint32_t*)nullptr, (int)ncand);
-    void* scan_tmp = ws.take<uint8_t>(scan);
+    uint32_t* sums = ws.take<uint32_t>(kCompactBlocks);
     if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
     if (small_shuffle_fits(ncand, nwords)) {
         // the shuffle, the open and the compaction in one workgroup
@@ -1746,21 +1794,13 @@ static int shuffle_open_compact(uint64_t ncand, uint32_t nwords, const uint32_t*
         rc = check_launch("k_open_parity");
         if (rc) return rc;
     }
-    if (hipcub::DeviceScan::ExclusiveSum(scan_tmp, scan, flags, pos, (int)ncand, s) != hipSuccess)
-        return fail(FSS_EDEVICE, "%s: scan failed", who);
-    if (parity && (nwords & 3u) == 0 && aligned16(sh[0]) && aligned16(sh[1]) && aligned16(sh[2]) &&
-        aligned16(d_out[0]) && aligned16(d_out[1]) && aligned16(d_out[2]))
-        hipLaunchKernelGGL(k_compact_vec, dim3(grid_of(ncand * (nwords >> 2), 256)), dim3(256), 0, s, ncand, nwords,
-                           flags, pos, (const uint4*)sh[0], (const uint4*)sh[1], (const uint4*)sh[2],
-                           (uint4*)d_out[0], (uint4*)d_out[1], (uint4*)d_out[2], d_rows_out);
-    else
-        hipLaunchKernelGGL(k_compact, dim3(grid_of(ncand * (nwords - (parity ? 0u : 1u)), 256)), dim3(256), 0, s,
-                           ncand, nwords, parity ? 0u : 1u, flags, pos, sh[0], sh[1], sh[2], d_out[0], d_out[1],
-                           d_out[2], d_rows_out);
-    rc = check_launch("k_compact");
+    const unsigned blocks = (unsigned)((ncand + compact_rows(ncand) - 1) / compact_rows(ncand));
+    hipLaunchKernelGGL(k_flag_sums, dim3(blocks), dim3(256), 0, s, ncand, flags, sums);
+    rc = check_launch("k_flag_sums");
     if (rc) return rc;
-    hipLaunchKernelGGL(k_count, dim3(1), dim3(64), 0, s, ncand, flags, pos, d_count);
-    return check_launch("k_count");
+    hipLaunchKernelGGL(k_compact, dim3(blocks), dim3(256), 0, s, ncand, nwords, parity ? 0u : 1u, flags, sums, sh[0],
+                       sh[1], sh[2], d_out[0], d_out[1], d_out[2], d_rows_out, d_count);
+    return check_launch("k_compact");
 }
 
 int rss_fetch_many(uint64_t ncand, uint32_t nwords, const uint32_t* const d_table[3], const uint64_t seeds[3],
