@@ -279,6 +279,38 @@ __device__ __forceinline__ uint32_t every_fourth(uint64_t x) {
     return (uint32_t)(x | x >> 24) & 0xFFFFu;
 }
 
+// A walk by a quad of lanes: this lane's column of the leaf under its
+// correction word.  For a DCF, bit 0 of `v` on the first lane is its value sum.
+__device__ __forceinline__ uint32_t quad_walk(const uint8_t* tree, uint64_t np, uint64_t row, uint32_t nbits, uint32_t x,
+                                              bool dcf, uint32_t vcw, uint32_t& v, const QuadKey& hk,
+                                              const uint32_t* tab, LaneOff loff) {
+    const uint32_t nu = nbits - 7, c = threadIdx.x & 3u;
+    const uint64_t plane = 16 * np;
+    const uint8_t* p = tree + 16 * row + 4 * c;
+    uint32_t s = *(const uint32_t*)p;
+    p += plane;
+    uint32_t cw = *(const uint32_t*)p;
+    uint32_t hv = 0, tv = 0;
+    x <<= 32 - nbits;
+    const uint32_t keep = c ? ~0u : ~2u;         // clears the value bit of the first column
+    for (uint32_t i = 0; i < nu; i++) {
+        p += plane;
+        if (dcf && i + 1 == nu) p += 4 * np;
+        const uint32_t next = *(const uint32_t*)p;
+        const uint32_t h = tree_hash_quad(s, hk, tab, loff);
+        hv ^= h;                                 // of these the first column's lane is used
+        tv ^= s & vcw;
+        vcw >>= 1;
+        const uint32_t tm = 0u - (quad_first(s) & 1u), xm = 0u - (x >> 31);
+        s = (h & keep) ^ (cw & tm) ^ (s & xm);
+        x <<= 1;
+        cw = next;
+    }
+    v = (hv >> 1) ^ tv;
+    const uint32_t tm = 0u - (quad_first(s) & 1u);
+    return tree_hash_quad(s ^ (c ? 0u : 2u), hk, tab, loff) ^ (cw & tm);
+}
+
 __device__ __forceinline__ void eval_quad_tile(const EvalDesc& D, uint64_t tile, const QuadKey& hk, const uint32_t* tab,
                                                LaneOff loff) {
     const uint32_t lane = threadIdx.x & 63u, c = lane & 3u;
@@ -288,35 +320,14 @@ __device__ __forceinline__ void eval_quad_tile(const EvalDesc& D, uint64_t tile,
     const uint64_t row = dcf ? tile * 8 + ((lane & 31u) >> 2) : tile * 16 + (lane >> 2);
     uint32_t bit = 0;
     if (row < D.n) {                             // whole quads
-        const uint32_t nu = D.nbits - 7, x0 = D.xhat[row];
-        const DcfPlanes P{np, nu};
+        const uint32_t x = D.xhat[row];
+        const DcfPlanes P{np, D.nbits - 7};
         const uint8_t* tree = D.key + (lower ? P.bytes() : 0);
-        const uint64_t plane = 16 * np;
-        const uint8_t* p = tree + 16 * row + 4 * c;
-        uint32_t vcw = dcf ? at<uint32_t>(tree, P.vcw(), row) : 0u;
-        const uint32_t wrap = lower ? 0u : vcw >> 31;
-        uint32_t s = *(const uint32_t*)p;
-        p += plane;
-        uint32_t cw = *(const uint32_t*)p;
-        uint32_t hv = 0, tv = 0, x = x0 << (32 - D.nbits);
-        const uint32_t keep = c ? ~0u : ~2u;     // clears the value bit of the first column
-        for (uint32_t i = 0; i < nu; i++) {
-            p += plane;
-            if (dcf && i + 1 == nu) p += 4 * np;
-            const uint32_t next = *(const uint32_t*)p;
-            const uint32_t h = tree_hash_quad(s, hk, tab, loff);
-            hv ^= h;                             // of these the first column's lane is used
-            tv ^= s & vcw;
-            vcw >>= 1;
-            const uint32_t tm = 0u - (quad_first(s) & 1u), xm = 0u - (x >> 31);
-            s = (h & keep) ^ (cw & tm) ^ (s & xm);
-            x <<= 1;
-            cw = next;
-        }
-        const uint32_t tm = 0u - (quad_first(s) & 1u);
-        const uint32_t g = tree_hash_quad(s ^ (c ? 0u : 2u), hk, tab, loff) ^ (cw & tm);
-        bit = c == ((x0 >> 5) & 3u) ? g >> (x0 & 31u) : 0u;
-        if (dcf && c == 0) bit ^= (hv >> 1) ^ tv ^ wrap;
+        const uint32_t vcw = dcf ? at<uint32_t>(tree, P.vcw(), row) : 0u;
+        uint32_t v;
+        const uint32_t g = quad_walk(tree, np, row, D.nbits, x, dcf, vcw, v, hk, tab, loff);
+        bit = c == ((x >> 5) & 3u) ? g >> (x & 31u) : 0u;
+        if (dcf && c == 0) bit ^= v ^ (lower ? 0u : vcw >> 31);
         bit &= 1u;
         bit ^= quad_lane<1>(bit);                // the quad's four bits together
         bit ^= quad_lane<2>(bit);
@@ -778,11 +789,11 @@ __global__ __launch_bounds__(kBlock) void k_triples(TripleArgs A) {
 // ----------------------------------------------------------------- one-hot RSS secEval (Eq. predEval)
 
 // Full-domain evaluation of one key at every point x in [0, npoints).  The
-// 128 points of a leaf share one walk, so a lane walks to its leaf and answers
-// them all: four packed words (a range's two trees on lanes l and l + 32 of a
-// wave).  Up to eight requests run in one launch (blockIdx.y = request): the
+// 128 points of a leaf share one walk, so a quad of lanes walks to its leaf and
+// answers them all, a packed word per lane (a range's two trees on the halves of
+// a wave).  Up to eight requests run in one launch (blockIdx.y = request): the
 // six keys of one secEval predicate are small and latency-bound.  Six range
-// keys over 2,000 points (192 walks of 5 hashes in all): 11 us, against 33 us
+// keys over 2,000 points (192 walks of 5 hashes in all): 6 us, against 33 us
 // with a pair of walks per point.
 constexpr int kEvalAllMax = 8;
 constexpr int kEvalAllBlock = 256;
@@ -804,48 +815,36 @@ struct EvalAllBatch {
 __global__ __launch_bounds__(kEvalAllBlock) void k_eval_points(EvalAllBatch B) {
     const EvalAllReq& R = B.r[blockIdx.y];
     const uint64_t leaves = (R.npoints + 127) >> 7;
-    const uint32_t per = R.kind == FSS_EQ ? 64 : 32;                       // leaves per wave
+    const bool dcf = R.kind != FSS_EQ;
+    const uint32_t per = dcf ? 8 : 16;                                     // leaves per wave
     const uint64_t leaf0 = (uint64_t)blockIdx.x * (kEvalAllBlock / 64) * per;
     if (leaf0 >= leaves) return;                                           // the whole block leaves
     __shared__ uint32_t tab[kLdsTableWords];
     lds_table_fill(tab, g_tables.t0);
     __syncthreads();
-    const LaneOff loff = lane_offset();
     const uint64_t np = pad_rows(R.n);
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t j = leaf0 + (threadIdx.x >> 6) * per + (lane & (per - 1));   // this lane's leaf
-    uint4 g = make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t lane = threadIdx.x & 63u, c = lane & 3u, lower = dcf ? lane >> 5 : 0u;
+    const uint64_t j = leaf0 + (threadIdx.x >> 6) * per + ((dcf ? lane & 31u : lane) >> 2);   // this quad's leaf
+    uint32_t g = 0;
     if (j < leaves) {
-        const uint32_t x = (uint32_t)j << 7;
-        uint32_t v = 0;
-        if (R.kind == FSS_EQ) {
-            g = walk_leaf<false>(R.key, np, R.row, R.nbits, x, 0u, v, tab, loff);
-        } else {
-            const DcfPlanes P{np, R.nbits - 7};
-            const uint32_t lower = lane >> 5;
-            const uint8_t* tree = R.key + (lower ? P.bytes() : 0);
-            const uint32_t vcw = at<uint32_t>(tree, P.vcw(), R.row);
-            g = walk_leaf<true>(tree, np, R.row, R.nbits, x, vcw, v, tab, loff);
-            const uint32_t flip = 0u - ((v ^ (lower ? 0u : vcw >> 31)) & 1u);
-            g = make_uint4(g.x ^ flip, g.y ^ flip, g.z ^ flip, g.w ^ flip);
-        }
+        const DcfPlanes P{np, R.nbits - 7};
+        const uint8_t* tree = R.key + (lower ? P.bytes() : 0);
+        const uint32_t vcw = dcf ? at<uint32_t>(tree, P.vcw(), R.row) : 0u;
+        uint32_t v;
+        g = quad_walk(tree, np, R.row, R.nbits, (uint32_t)j << 7, dcf, vcw, v, quad_key(FixedHashKey{}), tab, lane_offset());
+        if (dcf) g ^= 0u - ((quad_first(v) ^ (lower ? 0u : vcw >> 31)) & 1u);
     }
-    if (R.kind != FSS_EQ) {                                                // XOR of the two trees
-        g.x ^= (uint32_t)__shfl_xor((int)g.x, 32);
-        g.y ^= (uint32_t)__shfl_xor((int)g.y, 32);
-        g.z ^= (uint32_t)__shfl_xor((int)g.z, 32);
-        g.w ^= (uint32_t)__shfl_xor((int)g.w, 32);
+    if (dcf) {                                                             // XOR of the two trees
+        uint32_t a, b;
+        both_halves(g, a, b);
+        g = a ^ b;
         if (lane >= 32) return;
     }
     if (j >= leaves) return;
-    const uint32_t w[4] = {g.x, g.y, g.z, g.w};
-#pragma unroll
-    for (uint32_t k = 0; k < 4; k++) {
-        const uint64_t first = 128 * j + 32 * k;                           // first point of the word
-        if (first >= R.npoints) break;
-        const uint64_t left = R.npoints - first;
-        R.out[4 * j + k] = left >= 32 ? w[k] : w[k] & ((1u << (uint32_t)left) - 1u);
-    }
+    const uint64_t first = 128 * j + 32 * c;                               // first point of this lane's word
+    if (first >= R.npoints) return;
+    const uint64_t left = R.npoints - first;
+    R.out[4 * j + c] = left >= 32 ? g : g & ((1u << (uint32_t)left) - 1u);
 }
 
 // One server's share of the predicate bit of every candidate: the XOR over
@@ -2592,7 +2591,7 @@ static EvalAllReq eval_all_req(const uint8_t* key, uint32_t* out, const fss_keyb
 static int launch_eval_all(const EvalAllBatch& B, uint32_t m, hipStream_t s) {
     uint64_t blocks = 0;
     for (uint32_t j = 0; j < m; j++) {
-        const uint64_t per = (kEvalAllBlock / 64) * (B.r[j].kind == FSS_EQ ? 64 : 32);
+        const uint64_t per = (kEvalAllBlock / 64) * (B.r[j].kind == FSS_EQ ? 16 : 8);
         blocks = std::max(blocks, ((B.r[j].npoints + 127) / 128 + per - 1) / per);
     }
     if (blocks == 0) return FSS_OK;
