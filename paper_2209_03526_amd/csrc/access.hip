@@ -301,6 +301,7 @@ __global__ __launch_bounds__(kSelBlock) void k_attr_select(uint32_t x_bits, uint
     __shared__ uint32_t part[3][kSelBlock];
     if (blockIdx.y >= count[blockIdx.z]) return;                  // uniform over the block
     const uint64_t k = (uint64_t)blockIdx.z * gridDim.y + blockIdx.y;
+    const uint32_t* id[3] = {ids.p[0] + k * wx, ids.p[1] + k * wx, ids.p[2] + k * wx};
     const uint64_t per = ((uint64_t)x_bits + gridDim.x - 1) / gridDim.x;
     const uint64_t x0 = (uint64_t)blockIdx.x * per;
     const uint64_t x1 = x0 + per < x_bits ? x0 + per : x_bits;
@@ -315,7 +316,7 @@ __global__ __launch_bounds__(kSelBlock) void k_attr_select(uint32_t x_bits, uint
                 uint32_t m[3], r[3];
 #pragma unroll
                 for (int i = 0; i < 3; i++) {
-                    m[i] = 0u - ((ids.p[i][k * wx + (x >> 5)] >> (x & 31)) & 1u);
+                    m[i] = 0u - ((id[i][x >> 5] >> (x & 31)) & 1u);
                     r[i] = attr.p[i][x * wd + w0 + w];
                 }
                 rss_product(m, r, acc);

@@ -90,12 +90,13 @@ __global__ __launch_bounds__(kBlock) void k_perm_keys(ChachaKey pk, uint32_t p, 
 }
 
 // Small tables (at most kSmallPerm rows, as in secAccess, which shuffles one
-// fetched posting list): the three permutations of a shuffle in one launch,
-// one workgroup each.  The workgroup makes its rows' keys into LDS (the same
-// keys as k_perm_keys, not rotated), then row i's position is its rank: the
-// rows with a smaller key, or an equal key and a smaller row number -- the
-// stable argsort, as the sort path makes it.  Every lane of the wave reads the
-// same key at a time (an LDS broadcast).
+// fetched posting list): the three permutations of a shuffle in one launch.  A
+// workgroup makes all rows' keys into LDS (the same keys as k_perm_keys, not
+// rotated), then row i's position is its rank: the rows with a smaller key, or
+// an equal key and a smaller row number -- the stable argsort, as the sort path
+// makes it.  With one workgroup and one thread per row 700 rows took 26 us (700
+// LDS reads in a row); with 128 rows a workgroup and eight threads a row the
+// whole shuffle of 700 records of 96 bytes takes 17 us instead of 34.
 constexpr uint32_t kSmallPerm = 1024;
 
 struct SmallPerms {
@@ -105,39 +106,55 @@ struct SmallPerms {
     uint32_t* out[3];
 };
 
-// One permutation of n <= kSmallPerm rows made by the whole workgroup: keys
-// into `key` (LDS), then each row's rank; `out` gets the permutation (or its
-// inverse).  Every thread of the workgroup calls it; `key` is free again when
-// it returns.
-__device__ __forceinline__ void small_perm(ChachaKey pk, uint32_t p, uint32_t inverse, uint32_t n, uint64_t* key,
-                                           uint32_t* out) {
+// Rows [r0, r1) of one permutation of n <= kSmallPerm rows, made by the whole
+// workgroup of 1024 threads: the keys of all n rows into `key` (LDS), then each
+// row's rank; `out` gets the permutation (or its inverse).  Comparing all keys
+// is a loop of n LDS reads, so several threads share a row, each with a part of
+// the keys, and add their counts to `rank` (LDS).  `key` and `rank` are free
+// again when it returns.
+__device__ __forceinline__ void small_perm(ChachaKey pk, uint32_t p, uint32_t inverse, uint32_t n, uint32_t r0,
+                                           uint32_t r1, uint64_t* key, uint32_t* rank, uint32_t* out) {
     const uint32_t lanes = (n + 7) / 8 * 4;              // whole quads: a quad makes the keys of 8 rows
     for (uint32_t t = threadIdx.x; t < lanes; t += blockDim.x) {
         const uint4 o = chacha_quad(pk, t >> 2, 0u, 16u + p, 0u);
-        const uint32_t r0 = (t >> 2) * 8 + 2 * (t & 3);
-        if (r0 < n) key[r0] = (uint64_t)o.x | ((uint64_t)o.y << 32);
-        if (r0 + 1 < n) key[r0 + 1] = (uint64_t)o.z | ((uint64_t)o.w << 32);
+        const uint32_t k0 = (t >> 2) * 8 + 2 * (t & 3);
+        if (k0 < n) key[k0] = (uint64_t)o.x | ((uint64_t)o.y << 32);
+        if (k0 + 1 < n) key[k0 + 1] = (uint64_t)o.z | ((uint64_t)o.w << 32);
+    }
+    const uint32_t rows = r1 - r0, parts = blockDim.x / rows;        // rows <= 1024 threads
+    if (threadIdx.x < rows) rank[threadIdx.x] = 0u;
+    __syncthreads();
+    const uint32_t part = threadIdx.x / rows, own = threadIdx.x - part * rows;
+    if (part < parts) {
+        const uint32_t i = r0 + own, len = (n + parts - 1) / parts;
+        const uint32_t j0 = min(part * len, n), j1 = min(j0 + len, n);
+        const uint64_t ki = key[i];
+        uint32_t c = 0;
+        for (uint32_t j = j0; j < j1; j++) {
+            const uint64_t kj = key[j];
+            c += (kj < ki || (kj == ki && j < i)) ? 1u : 0u;
+        }
+        if (c) atomicAdd(&rank[own], c);
     }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-        const uint64_t ki = key[i];
-        uint32_t rank = 0;
-        for (uint32_t j = 0; j < n; j++) {
-            const uint64_t kj = key[j];
-            rank += (kj < ki || (kj == ki && j < i)) ? 1u : 0u;
-        }
+    if (threadIdx.x < rows) {
+        const uint32_t i = r0 + threadIdx.x;
         if (inverse)
-            out[i] = rank;
+            out[i] = rank[threadIdx.x];
         else
-            out[rank] = i;
+            out[rank[threadIdx.x]] = i;
     }
     __syncthreads();
 }
 
+// blockIdx.x = permutation, blockIdx.y = kSmallRows of its rows.
+constexpr uint32_t kSmallRows = 128;
+
 __global__ __launch_bounds__(1024) void k_perm_small(uint32_t n, SmallPerms J) {
     __shared__ uint64_t key[kSmallPerm];
-    const uint32_t q = blockIdx.x;
-    small_perm(J.pk[q], J.p[q], J.inverse[q], n, key, J.out[q]);
+    __shared__ uint32_t rank[kSmallRows];
+    const uint32_t q = blockIdx.x, r0 = blockIdx.y * kSmallRows;
+    small_perm(J.pk[q], J.p[q], J.inverse[q], n, r0, min(r0 + kSmallRows, n), key, rank, J.out[q]);
 }
 
 // The permutation is the stable argsort of the 64-bit keys.  It is made in two
@@ -942,6 +959,12 @@ __global__ void k_zero(uint64_t n, uint32_t* __restrict__ p) {
     for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) p[k] = 0u;
 }
 
+// n words of each of three buffers (blockIdx.x picks one).
+__global__ void k_zero_shares(uint32_t n, uint32_t* __restrict__ a, uint32_t* __restrict__ b, uint32_t* __restrict__ c) {
+    uint32_t* p = blockIdx.x == 0 ? a : blockIdx.x == 1 ? b : c;
+    for (uint32_t k = threadIdx.x; k < n; k += blockDim.x) p[k] = 0u;
+}
+
 // secAccess filter: flag of shuffled record i = parity of all bits of R1 ^ R2 ^ R3
 // (1 for a one-hot ID, 0 for a dummy all-zero ID).  A quad of lanes takes a
 // record, lane c its 16-byte quarters c, c + 4, ... (with vec: width a
@@ -975,7 +998,7 @@ __global__ void k_open_parity(uint64_t nrows, uint32_t nwords, uint32_t vec, con
 // Compaction of the kept records (words first .. W-1 of the three share tables)
 // in two launches: the number of kept records of every block of rows, then
 // each block, with the sum of the blocks before it, lists its kept rows in LDS
-// and copies their records, 16 bytes a thread.  (A scan of all flags by a sort
+// and copies their records, 16 bytes or a word a thread.  (A scan of all flags by a sort
 // library, a copy that looked at every word of every record and a launch for
 // the count took four launches: 20 of 85 us at 100,003 records of 21 words.)
 constexpr uint32_t kCompactStep = 256;       // rows listed at a time, one a thread
@@ -1019,7 +1042,10 @@ __global__ __launch_bounds__(256) void k_compact(uint64_t nrows, uint32_t nwords
     for (uint32_t b = t; b < blockIdx.x; b += 256) v += sums[b];
     uint32_t base = block_sum256(v, sh);             // kept rows before this block's
     const uint64_t per = compact_rows(nrows), r0 = blockIdx.x * per, r1 = min(r0 + per, nrows);
-    const uint32_t rw = nwords - first, nq = (rw + 3) >> 2;
+    // 16 bytes a thread where the records are whole quarters, else a word (a
+    // branch for the last words of a record costs a third: 900,000 records of 15
+    // words 81 us, word by word 52)
+    const uint32_t rw = nwords - first, nq = rw & 3u ? rw : rw >> 2;
     for (uint64_t c0 = r0; c0 < r1; c0 += kCompactStep) {
         // the kept rows' places by a scan over the block
         const uint64_t r = c0 + t;
@@ -1034,9 +1060,13 @@ __global__ __launch_bounds__(256) void k_compact(uint64_t nrows, uint32_t nwords
         __syncthreads();
         for (uint32_t j = t; j < kept; j += 256) rows_out[base + j] = (uint32_t)c0 + list[j];
         for (uint32_t k = t; k < kept * nq; k += 256) {
-            const uint32_t j = k / nq, w = 4 * (k - j * nq);
+            const uint32_t j = k / nq, w = rw & 3u ? k - j * nq : 4 * (k - j * nq);
             const uint64_t src = (c0 + list[j]) * nwords + first + w, dst = (uint64_t)(base + j) * rw + w;
-            if (w + 4 <= rw) {
+            if (rw & 3u) {
+                o0[dst] = s0[src];
+                o1[dst] = s1[src];
+                o2[dst] = s2[src];
+            } else {
                 uint4 a, b, c;
                 __builtin_memcpy(&a, s0 + src, 16);
                 __builtin_memcpy(&b, s1 + src, 16);
@@ -1044,12 +1074,6 @@ __global__ __launch_bounds__(256) void k_compact(uint64_t nrows, uint32_t nwords
                 __builtin_memcpy(o0 + dst, &a, 16);
                 __builtin_memcpy(o1 + dst, &b, 16);
                 __builtin_memcpy(o2 + dst, &c, 16);
-            } else {
-                for (uint32_t q = 0; w + q < rw; q++) {
-                    o0[dst + q] = s0[src + q];
-                    o1[dst + q] = s1[src + q];
-                    o2[dst + q] = s2[src + q];
-                }
             }
         }
         base += kept;
@@ -1058,10 +1082,10 @@ __global__ __launch_bounds__(256) void k_compact(uint64_t nrows, uint32_t nwords
     if (blockIdx.x == gridDim.x - 1 && t == 0) *count = base;
 }
 
-// Tables of at most kSmallPerm records (secAccess shuffles one posting list):
-// the open, the exclusive scan of the flags, the compaction and the count in
-// one workgroup of 1024 threads.  A wavefront opens a record at a time, its
-// lanes over the record's words (the parity of all bits for the secAccess
+// Tables of at most kAloneRows records too wide for one workgroup's shuffle, and
+// the small shuffles: the open, the exclusive scan of the flags, the compaction
+// and the count in one workgroup of 1024 threads.  A wavefront opens a record at
+// a time, its lanes over the record's words (the parity of all bits for the secAccess
 // filter, bit 0 of word 0 for secFetch); then the kept records' words
 // [first, nwords) go to their positions in shuffled order.
 __device__ __forceinline__ void open_compact_block(uint32_t n, uint32_t nwords, uint32_t parity,
@@ -1131,6 +1155,7 @@ __global__ __launch_bounds__(1024) void k_open_compact_small(uint32_t n, uint32_
 // us, a chain of barriers and ChaCha blocks on one CU, so the shuffles of a
 // batch run side by side (blockIdx.x = call).
 constexpr uint32_t kFusedSlices = 1024;
+constexpr uint32_t kAloneRows = 64;
 
 struct SmallShuffle {
     const uint32_t* g[3];
@@ -1165,9 +1190,9 @@ __global__ __launch_bounds__(1024) void k_shuffle_small(SmallShuffle A) {
                     k31 = pair_key_of(A.seeds[call][2]);
     const uint64_t at = (uint64_t)r0 * nwords;
     uint32_t *xv = A.xv + 2 * at, *s0 = A.out[0] + at, *s1 = A.out[1] + at, *s2 = A.out[2] + at;
-    small_perm(k12, kP12, 1u, n, key, perm[0]);
-    small_perm(k31, kP31, 1u, n, key, perm[1]);
-    small_perm(k23, kP23, 0u, n, key, perm[2]);
+    small_perm(k12, kP12, 1u, n, 0u, n, key, flag, perm[0]);
+    small_perm(k31, kP31, 1u, n, 0u, n, key, flag, perm[1]);
+    small_perm(k23, kP23, 0u, n, 0u, n, key, flag, perm[2]);
     const uint64_t total = (uint64_t)n * ((nwords + 15) >> 4) * 4;
     for (uint64_t t = threadIdx.x; t < total; t += blockDim.x)
         first_slice<WHOLE>(t, n, nwords, k12, k31, perm[0], perm[1], A.g[0] + at, A.g[1] + at, A.g[2] + at, xv, s1, s0);
@@ -1439,7 +1464,8 @@ struct PermSet {
                 J.inverse[q] = inv[q];
                 J.out[q] = outs[q];
             }
-            hipLaunchKernelGGL(k_perm_small, dim3(3), dim3(1024), 0, s, (uint32_t)nrows, J);
+            const unsigned blocks = (unsigned)((nrows + kSmallRows - 1) / kSmallRows);
+            hipLaunchKernelGGL(k_perm_small, dim3(3, blocks), dim3(1024), 0, s, (uint32_t)nrows, J);
             rc = check_launch("k_perm_small");
             return;
         }
@@ -1518,6 +1544,14 @@ int shuffle_rounds(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], 
     return rc;
 }
 
+// Whether a single shuffle runs in one workgroup: up to kAloneRows rows, where
+// its one launch beats three that rank and mask over the chip (records of 64
+// bytes: 300 rows 39 us in one workgroup, 15 in three launches; 1,000 rows 157
+// and 19; 40 rows 10 in one workgroup).
+bool shuffle_alone(uint64_t nrows, uint32_t nwords) {
+    return nrows <= kAloneRows && small_shuffle_fits(nrows, nwords);
+}
+
 // Alg. 5 with all three servers simulated; out[0..2] = R1, R2, R3.  The
 // permutation pi23 is still being made while the first launch runs.  A table
 // that one workgroup shuffles takes no permutation buffers.
@@ -1529,7 +1563,7 @@ int run_shuffle(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], con
     uint32_t* inv31 = ws.take<uint32_t>(nrows);
     uint32_t* p23 = ws.take<uint32_t>(nrows);
     if (!ws.ok) return fail(FSS_ENOMEM, "rss_shuffle: workspace too small");
-    if (small_shuffle_fits(nrows, nwords)) {
+    if (shuffle_alone(nrows, nwords)) {
         const uint32_t row0[2] = {0u, (uint32_t)nrows};
         return small_shuffles(1, row0, nwords, d, seeds, xv, out, 0, nullptr, nullptr, nullptr, s);
     }
@@ -1699,11 +1733,9 @@ int rss_fetch_unique(uint64_t ncand, uint32_t nwords, const uint32_t* const d_x[
     for (int i = 0; i < 3; i++)
         if (!d_x[i] || !d_rows[i] || !d_out[i]) return fail(FSS_EINVAL, "rss_fetch_unique: NULL share %d", i);
     hipStream_t s = (hipStream_t)stream;
-    for (int i = 0; i < 3; i++) {
-        hipLaunchKernelGGL(k_zero, dim3(1), dim3(256), 0, s, (uint64_t)nwords, d_out[i]);
-        int rc = check_launch("k_zero");
-        if (rc) return rc;
-    }
+    hipLaunchKernelGGL(k_zero_shares, dim3(3), dim3(256), 0, s, nwords, d_out[0], d_out[1], d_out[2]);
+    int rc = check_launch("k_zero_shares");
+    if (rc) return rc;
     if (ncand == 0) return FSS_OK;
     // about 8 blocks per CU; each block takes a contiguous run of candidates
     const unsigned grid = grid_of(ncand, kFetchBlock) > 2048 ? 2048 : grid_of(ncand, kFetchBlock);
@@ -1769,14 +1801,14 @@ static int shuffle_open_compact(uint64_t ncand, uint32_t nwords, const uint32_t*
     uint32_t* flags = ws.take<uint32_t>(ncand);
     uint32_t* sums = ws.take<uint32_t>(kCompactBlocks);
     if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
-    if (small_shuffle_fits(ncand, nwords)) {
+    if (shuffle_alone(ncand, nwords)) {
         // the shuffle, the open and the compaction in one workgroup
         uint32_t* xv = ws.take<uint32_t>(2 * tw);
         if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
         const uint32_t row0[2] = {0u, (uint32_t)ncand};
         return small_shuffles(1, row0, nwords, d_table, seeds, xv, sh, parity ? 2u : 1u, d_out, d_rows_out, d_count, s);
     }
-    const bool small = ncand <= kSmallPerm;
+    const bool small = ncand <= kAloneRows;
     // the final round opens secFetch's bit, and the secAccess filter's parity
     // of records of one slice; wider records are opened by k_open_parity
     const uint32_t open = small ? 0u : !parity ? 1u : nwords <= 16 ? 2u : 0u;

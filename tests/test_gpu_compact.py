@@ -52,6 +52,30 @@ def test_kept_records(fss, n, w, share, parity, off):
         assert (got[rows.size * rw:] == 0xFFFFFFFF).all()
 
 
+@pytest.mark.parametrize("n,w", [(1, 3), (64, 16), (65, 16), (64, 300), (127, 5), (128, 16), (129, 4), (255, 17), (513, 2),
+                                 (1023, 16), (1024, 33)])
+def test_small_shuffles_and_fetches(fss, n, w):
+    """Tables that one workgroup shuffles (up to 64 rows) and those that several rank, 128 rows each."""
+    rng = np.random.default_rng(n * w)
+    sh = [rng.integers(0, 2**32, (n, w), dtype=np.uint64).astype(np.uint32) for _ in range(3)]
+    seeds = (31 + n, 32 + w, 33)
+    dev, out = [T(s.ravel()) for s in sh], [torch.empty(n * w, dtype=torch.int32, device=DEV) for _ in range(3)]
+    fss.rss_shuffle(n, w, dev, seeds, out)
+    want = shuffle.sec_shuffle(sh, *seeds)
+    for i in range(3):
+        np.testing.assert_array_equal(U(out[i]).reshape(n, w), want[i])
+    for parity in (False, True):
+        plain = want[0] ^ want[1] ^ want[2]
+        rows = np.flatnonzero(np.bitwise_count(plain).sum(axis=1) & 1 if parity else plain[:, 0] & 1)
+        rw = w if parity else w - 1
+        kept, pos, cnt = [torch.empty(n * rw, dtype=torch.int32, device=DEV) for _ in range(3)], T(np.zeros(n)), T([0])
+        (fss.rss_compact_valid if parity else fss.rss_fetch_many)(n, w, dev, seeds, kept, pos, cnt)
+        assert U(cnt)[0] == rows.size
+        np.testing.assert_array_equal(U(pos)[:rows.size], rows)
+        for i in range(3):
+            np.testing.assert_array_equal(U(kept[i])[:rows.size * rw].reshape(-1, rw), want[i][rows][:, w - rw:])
+
+
 @pytest.mark.parametrize("n", [2047, 2048, 2049, 4097, 131073, 262144, 262145])
 def test_permutations_at_chunk_edges(fss, n):
     seeds = [1000 + n, 2000 + n, 3000 + n]
