@@ -9,7 +9,7 @@ evaluated by both simulated parties: filter -> shared edge join -> shared
 result bits over every edge.
 
 One step is the whole path over that graph: for each predicate the masked
-open and the dealer's key generation, then one persistent evaluation launch
+open and the dealer's key generation, then one batch evaluation launch
 over all predicates and both parties, then match_query on the share bits (the
 ANDs of each vertex and edge fold and both hop joins).  The reported value
 counts DPF and DCF tree walks of both parties (a range is two DCF walks) per
@@ -326,7 +326,7 @@ def run_full(args, torch, fss, dev, graph, query):
     ev_blocks = sum(AES_WORK["eval_" + d["p"].kind] * d["rows"] for d in preds)
     ev_bytes = sum(2 * d["rows"] * ((kb_eq if d["p"].kind == "eq" else kb_rg) + 4) + 8 * fss.words(d["rows"])
                    for d in preds)
-    kernels["k_eval_queue"] = kernel_row(tm.ms("eval"), 1, ev_blocks, ev_bytes)
+    kernels["k_eval_list"] = kernel_row(tm.ms("eval"), 1, ev_blocks, ev_bytes)
     share = {k: v["ms"] * v["launches_per_step"] for k, v in kernels.items()}
     dom = max(share, key=share.get)
     tail_ms = tm.ms("tail")
@@ -344,14 +344,14 @@ def run_full(args, torch, fss, dev, graph, query):
                            "walks per second, served vs plain p50/p99 in 'serving'",
                    "evals_per_step": walks, "key_gb_both_parties": round(key_gb, 2),
                    "eval_tuning": list(tuning)},
-        "eval_only_evals_per_s": walks / (kernels["k_eval_queue"]["ms"] / 1e3),
+        "eval_only_evals_per_s": walks / (kernels["k_eval_list"]["ms"] / 1e3),
         "kernels": kernels,
         "tail": {"ms": round(tail_ms, 4), "what": "match_query on evaluated bits: 3 fold ANDs, 2 hop joins "
                                                   "(gathers of both endpoints and 2 ANDs each)"},
         "hbm_kernels": {"k_mask_open": {"ms": round(open_ms, 4), "launches_per_step": len(preds),
                                         "hbm_gb_per_s": round(open_bytes / (open_ms / 1e3) / 1e9, 1),
                                         "frac_of_hbm_peak": round(open_bytes / (open_ms / 1e3) / HBM_BYTES_PER_S, 4)}},
-        "roofline": roofline_of(dom if dom == "k_eval_queue" else dom.split("[")[0], kernels[dom]),
+        "roofline": roofline_of(dom if dom == "k_eval_list" else dom.split("[")[0], kernels[dom]),
         "cpu_baseline": None,
     }
     out["roofline"]["kernel_launch"] = dom
@@ -503,8 +503,8 @@ def batch_graph_replay(torch, runner, jobs, plain_out, outputs):
 def run_batch64(args, torch, fss, dev):
     """64 uneven queries over the power-law graph (2^22 vertices, 2^25 edges):
     plain = one query after another (per-predicate keygen launches, then
-    match_query); batched = chunked waves of one persistent keygen launch and
-    one persistent eval launch, then the queries' ANDs and joins."""
+    match_query); batched = chunked waves of one batch keygen launch and
+    one batch eval launch, then the queries' ANDs and joins."""
     from paper_2209_03526_amd import autotune
     from paper_2209_03526_amd.runner import ChunkedRunner, QueryJob
 
@@ -565,7 +565,7 @@ def run_batch64(args, torch, fss, dev):
 
     budget_gb = args.budget_gb or 96.0
     runner = ChunkedRunner(int(budget_gb * 1e9), chunk_rows=1 << args.chunk_log_rows, device=dev)
-    # autotune the persistent evaluation shape on one representative wave
+    # autotune the batch evaluation shape on one representative wave
     probe = [j for j in jobs if any(p["rows"] >= 1 << 20 for p in j.preds)][:1] or jobs[:1]
     probe_rows = sum(p["rows"] for j in probe for p in j.preds)
     autotune.tune(lambda: runner.run(probe), probe_rows)
@@ -593,7 +593,7 @@ def run_batch64(args, torch, fss, dev):
             torch.cuda.empty_cache()
     exact = all(np.array_equal(a[b], outputs(j.plan, j)[b]) for a, j in zip(plain_out, jobs) for b in range(2))
 
-    # one more batched pass with the persistent launches timed on the stream
+    # one more batched pass with the batch launches timed on the stream
     timings = []
     runner.run(jobs, timings)
     torch.cuda.synchronize()
@@ -607,11 +607,11 @@ def run_batch64(args, torch, fss, dev):
     persistent = {}
     for k in ("keygen", "eval"):
         f = aes_floor(blocks[k])
-        persistent["k_" + k + "_queue"] = {
+        persistent["k_" + k + "_list"] = {
             "ms_total": round(t_kind[k] * 1e3, 3), "aes_gblocks_per_s": round(f["blocks"] / t_kind[k] / 1e9, 3),
             "floor_gblocks_per_s": round(f["blocks"] / f["t_floor"] / 1e9, 3),
             "frac_of_floor": round(f["t_floor"] / t_kind[k], 4), "binding_unit": f["binding"]}
-    log(f"persistent launches: {persistent}")
+    log(f"batch launches: {persistent}")
     graph_replay = batch_graph_replay(torch, runner, jobs, plain_out, outputs)
     out = {
         "metric": "queries/s, 64 uneven queries (1-5 predicates, 1-4 query vertices, 2^12..2^22 candidate rows)",
@@ -800,7 +800,7 @@ def run_serve(args, torch, fss, dev):
            "config": {"workload": "serve: Chung-Lu 2^22 vertices / 2^25 edges resident, 64-shape query mix "
                                   "(1-5 predicates, 1-4 query vertices, 2^12..2^22 candidate rows)"},
            "paths": {"served": "continuous batching: the requests that arrive while <= 2 waves run form the next "
-                               "wave (one persistent evaluation launch + one match_query_batch)",
+                               "wave (one batch evaluation launch + one match_query_batch)",
                      "plain": "one request at a time, results awaited before the next request starts",
                      "plain_pipelined": "one request at a time on one stream, host runs ahead (no wait)"}}
     if args.keygen_rates:

@@ -1,11 +1,11 @@
-"""Autotuner for the tile / occupancy shape of the persistent launches.
+"""Autotuner for the tile / occupancy shape of the batch launches.
 
-The shape (rows per thread of an evaluation tile, workgroups per CU of the
-persistent grids, rows of a keygen tile) never changes results, only speed.
+The shape (wave tiles that a wave of an evaluation or of a keygen batch takes,
+workgroups per CU) never changes results, only speed.
 ``tune`` times each evaluation shape on the caller's own batch with HIP
 events on the launch stream and keeps the fastest per size bucket (log2 of the
-batch's total rows); ``tune_keygen`` then does the same for the keygen tile
-(512, 1024, 2048 or 4096 rows) with that shape set.  Later batches in the same
+batch's total rows); ``tune_keygen`` then does the same for the keygen tiles
+(1, 2, 4 or 8 a wave) with that shape set.  Later batches in the same
 bucket reuse the choices.
 """
 from __future__ import annotations

@@ -2,7 +2,7 @@
 
 Every predicate of every query is cut into row chunks.  Chunks are grouped
 into waves whose keys (both parties) fit ``budget_bytes``; each wave is one
-persistent dealer launch (``fss_keygen_batch``) and one persistent evaluation
+batch dealer launch (``fss_keygen_batch``) and one batch evaluation
 launch (``fss_eval_batch``) over all its chunks, and its key memory is reused
 by the next wave.  A query whose predicate bits are complete is finished --
 its ANDs and edge joins -- by ``match_query_batch`` with the bits supplied.

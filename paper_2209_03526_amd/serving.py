@@ -12,13 +12,13 @@ over time.  Two protocols:
   GivenServedPath runs continuous batching: while the GPU runs a wave, the
   requests that arrive are admitted (in arrival order, while the device memory
   of their intermediates fits the budget) and form the next wave -- one
-  persistent evaluation launch over all their predicates and parties, then one
+  batch evaluation launch over all their predicates and parties, then one
   match_query_batch for their tails; at most two waves are in flight.
   GivenPlainPath serves one request at a time.
 * keygen included: each request's token is dealt on arrival, inside its
   latency (ServedPath and PlainPath): the served path cuts every request's
-  rows into chunks and runs each wave as one persistent dealer launch and one
-  persistent evaluation launch over a key arena.
+  rows into chunks and runs each wave as one batch dealer launch and one
+  batch evaluation launch over a key arena.
 
 Latency is arrival -> result shares in device memory, timed by HIP events on
 the serving stream against an event recorded when the clock starts.  Results
