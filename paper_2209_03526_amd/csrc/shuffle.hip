@@ -375,13 +375,15 @@ __global__ __launch_bounds__(256) void k_rank_runs(uint64_t n, uint32_t hb, uint
 //   scan:  per bucket, the workgroups' exclusive offsets and the total; then
 //          the buckets' starts;
 //   place: the workgroups make their keys again, group them by bucket in
-//          LDS and store each row (key and row number) in its bucket's range
-//          (the order inside a bucket follows LDS counters: arbitrary);
+//          LDS and store each row in its bucket's range, as one word of 64 bits:
+//          the key's leading 41 bits and the row number's 23 (the order inside a
+//          bucket follows LDS counters: arbitrary);
 //   rank:  one workgroup per bucket loads it into LDS, groups it by run (LDS
 //          counters again), and orders each run by (key, row number) as the
 //          radix path's ranking does: a sorting network over the wavefront
 //          for runs of at most 128 rows whose leading 25 bits after the run
-//          id differ, exact comparisons otherwise.  A bucket of more than
+//          id differ, exact comparisons otherwise, of whole keys that are
+//          made again from the row numbers.  A bucket of more than
 //          kBucketCap rows (about 50 standard deviations above the mean for
 //          keys drawn by ChaCha12) is ordered by comparing every pair.
 // Row r's position is its bucket's start + its run's start in the bucket +
@@ -396,15 +398,16 @@ constexpr uint64_t kSmallChunkMost = 1ull << 18;
 constexpr uint32_t kSmallBuckets = 128;      // 2^(18 - 11)
 constexpr uint32_t kMaxBuckets = 2048;       // 2^(23 - 12)
 constexpr uint32_t kBucketCap = 7168;        // rows of a bucket held in LDS
-constexpr uint64_t kBucketMaxRows = 1ull << 23;
+constexpr uint32_t kRowBits = 23;
+constexpr uint64_t kBucketMaxRows = 1ull << kRowBits;
+constexpr uint64_t kRowMask = kBucketMaxRows - 1;
 
 // The three permutations of a shuffle, made together: blockIdx.y picks one.
 struct BucketSet {
     ChachaKey pk[3];
     uint32_t p[3], inverse[3];
     uint32_t* perm[3];          // output: the permutation or its inverse
-    uint64_t* skeys[3];         // keys placed by bucket
-    uint32_t* srows[3];         // their row numbers
+    uint64_t* srows[3];         // rows placed by bucket: leading key bits and row number
     uint32_t* counts[3];        // per bucket and counting workgroup
     uint32_t* totals[3];        // per bucket
     uint32_t* starts[3];        // bucket starts, nb + 1
@@ -506,8 +509,11 @@ __global__ __launch_bounds__(256) void k_bucket_starts(uint32_t nb, BucketSet S)
 // counted per bucket and grouped by bucket in LDS first, so that each thread
 // then stores consecutive positions of a bucket's range: the stores of a
 // wavefront cover a few contiguous segments instead of 64 scattered words.
+// A row is 8 bytes (12 with the whole key and the row number beside it), and
+// the workgroup takes 80 KiB of LDS (124 before), so that two of them share a
+// CU: three permutations of 2^22 rows 126 -> 68 us.
 template <uint32_t CHUNK, uint32_t BUCKETS>
-__global__ __launch_bounds__(CHUNK / 8) void k_perm_place(uint64_t n, uint32_t d1, uint32_t nblk, BucketSet S) {
+__global__ __launch_bounds__(CHUNK / 8, 8) void k_perm_place(uint64_t n, uint32_t d1, uint32_t nblk, BucketSet S) {
     constexpr uint32_t T = CHUNK / 8;          // threads; a thread scans two buckets
     static_assert(BUCKETS <= 2 * T, "two buckets a thread");
     const uint32_t q = blockIdx.y;
@@ -515,34 +521,30 @@ __global__ __launch_bounds__(CHUNK / 8) void k_perm_place(uint64_t n, uint32_t d
     const uint32_t p = S.p[q];
     const uint32_t* __restrict__ counts = S.counts[q];
     const uint32_t* __restrict__ starts = S.starts[q];
-    uint64_t* __restrict__ skeys = S.skeys[q];
-    uint32_t* __restrict__ srows = S.srows[q];
-    __shared__ uint64_t lkeys[CHUNK];
-    __shared__ uint32_t lrows[CHUNK];
-    __shared__ uint32_t loff[BUCKETS];     // the bucket's first slot in the workgroup's group
+    uint64_t* __restrict__ srows = S.srows[q];
+    __shared__ uint64_t lrows[CHUNK];
     __shared__ uint32_t lcur[BUCKETS];     // counts, then slot cursors
-    __shared__ uint32_t gpos[BUCKETS];     // the bucket's first position for this workgroup
-    __shared__ uint32_t scan[T];
+    __shared__ uint32_t lpos[BUCKETS];     // the bucket's first position for this workgroup, less its first slot
+    uint32_t* scan = (uint32_t*)lrows;     // T words, before the rows come
     const uint32_t nb = 1u << d1, tid = threadIdx.x;
     for (uint32_t i = tid; i < nb; i += T) lcur[i] = 0;
     __syncthreads();
-    uint64_t key[8], row0[4];
-    const uint64_t q0 = (uint64_t)blockIdx.x * (CHUNK / 8);
+    uint64_t row[8];
+    const uint64_t first = (uint64_t)blockIdx.x * CHUNK;
+    const uint32_t rows_here = (uint32_t)(n - first < CHUNK ? n - first : CHUNK);
     // the rows and keys of chunk_keys (which k_perm_count counts), unrolled
-    // so that the eight keys stay in registers
+    // so that the eight rows stay in registers
 #pragma unroll
     for (uint32_t it = 0; it < 4; it++) {         // CHUNK / 2 lanes' worth: 4 x T
-        const uint32_t t = tid + T * it;
-        const uint64_t q = q0 + (t >> 2);
-        const uint4 o = chacha_quad(pk, (uint32_t)q, 0u, 16u + p, 0u);
-        row0[it] = q * 8 + 2 * (t & 3);
-        key[2 * it] = (uint64_t)o.x | ((uint64_t)o.y << 32);
-        key[2 * it + 1] = (uint64_t)o.z | ((uint64_t)o.w << 32);
-        if (row0[it] < n) atomicAdd(&lcur[bucket_of(key[2 * it], d1)], 1u);
-        if (row0[it] + 1 < n) atomicAdd(&lcur[bucket_of(key[2 * it + 1], d1)], 1u);
+        const uint32_t r0 = 2 * (tid + T * it);
+        const uint4 o = chacha_quad(pk, (uint32_t)((first + r0) >> 3), 0u, 16u + p, 0u);
+        row[2 * it] = (((uint64_t)o.x | ((uint64_t)o.y << 32)) & ~kRowMask) | (first + r0);
+        row[2 * it + 1] = (((uint64_t)o.z | ((uint64_t)o.w << 32)) & ~kRowMask) | (first + r0 + 1);
+        if (r0 < rows_here) atomicAdd(&lcur[bucket_of(row[2 * it], d1)], 1u);
+        if (r0 + 1 < rows_here) atomicAdd(&lcur[bucket_of(row[2 * it + 1], d1)], 1u);
     }
     __syncthreads();
-    {   // exclusive scan of the counts, two buckets per thread 
+    {   // exclusive scan of the counts, two buckets per thread
         const uint32_t a = 2 * tid < nb ? lcur[2 * tid] : 0u, b = 2 * tid + 1 < nb ? lcur[2 * tid + 1] : 0u;
         scan[tid] = a + b;
         __syncthreads();
@@ -553,32 +555,37 @@ __global__ __launch_bounds__(CHUNK / 8) void k_perm_place(uint64_t n, uint32_t d
             __syncthreads();
         }
         const uint32_t ex = scan[tid] - (a + b);
-        if (2 * tid < nb) loff[2 * tid] = lcur[2 * tid] = ex;
-        if (2 * tid + 1 < nb) loff[2 * tid + 1] = lcur[2 * tid + 1] = ex + a;
+        if (2 * tid < nb) lcur[2 * tid] = ex;
+        if (2 * tid + 1 < nb) lcur[2 * tid + 1] = ex + a;
     }
-    for (uint32_t i = tid; i < nb; i += T) gpos[i] = starts[i] + counts[(uint64_t)i * nblk + blockIdx.x];
+    __syncthreads();
+    for (uint32_t i = tid; i < nb; i += T) lpos[i] = starts[i] + counts[(uint64_t)i * nblk + blockIdx.x] - lcur[i];
     __syncthreads();
 #pragma unroll
-    for (uint32_t it = 0; it < 4; it++)
-#pragma unroll
-        for (uint32_t e = 0; e < 2; e++)
-            if (row0[it] + e < n) {
-                const uint32_t slot = atomicAdd(&lcur[bucket_of(key[2 * it + e], d1)], 1u);
-                lkeys[slot] = key[2 * it + e];
-                lrows[slot] = (uint32_t)(row0[it] + e);
-            }
+    for (uint32_t k = 0; k < 8; k++)
+        if (2 * (tid + T * (k >> 1)) + (k & 1) < rows_here) lrows[atomicAdd(&lcur[bucket_of(row[k], d1)], 1u)] = row[k];
     __syncthreads();
-    const uint64_t first = (uint64_t)blockIdx.x * CHUNK;
-    const uint32_t rows_here = (uint32_t)(n - first < CHUNK ? n - first : CHUNK);
     for (uint32_t i = tid; i < rows_here; i += T) {
-        const uint64_t k = lkeys[i];
-        const uint32_t bk = bucket_of(k, d1);
-        const uint32_t dst = gpos[bk] + (i - loff[bk]);
-        if (dst < n) {                            // always, with counts from k_perm_count
-            skeys[dst] = k;
-            srows[dst] = lrows[i];
-        }
+        const uint64_t v = lrows[i];
+        const uint32_t dst = lpos[bucket_of(v, d1)] + i;
+        if (dst < n) srows[dst] = v;              // always, with counts from k_perm_count
     }
+}
+
+// The whole key of each lane's row (all 64 lanes active): a quad makes its four
+// rows' blocks in turn, and each lane takes its own row's two words.
+__device__ __forceinline__ uint64_t row_key(ChachaKey pk, uint32_t p, uint32_t row) {
+    const int lane = (int)(threadIdx.x & 63u), quad = lane & ~3;
+    uint64_t key = 0;
+    for (int i = 0; i < 4; i++) {
+        const uint32_t r = (uint32_t)__shfl((int)row, quad + i);
+        const uint4 o = chacha_quad(pk, r >> 3, 0u, 16u + p, 0u);
+        const int src = quad + (int)((r & 7u) >> 1);
+        const uint32_t lo = (uint32_t)__shfl((int)(r & 1u ? o.z : o.x), src);
+        const uint32_t hi = (uint32_t)__shfl((int)(r & 1u ? o.w : o.y), src);
+        if (lane == quad + i) key = (uint64_t)lo | ((uint64_t)hi << 32);
+    }
+    return key;
 }
 
 // perm entry of the row at position pos (or its inverse).
@@ -596,12 +603,12 @@ __global__ __launch_bounds__(1024) void k_bucket_rank(uint64_t n, uint32_t hb, u
     const uint32_t q = blockIdx.y;
     const uint32_t inverse = S.inverse[q];
     const uint32_t* __restrict__ starts = S.starts[q];
-    const uint64_t* __restrict__ skeys = S.skeys[q];
-    const uint32_t* __restrict__ srows = S.srows[q];
+    const ChachaKey pk = S.pk[q];
+    const uint32_t p = S.p[q];
+    const uint64_t* __restrict__ srows = S.srows[q];
     uint32_t* __restrict__ perm = S.perm[q];
-    __shared__ uint32_t part[kBucketCap];     // 25 key bits after the run id << 7 | slot in the run
+    __shared__ uint32_t part[kBucketCap];     // 25 key bits after the run id (24 of them with 17 bits of run id) << 7 | slot in the run
     __shared__ uint32_t lrow[kBucketCap];     // row number
-    __shared__ uint16_t sidx[kBucketCap];     // index in the bucket's range
     __shared__ uint32_t rcount[64];
     __shared__ uint32_t rstart[65];
     constexpr uint32_t kPer = (kBucketCap + 1023) / 1024;
@@ -612,17 +619,25 @@ __global__ __launch_bounds__(1024) void k_bucket_rank(uint64_t n, uint32_t hb, u
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     if (size > kBucketCap || mode == 2) {
-        // every pair: position = rows of the bucket with a smaller (key, row)
-        for (uint32_t i = tid; i < size; i += blockDim.x) {
-            const uint64_t ki = skeys[s + i];
-            const uint32_t ri = srows[s + i];
+        // every pair: position = rows of the bucket with a smaller (key, row);
+        // whole keys where the leading 41 bits are equal (a row meets itself there)
+        for (uint32_t i0 = 0; i0 < size; i0 += blockDim.x) {
+            const bool has = i0 + tid < size;
+            const uint64_t vi = srows[s + (has ? i0 + tid : 0u)];
+            const uint32_t ri = (uint32_t)(vi & kRowMask);
             uint32_t rank = 0;
             for (uint32_t j = 0; j < size; j++) {
-                const uint64_t kj = skeys[s + j];
-                const uint32_t rj = srows[s + j];
-                rank += (uint32_t)(kj < ki) | ((uint32_t)(kj == ki) & (uint32_t)(rj < ri));
+                const uint64_t vj = srows[s + j];
+                bool less = vj < vi;
+                const bool tie = ((vj ^ vi) & ~kRowMask) == 0;
+                if (__ballot(tie) != 0) {
+                    const uint32_t rj = (uint32_t)(vj & kRowMask);
+                    const uint64_t ki = row_key(pk, p, ri), kj = row_key(pk, p, rj);
+                    if (tie) less = kj < ki || (kj == ki && rj < ri);
+                }
+                rank += (uint32_t)less;
             }
-            put_position(perm, inverse, n32, s + rank, ri);
+            if (has) put_position(perm, inverse, n32, s + rank, ri);
         }
         return;
     }
@@ -630,22 +645,17 @@ __global__ __launch_bounds__(1024) void k_bucket_rank(uint64_t n, uint32_t hb, u
     const uint32_t run_mask = nr - 1u;
     for (uint32_t i = tid; i < nr; i += blockDim.x) rcount[i] = 0;
     __syncthreads();
-    uint64_t key[kPer];
-    uint32_t slot[kPer], row[kPer];
+    uint64_t v[kPer];
+    uint32_t slot[kPer];
 #pragma unroll
     for (uint32_t k = 0; k < kPer; k++) {
         const uint32_t i = tid + 1024u * k;
-        key[k] = 0;
-        row[k] = 0;
-        if (i < size) {
-            key[k] = skeys[s + i];
-            row[k] = srows[s + i];
-        }
+        v[k] = i < size ? srows[s + i] : 0ull;
     }
 #pragma unroll
     for (uint32_t k = 0; k < kPer; k++) {
         slot[k] = 0;
-        if (tid + 1024u * k < size) slot[k] = atomicAdd(&rcount[(uint32_t)(key[k] >> (64 - hb)) & run_mask], 1u);
+        if (tid + 1024u * k < size) slot[k] = atomicAdd(&rcount[(uint32_t)(v[k] >> (64 - hb)) & run_mask], 1u);
     }
     __syncthreads();
     if (tid == 0) {
@@ -661,10 +671,9 @@ __global__ __launch_bounds__(1024) void k_bucket_rank(uint64_t n, uint32_t hb, u
     for (uint32_t k = 0; k < kPer; k++) {
         const uint32_t i = tid + 1024u * k;
         if (i < size) {
-            const uint32_t pos = rstart[(uint32_t)(key[k] >> (64 - hb)) & run_mask] + slot[k];
-            part[pos] = (((uint32_t)(key[k] >> (39 - hb)) & 0x1FFFFFFu) << 7) | (slot[k] & 127u);
-            lrow[pos] = row[k];
-            sidx[pos] = (uint16_t)i;
+            const uint32_t pos = rstart[(uint32_t)(v[k] >> (64 - hb)) & run_mask] + slot[k];
+            part[pos] = (((uint32_t)((v[k] & ~kRowMask) >> (39 - hb)) & 0x1FFFFFFu) << 7) | (slot[k] & 127u);
+            lrow[pos] = (uint32_t)(v[k] & kRowMask);
         }
     }
     __syncthreads();
@@ -694,18 +703,17 @@ __global__ __launch_bounds__(1024) void k_bucket_rank(uint64_t n, uint32_t hb, u
             }
         }
         if (!exact) continue;
-        // exact: rank = members with a smaller (key, row), keys from the
-        // bucket's range, 64 at a time broadcast with readlane
+        // exact: rank = members with a smaller (whole key, row), 64 at a time
+        // broadcast with readlane
         for (uint32_t c0 = 0; c0 < m; c0 += 64) {
             const uint32_t ei = c0 + lane;
             const bool has = ei < m;
-            const uint64_t ke = has ? skeys[s + sidx[rs + ei]] : 0ull;
             const uint32_t re = has ? lrow[rs + ei] : 0u;
+            const uint64_t ke = row_key(pk, p, re);
             uint32_t rank = 0;
             for (uint32_t j0 = 0; j0 < m; j0 += 64) {
-                const bool hj = j0 + lane < m;
-                const uint64_t kj = hj ? skeys[s + sidx[rs + j0 + lane]] : 0ull;
-                const uint32_t rj = hj ? lrow[rs + j0 + lane] : 0u;
+                const uint32_t rj = j0 + lane < m ? lrow[rs + j0 + lane] : 0u;
+                const uint64_t kj = row_key(pk, p, rj);
                 const uint32_t cnt = (uint32_t)__builtin_amdgcn_readfirstlane((int)(m - j0 < 64 ? m - j0 : 64));
                 for (uint32_t t = 0; t < cnt; t++) {
                     const uint64_t kt = lane_value(kj, t);
@@ -1316,8 +1324,8 @@ int bucket_perms(uint64_t nrows, const PermJob (&jobs)[3], uint32_t method, hipS
     const bool small = nrows <= kSmallChunkMost;
     const uint32_t chunk = small ? kSmallChunkRows : kChunkRows;
     const uint32_t nblk = (uint32_t)((nrows + chunk - 1) / chunk);
-    // scratch of each permutation: keys and rows placed by bucket in keys /
-    // idx, per-workgroup counts in keys_sorted, bucket totals and starts in
+    // scratch of each permutation: rows placed by bucket in keys,
+    // per-workgroup counts in keys_sorted, bucket totals and starts in
     // idx_sorted; they fit for every table the method takes
     if ((uint64_t)nb * nblk > 2 * nrows || 2ull * nb + 1 > nrows || nblk > 1024)
         return fail(FSS_EDEVICE, "rss_shuffle: bucket scratch does not fit");
@@ -1328,8 +1336,7 @@ int bucket_perms(uint64_t nrows, const PermJob (&jobs)[3], uint32_t method, hipS
         S.p[q] = jobs[q].p;
         S.inverse[q] = jobs[q].inverse ? 1u : 0u;
         S.perm[q] = jobs[q].perm;
-        S.skeys[q] = w.keys;
-        S.srows[q] = w.idx;
+        S.srows[q] = w.keys;
         S.counts[q] = (uint32_t*)w.keys_sorted;
         S.totals[q] = w.idx_sorted;
         S.starts[q] = w.idx_sorted + nb;
