@@ -373,7 +373,9 @@ __global__ __launch_bounds__(256) void k_rank_runs(uint64_t n, uint32_t hb, uint
 //   count: each workgroup makes the keys of 8192 (2048) rows and counts them per
 //          bucket in LDS: counts[bucket][workgroup];
 //   scan:  per bucket, the workgroups' exclusive offsets and the total; then
-//          the buckets' starts;
+//          the buckets' starts.  Up to 2^18 rows each placing workgroup sums the
+//          few counts itself: two launches of 3 us less for 2 us in placing, a
+//          fetch of 100,003 records 66.8 -> 63.8 us;
 //   place: the workgroups make their keys again, group them by bucket in
 //          LDS and store each row in its bucket's range, as one word of 64 bits:
 //          the key's leading 41 bits and the row number's 23 (the order inside a
@@ -391,7 +393,7 @@ __global__ __launch_bounds__(256) void k_rank_runs(uint64_t n, uint32_t hb, uint
 // the result is the stable argsort whatever order the placing left.
 // Rows per counting / placing workgroup (eight a thread).  Up to 2^18 rows small
 // chunks and buckets of about 2^10 to 2^11 rows spread the work over the chip
-// (100,003 rows: counting 7.3 -> 4.5 us, placing 13 -> 7.6, ranking 9.9 -> 7.3);
+// (100,003 rows: counting 7.3 -> 4.6 us, placing 13 -> 7.4, ranking 9.9 -> 7.6);
 // large tables need the long store runs of large chunks.
 constexpr uint32_t kChunkRows = 8192, kSmallChunkRows = 2048;
 constexpr uint64_t kSmallChunkMost = 1ull << 18;
@@ -401,6 +403,11 @@ constexpr uint32_t kBucketCap = 7168;        // rows of a bucket held in LDS
 constexpr uint32_t kRowBits = 23;
 constexpr uint64_t kBucketMaxRows = 1ull << kRowBits;
 constexpr uint64_t kRowMask = kBucketMaxRows - 1;
+
+// Small chunks: at most 128 buckets and 128 counting workgroups, so a placing
+// workgroup reads all counts ([workgroup][bucket]) itself.
+template <uint32_t CHUNK>
+constexpr bool kOwnSums = CHUNK == kSmallChunkRows;
 
 // The three permutations of a shuffle, made together: blockIdx.y picks one.
 struct BucketSet {
@@ -443,7 +450,8 @@ __global__ __launch_bounds__(CHUNK / 8) void k_perm_count(uint64_t n, uint32_t d
     __syncthreads();
     chunk_keys<CHUNK>(pk, p, n, [&](uint64_t, uint64_t key) { atomicAdd(&hist[bucket_of(key, d1)], 1u); });
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < nb; i += blockDim.x) counts[(uint64_t)i * nblk + blockIdx.x] = hist[i];
+    for (uint32_t i = threadIdx.x; i < nb; i += blockDim.x)
+        counts[kOwnSums<CHUNK> ? (blockIdx.x << d1) + i : (uint64_t)i * nblk + blockIdx.x] = hist[i];
 }
 
 // Exclusive scan of 256 values in LDS (blockDim.x = 256); returns this
@@ -520,14 +528,19 @@ __global__ __launch_bounds__(CHUNK / 8, 8) void k_perm_place(uint64_t n, uint32_
     const ChachaKey pk = S.pk[q];
     const uint32_t p = S.p[q];
     const uint32_t* __restrict__ counts = S.counts[q];
-    const uint32_t* __restrict__ starts = S.starts[q];
     uint64_t* __restrict__ srows = S.srows[q];
     __shared__ uint64_t lrows[CHUNK];
     __shared__ uint32_t lcur[BUCKETS];     // counts, then slot cursors
     __shared__ uint32_t lpos[BUCKETS];     // the bucket's first position for this workgroup, less its first slot
-    uint32_t* scan = (uint32_t*)lrows;     // T words, before the rows come
+    constexpr bool OWN = kOwnSums<CHUNK>;
+    __shared__ uint32_t total[OWN ? BUCKETS : 1];    // rows of each bucket, then its start
+    __shared__ uint32_t before[OWN ? BUCKETS : 1];   // its rows in the workgroups before this one
+    static_assert(!OWN || BUCKETS <= 128, "one wavefront scans the totals");
     const uint32_t nb = 1u << d1, tid = threadIdx.x;
-    for (uint32_t i = tid; i < nb; i += T) lcur[i] = 0;
+    for (uint32_t i = tid; i < nb; i += T) {
+        lcur[i] = 0;
+        if constexpr (OWN) total[i] = before[i] = 0;
+    }
     __syncthreads();
     uint64_t row[8];
     const uint64_t first = (uint64_t)blockIdx.x * CHUNK;
@@ -543,8 +556,41 @@ __global__ __launch_bounds__(CHUNK / 8, 8) void k_perm_place(uint64_t n, uint32_
         if (r0 < rows_here) atomicAdd(&lcur[bucket_of(row[2 * it], d1)], 1u);
         if (r0 + 1 < rows_here) atomicAdd(&lcur[bucket_of(row[2 * it + 1], d1)], 1u);
     }
+    if constexpr (OWN) {                          // T / nb threads a bucket
+        const uint32_t i = tid & (nb - 1u);
+        uint32_t all = 0, pre = 0;
+#pragma unroll 4
+        for (uint32_t w = tid >> d1; w < nblk; w += T >> d1) {
+            const uint32_t c = counts[(w << d1) + i];
+            all += c;
+            pre += w < blockIdx.x ? c : 0u;
+        }
+        atomicAdd(&total[i], all);
+        atomicAdd(&before[i], pre);
+    }
     __syncthreads();
-    {   // exclusive scan of the counts, two buckets per thread
+    // exclusive scans, two buckets per thread
+    if constexpr (OWN) {                          // wavefront 0: this workgroup's counts; 1: the totals
+        if (tid < 128) {
+            uint32_t* v = tid < 64 ? lcur : total;
+            const uint32_t l = tid & 63u;
+            const uint32_t a = 2 * l < nb ? v[2 * l] : 0u, b = 2 * l + 1 < nb ? v[2 * l + 1] : 0u;
+            uint32_t sum = a + b;
+            for (uint32_t d = 1; d < 64; d <<= 1) {
+                const uint32_t x = (uint32_t)__shfl_up((int)sum, d);
+                if (l >= d) sum += x;
+            }
+            const uint32_t ex = sum - (a + b);
+            if (2 * l < nb) v[2 * l] = ex;
+            if (2 * l + 1 < nb) v[2 * l + 1] = ex + a;
+            if (tid >= 64 && blockIdx.x == 0) {   // for the ranking
+                if (2 * l < nb) S.starts[q][2 * l] = ex;
+                if (2 * l + 1 < nb) S.starts[q][2 * l + 1] = ex + a;
+                if (l == 63) S.starts[q][nb] = sum;
+            }
+        }
+    } else {
+        uint32_t* scan = (uint32_t*)lrows;        // T words, before the rows come
         const uint32_t a = 2 * tid < nb ? lcur[2 * tid] : 0u, b = 2 * tid + 1 < nb ? lcur[2 * tid + 1] : 0u;
         scan[tid] = a + b;
         __syncthreads();
@@ -559,7 +605,12 @@ __global__ __launch_bounds__(CHUNK / 8, 8) void k_perm_place(uint64_t n, uint32_
         if (2 * tid + 1 < nb) lcur[2 * tid + 1] = ex + a;
     }
     __syncthreads();
-    for (uint32_t i = tid; i < nb; i += T) lpos[i] = starts[i] + counts[(uint64_t)i * nblk + blockIdx.x] - lcur[i];
+    for (uint32_t i = tid; i < nb; i += T) {
+        if constexpr (OWN)
+            lpos[i] = total[i] + before[i] - lcur[i];
+        else
+            lpos[i] = S.starts[q][i] + counts[(uint64_t)i * nblk + blockIdx.x] - lcur[i];
+    }
     __syncthreads();
 #pragma unroll
     for (uint32_t k = 0; k < 8; k++)
@@ -1317,8 +1368,8 @@ uint32_t perm_method(uint64_t nrows, uint32_t m) {
     return m;
 }
 
-// The bucket method for all three permutations at once, five launches on
-// stream s (blockIdx.y picks the permutation).
+// The bucket method for all three permutations at once, five launches (three
+// with small chunks) on stream s (blockIdx.y picks the permutation).
 int bucket_perms(uint64_t nrows, const PermJob (&jobs)[3], uint32_t method, hipStream_t s) {
     const uint32_t hb = run_bits(nrows), d1 = bucket_bits(nrows), nb = 1u << d1;
     const bool small = nrows <= kSmallChunkMost;
@@ -1344,10 +1395,12 @@ int bucket_perms(uint64_t nrows, const PermJob (&jobs)[3], uint32_t method, hipS
     auto count = small ? k_perm_count<kSmallChunkRows, kSmallBuckets> : k_perm_count<kChunkRows, kMaxBuckets>;
     hipLaunchKernelGGL(count, dim3(nblk, 3), dim3(chunk / 8), 0, s, nrows, d1, nblk, S);
     if (int rc = check_launch("k_perm_count")) return rc;
-    hipLaunchKernelGGL(k_bucket_offsets, dim3(nb, 3), dim3(256), 0, s, nblk, S);
-    if (int rc = check_launch("k_bucket_offsets")) return rc;
-    hipLaunchKernelGGL(k_bucket_starts, dim3(1, 3), dim3(256), 0, s, nb, S);
-    if (int rc = check_launch("k_bucket_starts")) return rc;
+    if (!small) {
+        hipLaunchKernelGGL(k_bucket_offsets, dim3(nb, 3), dim3(256), 0, s, nblk, S);
+        if (int rc = check_launch("k_bucket_offsets")) return rc;
+        hipLaunchKernelGGL(k_bucket_starts, dim3(1, 3), dim3(256), 0, s, nb, S);
+        if (int rc = check_launch("k_bucket_starts")) return rc;
+    }
     auto place = small ? k_perm_place<kSmallChunkRows, kSmallBuckets> : k_perm_place<kChunkRows, kMaxBuckets>;
     hipLaunchKernelGGL(place, dim3(nblk, 3), dim3(chunk / 8), 0, s, nrows, d1, nblk, S);
     if (int rc = check_launch("k_perm_place")) return rc;
