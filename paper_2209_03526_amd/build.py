@@ -11,7 +11,7 @@ SRCS = [os.path.join(HERE, "csrc", "fss_lib.hip"), os.path.join(HERE, "csrc", "s
         os.path.join(HERE, "csrc", "access.hip")]
 SRC = SRCS[0]
 HEADERS = [os.path.join(HERE, "csrc", "aes_gfx950.hpp"), os.path.join(HERE, "csrc", "chacha_gfx950.hpp"),
-           os.path.join(HERE, "csrc", "common.hpp"),
+           os.path.join(HERE, "csrc", "common.hpp"), os.path.join(HERE, "csrc", "shapes.hpp"),
            os.path.join(ROOT, "include", "oblivgm_fss.h")]
 LIB = os.path.join(HERE, "liboblivgm_fss.so")
 

@@ -31,6 +31,7 @@
 #include "../../include/oblivgm_fss.h"
 #include "chacha_gfx950.hpp"
 #include "common.hpp"
+#include "shapes.hpp"
 
 using namespace ogm;
 
@@ -1118,8 +1119,8 @@ __global__ __launch_bounds__(256) void k_compact(uint64_t nrows, uint32_t nwords
         if (f) list[at] = t;
         __syncthreads();
         for (uint32_t j = t; j < kept; j += 256) rows_out[base + j] = (uint32_t)c0 + list[j];
-        for (uint32_t k = t; k < kept * nq; k += 256) {
-            const uint32_t j = k / nq, w = rw & 3u ? k - j * nq : 4 * (k - j * nq);
+        record_items(kept, nq, t, 256, [&](uint32_t j, uint32_t piece) {
+            const uint32_t w = rw & 3u ? piece : 4 * piece;
             const uint64_t src = (c0 + list[j]) * nwords + first + w, dst = (uint64_t)(base + j) * rw + w;
             if (rw & 3u) {
                 o0[dst] = s0[src];
@@ -1134,7 +1135,7 @@ __global__ __launch_bounds__(256) void k_compact(uint64_t nrows, uint32_t nwords
                 __builtin_memcpy(o1 + dst, &b, 16);
                 __builtin_memcpy(o2 + dst, &c, 16);
             }
-        }
+        });
         base += kept;
         __syncthreads();                             // list and sums are free again
     }

@@ -1,0 +1,18 @@
+// The library's index rules (csrc/shapes.hpp) built by the host compiler, for test_shapes.py.
+#include "../paper_2209_03526_amd/csrc/shapes.hpp"
+
+extern "C" {
+
+// Items that thread t of T takes, at most `most` of them counted, and a sum over their numbers.
+uint64_t items_of(uint32_t kept, uint32_t pieces, uint32_t t, uint32_t T, uint64_t* sum, uint8_t* seen) {
+    uint64_t n = 0;
+    *sum = 0;
+    ogm::record_items(kept, pieces, t, T, [&](uint32_t j, uint32_t p) {
+        n++;
+        *sum += (uint64_t)j * pieces + p;
+        if (seen) seen[(uint64_t)j * pieces + p]++;
+    });
+    return n;
+}
+
+}

@@ -1,0 +1,44 @@
+"""The index rules that the kernels share with host code, run on the CPU: the
+same header built by the host compiler."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("shapes") / "libshapes.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", out, os.path.join(HERE, "shapes_host.cpp")],
+                   check=True)
+    lib = ctypes.CDLL(out)
+    u32, u64, P = ctypes.c_uint32, ctypes.c_uint64, ctypes.c_void_p
+    lib.items_of.restype = u64
+    lib.items_of.argtypes = [u32, u32, u32, u32, P, P]
+    return lib
+
+
+def _items(lib, kept, pieces, t, threads, seen=None):
+    total = ctypes.c_uint64()
+    n = lib.items_of(kept, pieces, t, threads, ctypes.byref(total), seen.ctypes.data if seen is not None else None)
+    return n, total.value
+
+
+@pytest.mark.parametrize("kept,pieces", [(0, 5), (1, 1), (3, 100), (256, 7), (255, 33), (17, (1 << 20) + 3)])
+def test_record_items_take_every_piece_once(lib, kept, pieces):
+    seen = np.zeros(max(1, kept * pieces), np.uint8)
+    n = sum(_items(lib, kept, pieces, t, 256, seen)[0] for t in range(256))
+    assert n == kept * pieces
+    assert (seen[:n] == 1).all()
+
+
+@pytest.mark.parametrize("kept,pieces", [(256, 1 << 24), (255, 16843009), (64, (1 << 26) + 1)])
+def test_record_items_of_very_wide_records(lib, kept, pieces):
+    """Items past 2^32: kept * pieces = 2^32, 2^32 - 1 and 2^32 + 64; each thread ends after its share."""
+    counts = [_items(lib, kept, pieces, t, 256)[0] for t in (0, 1, 255)]
+    for n in counts:
+        assert abs(n - kept * pieces / 256) <= pieces / (1 << 20) + 1
