@@ -29,4 +29,15 @@ OGM_HD void record_items(uint32_t kept, uint32_t pieces, uint32_t t, uint32_t T,
     }
 }
 
+// Where slice b of row l lies in the two tables that a shuffle's final round
+// gathers (word offsets of its X1 and V words, len of each): interleaved slice by
+// slice where `whole`, one after the other otherwise.  16 * b is a word of a
+// record and fits 32 bits; 32 * b does not from 2^31 words a record on, so the
+// doubling is in 64.
+struct XvOffsets {
+    uint64_t x1, v;
+    OGM_HD XvOffsets(bool whole, uint64_t l, uint32_t b, uint32_t len, uint64_t nrows, uint32_t nwords)
+        : x1((l * nwords + 16 * b) << (whole ? 1 : 0)), v(whole ? x1 + len : x1 + nrows * nwords) {}
+};
+
 }  // namespace ogm

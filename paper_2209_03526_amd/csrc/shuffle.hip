@@ -846,13 +846,6 @@ __device__ __forceinline__ void pin(uint4& v) {
 // -> 240-290 us); one after the other for ragged widths, whose slices straddle
 // lines either way (100,003 records of 21 words: 23.4 us, interleaved 25.8).
 template <bool WHOLE>
-struct XvAt {
-    uint64_t x1, v;      // word offsets of slice b of row l
-    __device__ __forceinline__ XvAt(uint64_t l, uint32_t b, uint32_t len, uint64_t nrows, uint32_t nwords)
-        : x1(WHOLE ? 2 * l * nwords + 32 * b : l * nwords + 16 * b), v(WHOLE ? x1 + len : x1 + nrows * nwords) {}
-};
-
-template <bool WHOLE>
 __device__ __forceinline__ void first_slice(uint64_t t, uint64_t nrows, uint32_t nwords, ChachaKey k12, ChachaKey k31,
                                             const uint32_t* __restrict__ inv12, const uint32_t* __restrict__ inv31,
                                             const uint32_t* __restrict__ g0, const uint32_t* __restrict__ g1,
@@ -877,7 +870,7 @@ __device__ __forceinline__ void first_slice(uint64_t t, uint64_t nrows, uint32_t
     const uint4 r2 = chacha_quad(k12, i, b, kR2, nwords), r1 = chacha_quad(k31, i, b, kR1, nwords);
     const uint4 m = xor4(t12, chacha_quad(k31, j, b, kT31, nwords));
     if (l >= nrows) return;
-    const XvAt<WHOLE> dst(l, b, len, nrows, nwords);
+    const XvOffsets dst(WHOLE, l, b, len, nrows, nwords);
     store_quarter<WHOLE>(r12, src, c, len, r2);
     store_quarter<WHOLE>(r31, src, c, len, r1);
     store_quarter<WHOLE>(xv, dst.x1, c, len, xor4(xor4(x, y), m));
@@ -926,7 +919,7 @@ __device__ __forceinline__ void final_slice(uint64_t t, uint64_t nrows, uint32_t
         if (open && b == 0 && c == 0) flags[i] = 0u;
         return;
     }
-    const XvAt<WHOLE> src(p, b, len, nrows, nwords);
+    const XvOffsets src(WHOLE, p, b, len, nrows, nwords);
     const uint64_t dst = (uint64_t)i * nwords + 16 * b;
     const uint4 x = load_quarter<WHOLE>(xv, src.x1, c, len), y = load_quarter<WHOLE>(xv, src.v, c, len);
     const uint4 m = chacha_quad(k23, p, b, kT23, nwords);

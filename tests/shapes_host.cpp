@@ -15,4 +15,10 @@ uint64_t items_of(uint32_t kept, uint32_t pieces, uint32_t t, uint32_t T, uint64
     return n;
 }
 
+void xv_offsets(int32_t whole, uint64_t l, uint32_t b, uint32_t len, uint64_t nrows, uint32_t nwords, uint64_t* to) {
+    const ogm::XvOffsets at(whole != 0, l, b, len, nrows, nwords);
+    to[0] = at.x1;
+    to[1] = at.v;
+}
+
 }

@@ -19,6 +19,8 @@ def lib(tmp_path_factory):
     u32, u64, P = ctypes.c_uint32, ctypes.c_uint64, ctypes.c_void_p
     lib.items_of.restype = u64
     lib.items_of.argtypes = [u32, u32, u32, u32, P, P]
+    lib.xv_offsets.argtypes = [ctypes.c_int32, u64, u32, u32, u64, u32, P]
+    lib.xv_offsets.restype = None
     return lib
 
 
@@ -42,3 +44,17 @@ def test_record_items_of_very_wide_records(lib, kept, pieces):
     counts = [_items(lib, kept, pieces, t, 256)[0] for t in (0, 1, 255)]
     for n in counts:
         assert abs(n - kept * pieces / 256) <= pieces / (1 << 20) + 1
+
+
+@pytest.mark.parametrize("rows,words,whole", [(1, 3, 0), (5, 16, 1), (5, 16, 0), (3, 20, 1), (2, 4096, 1), (2, (1 << 31) + 21, 0),
+                                              (3, (1 << 31) + 16, 1), (2, (1 << 32) - 16, 1), (2, (1 << 32) - 16, 0)])
+def test_gathered_tables_tile_their_words(lib, rows, words, whole):
+    """The X1 and V slices of neighbouring rows and slices follow one another without overlap, to the tables' end."""
+    nb = (words + 15) // 16
+    to = np.zeros(2, np.uint64)
+    for row in range(rows):
+        for b in sorted(b for b in {0, 1, nb // 2, nb - 2, nb - 1, (1 << 27) - 1, 1 << 27} if 0 <= b < nb):
+            length = min(16, words - 16 * b)
+            lib.xv_offsets(whole, row, b, length, rows, words, to.ctypes.data)
+            at = 2 * row * words + 32 * b if whole else row * words + 16 * b
+            assert to.tolist() == [at, at + length if whole else rows * words + at]
