@@ -600,17 +600,20 @@ int rss_sec_access(uint64_t ncand, uint32_t x_bits, const uint32_t* const d_idm[
                    const uint32_t* const d_attr[3], const uint64_t prf_keys[3], uint32_t counter,
                    const uint64_t seeds[3], uint32_t* const d_ids[3], uint32_t* const d_attrs[3],
                    uint32_t* d_rows_out, uint32_t* d_count, void* d_work, uint64_t work_bytes, void* stream);
-/* rss_sec_access_batch: `count` independent rss_sec_access calls over the
+/* rss_sec_access_batch: `count` rss_sec_access calls over the
  * same posting lists and attributes (Alg. 2 runs one per kept vertex),
- * enqueued on `stream`, one call of the library instead of count.  Call c takes d_idm[3c .. 3c+2] (host array of device
- * pointers), counters[c] and seeds[3c .. 3c+2] (host arrays), and writes
+ * enqueued on `stream`, one call of the library instead of count.  Call c takes
+ * d_idm[3c .. 3c+2] (host array of device pointers), counters[c] and
+ * seeds[3c .. 3c+2] (host arrays), and writes
  * d_ids[i] + c * lmax * ceil(x_bits/32), d_attrs[i] + c * lmax * attr_words,
  * d_rows_out + c * lmax and d_count + c; its results are those of the single
- * call with the same arguments.  A workspace of
+ * calls made in order c = 0 .. count-1 (so a call's matched ID may be one that
+ * an earlier call keeps).  A workspace of
  * rss_sec_access_workspace_bytes(lmax, x_bits, attr_words) serves every call,
- * one after another; with k times that, up to min(k, 64) calls run side by
- * side and read the posting lists once for every eight of them.  The calls'
- * outputs must not overlap the inputs.  count = 0 enqueues nothing.  EINVAL for a NULL
+ * one after another; with k times that, up to min(k, 64) calls, none of which
+ * reads an earlier one's output, run side by side and read the posting lists
+ * once for every eight of them.  The calls' outputs must not overlap the
+ * posting lists, their offsets or the attributes.  count = 0 enqueues nothing.  EINVAL for a NULL
  * array or pointer, and the errors of rss_sec_access (returned by the first
  * call, before anything is enqueued). */
 int rss_sec_access_batch(uint32_t count, uint64_t ncand, uint32_t x_bits, const uint32_t* const* d_idm,

@@ -612,8 +612,15 @@ int rss_sec_fetch_groups(uint32_t ngroups, const uint32_t* src, const uint32_t* 
     return FSS_OK;
 }
 
+// Whether `words` words from p on meet the `n` words from `from` on.
+static bool meets(const uint32_t* p, uint64_t words, const uint32_t* from, uint64_t n) {
+    return (uintptr_t)p < (uintptr_t)(from + n) && (uintptr_t)from < (uintptr_t)(p + words);
+}
+
 // The calls of a secAccess batch, as many side by side as the workspace holds
-// single calls (each step one launch for all of them), the rest after them.
+// single calls (each step one launch for all of them), the rest after them.  A
+// call that reads an output of one before it (a matched ID that is a kept one)
+// starts a new group: side by side the selections of all run first.
 static int sec_access_calls(uint32_t count, uint64_t ncand, uint32_t x_bits, const uint32_t* const* d_idm,
                             const uint32_t* d_off, uint32_t lmax, const uint32_t* const* d_post, uint32_t attr_words,
                             const uint32_t* const* d_attr, const uint64_t* prf_keys, const uint32_t* counters,
@@ -638,8 +645,19 @@ static int sec_access_calls(uint32_t count, uint64_t ncand, uint32_t x_bits, con
                                 : 1u;
     std::vector<uint32_t> row0(most + 1);
     for (uint32_t c = 0; c <= most; c++) row0[c] = c * lmax;
-    for (uint32_t c0 = 0; c0 < count; c0 += most) {
-        const uint32_t n = std::min(count - c0, most);
+    const uint64_t mw = (ncand + 31) / 32;             // words of a matched ID's share
+    for (uint32_t c0 = 0, n; c0 < count; c0 += n) {
+        auto reads_earlier = [&](uint32_t c) {          // an output of the calls c0 .. c - 1
+            const uint64_t k = c - c0;
+            for (int j = 0; j < 3; j++) {
+                const uint32_t* p = d_idm[3 * (uint64_t)c + j];
+                for (int i = 0; i < 3; i++)
+                    if (meets(p, mw, d_ids[i] + c0 * tw, k * tw) || meets(p, mw, d_attrs[i] + c0 * ta, k * ta)) return true;
+                if (meets(p, mw, d_rows_out + (uint64_t)c0 * lmax, k * lmax) || meets(p, mw, d_count + c0, k)) return true;
+            }
+            return false;
+        };
+        for (n = 1; n < most && c0 + n < count && !reads_earlier(c0 + n);) n++;
         Carve ws{(uint8_t*)d_work, work_bytes};
         uint32_t* zeroed = ws.take(3 * n * (tw + ta));
         uint32_t* add[3] = {zeroed, zeroed + n * tw, zeroed + 2 * n * tw};
