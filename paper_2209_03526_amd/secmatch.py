@@ -58,6 +58,12 @@ def words(bits: int) -> int:
     return (bits + 31) // 32
 
 
+def _plus(base: int, steps) -> list:
+    """base + steps (an array of whole numbers) modulo 2^64, as Python integers: seeds and counters are
+    C integers, of which the library takes the low bits, and base may be any of them."""
+    return (np.uint64(base % 2**64) + np.asarray(steps).astype(np.uint64)).tolist()
+
+
 def domain_bits(npos: int) -> int:
     """Input width of the token's keys for positions 0 .. npos - 1 (at least 8)."""
     return max(8, int(np.ceil(np.log2(max(npos, 2)))))
@@ -217,10 +223,10 @@ def sec_match(eg: EncodedGraph, query, tok_seed: int, prf_keys, counter0: int, s
             cnt = empty(nc)
             if nc:
                 idm = (np.array(base, np.int64)[None, :] + at[:, None]).ravel()
-                seeds = (seed0 + 3 * (step + k)[:, None] + np.arange(3)[None, :]).ravel()
+                seeds = _plus(seed0, (3 * (step + k)[:, None] + np.arange(3)[None, :]).ravel())
                 work = fss.rss_sec_access_batch(eg.n[tgt.vtype], eg.n[nt.vtype], idm.tolist(), eg.off[pair], lmax,
                                                 eg.post[pair], wv2, eg.shares[("attr", nt.vtype, nt.attr)], prf_keys,
-                                                (counter + 2 * k).tolist(), seeds.tolist(), ids3, vals3,
+                                                _plus(counter, 2 * k), seeds, ids3, vals3,
                                                 empty(nc * lmax), cnt)
                 del work
             targets[c] = _Target(ids3, vals3, (np.arange(nc) * lmax).astype(np.uint32), None,
