@@ -142,13 +142,13 @@ class _Target:
     one-hot records ids / vals (three device tensors each), n[g] of them, the
     neighbours of the kept vertex parent[g] = (group, kept row) of the parent
     target (None at target 0).  After secFetch: nkept[g] kept {id || d}
-    records from row row0[g] of kept."""
+    records from row row0[g] of kept (one tensor: share, row, word)."""
     ids: list
     vals: list
     base: np.ndarray
     n: np.ndarray
     parent: list
-    kept: list = None
+    kept: torch.Tensor = None
     row0: np.ndarray = None
     nkept: np.ndarray = None
 
@@ -190,7 +190,7 @@ def sec_match(eg: EncodedGraph, query, tok_seed: int, prf_keys, counter0: int, s
         st.row0 = np.zeros(st.n.size, np.int64)
         st.row0[live] = np.cumsum(n_live, dtype=np.int64) - n_live
         st.nkept = np.zeros(st.n.size, np.int64)
-        st.kept = [empty(total * rec) for _ in range(3)]
+        st.kept = torch.empty((3, max(1, total), rec), dtype=torch.int32, device=dev)
         if live.size:
             fetched = empty(live.size)
             evals = [ev[(p, r)] for terms in SERVER_TERMS for p, r, _ in terms]
@@ -247,10 +247,13 @@ def _results(targets, query, eg):
     out = []
     if not all(t.nkept.any() for t in targets):
         return out                           # some target keeps no vertex: no result, and nothing to copy
-    ids = []                                 # per target, the kept one-hot IDs of the three shares
-    for t, st in zip(query.targets, targets):
-        wi, wv = words(eg.n[t.vtype]), words(eg.domains[(t.vtype, t.attr)])
-        ids.append([k.cpu().numpy().view(np.uint32).reshape(-1, wi + wv)[:, :wi] for k in st.kept])
+    # a target keeps few of its candidates, and its records are as wide as it has vertices / 32: the kept
+    # rows' ID words are gathered on the device, group after group, and copied alone
+    first = [np.cumsum(st.nkept) - st.nkept for st in targets]       # each group's first kept row
+    rows = [np.repeat(st.row0 - f, st.nkept) + np.arange(int(st.nkept.sum())) for st, f in zip(targets, first)]
+    at = torch.from_numpy(np.concatenate(rows)).to(targets[0].kept.device).split([r.size for r in rows])
+    ids = [st.kept[:, :, :words(eg.n[t.vtype])].index_select(1, r).cpu().numpy().view(np.uint32)
+           for t, st, r in zip(query.targets, targets, at)]
     groups_of = []                           # per target, the groups that a parent's kept vertex made
     for st in targets:
         of = {}
@@ -260,7 +263,7 @@ def _results(targets, query, eg):
 
     def walk(i, chosen):
         if i == q:
-            out.append([[ids[t][j][targets[t].row0[gi] + r] for j in range(3)] for t, (gi, r) in enumerate(chosen)])
+            out.append([[ids[t][j][first[t][gi] + r] for j in range(3)] for t, (gi, r) in enumerate(chosen)])
             return
         for gi in groups_of[i].get(None if i == 0 else chosen[query.parent(i)], []):
             for r in range(int(targets[i].nkept[gi])):

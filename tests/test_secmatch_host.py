@@ -1,6 +1,9 @@
 """Host parts of secMatch that need no GPU."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
+import torch
 
 from paper_2209_03526_amd import secmatch
 
@@ -10,3 +13,31 @@ def test_seeds_of_any_64_bits(base):
     """Every 64-bit seed (and what wraps past it) gives the low 64 bits of base + step."""
     steps = np.array([0, 1, 2, 3, 3_000_000_001], np.int64)
     assert secmatch._plus(base, steps) == [(base + int(v)) % 2**64 for v in steps]
+
+
+def test_results_copy_the_kept_records_alone(monkeypatch):
+    """Two targets of 500 and 3 x 40 candidates, few of them kept: the results are the kept vertices' ID words,
+    group by group, and no more than those leave the device."""
+    rng = np.random.default_rng(1)
+    n, domain = {"U": 500, "P": 100}, {("U", "a"): 40, ("P", "b"): 70}
+    graph = SimpleNamespace(n=n, domains=domain)
+    query = SimpleNamespace(targets=[SimpleNamespace(vtype="U", attr="a"), SimpleNamespace(vtype="P", attr="b")],
+                            parent=lambda i: i - 1)
+    targets, plain = [], []
+    for t, name, sizes, nkept, parent in (("U", "a", [500], [2], [None]), ("P", "b", [40, 40, 40], [1, 0, 3], [(0, 0), (0, 1), (0, 1)])):
+        wi, wv = secmatch.words(n[t]), secmatch.words(domain[(t, name)])
+        kept = [rng.integers(-2**31, 2**31, (sum(sizes), wi + wv), dtype=np.int64).astype(np.int32) for _ in range(3)]
+        row0 = np.cumsum(sizes) - sizes
+        targets.append(secmatch._Target(None, None, None, np.array(sizes), parent, torch.from_numpy(np.stack(kept)),
+                                        row0, np.array(nkept)))
+        plain.append([[[k[row0[g] + r, :wi].view(np.uint32) for k in kept] for r in range(nkept[g])] for g in range(len(sizes))])
+    want = [[plain[0][0][0], plain[1][0][0]]] + [[plain[0][0][1], plain[1][2][r]] for r in range(3)]
+    moved, cpu = [], torch.Tensor.cpu
+    monkeypatch.setattr(torch.Tensor, "cpu", lambda self, *a, **k: moved.append(self.numel()) or cpu(self, *a, **k))
+    got = secmatch._results(targets, query, graph)
+    assert len(got) == len(want)
+    for g, w in zip(got, want):
+        for gr, wr in zip(g, w):
+            for j in range(3):
+                np.testing.assert_array_equal(gr[j], wr[j])
+    assert sum(moved) <= 3 * (2 * secmatch.words(500) + 4 * secmatch.words(100))
