@@ -64,6 +64,25 @@ def _plus(base: int, steps) -> list:
     return (np.uint64(base % 2**64) + np.asarray(steps).astype(np.uint64)).tolist()
 
 
+# Rows that one library call numbers: the rows of a record table with 32 bits, a
+# call's own rows with 31.
+ROW_SPAN, CALL_ROWS = 1 << 32, (1 << 31) - 1
+
+
+def _row_runs(base, n):
+    """Runs (lo, hi) of consecutive groups (rows base[g] .. base[g] + n[g] - 1, base increasing) that one
+    `rss_sec_fetch_groups` call takes: rows within ROW_SPAN of the run's first, at most CALL_ROWS in all."""
+    if base[-1] + n[-1] - base[0] <= ROW_SPAN and n.sum() <= CALL_ROWS:
+        return [(0, n.size)]
+    runs, lo, rows = [], 0, 0
+    for g in range(n.size):
+        if g > lo and (base[g] + n[g] - base[lo] > ROW_SPAN or rows + n[g] > CALL_ROWS):
+            runs.append((lo, g))
+            lo, rows = g, 0
+        rows += n[g]
+    return runs + [(lo, n.size)]
+
+
 def domain_bits(npos: int) -> int:
     """Input width of the token's keys for positions 0 .. npos - 1 (at least 8)."""
     return max(8, int(np.ceil(np.log2(max(npos, 2)))))
@@ -164,7 +183,7 @@ def sec_match(eg: EncodedGraph, query, tok_seed: int, prf_keys, counter0: int, s
     q = len(query.targets)
     children = [[c for c in range(1, q) if query.parent(c) == i] for i in range(q)]
     t0 = query.targets[0]
-    one = lambda v: np.array([v], np.uint32)  # noqa: E731
+    one = lambda v: np.array([v], np.int64)  # noqa: E731
     targets = [None] * q
     targets[0] = _Target(eg.shares[("id", t0.vtype)], eg.shares[("attr", t0.vtype, t0.attr)], one(0),
                          one(eg.n[t0.vtype]), [None])
@@ -185,19 +204,26 @@ def sec_match(eg: EncodedGraph, query, tok_seed: int, prf_keys, counter0: int, s
         # every group's secEval, re-share and secFetch, one library call (an
         # empty group takes no randomness)
         live = np.flatnonzero(st.n)
-        n_live = np.ascontiguousarray(st.n[live])
+        base, n_live = st.base[live], st.n[live]
         total = int(n_live.sum())
         st.row0 = np.zeros(st.n.size, np.int64)
-        st.row0[live] = np.cumsum(n_live, dtype=np.int64) - n_live
+        st.row0[live] = np.cumsum(n_live) - n_live
         st.nkept = np.zeros(st.n.size, np.int64)
         st.kept = torch.empty((3, max(1, total), rec), dtype=torch.int32, device=dev)
         if live.size:
             fetched = empty(live.size)
             evals = [ev[(p, r)] for terms in SERVER_TERMS for p, r, _ in terms]
-            seeds = range(seed0 + 3 * step, seed0 + 3 * (step + live.size))
-            work = fss.rss_sec_fetch_groups(np.ascontiguousarray(st.base[live]), n_live, npos, evals, wi, st.ids,
-                                            st.vals, prf_keys, counter, seeds, st.kept, empty(total), fetched)
-            del work                             # stream-ordered: reused only after the call's kernels
+            b0, r0, ids, vals, out, cnt = 0, 0, st.ids, st.vals, st.kept.unbind(), fetched
+            for lo, hi in _row_runs(base, n_live):
+                if lo or base[-1] >= ROW_SPAN:   # the run's first group is row 0 of its call
+                    b0, r0 = int(base[lo]), int(st.row0[live[lo]])
+                    ids, vals = [t[b0 * wi:] for t in st.ids], [t[b0 * wv:] for t in st.vals]
+                    out, cnt = [k[r0:] for k in st.kept], fetched[lo:]
+                seeds = range(seed0 + 3 * (step + lo), seed0 + 3 * (step + hi))
+                work = fss.rss_sec_fetch_groups((base[lo:hi] - b0).astype(np.uint32), n_live[lo:hi].astype(np.uint32),
+                                                npos, evals, wi, ids, vals, prf_keys, counter + lo, seeds, out,
+                                                empty(total - r0), cnt)
+                del work                         # stream-ordered: reused only after the call's kernels
             counter += live.size
             step += live.size
             # the opens reveal how many candidates of each group match
@@ -229,14 +255,14 @@ def sec_match(eg: EncodedGraph, query, tok_seed: int, prf_keys, counter0: int, s
                                                 _plus(counter, 2 * k), seeds, ids3, vals3,
                                                 empty(nc * lmax), cnt)
                 del work
-            targets[c] = _Target(ids3, vals3, (np.arange(nc) * lmax).astype(np.uint32), None,
+            targets[c] = _Target(ids3, vals3, np.arange(nc) * lmax, None,
                                  list(zip(group.tolist(), r.tolist())))
             opened.append((c, nc, cnt))
         calls = len(children[i]) * int(nk.sum())
         counter += 2 * calls
         step += calls
         for c, nc, cnt in opened:            # the first read waits for all of them
-            targets[c].n = cnt.cpu().numpy()[:nc].astype(np.uint32)
+            targets[c].n = cnt.cpu().numpy()[:nc].astype(np.int64)
     return _results(targets, query, eg)
 
 

@@ -27,3 +27,16 @@ def _equal(lib, q, seed, counter, seed0):  # noqa: F811
 @pytest.mark.parametrize("seed0", [2**62, 2**63 - 7, 2**63 + 5])
 def test_any_64_bit_shuffle_seed(lib, seed0):  # noqa: F811
     _equal(lib, QUERIES[0], 1, 7, seed0)
+
+
+@pytest.mark.parametrize("span,most", [(1, 1 << 20), (1 << 20, 1)])
+def test_groups_in_several_library_calls(lib, monkeypatch, span, most):  # noqa: F811
+    """Groups whose rows one call does not number (here a lowered limit) go in several calls with the same results."""
+    fss, secmatch = lib
+    monkeypatch.setattr(secmatch, "ROW_SPAN", span)
+    monkeypatch.setattr(secmatch, "CALL_ROWS", most)
+    calls = []
+    one = fss.rss_sec_fetch_groups
+    monkeypatch.setattr(fss, "rss_sec_fetch_groups", lambda src, *a, **k: calls.append(src.size) or one(src, *a, **k))
+    _equal(lib, QUERIES[0], 1, 7, 600)
+    assert len(calls) > len(QUERIES[0].targets)

@@ -43,3 +43,29 @@ def test_results_copy_the_kept_records_alone(monkeypatch, whole):
             for j in range(3):
                 np.testing.assert_array_equal(gr[j], wr[j])
     assert whole or sum(moved) <= 3 * (2 * secmatch.words(500) + 4 * secmatch.words(100))
+
+
+@pytest.mark.parametrize("span,most", [(1 << 32, (1 << 31) - 1), (100, 1000), (1 << 20, 33), (1, 1)])
+def test_row_runs(monkeypatch, span, most):
+    """Runs of groups that one library call numbers: every group once, in order, within the span and the rows a call
+    takes (unless it is alone); one run where all fit."""
+    monkeypatch.setattr(secmatch, "ROW_SPAN", span)
+    monkeypatch.setattr(secmatch, "CALL_ROWS", most)
+    rng = np.random.default_rng(5)
+    n = rng.integers(1, 24, 50)
+    base = np.arange(50) * 24
+    runs = secmatch._row_runs(base, n)
+    assert [g for lo, hi in runs for g in range(lo, hi)] == list(range(50))
+    for lo, hi in runs:
+        assert hi - lo == 1 or (base[hi - 1] + n[hi - 1] - base[lo] <= span and n[lo:hi].sum() <= most)
+        if hi < 50:
+            assert base[hi] + n[hi] - base[lo] > span or n[lo:hi + 1].sum() > most
+    assert span < 1 << 20 or most < 1000 or len(runs) == 1
+
+
+def test_row_numbers_past_32_bits():
+    """2^22 calls' lists of 1,024: the rows of the last groups lie past 2^32, in a second run."""
+    base = np.arange((1 << 22) + 3) * 1024
+    live = np.array([0, 1, (1 << 22) - 1, 1 << 22, (1 << 22) + 2])
+    runs = secmatch._row_runs(base[live], np.full(5, 7))
+    assert runs == [(0, 3), (3, 5)]
