@@ -639,6 +639,8 @@ static int sec_access_calls(uint32_t count, uint64_t ncand, uint32_t x_bits, con
         return fail(FSS_ENOMEM, "%s: workspace needs %llu bytes", who, (unsigned long long)single);
     hipStream_t s = (hipStream_t)stream;
     const uint64_t tw = (uint64_t)lmax * wx, ta = (uint64_t)lmax * wd;
+    if (std::max(tw, ta) > 1ull << 36)      // the re-shares' PRF block numbers are 32-bit: 16 words a block
+        return fail(FSS_EUNSUPPORTED, "%s: more than 2^36 words of fetched records", who);
     // side by side: tables that one workgroup shuffles
     const bool small = small_shuffle_fits(lmax, wx);
     const uint32_t most = small ? (uint32_t)std::min<uint64_t>(std::min<uint64_t>(count, kSideCalls), work_bytes / single)
