@@ -35,6 +35,7 @@
 #include "aes_gfx950.hpp"
 #include "chacha_gfx950.hpp"
 #include "common.hpp"
+#include "shapes.hpp"
 
 using namespace ogm;
 
@@ -2334,24 +2335,21 @@ bool eval_before(uint32_t kind_a, uint64_t n_a, uint32_t kind_b, uint64_t n_b) {
 // (the rule of launch_eval), else wave tiles.
 struct EvalTiles {
     bool quad;
-    uint64_t total = 0;
-    // first tile of a descriptor of n rows, appended after the ones before it
-    uint32_t add(uint32_t kind, uint64_t n) {
-        const uint64_t first = total;
-        total += quad ? eval_quad_tiles(kind, n) : eval_tiles(kind, n);
-        return (uint32_t)first;
-    }
+    LaunchTiles number{};
+    uint64_t tiles(uint32_t kind, uint64_t n) const { return quad ? eval_quad_tiles(kind, n) : eval_tiles(kind, n); }
+    // first tile of a descriptor of n rows, appended after the ones before it in its launch
+    uint32_t add(uint32_t kind, uint64_t n) { return number.add(tiles(kind, n)); }
 };
 
 bool eval_quad(uint64_t wave_tiles) {
     return wave_tiles <= kEvalQuadTiles && g_tuning.rows_per_thread == 1 && g_tuning.wg_per_cu == 2;
 }
 
-// The evaluation of descriptors already in device memory.
+// One launch of descriptors already in device memory.
 int launch_eval_list(const EvalDesc* dq, uint32_t n, const EvalTiles& T, hipStream_t s) {
-    const BatchShape b = batch_shape(T.total, g_tuning.rows_per_thread);
+    const BatchShape b = batch_shape(T.number.total, g_tuning.rows_per_thread);
     const dim3 block(b.t.block);
-    const uint32_t nt = (uint32_t)T.total;
+    const uint32_t nt = (uint32_t)T.number.total;
     return launch_tiles(b.t, b.per, "k_eval_list", [&](uint32_t first, dim3 grid) {
         if (T.quad)
             hipLaunchKernelGGL((k_eval_list<true, false>), grid, block, b.lds, s, dq, n, nt, first, 1u);
@@ -2360,6 +2358,23 @@ int launch_eval_list(const EvalDesc* dq, uint32_t n, const EvalTiles& T, hipStre
         else
             hipLaunchKernelGGL((k_eval_list<false, true>), grid, block, b.lds, s, dq, n, nt, first, b.per);
     });
+}
+
+// The evaluation of n descriptors already in device memory, their tiles numbered
+// by EvalTiles::add in this order, launch after launch; kind(i) and rows(i) of the i-th.
+template <class Kind, class Rows>
+int launch_eval_lists(const EvalDesc* dq, uint32_t n, bool quad, Kind kind, Rows rows, hipStream_t s) {
+    EvalTiles T{quad};
+    uint32_t first = 0;
+    for (uint32_t i = 0; i <= n; i++) {
+        if (i == n || !T.number.fits(T.tiles(kind(i), rows(i)))) {
+            const int rc = launch_eval_list(dq + first, i - first, T, s);
+            if (rc) return rc;
+            first = i;
+        }
+        if (i < n) T.add(kind(i), rows(i));
+    }
+    return FSS_OK;
 }
 
 // Heaviest descriptors first, tile offsets, one upload, one launch.
@@ -2374,7 +2389,6 @@ int launch_eval_queue(std::vector<EvalDesc>& descs, void* d_ws, uint64_t ws_byte
     if (q.empty()) return FSS_OK;
     uint64_t tiles = 0;
     for (auto& e : q) tiles += eval_tiles(e.kind, e.n);
-    if (tiles > 0xFFFFFFF0ull) return fail(FSS_EUNSUPPORTED, "batch: too many tiles");
     EvalTiles T{eval_quad(tiles)};
     for (auto& e : q) e.tile_start = T.add(e.kind, e.n);
     const uint64_t need = kQueueHeader + q.size() * sizeof(EvalDesc);
@@ -2383,7 +2397,8 @@ int launch_eval_queue(std::vector<EvalDesc>& descs, void* d_ws, uint64_t ws_byte
     EvalDesc* dq = (EvalDesc*)((uint8_t*)d_ws + kQueueHeader);
     const int rc = upload(q.data(), q.size() * sizeof(EvalDesc), dq, s);
     if (rc) return rc;
-    return launch_eval_list(dq, (uint32_t)q.size(), T, s);
+    return launch_eval_lists(dq, (uint32_t)q.size(), T.quad, [&](uint32_t i) { return q[i].kind; },
+                             [&](uint32_t i) { return q[i].n; }, s);
 }
 
 // Device image of a batch's tail: the plans' key schedules, the fold inputs,
@@ -2415,7 +2430,7 @@ int launch_tail_queue(const match_plan* plans, uint32_t count, const TailOps& T,
         if (l.empty()) continue;
         std::copy(l.begin(), l.end(), ops + k);
         const TailShape S = tail_shape(ops + k, l.size());
-        if (S.tiles > 0xFFFFFFF0ull) return fail(FSS_EUNSUPPORTED, "match_query_batch: too many tiles");
+        if (S.tiles > kLaunchTiles) return fail(FSS_EUNSUPPORTED, "match_query_batch: too many tiles");
         if (S.tiles) launches.push_back(Launch{k, (uint32_t)l.size(), S});
         k += l.size();
     }
@@ -2797,7 +2812,7 @@ int fss_keygen_batch(const fss_keygen_req* reqs, uint32_t count, void* d_queue, 
     uint64_t tiles[2] = {0, 0};
     bool quad[2];
     for (const QKeygen& e : q) tiles[e.a.kind == FSS_RANGE ? 0 : 1] += keygen_tiles(e.a.kind, e.a.n);
-    if (tiles[0] > 0xFFFFFFF0ull || tiles[1] > 0xFFFFFFF0ull)
+    if (tiles[0] > kLaunchTiles || tiles[1] > kLaunchTiles)
         return fail(FSS_EUNSUPPORTED, "fss_keygen_batch: too many tiles");
     for (int k = 0; k < 2; k++) {       // quad tiles when a launch is small (the rule of fss_keygen)
         quad[k] = tiles[k] <= kKeygenQuadTiles && per == 1 && g_tuning.wg_per_cu == 2;
@@ -2889,7 +2904,6 @@ int fss_eval_batch_noalloc(const fss_eval_req* reqs, uint32_t count, void* strea
     const uint16_t* order = idx[cur];
     uint64_t tiles = 0;
     for (uint32_t j = 0; j < m; j++) tiles += eval_tiles((uint32_t)reqs[order[j]].keys->kind, reqs[order[j]].keys->n);
-    if (tiles > 0xFFFFFFF0ull) return fail(FSS_EUNSUPPORTED, "%s: too many tiles", who);
     EvalTiles T{eval_quad(tiles)};
     void* d_scratch = nullptr;
     int rc = scratch_ptr(&d_scratch, who);
@@ -2912,7 +2926,8 @@ int fss_eval_batch_noalloc(const fss_eval_req* reqs, uint32_t count, void* strea
         rc = check_launch("k_put_words");
         if (rc) return rc;
     }
-    return launch_eval_list(dq, m, T, s);
+    return launch_eval_lists(dq, m, T.quad, [&](uint32_t i) { return (uint32_t)reqs[order[i]].keys->kind; },
+                             [&](uint32_t i) { return reqs[order[i]].keys->n; }, s);
 }
 
 int match_query_batch(const match_plan* plans, uint32_t count, int32_t party_mask, void* d_queue,

@@ -40,4 +40,21 @@ struct XvOffsets {
         : x1((l * nwords + 16 * b) << (whole ? 1 : 0)), v(whole ? x1 + len : x1 + nrows * nwords) {}
 };
 
+// Numbers the tiles of a batch's descriptors.  A launch numbers its tiles with 32
+// bits, so a batch of more (2^32 tiles are 2^37 rows of ranges) takes several
+// launches: a descriptor whose tiles no longer fit starts the next one.
+constexpr uint64_t kLaunchTiles = 0xFFFFFFF0ull;
+
+struct LaunchTiles {
+    uint64_t total = 0;      // of the launch so far
+    OGM_HD bool fits(uint64_t tiles) const { return total + tiles <= kLaunchTiles; }
+    // first tile of the next descriptor in its launch
+    OGM_HD uint32_t add(uint64_t tiles) {
+        if (!fits(tiles)) total = 0;
+        const uint32_t first = (uint32_t)total;
+        total += tiles;
+        return first;
+    }
+};
+
 }  // namespace ogm

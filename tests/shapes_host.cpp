@@ -21,4 +21,13 @@ void xv_offsets(int32_t whole, uint64_t l, uint32_t b, uint32_t len, uint64_t nr
     to[1] = at.v;
 }
 
+// First tiles of n descriptors, and whether each starts a launch.
+void number_tiles(uint32_t n, const uint64_t* tiles, uint32_t* first, uint8_t* starts) {
+    ogm::LaunchTiles L;
+    for (uint32_t i = 0; i < n; i++) {
+        starts[i] = i == 0 || !L.fits(tiles[i]);
+        first[i] = L.add(tiles[i]);
+    }
+}
+
 }

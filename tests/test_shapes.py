@@ -21,6 +21,8 @@ def lib(tmp_path_factory):
     lib.items_of.argtypes = [u32, u32, u32, u32, P, P]
     lib.xv_offsets.argtypes = [ctypes.c_int32, u64, u32, u32, u64, u32, P]
     lib.xv_offsets.restype = None
+    lib.number_tiles.argtypes = [u32, P, P, P]
+    lib.number_tiles.restype = None
     return lib
 
 
@@ -58,3 +60,18 @@ def test_gathered_tables_tile_their_words(lib, rows, words, whole):
             lib.xv_offsets(whole, row, b, length, rows, words, to.ctypes.data)
             at = 2 * row * words + 32 * b if whole else row * words + 16 * b
             assert to.tolist() == [at, at + length if whole else rows * words + at]
+
+
+@pytest.mark.parametrize("tiles", [[5, 7, 1], [1 << 27] * 70, [0xFFFFFFF0, 1, 0xFFFFFFEF, 1, 1], [3] + [1 << 27] * 33])
+def test_tiles_of_a_batch_are_numbered_launch_by_launch(lib, tiles):
+    t = np.array(tiles, np.uint64)
+    first, starts = np.zeros(t.size, np.uint32), np.zeros(t.size, np.uint8)
+    lib.number_tiles(t.size, t.ctypes.data, first.ctypes.data, starts.ctypes.data)
+    total = 0
+    for i, k in enumerate(tiles):
+        if starts[i]:
+            assert i == 0 or total + k > 0xFFFFFFF0          # no launch ends early
+            total = 0
+        assert first[i] == total
+        total += k
+        assert total <= 0xFFFFFFF0
