@@ -13,7 +13,7 @@
 namespace ogm {
 
 // f(record, piece) for the items of `kept` records of `pieces` pieces each
-// that thread t of T takes, kept and T at most 256.  The pieces go in tiles of
+// that thread t of T takes, kept at most 256 and T at most 2^31.  The pieces go in tiles of
 // 2^20, so that an item's number in a tile fits 32 bits however wide the records
 // are (one number over all of them passes 2^32 at 256 records of 2^24 pieces).
 constexpr uint32_t kPieceTile = 1u << 20;
@@ -27,6 +27,24 @@ OGM_HD void record_items(uint32_t kept, uint32_t pieces, uint32_t t, uint32_t T,
             f(j, first + (k - j * n));
         }
     }
+}
+
+// Workgroups that share the copying of a compaction's blocks of rows (`blocks` of
+// them, at most 256 rows at a time), records of rw words: as many as fill the
+// chip while each thread has kCopyItems pieces (16 bytes, or a word of ragged
+// records) to move.  Records of a one-hot ID are as wide as the table has rows
+// / 32, so a table of few blocks may hold megabytes: with one workgroup a block,
+// secFetch of 2,000 records of 500 words, all kept, took 254 us, of 70 of 2,000
+// words 245; 46 and 23 now (1,024 or 2,048 workgroups, 4 or 8 pieces: the same;
+// 100,003 of 21 words 64 us either way).
+constexpr uint32_t kCopyGroups = 1024, kCopyItems = 4;
+
+OGM_HD uint32_t compact_copiers(uint32_t blocks, uint64_t nrows, uint32_t rw) {
+    const uint64_t pieces = rw & 3u ? rw : rw >> 2, rows = nrows < 256 ? nrows : 256;
+    const uint64_t most = (rows * pieces + 256 * kCopyItems - 1) / (256 * kCopyItems);
+    const uint64_t want = (kCopyGroups + blocks - 1) / blocks;
+    const uint64_t y = want < most ? want : most;
+    return y ? (uint32_t)y : 1u;
 }
 
 // Where slice b of row l lies in the two tables that a shuffle's final round

@@ -1051,7 +1051,8 @@ __global__ void k_open_parity(uint64_t nrows, uint32_t nwords, uint32_t vec, con
 // Compaction of the kept records (words first .. W-1 of the three share tables)
 // in two launches: the number of kept records of every block of rows, then
 // each block, with the sum of the blocks before it, lists its kept rows in LDS
-// and copies their records, 16 bytes or a word a thread.  (A scan of all flags by a sort
+// and copies their records, 16 bytes or a word a thread; where few blocks hold
+// wide records, several workgroups (blockIdx.y) share a block's pieces.  (A scan of all flags by a sort
 // library, a copy that looked at every word of every record and a launch for
 // the count took four launches: 20 of 85 us at 100,003 records of 21 words.)
 constexpr uint32_t kCompactStep = 256;       // rows listed at a time, one a thread
@@ -1111,8 +1112,8 @@ __global__ __launch_bounds__(256) void k_compact(uint64_t nrows, uint32_t nwords
         const uint32_t kept = sh[0] + sh[1] + sh[2] + sh[3];
         if (f) list[at] = t;
         __syncthreads();
-        for (uint32_t j = t; j < kept; j += 256) rows_out[base + j] = (uint32_t)c0 + list[j];
-        record_items(kept, nq, t, 256, [&](uint32_t j, uint32_t piece) {
+        for (uint32_t j = t; blockIdx.y == 0 && j < kept; j += 256) rows_out[base + j] = (uint32_t)c0 + list[j];
+        record_items(kept, nq, blockIdx.y * 256 + t, gridDim.y * 256, [&](uint32_t j, uint32_t piece) {
             const uint32_t w = rw & 3u ? piece : 4 * piece;
             const uint64_t src = (c0 + list[j]) * nwords + first + w, dst = (uint64_t)(base + j) * rw + w;
             if (rw & 3u) {
@@ -1132,7 +1133,7 @@ __global__ __launch_bounds__(256) void k_compact(uint64_t nrows, uint32_t nwords
         base += kept;
         __syncthreads();                             // list and sums are free again
     }
-    if (blockIdx.x == gridDim.x - 1 && t == 0) *count = base;
+    if (blockIdx.x == gridDim.x - 1 && blockIdx.y == 0 && t == 0) *count = base;
 }
 
 // Tables of at most kAloneRows records too wide for one workgroup's shuffle, and
@@ -1884,7 +1885,8 @@ static int shuffle_open_compact(uint64_t ncand, uint32_t nwords, const uint32_t*
     hipLaunchKernelGGL(k_flag_sums, dim3(blocks), dim3(256), 0, s, ncand, flags, sums);
     rc = check_launch("k_flag_sums");
     if (rc) return rc;
-    hipLaunchKernelGGL(k_compact, dim3(blocks), dim3(256), 0, s, ncand, nwords, parity ? 0u : 1u, flags, sums, sh[0],
+    const uint32_t rw = parity ? nwords : nwords - 1;
+    hipLaunchKernelGGL(k_compact, dim3(blocks, compact_copiers(blocks, ncand, rw)), dim3(256), 0, s, ncand, nwords, parity ? 0u : 1u, flags, sums, sh[0],
                        sh[1], sh[2], d_out[0], d_out[1], d_out[2], d_rows_out, d_count);
     return check_launch("k_compact");
 }

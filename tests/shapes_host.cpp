@@ -30,4 +30,6 @@ void number_tiles(uint32_t n, const uint64_t* tiles, uint32_t* first, uint8_t* s
     }
 }
 
+uint32_t copiers(uint32_t blocks, uint64_t nrows, uint32_t rw) { return ogm::compact_copiers(blocks, nrows, rw); }
+
 }

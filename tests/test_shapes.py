@@ -23,6 +23,8 @@ def lib(tmp_path_factory):
     lib.xv_offsets.restype = None
     lib.number_tiles.argtypes = [u32, P, P, P]
     lib.number_tiles.restype = None
+    lib.copiers.argtypes = [u32, u64, u32]
+    lib.copiers.restype = u32
     return lib
 
 
@@ -75,3 +77,25 @@ def test_tiles_of_a_batch_are_numbered_launch_by_launch(lib, tiles):
         assert first[i] == total
         total += k
         assert total <= 0xFFFFFFF0
+
+
+@pytest.mark.parametrize("rows,words", [(1, 1), (70, 1999), (300, 500), (1100, 999), (2000, 500), (8000, 256), (8000, 4),
+                                        (100003, 20), (1 << 22, 16), (65, 1 << 24), (1 << 20, 1 << 16)])
+def test_wide_records_are_copied_by_many_workgroups(lib, rows, words):
+    """A compaction whose records hold 16 KB and more for every CU has a workgroup for each of the 256; no table takes
+    more than a grid allows, and none a workgroup without a row's worth of pieces."""
+    blocks = max(1, min(2048, rows // 256))
+    y = lib.copiers(blocks, rows, words)
+    assert 1 <= y <= 65535
+    if rows * words * 4 >= 256 * 16384:
+        assert blocks * y >= 256
+    pieces = min(rows, 256) * (words if words % 4 else words // 4)
+    assert y == 1 or y * 256 <= pieces
+
+
+@pytest.mark.parametrize("kept,pieces,groups", [(256, 33, 3), (7, 500, 9), (1, 5, 2)])
+def test_copiers_share_the_pieces(lib, kept, pieces, groups):
+    seen = np.zeros(kept * pieces, np.uint8)
+    for t in range(256 * groups):
+        _items(lib, kept, pieces, t, 256 * groups, seen)
+    assert (seen == 1).all()
