@@ -26,6 +26,7 @@
 #include "../../include/oblivgm_fss.h"
 #include "chacha_gfx950.hpp"
 #include "common.hpp"
+#include "shapes.hpp"
 
 using namespace ogm;
 
@@ -146,18 +147,15 @@ struct Out3 {
 // operations a word.  The threads' sums meet in LDS by XOR atomics, then go to
 // the zeroed output by 8-byte XOR atomics, 3 M wx / 2 a block.  Those bound a
 // grid of many blocks (86, 171 and 341 blocks a slot, 4-byte atomics: 109, 182
-// and 323 us), so the
-// sparse slots take fewer: N posting records in all leave at most N / (l + 1)
-// lists that reach slot l, and slot l gets 1 / (l + 1) of slot 0's blocks.
+// and 323 us), so each slot takes only as many as its lists want (sel_chunks):
+// blocks beyond leave at once, so what they evaluate of the rule is kept short
+// (in 64-bit integers from two loads it cost 8 of 166 us).  With 1 / (l + 1) of
+// slot 0's blocks in slot l, whatever the lists, a secAccess over 3,000 lists of 24
+// records of 94 words took 83 us and eight took 161, now 58 and 80.
 constexpr int kSelThreads = 512;
 constexpr uint32_t kSelCand = 1024;       // candidates listed at a time
+static_assert(kSelMost == 2 * kSelCand, "a block lists its candidates in two steps at most");
 constexpr uint32_t kSelTile = 256;        // record words per pass
-
-// Blocks of slot l, of which slot 0 has `most`; a block takes at most 2 kSelCand candidates.
-__host__ __device__ inline uint64_t sel_chunks(uint64_t ncand, uint64_t most, uint32_t l) {
-    const uint64_t least = (ncand + 2 * kSelCand - 1) / (2 * kSelCand), c = (most + l) / (l + 1);
-    return c > least ? c : least;
-}
 
 struct IdmSet {
     const uint32_t* p[kSideCalls][3];
@@ -197,19 +195,19 @@ __device__ __forceinline__ void sel_add(uint32_t (&acc)[M][3][V], const uint32_t
 
 template <int M, int V>
 __global__ __launch_bounds__(kSelThreads) void k_csr_select(uint64_t ncand, uint32_t wx, uint32_t ncalls, uint64_t tw,
-                                                            IdmSet idm, const uint32_t* __restrict__ off, Shares3 post,
-                                                            Out3 out) {
+                                                            SelRule rule, IdmSet idm, const uint32_t* __restrict__ off,
+                                                            Shares3 post, Out3 out) {
     __shared__ uint32_t rec[kSelCand];
     __shared__ uint32_t msk[kSelCand];
     __shared__ uint32_t nsel;
     __shared__ uint32_t sum[M * 3][kSelTile];
     const uint32_t l = blockIdx.y, call0 = blockIdx.z * M;
     const uint32_t nm = min(ncalls - call0, (uint32_t)M);
-    const uint64_t chunks = sel_chunks(ncand, gridDim.x, l);
+    const uint32_t t = threadIdx.x;
+    const uint64_t chunks = sel_chunks(rule, gridDim.x, l, off[ncand]);
     if (blockIdx.x >= chunks) return;
     const uint64_t per = (ncand + chunks - 1) / chunks;
     const uint64_t c1 = min((blockIdx.x + 1) * per, ncand);
-    const uint32_t t = threadIdx.x;
     for (uint64_t c0 = blockIdx.x * per; c0 < c1; c0 += kSelCand) {
         if (t == 0) nsel = 0;
         __syncthreads();
@@ -680,13 +678,15 @@ static int sec_access_calls(uint32_t count, uint64_t ncand, uint32_t x_bits, con
             for (uint32_t c = 0; c < n; c++)
                 for (int i = 0; i < 3; i++) idm.p[c][i] = d_idm[3 * (uint64_t)(c0 + c) + i];
             // blocks of slot 0, the most of any slot: enough to fill the chip over lmax slots
-            const uint64_t chunks = sel_chunks(ncand, std::min<uint64_t>((ncand + 63) / 64, 4096 / lmax + 1), 0);
+            const uint64_t chunks = std::max((ncand + kSelMost - 1) / kSelMost,
+                                             std::min<uint64_t>((ncand + 63) / 64, 4096 / lmax + 1));
             const uint32_t m = n > 4 ? 8 : n > 1 ? 4 : 1;      // calls per pass over the lists
             const dim3 grid((unsigned)chunks, lmax, (n + m - 1) / m);
             const Shares3 post{{d_post[0], d_post[1], d_post[2]}};
             const Out3 o{{add[0], add[1], add[2]}};
             auto k = m == 8 ? k_csr_select<8, 2> : m == 4 ? k_csr_select<4, 4> : k_csr_select<1, 4>;
-            hipLaunchKernelGGL(k, grid, dim3(kSelThreads), 0, s, ncand, wx, n, tw, idm, d_off, post, o);
+            hipLaunchKernelGGL(k, grid, dim3(kSelThreads), 0, s, ncand, wx, n, tw,
+                               sel_rule(ncand, lmax, m, m == 8 ? 2 : 4, wx), idm, d_off, post, o);
         }
         int rc = check_launch("k_csr_select");
         if (rc) return rc;

@@ -2,6 +2,7 @@
 // arithmetic that a host compiler builds too.
 #pragma once
 
+#include <math.h>
 #include <stdint.h>
 
 #ifdef __HIPCC__
@@ -57,6 +58,44 @@ struct XvOffsets {
     OGM_HD XvOffsets(bool whole, uint64_t l, uint32_t b, uint32_t len, uint64_t nrows, uint32_t nwords)
         : x1((l * nwords + 16 * b) << (whole ? 1 : 0)), v(whole ? x1 + len : x1 + nrows * nwords) {}
 };
+
+// How a secAccess selection over ncand posting lists splits the lists among the
+// workgroups of each slot l < lmax, given nrec, the lists' records in all, which
+// only the device has.
+//
+// How many lists reach slot l is taken to be ncand (l + 1)^-b, with the b that
+// gives nrec in all: b = 0 for lists of one length; 1 where nrec is ncand times
+// the sum h of 1 / (l + 1); between and beyond, on the line through both in ln nrec.
+//
+// A workgroup adds its sums to the output by 3 M wx / 2 atomics (M calls, records
+// of wx words), after adding its threads' partial sums (V words each) in LDS, where
+// 64 V / wx lanes meet in a word.  The two cost as much as streaming about 8 M and
+// 1000 M V^2 / wx^2 records, so a workgroup is given several times that, or what
+// fills the chip where the records are few; at most kSelMost candidates.
+constexpr uint32_t kSelMost = 2048, kSelFill = 512;
+
+struct SelRule {
+    float ncand, lmax;      // base-2 logarithms
+    float slope;            // b / log2(lmax / mean length)
+    float records;          // a workgroup's records, at most
+    uint32_t least;         // workgroups a slot, at least
+};
+
+inline SelRule sel_rule(uint64_t ncand, uint32_t lmax, uint32_t M, uint32_t V, uint32_t wx) {
+    const double n = (double)ncand, L = (double)lmax, h = log(L) + 0.5772 + 0.5 / L;
+    return SelRule{(float)log2(n), (float)log2(L), lmax > 1 ? (float)(1.0 / log2(L / h)) : 0.0f,
+                   (float)(48.0 * M + 4000.0 * M * V * V / ((double)wx * wx)),
+                   (uint32_t)((ncand + kSelMost - 1) / kSelMost)};
+}
+
+OGM_HD uint32_t sel_chunks(const SelRule& r, uint32_t most, uint32_t l, uint32_t nrec) {
+    const float n = (float)(nrec ? nrec : 1u), fill = n * (1.0f / kSelFill) + 1.0f;
+    const float shorter = r.lmax + r.ncand - log2f(n);                      // log2(lmax / mean length)
+    const float lists = exp2f(r.ncand - (shorter > 0.0f ? shorter : 0.0f) * r.slope * log2f((float)(l + 1)));
+    const float want = lists / (fill < r.records ? fill : r.records) + 1.0f;
+    const uint32_t c = want < (float)most ? (uint32_t)want : most;
+    return c > r.least ? c : r.least;
+}
 
 // Numbers the tiles of a batch's descriptors.  A launch numbers its tiles with 32
 // bits, so a batch of more (2^32 tiles are 2^37 rows of ranges) takes several

@@ -32,4 +32,8 @@ void number_tiles(uint32_t n, const uint64_t* tiles, uint32_t* first, uint8_t* s
 
 uint32_t copiers(uint32_t blocks, uint64_t nrows, uint32_t rw) { return ogm::compact_copiers(blocks, nrows, rw); }
 
+uint32_t slot_groups(uint64_t ncand, uint32_t lmax, uint32_t M, uint32_t V, uint32_t wx, uint32_t most, uint32_t l, uint32_t nrec) {
+    return ogm::sel_chunks(ogm::sel_rule(ncand, lmax, M, V, wx), most, l, nrec);
+}
+
 }

@@ -1,10 +1,12 @@
-"""rss_sec_access_batch beyond independent calls: calls that
-read an earlier call's outputs, against the same calls made one by one."""
+"""rss_sec_access_batch beyond independent calls over short lists: calls that
+read an earlier call's outputs, against the same calls made one by one, and
+lists of one length, records of more than a tile, against the oracle."""
 import numpy as np
 import pytest
 import torch
 
 from gpu_util import DEV, T, U
+from oracle import access
 
 pytestmark = pytest.mark.gpu
 
@@ -80,3 +82,25 @@ def test_calls_that_read_an_earlier_calls_ids(fss, reads):
     got = L.outputs()
     L.batch(got, [t.data_ptr() for c in range(L.calls) for t in idm(got)(c)])
     _equal(got, want)
+
+
+@pytest.mark.parametrize("n,length,ids,calls", [(700, 12, 9000, 8), (700, 12, 9000, 4), (2100, 24, 100, 8), (90, 40, 321, 2),
+                                                (1, 5, 33, 5), (65, 1, 64, 9)])
+def test_equal_lists_and_wide_records_equal_oracle(fss, n, length, ids, calls):
+    """Lists of one length (every slot as full as the first), records of one word to more than a tile of 256 words,
+    four and eight calls a pass: kept IDs, attributes and counts equal the oracle's single calls."""
+    rng = np.random.default_rng(n + ids)
+    L = _Lists(fss, rng, np.full(n, length), ids, calls)
+    out = L.outputs()
+    L.batch(out, [t.data_ptr() for c in L.idm for t in c])
+    post = [U(t).reshape(-1, L.wx) for t in L.post]
+    attr = [U(t).reshape(ids, L.wd) for t in L.attr]
+    bits = lambda t: np.unpackbits(U(t).view(np.uint8), bitorder="little")[:n]  # noqa: E731
+    for c in range(0, calls, 3):
+        want_ids, want_attrs = access.sec_access_csr([bits(t) for t in L.idm[c]], post, np.arange(n + 1) * length, attr, ids,
+                                                     list(KEYS), L.seeds[3 * c:3 * c + 3], L.counters[c])
+        m = want_ids[0].shape[0]
+        assert U(out[3])[c] == m
+        for i in range(3):
+            np.testing.assert_array_equal(U(out[0][i]).reshape(calls, length, L.wx)[c, :m], want_ids[i])
+            np.testing.assert_array_equal(U(out[1][i]).reshape(calls, length, L.wd)[c, :m], want_attrs[i])

@@ -25,6 +25,8 @@ def lib(tmp_path_factory):
     lib.number_tiles.restype = None
     lib.copiers.argtypes = [u32, u64, u32]
     lib.copiers.restype = u32
+    lib.slot_groups.argtypes = [u64, u32, u32, u32, u32, u32, u32, u32]
+    lib.slot_groups.restype = u32
     return lib
 
 
@@ -99,3 +101,44 @@ def test_copiers_share_the_pieces(lib, kept, pieces, groups):
     for t in range(256 * groups):
         _items(lib, kept, pieces, t, 256 * groups, seen)
     assert (seen == 1).all()
+
+
+def _slots(lib, lens, calls, wx):
+    """Workgroups of each slot of a selection over these lists, as the library launches it."""
+    n, lmax, nrec = len(lens), int(max(lens)), int(sum(lens))
+    least = -(-n // 2048)
+    most = max(least, min(-(-n // 64), 4096 // lmax + 1))
+    m = 8 if calls > 4 else 4 if calls > 1 else 1
+    got = [lib.slot_groups(n, lmax, m, 2 if m == 8 else 4, wx, most, l, nrec) for l in range(lmax)]
+    for c in got:
+        assert least <= c <= most                           # within the grid, at most 2,048 candidates each
+    return got, least, most
+
+
+@pytest.mark.parametrize("n,length,wx,calls", [(3000, 24, 94, 1), (3000, 24, 94, 8), (200, 24, 250, 1), (30011, 24, 32, 3),
+                                               (1000, 300, 32, 8), (60000, 4, 500, 1), (20000, 16, 4, 1)])
+def test_slots_of_equal_lists_are_shared_alike(lib, n, length, wx, calls):
+    """Lists of one length reach every slot alike, so every slot has as many workgroups (the float rule may differ by
+    one), and together they fill the chip as far as the lists go."""
+    got, least, most = _slots(lib, [length] * n, calls, wx)
+    assert max(got) - min(got) <= 1
+    assert sum(got) >= min(256, length * most)
+
+
+@pytest.mark.parametrize("calls", [1, 3, 8])
+@pytest.mark.parametrize("n,longest,wx", [(30011, 24, 250), (3000, 24, 94), (500, 300, 7), (1, 1, 1), (70, 9, 1000)])
+def test_slots_of_skewed_lists(lib, n, longest, wx, calls):
+    """Short lists mostly: the first slot has the most workgroups, later ones no more than the ones before."""
+    lens = np.minimum(np.random.default_rng(1).zipf(1.8, n) - 1, longest)
+    lens[-1] = longest
+    got, least, most = _slots(lib, lens, calls, wx)
+    assert got == sorted(got, reverse=True)
+    assert got[-1] == least or got[-1] < got[0] or most < 8
+
+
+@pytest.mark.parametrize("nrec", [0, 1, 2**32 - 1])
+def test_slots_at_the_ends(lib, nrec):
+    for n, lmax, most in ((1, 1, 1), (2**32 - 1, 65535, 2**21), (5, 65535, 1), (2**32 - 1, 1, 2**26)):
+        for l in {0, lmax - 1}:
+            c = lib.slot_groups(n, lmax, 8, 2, 3, max(most, -(-n // 2048)), l, nrec)
+            assert -(-n // 2048) <= c <= max(most, -(-n // 2048))
