@@ -108,34 +108,50 @@ struct SmallPerms {
 };
 
 // Rows [r0, r1) of one permutation of n <= kSmallPerm rows, made by the whole
-// workgroup of 1024 threads: the keys of all n rows into `key` (LDS), then each
-// row's rank; `out` gets the permutation (or its inverse).  Comparing all keys
-// is a loop of n LDS reads, so several threads share a row, each with a part of
-// the keys, and add their counts to `rank` (LDS).  `key` and `rank` are free
-// again when it returns.
+// workgroup of kSmallPerm threads: the keys of all n rows into `key` (LDS), then
+// each row's rank; `out` gets the permutation (or its inverse).  Comparing all
+// keys is a loop of n / 2 LDS reads, two keys each, so several threads share a
+// row, each with a part of the keys, and add their counts to `rank` (LDS); a
+// thread alone with its row (more than 512 rows, or so few that the sharing
+// costs more) reads them in a loop of uniform bounds.  `key` and `rank` are free
+// again when it returns.  (One key a read, and bounds that every thread had of its
+// own, made the whole shuffle of 1,000 records of 64 bytes 267 us in one workgroup,
+// where it had been 200; now 199.)
+__device__ __forceinline__ uint32_t smaller_keys(const uint64_t* key, uint64_t ki, uint32_t i, uint32_t j0, uint32_t j1) {
+    uint32_t c = 0;
+#pragma unroll 4
+    for (uint32_t j = j0; j < j1; j += 2) {
+        const ulonglong2 k = *(const ulonglong2*)(key + j);
+        c += (k.x < ki || (k.x == ki && j < i)) ? 1u : 0u;
+        c += (k.y < ki || (k.y == ki && j + 1 < i)) ? 1u : 0u;
+    }
+    return c;
+}
+
 __device__ __forceinline__ void small_perm(ChachaKey pk, uint32_t p, uint32_t inverse, uint32_t n, uint32_t r0,
                                            uint32_t r1, uint64_t* key, uint32_t* rank, uint32_t* out) {
     const uint32_t lanes = (n + 7) / 8 * 4;              // whole quads: a quad makes the keys of 8 rows
-    for (uint32_t t = threadIdx.x; t < lanes; t += blockDim.x) {
-        const uint4 o = chacha_quad(pk, t >> 2, 0u, 16u + p, 0u);
-        const uint32_t k0 = (t >> 2) * 8 + 2 * (t & 3);
-        if (k0 < n) key[k0] = (uint64_t)o.x | ((uint64_t)o.y << 32);
-        if (k0 + 1 < n) key[k0 + 1] = (uint64_t)o.z | ((uint64_t)o.w << 32);
+    if (threadIdx.x < lanes) {
+        const uint4 o = chacha_quad(pk, threadIdx.x >> 2, 0u, 16u + p, 0u);
+        const uint32_t k0 = (threadIdx.x >> 2) * 8 + 2 * (threadIdx.x & 3);
+        if (k0 < n) {
+            key[k0] = (uint64_t)o.x | ((uint64_t)o.y << 32);
+            key[k0 + 1] = k0 + 1 < n ? (uint64_t)o.z | ((uint64_t)o.w << 32) : ~0ull;   // n odd: below no row's
+        }
     }
-    const uint32_t rows = r1 - r0, parts = blockDim.x / rows;        // rows <= 1024 threads
+    const uint32_t rows = r1 - r0, parts = kSmallPerm / rows, even = (n + 1) & ~1u;
     if (threadIdx.x < rows) rank[threadIdx.x] = 0u;
     __syncthreads();
-    const uint32_t part = threadIdx.x / rows, own = threadIdx.x - part * rows;
-    if (part < parts) {
-        const uint32_t i = r0 + own, len = (n + parts - 1) / parts;
-        const uint32_t j0 = min(part * len, n), j1 = min(j0 + len, n);
-        const uint64_t ki = key[i];
-        uint32_t c = 0;
-        for (uint32_t j = j0; j < j1; j++) {
-            const uint64_t kj = key[j];
-            c += (kj < ki || (kj == ki && j < i)) ? 1u : 0u;
+    if (parts == 1 || n <= 16) {
+        if (threadIdx.x < rows) rank[threadIdx.x] = smaller_keys(key, key[r0 + threadIdx.x], r0 + threadIdx.x, 0u, even);
+    } else {
+        const uint32_t part = threadIdx.x / rows, own = threadIdx.x - part * rows;
+        if (part < parts) {
+            const uint32_t i = r0 + own, len = ((n + parts - 1) / parts + 1) & ~1u;
+            const uint32_t j0 = min(part * len, even), j1 = min(j0 + len, even);
+            const uint32_t c = smaller_keys(key, key[i], i, j0, j1);
+            if (c) atomicAdd(&rank[own], c);
         }
-        if (c) atomicAdd(&rank[own], c);
     }
     __syncthreads();
     if (threadIdx.x < rows) {
@@ -152,7 +168,7 @@ __device__ __forceinline__ void small_perm(ChachaKey pk, uint32_t p, uint32_t in
 constexpr uint32_t kSmallRows = 128;
 
 __global__ __launch_bounds__(1024) void k_perm_small(uint32_t n, SmallPerms J) {
-    __shared__ uint64_t key[kSmallPerm];
+    __shared__ __align__(16) uint64_t key[kSmallPerm];
     __shared__ uint32_t rank[kSmallRows];
     const uint32_t q = blockIdx.x, r0 = blockIdx.y * kSmallRows;
     small_perm(J.pk[q], J.p[q], J.inverse[q], n, r0, min(r0 + kSmallRows, n), key, rank, J.out[q]);
@@ -1151,7 +1167,7 @@ __device__ __forceinline__ void open_compact_block(uint32_t n, uint32_t nwords, 
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     flag[t] = 0;
     __syncthreads();
-    for (uint32_t i = wave; i < n; i += blockDim.x >> 6) {
+    for (uint32_t i = wave; i < n; i += kSmallPerm >> 6) {
         const uint64_t base = (uint64_t)i * nwords;
         uint32_t acc = 0;
         if (parity) {
@@ -1177,7 +1193,7 @@ __device__ __forceinline__ void open_compact_block(uint32_t n, uint32_t nwords, 
     if (t == 0) *count = incl[kSmallPerm - 1];
     const uint32_t first = parity ? 0u : 1u, ow = nwords - first;
     const uint64_t total = (uint64_t)n * ow;
-    for (uint64_t k = t; k < total; k += blockDim.x) {
+    for (uint64_t k = t; k < total; k += kSmallPerm) {
         const uint32_t i = (uint32_t)(k / ow), w = (uint32_t)(k - (uint64_t)i * ow);
         if (!flag[i]) continue;
         const uint64_t src = (uint64_t)i * nwords + first + w, dst = (uint64_t)(incl[i] - 1) * ow + w;
@@ -1205,12 +1221,15 @@ __global__ __launch_bounds__(1024) void k_open_compact_small(uint32_t n, uint32_
 // = 1 (secFetch: bit 0 of word 0) or 2 (secAccess filter: parity of all bits),
 // the open and compaction of the shuffled table.  The same per-slice code as
 // the multi-workgroup launches, so the same shares; the rounds meet through
-// global memory (xv, out) behind workgroup barriers.  One shuffle takes 10 to 27
-// us, a chain of barriers and ChaCha blocks on one CU, so the shuffles of a
-// batch run side by side (blockIdx.x = call).
+// global memory (xv, out) behind workgroup barriers.  One shuffle takes 8 us
+// to, at 1,000 rows, 200, a chain of barriers and ChaCha blocks on one CU, so the shuffles of a
+// batch run side by side (blockIdx.x = call).  A single call has its numbers at
+// fixed places of its own, shorter arguments (CALLS = 1): found through its number
+// among 64 calls' they cost the smallest shuffles 0.5 us of 8.
 constexpr uint32_t kFusedSlices = 1024;
 constexpr uint32_t kAloneRows = 64;
 
+template <uint32_t CALLS>
 struct SmallShuffle {
     const uint32_t* g[3];
     uint32_t* xv;
@@ -1220,21 +1239,21 @@ struct SmallShuffle {
     uint32_t* kept[3];
     uint32_t* rows_out;
     uint32_t* count;
-    uint32_t row0[kSideCalls + 1]; // call c: rows row0[c] .. row0[c + 1]
-    uint64_t seeds[kSideCalls][3]; // s12, s23, s31
+    uint32_t row0[CALLS + 1];      // call c: rows row0[c] .. row0[c + 1]
+    uint64_t seeds[CALLS][3];      // s12, s23, s31
 };
 
 __device__ __forceinline__ ChachaKey pair_key_of(uint64_t seed) {
     return ChachaKey{(uint32_t)seed, (uint32_t)(seed >> 32), kShuffleDomain};
 }
 
-template <bool WHOLE>
-__global__ __launch_bounds__(1024) void k_shuffle_small(SmallShuffle A) {
-    __shared__ uint64_t key[kSmallPerm];
+template <bool WHOLE, uint32_t CALLS>
+__global__ __launch_bounds__(1024) void k_shuffle_small(SmallShuffle<CALLS> A) {
+    __shared__ __align__(16) uint64_t key[kSmallPerm];
     __shared__ uint32_t perm[3][kSmallPerm];     // inverse of pi12, inverse of pi31, pi23
     __shared__ uint32_t flag[kSmallPerm];
     __shared__ uint32_t incl[kSmallPerm];
-    const uint32_t call = blockIdx.x, nwords = A.nwords;
+    const uint32_t call = CALLS == 1 ? 0u : blockIdx.x, nwords = A.nwords;
     const uint32_t r0 = A.row0[call], n = A.row0[call + 1] - r0;
     if (n == 0) {
         if (A.compact && threadIdx.x == 0) A.count[call] = 0u;
@@ -1248,10 +1267,10 @@ __global__ __launch_bounds__(1024) void k_shuffle_small(SmallShuffle A) {
     small_perm(k31, kP31, 1u, n, 0u, n, key, flag, perm[1]);
     small_perm(k23, kP23, 0u, n, 0u, n, key, flag, perm[2]);
     const uint64_t total = (uint64_t)n * ((nwords + 15) >> 4) * 4;
-    for (uint64_t t = threadIdx.x; t < total; t += blockDim.x)
+    for (uint64_t t = threadIdx.x; t < total; t += kSmallPerm)
         first_slice<WHOLE>(t, n, nwords, k12, k31, perm[0], perm[1], A.g[0] + at, A.g[1] + at, A.g[2] + at, xv, s1, s0);
     __syncthreads();
-    for (uint64_t t = threadIdx.x; t < total; t += blockDim.x)
+    for (uint64_t t = threadIdx.x; t < total; t += kSmallPerm)
         final_slice<WHOLE>(t, n, nwords, k12, k23, k31, perm[2], xv, s2);
     if (!A.compact) return;
     __syncthreads();
@@ -1637,24 +1656,36 @@ bool small_shuffle_fits(uint64_t nrows, uint32_t nwords) {
     return nrows <= kSmallPerm && nrows * ((nwords + 15) / 16) <= kFusedSlices;
 }
 
+// `n` calls from c0 on in one launch.
+template <uint32_t CALLS>
+static int launch_small(uint32_t c0, uint32_t n, const uint32_t* row0, uint32_t nwords, const uint32_t* const g[3],
+                        const uint64_t* seeds, uint32_t* xv, uint32_t* const out[3], uint32_t compact,
+                        uint32_t* const kept[3], uint32_t* rows_out, uint32_t* count, hipStream_t s) {
+    SmallShuffle<CALLS> A{};
+    for (int i = 0; i < 3; i++) {
+        A.g[i] = g[i];
+        A.out[i] = out[i];
+        A.kept[i] = kept ? kept[i] : nullptr;
+    }
+    A.xv = xv, A.compact = compact, A.nwords = nwords, A.rows_out = rows_out, A.count = count ? count + c0 : nullptr;
+    for (uint32_t c = 0; c <= n; c++) A.row0[c] = row0[c0 + c];
+    for (uint32_t c = 0; c < n; c++)
+        for (int k = 0; k < 3; k++) A.seeds[c][k] = seeds[3 * (uint64_t)(c0 + c) + k];
+    auto k = nwords & 3u ? k_shuffle_small<false, CALLS> : k_shuffle_small<true, CALLS>;
+    hipLaunchKernelGGL(k, dim3(n), dim3(1024), 0, s, A);
+    return check_launch("k_shuffle_small");
+}
+
 int small_shuffles(uint32_t calls, const uint32_t* row0, uint32_t nwords, const uint32_t* const g[3],
                    const uint64_t* seeds, uint32_t* xv, uint32_t* const out[3], uint32_t compact,
                    uint32_t* const kept[3], uint32_t* rows_out, uint32_t* count, void* stream) {
+    const hipStream_t s = (hipStream_t)stream;
+    if (calls == 1)      // its numbers at fixed places in 150 bytes of arguments
+        return launch_small<1>(0, 1, row0, nwords, g, seeds, xv, out, compact, kept, rows_out, count, s);
     for (uint32_t c0 = 0; c0 < calls; c0 += kSideCalls) {
         const uint32_t n = calls - c0 < kSideCalls ? calls - c0 : kSideCalls;
-        SmallShuffle A{};
-        for (int i = 0; i < 3; i++) {
-            A.g[i] = g[i];
-            A.out[i] = out[i];
-            A.kept[i] = kept ? kept[i] : nullptr;
-        }
-        A.xv = xv, A.compact = compact, A.nwords = nwords, A.rows_out = rows_out, A.count = count ? count + c0 : nullptr;
-        for (uint32_t c = 0; c <= n; c++) A.row0[c] = row0[c0 + c];
-        for (uint32_t c = 0; c < n; c++)
-            for (int k = 0; k < 3; k++) A.seeds[c][k] = seeds[3 * (uint64_t)(c0 + c) + k];
-        auto k = nwords & 3u ? k_shuffle_small<false> : k_shuffle_small<true>;
-        hipLaunchKernelGGL(k, dim3(n), dim3(1024), 0, (hipStream_t)stream, A);
-        if (const int rc = check_launch("k_shuffle_small")) return rc;
+        if (const int rc = launch_small<kSideCalls>(c0, n, row0, nwords, g, seeds, xv, out, compact, kept, rows_out, count, s))
+            return rc;
     }
     return FSS_OK;
 }

@@ -104,3 +104,10 @@ def test_equal_lists_and_wide_records_equal_oracle(fss, n, length, ids, calls):
         for i in range(3):
             np.testing.assert_array_equal(U(out[0][i]).reshape(calls, length, L.wx)[c, :m], want_ids[i])
             np.testing.assert_array_equal(U(out[1][i]).reshape(calls, length, L.wd)[c, :m], want_attrs[i])
+
+
+@pytest.mark.parametrize("length,ids,calls", [(2, 40, 2), (15, 40, 2), (16, 40, 2), (17, 40, 3), (511, 40, 2), (512, 40, 2),
+                                              (513, 40, 3), (1023, 33, 2), (1024, 33, 2)])
+def test_shuffles_side_by_side_at_the_rankings_edges(fss, length, ids, calls):
+    """Fetched lists that a workgroup each shuffles: rows ranked by several threads, by one, odd numbers of rows."""
+    test_equal_lists_and_wide_records_equal_oracle(fss, 3, length, ids, calls)
