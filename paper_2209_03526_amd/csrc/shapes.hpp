@@ -48,6 +48,20 @@ OGM_HD uint32_t compact_copiers(uint32_t blocks, uint64_t nrows, uint32_t rw) {
     return y ? (uint32_t)y : 1u;
 }
 
+// Whether a single shuffle runs in one workgroup, where its one launch beats the
+// three that rank and mask over the chip: up to kAloneRows rows, and up to 128 of
+// at most 256 slices in all (one pass of a workgroup's quads), or 320 with the open
+// and the compaction behind it (one launch against six).  One workgroup against
+// the launches, microseconds, shuffle and (fetch): records of 64 bytes, 64 rows
+// 9.0 / 14.9 (12.1 / 22.1), 128 rows 11.6 / 14.9 (16.1 / 22.3), 160 rows 15.1 / 14.7
+// (20.0 / 22.3), 300 rows 28 / 15 (35 / 22); 96 rows of 33 words 17.5 / 15.4 (21.8 /
+// 22.9), 96 of 64 18.6 / 15.3 (23.7 / 22.6).
+constexpr uint32_t kAloneRows = 64;
+
+OGM_HD bool one_workgroup(uint64_t nrows, uint32_t nwords, bool fetch) {
+    return nrows <= kAloneRows || (nrows <= 128 && nrows * (((uint64_t)nwords + 15) / 16) <= (fetch ? 320 : 256));
+}
+
 // Where slice b of row l lies in the two tables that a shuffle's final round
 // gathers (word offsets of its X1 and V words, len of each): interleaved slice by
 // slice where `whole`, one after the other otherwise.  16 * b is a word of a

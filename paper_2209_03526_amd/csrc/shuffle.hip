@@ -1227,7 +1227,6 @@ __global__ __launch_bounds__(1024) void k_open_compact_small(uint32_t n, uint32_
 // fixed places of its own, shorter arguments (CALLS = 1): found through its number
 // among 64 calls' they cost the smallest shuffles 0.5 us of 8.
 constexpr uint32_t kFusedSlices = 1024;
-constexpr uint32_t kAloneRows = 64;
 
 template <uint32_t CALLS>
 struct SmallShuffle {
@@ -1618,12 +1617,8 @@ int shuffle_rounds(uint64_t nrows, uint32_t nwords, const uint32_t* const d[3], 
     return rc;
 }
 
-// Whether a single shuffle runs in one workgroup: up to kAloneRows rows, where
-// its one launch beats three that rank and mask over the chip (records of 64
-// bytes: 300 rows 39 us in one workgroup, 15 in three launches; 1,000 rows 157
-// and 19; 40 rows 10 in one workgroup).
-bool shuffle_alone(uint64_t nrows, uint32_t nwords) {
-    return nrows <= kAloneRows && small_shuffle_fits(nrows, nwords);
+bool shuffle_alone(uint64_t nrows, uint32_t nwords, bool fetch = false) {
+    return small_shuffle_fits(nrows, nwords) && one_workgroup(nrows, nwords, fetch);
 }
 
 // Alg. 5 with all three servers simulated; out[0..2] = R1, R2, R3.  The
@@ -1887,7 +1882,7 @@ static int shuffle_open_compact(uint64_t ncand, uint32_t nwords, const uint32_t*
     uint32_t* flags = ws.take<uint32_t>(ncand);
     uint32_t* sums = ws.take<uint32_t>(kCompactBlocks);
     if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
-    if (shuffle_alone(ncand, nwords)) {
+    if (shuffle_alone(ncand, nwords, true)) {
         // the shuffle, the open and the compaction in one workgroup
         uint32_t* xv = ws.take<uint32_t>(2 * tw);
         if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);

@@ -36,4 +36,6 @@ uint32_t slot_groups(uint64_t ncand, uint32_t lmax, uint32_t M, uint32_t V, uint
     return ogm::sel_chunks(ogm::sel_rule(ncand, lmax, M, V, wx), most, l, nrec);
 }
 
+int32_t alone(uint64_t nrows, uint32_t nwords, int32_t fetch) { return ogm::one_workgroup(nrows, nwords, fetch != 0); }
+
 }

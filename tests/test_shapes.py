@@ -27,6 +27,7 @@ def lib(tmp_path_factory):
     lib.copiers.restype = u32
     lib.slot_groups.argtypes = [u64, u32, u32, u32, u32, u32, u32, u32]
     lib.slot_groups.restype = u32
+    lib.alone.argtypes = [u64, u32, ctypes.c_int32]
     return lib
 
 
@@ -142,3 +143,10 @@ def test_slots_at_the_ends(lib, nrec):
         for l in {0, lmax - 1}:
             c = lib.slot_groups(n, lmax, 8, 2, 3, max(most, -(-n // 2048)), l, nrec)
             assert -(-n // 2048) <= c <= max(most, -(-n // 2048))
+
+
+@pytest.mark.parametrize("rows,words,shuffle,fetch", [(1, 1, 1, 1), (64, 1 << 20, 1, 1), (65, 16, 1, 1), (128, 32, 1, 1), (129, 2, 0, 0),
+                                                      (100, 48, 0, 1), (107, 48, 0, 0), (128, 2**32 - 1, 0, 0)])
+def test_one_workgroup_where_it_wins(lib, rows, words, shuffle, fetch):
+    """The line between one workgroup's shuffle and launches over the chip, on both sides of the measured crossings."""
+    assert (bool(lib.alone(rows, words, 0)), bool(lib.alone(rows, words, 1))) == (bool(shuffle), bool(fetch))
