@@ -1444,17 +1444,17 @@ int check_batch(const fss_keybatch* k, int32_t want_kind, const char* who) {
 // Workgroup size and grid of a launch of `tiles` wave tiles of an AES kernel,
 // one tile per wave.  Up to 16 waves in each of the two workgroups per CU that
 // the LDS tables allow, the workgroups are as small as spreads them over the
-// chip, so that the launch takes one tile's latency (three predicates over
-// 1,024 vertices and 8,192 edges: 52 us, against 148 us with 1024-thread
-// workgroups; four over 10,000: 61 us, against 154).  Beyond that, workgroups
-// of 16 waves are dispatched as others end.
+// chip, but for the four waves that the tables' fill takes (tile_waves), so that
+// the launch takes one tile's latency (three predicates over 1,024 vertices and
+// 8,192 edges: 52 us, against 148 us with 1024-thread workgroups; four over
+// 10,000: 61 us, against 154).  Beyond that, workgroups of 16 waves are dispatched
+// as others end.
 struct TileShape {
     unsigned grid, block;
 };
 
 TileShape tile_shape(uint64_t tiles) {
-    const uint64_t wgs = 2ull * (uint64_t)device_cus();
-    const uint64_t waves = std::min<uint64_t>(std::max<uint64_t>((tiles + wgs - 1) / wgs, 1), kBlock / 64);
+    const uint64_t waves = tile_waves(tiles, 2ull * (uint64_t)device_cus());
     return TileShape{(unsigned)std::max<uint64_t>((tiles + waves - 1) / waves, 1), (unsigned)(64 * waves)};
 }
 

@@ -111,6 +111,17 @@ OGM_HD uint32_t sel_chunks(const SelRule& r, uint32_t most, uint32_t l, uint32_t
     return c > r.least ? c : r.least;
 }
 
+// Waves of a workgroup in a launch of `tiles` wave tiles, `wgs` workgroups at a
+// time: as few as spread the tiles over the chip, but at least four, because the
+// workgroup fills 64 KiB of tables first.  One wave alone takes 3 us for it, so
+// the shortest walks (64 rows, 8-bit domains) took 7.7 us where workgroups of 16
+// waves had taken 6.3; with four waves 4.9 (eight: 4.5, but six launches of a small
+// query in turn 121 us instead of 120).
+OGM_HD uint64_t tile_waves(uint64_t tiles, uint64_t wgs) {
+    const uint64_t w = (tiles + wgs - 1) / wgs;
+    return w < 4 ? 4 : w > 16 ? 16 : w;
+}
+
 // Numbers the tiles of a batch's descriptors.  A launch numbers its tiles with 32
 // bits, so a batch of more (2^32 tiles are 2^37 rows of ranges) takes several
 // launches: a descriptor whose tiles no longer fit starts the next one.

@@ -38,4 +38,6 @@ uint32_t slot_groups(uint64_t ncand, uint32_t lmax, uint32_t M, uint32_t V, uint
 
 int32_t alone(uint64_t nrows, uint32_t nwords, int32_t fetch) { return ogm::one_workgroup(nrows, nwords, fetch != 0); }
 
+uint64_t waves(uint64_t tiles, uint64_t wgs) { return ogm::tile_waves(tiles, wgs); }
+
 }

@@ -27,6 +27,8 @@ def lib(tmp_path_factory):
     lib.copiers.restype = u32
     lib.slot_groups.argtypes = [u64, u32, u32, u32, u32, u32, u32, u32]
     lib.slot_groups.restype = u32
+    lib.waves.argtypes = [u64, u64]
+    lib.waves.restype = u64
     lib.alone.argtypes = [u64, u32, ctypes.c_int32]
     return lib
 
@@ -150,3 +152,10 @@ def test_slots_at_the_ends(lib, nrec):
 def test_one_workgroup_where_it_wins(lib, rows, words, shuffle, fetch):
     """The line between one workgroup's shuffle and launches over the chip, on both sides of the measured crossings."""
     assert (bool(lib.alone(rows, words, 0)), bool(lib.alone(rows, words, 1))) == (bool(shuffle), bool(fetch))
+
+
+@pytest.mark.parametrize("tiles", [0, 1, 4, 511, 512, 2048, 2049, 5000, 8192, 8193, 1 << 31])
+def test_aes_workgroups_have_waves_enough_for_their_tables(lib, tiles):
+    w = lib.waves(tiles, 512)
+    assert 4 <= w <= 16
+    assert w in (4, 16) or 512 * (w - 1) < tiles <= 512 * w
