@@ -577,16 +577,27 @@ def rss_enc_posting_lists(n: int, x_bits: int, adj_off, adj, slot, off, nrec: in
     return work
 
 
+def _side_by_side(single: int, calls: int, device):
+    """A workspace of `calls` calls of `single` bytes, or of as many as memory is free for: one serves them all."""
+    while True:
+        try:
+            return torch.empty(max(single * max(calls, 1), 256), dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            if calls <= 1:
+                raise
+            calls //= 2
+
+
 def rss_sec_access_batch(ncand: int, x_bits: int, idm_ptrs, off, lmax: int, post3, attr_words: int, attr3,
                          prf_keys, counters, seeds, ids3, attrs3, rows_out, count, stream=None):
     """len(counters) secAccess calls in one library call: idm_ptrs holds the
     3 device addresses of each call's matched-ID shares, seeds 3 values per
     call; call c's outputs sit at offset c times one call's capacity.  The
-    workspace holds up to 64 calls (within 256 MiB), which then run side by side."""
+    workspace holds up to 64 calls (within 256 MiB, and as far as memory is free),
+    which then run side by side."""
     n = len(counters)
     single = int(LIB.rss_sec_access_workspace_bytes(lmax, x_bits, attr_words))
-    nbytes = single * max(1, min(n, 64, (256 << 20) // max(single, 1)))
-    work = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=ids3[0].device)
+    work = _side_by_side(single, min(n, 64, (256 << 20) // max(single, 1)), ids3[0].device)
     _check(LIB.rss_sec_access_batch(n, ncand, x_bits, (ctypes.c_void_p * (3 * n))(*idm_ptrs), _ptr(off), lmax,
                                     _ptr3(post3), attr_words, _ptr3(attr3), (ctypes.c_uint64 * 3)(*prf_keys),
                                     (ctypes.c_uint32 * n)(*counters), (ctypes.c_uint64 * (3 * n))(*seeds),
