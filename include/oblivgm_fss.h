@@ -430,7 +430,8 @@ int rss_and(uint64_t nrows, const uint32_t* const d_x[3], const uint32_t* const 
  *   (high), e = r mod 8, of block (r div 8, 0, 16+p, 0), p = 0 / 1 / 2;
  *   a permutation applied to a table gathers out[i] = in[perm[i]].
  * Up to 2^23 rows the whole call runs on the caller's stream (a table of at
- * most 1024 rows and 1024 16-word slices is shuffled by one workgroup); with
+ * most 64 rows and 1024 16-word slices, or 128 rows and 256 slices, is shuffled
+ * by one workgroup); with
  * more rows, or a radix permutation method (rss_set_shuffle_tuning), the
  * permutations are made on two streams of the library's own besides the
  * caller's, ordered against the caller's stream with events.  Either way the

@@ -12,9 +12,10 @@
 //   k_rss, k_rss_eval, k_eval_points    the paper's own secEval and RSS arithmetic
 // and the host code of the C ABI (validation, launch, match_query plan).
 //
-// Every AES-using kernel runs 1024-thread workgroups that first fill the
-// 64 KiB replicated T-tables in LDS (aes_gfx950.hpp); evaluation uses smaller
-// workgroups where a launch has few tiles.  In evaluation one lane owns one
+// Every AES-using kernel's workgroups first fill the 64 KiB replicated T-tables in
+// LDS (aes_gfx950.hpp).  Evaluation, dealer and tails run workgroups of 4 to 16
+// waves, the more tiles a launch has, full-domain evaluation of four, the masks and
+// triples of 16.  In evaluation one lane owns one
 // tree walk (one element, one predicate, one party), a wave 64 consecutive
 // rows of an equality or 32 of a range, so the per-level correction words of a
 // wave are one contiguous 1 KiB read or two of 512 bytes, and the wave's
@@ -221,7 +222,6 @@ struct EvalDesc {
     uint64_t n;
     uint32_t kind;
     uint32_t nbits;
-    uint32_t party;
     uint32_t tile_start;    // first wave (or quad) tile of this descriptor
 };
 
@@ -1521,7 +1521,6 @@ int eval_one(int32_t party, const fss_keybatch* k, int32_t kind, const uint32_t*
     d.n = k->n;
     d.kind = (uint32_t)kind;
     d.nbits = k->nbits;
-    d.party = (uint32_t)party;
     return launch_eval(&d, 1, (hipStream_t)stream);
 }
 
@@ -2127,7 +2126,6 @@ void plan_evals(const TailPlan& T, int32_t mask, std::vector<EvalDesc>& out) {
             d.n = rows;
             d.kind = (uint32_t)p.keys->kind;
             d.nbits = p.keys->nbits;
-            d.party = (uint32_t)b;
             out.push_back(d);
         }
     }
@@ -2306,7 +2304,7 @@ int staging_release() {
     return rc;
 }
 
-constexpr uint64_t kQueueHeader = 256;   // descriptors start at this offset
+constexpr uint64_t kQueueHeader = 256;   // descriptors start at this offset (the bytes before it are not used)
 
 uint64_t queue_bytes(uint64_t count) {
     const uint64_t per = sizeof(QKeygen) > sizeof(EvalDesc) ? sizeof(QKeygen) : sizeof(EvalDesc);
@@ -2471,7 +2469,6 @@ int eval_request(const fss_eval_req& r, uint32_t i, const char* who, EvalDesc* d
     d->n = r.keys->n;
     d->kind = (uint32_t)r.keys->kind;
     d->nbits = r.keys->nbits;
-    d->party = (uint32_t)r.party;
     return FSS_OK;
 }
 

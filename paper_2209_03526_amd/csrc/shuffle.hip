@@ -383,8 +383,8 @@ __global__ __launch_bounds__(256) void k_rank_runs(uint64_t n, uint32_t hb, uint
 
 // ---------------------------------------------------------------- permutations by buckets
 //
-// Tables of 1025 .. 2^23 rows take the stable argsort of their keys in four
-// launches and no sort library: with hb run-id bits as above, the top
+// Tables of 1025 .. 2^23 rows take the stable argsort of their keys in five
+// launches (three up to 2^18 rows) and no sort library: with hb run-id bits as above, the top
 // d1 = ceil(log2 n) - 12 key bits (at least 0; one more up to 2^18 rows) name
 // the row's bucket (2^11 .. 2^12 rows on average), the next d2 = hb - d1 bits its run in the bucket.
 //   count: each workgroup makes the keys of 8192 (2048) rows and counts them per
@@ -893,6 +893,10 @@ __device__ __forceinline__ void first_slice(uint64_t t, uint64_t nrows, uint32_t
     store_quarter<WHOLE>(xv, dst.v, c, len, xor4(z, m));
 }
 
+// For widths of whole quarters eight waves a SIMD are asked for: the 64 registers that
+// leaves hold all but two values of a loop's turn, which go to scratch (12 bytes a
+// lane, in L1), and the pass, bound by memory, takes 418 us instead of 480 with 70
+// registers and seven waves (2^22 records of 64 bytes).
 template <bool WHOLE>
 __global__ __launch_bounds__(kBlock, WHOLE ? 8 : 1) void k_shuffle_first(uint64_t nrows, uint32_t nwords, ChachaKey k12, ChachaKey k31,
                                                         const uint32_t* __restrict__ inv12,

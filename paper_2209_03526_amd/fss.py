@@ -336,7 +336,7 @@ def fss_queue_workspace_bytes(count: int) -> int:
 
 
 class Queue:
-    """Device memory for the work queue of batch calls (counter + descriptors)."""
+    """Device memory for the descriptors of batch calls."""
 
     def __init__(self, capacity: int, device=None):
         self.capacity = capacity
