@@ -643,7 +643,7 @@ static int sec_access_calls(uint32_t count, uint64_t ncand, uint32_t x_bits, con
     const bool small = small_shuffle_fits(lmax, wx);
     const uint32_t most = small ? (uint32_t)std::min<uint64_t>(std::min<uint64_t>(count, kSideCalls), work_bytes / single)
                                 : 1u;
-    std::vector<uint32_t> row0(most + 1);
+    uint32_t row0[kSideCalls + 1];         // most is at most kSideCalls
     for (uint32_t c = 0; c <= most; c++) row0[c] = c * lmax;
     const uint64_t mw = (ncand + 31) / 32;             // words of a matched ID's share
     for (uint32_t c0 = 0, n; c0 < count; c0 += n) {
@@ -700,7 +700,7 @@ static int sec_access_calls(uint32_t count, uint64_t ncand, uint32_t x_bits, con
             uint32_t* sh[3] = {ws.take(n * tw), ws.take(n * tw), ws.take(n * tw)};
             uint32_t* xv = ws.take(2 * n * tw);
             if (!ws.ok) return fail(FSS_ENOMEM, "%s: workspace too small", who);
-            rc = small_shuffles(n, row0.data(), wx, r3, seeds + 3 * (uint64_t)c0, xv, sh, 2u, ids,
+            rc = small_shuffles(n, row0, wx, r3, seeds + 3 * (uint64_t)c0, xv, sh, 2u, ids,
                                 d_rows_out + (uint64_t)c0 * lmax, d_count + c0, stream);
         } else {
             const uint64_t cws = rss_fetch_many_workspace_bytes(lmax, wx);
