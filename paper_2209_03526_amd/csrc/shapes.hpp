@@ -14,9 +14,10 @@
 namespace ogm {
 
 // f(record, piece) for the items of `kept` records of `pieces` pieces each
-// that thread t of T takes, kept at most 256 and T at most 2^31.  The pieces go in tiles of
-// 2^20, so that an item's number in a tile fits 32 bits however wide the records
-// are (one number over all of them passes 2^32 at 256 records of 2^24 pieces).
+// that thread t of T takes, kept at most 256 and T at most 2^31.  The pieces go in
+// tiles of 2^20, so that an item's number in a tile fits 32 bits however wide the
+// records are (one number over all of them passes 2^32 at 256 records of 2^24
+// pieces).
 constexpr uint32_t kPieceTile = 1u << 20;
 
 template <class F>
@@ -86,6 +87,10 @@ struct XvOffsets {
 // 64 V / wx lanes meet in a word.  The two cost as much as streaming about 8 M and
 // 1000 M V^2 / wx^2 records, so a workgroup is given several times that, or what
 // fills the chip where the records are few; at most kSelMost candidates.
+// Measured, whole calls: eight over 30,011 skewed lists of 1,000-byte records, 24 M,
+// 32 M, 48 M and 64 M records a workgroup, 173, 172, 164 and 166 us; eight over 3,000
+// lists of 24 records of 94 words, 512, 640 and 768 workgroups, 80, 79 and 79 us;
+// over 20,000 lists of 16 records of 4 words 79, 91 and 94.
 constexpr uint32_t kSelMost = 2048, kSelFill = 512;
 
 struct SelRule {
