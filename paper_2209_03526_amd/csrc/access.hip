@@ -151,11 +151,16 @@ struct Out3 {
 // blocks beyond leave at once, so what they evaluate of the rule is kept short
 // (in 64-bit integers from two loads it cost 8 of 166 us).  With 1 / (l + 1) of
 // slot 0's blocks in slot l, whatever the lists, a secAccess over 3,000 lists of 24
-// records of 94 words took 83 us and eight took 161, now 58 and 80.
+// records of 94 words took 83 us and eight took 161, now 54 and 76.
 constexpr int kSelThreads = 512;
 constexpr uint32_t kSelCand = 1024;       // candidates listed at a time
 static_assert(kSelMost == 2 * kSelCand, "a block lists its candidates in two steps at most");
 constexpr uint32_t kSelTile = 256;        // record words per pass
+// Records of up to so many words are loaded word by word by a single call, whose
+// threads then meet in more words of the LDS sums.  Words against 16 bytes: 20,000
+// skewed lists over 100 IDs (4 words) 38 / 70 us, over 1,200 (38) 45 / 48, over 4,000
+// (125) 59.1 / 60.6.
+constexpr uint32_t kSelNarrow = 128;
 
 struct IdmSet {
     const uint32_t* p[kSideCalls][3];
@@ -684,9 +689,10 @@ static int sec_access_calls(uint32_t count, uint64_t ncand, uint32_t x_bits, con
             const dim3 grid((unsigned)chunks, lmax, (n + m - 1) / m);
             const Shares3 post{{d_post[0], d_post[1], d_post[2]}};
             const Out3 o{{add[0], add[1], add[2]}};
-            auto k = m == 8 ? k_csr_select<8, 2> : m == 4 ? k_csr_select<4, 4> : k_csr_select<1, 4>;
-            hipLaunchKernelGGL(k, grid, dim3(kSelThreads), 0, s, ncand, wx, n, tw,
-                               sel_rule(ncand, lmax, m, m == 8 ? 2 : 4, wx), idm, d_off, post, o);
+            const uint32_t v = m == 8 ? 2 : m == 1 && wx <= kSelNarrow ? 1 : 4;      // words a load
+            auto k = m == 8 ? k_csr_select<8, 2> : m == 4 ? k_csr_select<4, 4> : v == 1 ? k_csr_select<1, 1> : k_csr_select<1, 4>;
+            hipLaunchKernelGGL(k, grid, dim3(kSelThreads), 0, s, ncand, wx, n, tw, sel_rule(ncand, lmax, m, v, wx), idm,
+                               d_off, post, o);
         }
         int rc = check_launch("k_csr_select");
         if (rc) return rc;

@@ -85,18 +85,21 @@ struct XvOffsets {
 // A workgroup adds its sums to the output by 3 M wx / 2 atomics (M calls, records
 // of wx words), after adding its threads' partial sums (V words each) in LDS, where
 // 64 V / wx lanes meet in a word.  The two cost as much as streaming about 8 M and
-// 1000 M V^2 / wx^2 records, so a workgroup is given several times that, or what
-// fills the chip where the records are few; at most kSelMost candidates.
+// 1000 M V^2 / wx^2 records, so a workgroup is given several times that, or 1 /
+// kSelLarge of the records where that is more; but no more than 1 / kSelFill of
+// them, which fills the chip, nor more than kSelMost candidates.
 // Measured, whole calls: eight over 30,011 skewed lists of 1,000-byte records, 24 M,
 // 32 M, 48 M and 64 M records a workgroup, 173, 172, 164 and 166 us; eight over 3,000
-// lists of 24 records of 94 words, 512, 640 and 768 workgroups, 80, 79 and 79 us;
-// over 20,000 lists of 16 records of 4 words 79, 91 and 94.
-constexpr uint32_t kSelMost = 2048, kSelFill = 512;
+// lists of 24 records of 94 words, 1 / 512, 1 / 640 and 1 / 768 of the records, 80,
+// 79 and 79 us, over 20,000 lists of 16 of 4 words 79, 91 and 94; one over 20,000
+// lists of 16 of 47 words, 1 / 1024, 1 / 2048 and 1 / 4096, 75, 77 and 91 us, over
+// 30,011 lists of 24 of 32 words 82, 78 and 75.
+constexpr uint32_t kSelMost = 2048, kSelFill = 512, kSelLarge = 2048;
 
 struct SelRule {
     float ncand, lmax;      // base-2 logarithms
     float slope;            // b / log2(lmax / mean length)
-    float records;          // a workgroup's records, at most
+    float records;          // a workgroup's records, for the cost of its end
     uint32_t least;         // workgroups a slot, at least
 };
 
@@ -111,7 +114,8 @@ OGM_HD uint32_t sel_chunks(const SelRule& r, uint32_t most, uint32_t l, uint32_t
     const float n = (float)(nrec ? nrec : 1u), fill = n * (1.0f / kSelFill) + 1.0f;
     const float shorter = r.lmax + r.ncand - log2f(n);                      // log2(lmax / mean length)
     const float lists = exp2f(r.ncand - (shorter > 0.0f ? shorter : 0.0f) * r.slope * log2f((float)(l + 1)));
-    const float want = lists / (fill < r.records ? fill : r.records) + 1.0f;
+    const float large = n * (1.0f / kSelLarge), some = large > r.records ? large : r.records;
+    const float want = lists / (fill < some ? fill : some) + 1.0f;
     const uint32_t c = want < (float)most ? (uint32_t)want : most;
     return c > r.least ? c : r.least;
 }

@@ -85,7 +85,8 @@ def test_calls_that_read_an_earlier_calls_ids(fss, reads):
 
 
 @pytest.mark.parametrize("n,length,ids,calls", [(700, 12, 9000, 8), (700, 12, 9000, 4), (2100, 24, 100, 8), (90, 40, 321, 2),
-                                                (1, 5, 33, 5), (65, 1, 64, 9)])
+                                                (1, 5, 33, 5), (65, 1, 64, 9), (300, 9, 20, 1), (2100, 24, 100, 1),
+                                                (300, 7, 4096, 1), (300, 7, 4097, 1)])
 def test_equal_lists_and_wide_records_equal_oracle(fss, n, length, ids, calls):
     """Lists of one length (every slot as full as the first), records of one word to more than a tile of 256 words,
     four and eight calls a pass: kept IDs, attributes and counts equal the oracle's single calls."""

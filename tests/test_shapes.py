@@ -112,7 +112,8 @@ def _slots(lib, lens, calls, wx):
     least = -(-n // 2048)
     most = max(least, min(-(-n // 64), 4096 // lmax + 1))
     m = 8 if calls > 4 else 4 if calls > 1 else 1
-    got = [lib.slot_groups(n, lmax, m, 2 if m == 8 else 4, wx, most, l, nrec) for l in range(lmax)]
+    v = 2 if m == 8 else 1 if m == 1 and wx <= 128 else 4
+    got = [lib.slot_groups(n, lmax, m, v, wx, most, l, nrec) for l in range(lmax)]
     for c in got:
         assert least <= c <= most                           # within the grid, at most 2,048 candidates each
     return got, least, most
